@@ -173,12 +173,15 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                of K_hat)
  *   "otf_split"  number of row chunks an on-the-fly product is split into (with "otf_sym": number
  *                of workgroups of each of its two launches, default two per compute unit)
- *   "otf_sym"    1 (default): an on-the-fly product of at most 16 columns over at most 32 input
- *                dimensions and at least 12288 (padded) rows evaluates only the tiles on and above
- *                the diagonal and uses each for both of its contributions (K is symmetric);
- *                2: the same for any number of rows; 0: every tile is evaluated for the one
- *                contribution, as it is for wider blocks and inputs.  Same values, fp64 sums in
- *                another order
+ *   "otf_sym"    1 (default): an on-the-fly product over at most 16 input dimensions and at least 6144
+ *                (padded) rows is formed on the 8-bit matrix pipe from the digits of the entries and of
+ *                the block (exact integer sums; entries in 32-bit fixed point, within 2.4e-10 of the
+ *                outputscale); otherwise one of at most 16 columns over 17 to 32 dimensions and at least
+ *                12288 rows evaluates only the tiles on and above the diagonal and uses each for both of
+ *                its contributions (K is symmetric).  2: where the first does not apply, the second for
+ *                any number of rows and up to 32 dimensions; 0: every tile is evaluated for the one
+ *                contribution, in fp64, as it is for wider blocks and inputs.  Same products to the
+ *                rounding of the entries
  *   "ur_blocks"  upper limit of the workgroups of the fused U/R update (default 128, at most 512)
  *   "khat_panel" layout of the materialised K_hat: column panels of that width (a multiple of
  *                256; default 1024), each panel row-major; 1 = plain row-major.  Takes effect at

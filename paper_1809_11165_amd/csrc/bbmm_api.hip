@@ -41,9 +41,13 @@ struct TriLists {
 
 constexpr int kMaxVecBlocks = 512;   // at most 32 reduction groups of 16 blocks
 constexpr int kMaxSplit = bbmm_plan::kMaxSplit;
-// Measured, product in us (two-use / one-use form): n = 5 000: 88 / 60; 10 000: 125 / 121; 20 000: 312 / 331;
-// 30 000: 630 / 696; 50 000: 1950 / 2630.
+// More than 16 input dimensions (up to 16 the digit form takes over earlier); product in us (two-use /
+// one-use form, d = 16): n = 5 000: 88 / 60; 10 000: 125 / 121; 20 000: 312 / 331; 30 000: 630 / 696; 50 000: 1950 / 2630.
 constexpr int kOtfSymMinRows = 12288;
+// Product on the fly, 11 columns, us per call (fp64 matrix pipe, the faster of its two forms / digits): n = 3 000:
+// 41 / 48; 5 000: 58 / 60 (d = 8), 66 / 64 (d = 16); 8 000: 81 / 69, 100 / 81; 20 000: 303 / 203, 358 / 261; 32 000:
+// 687 / 442, 820 / 589.  17 columns, n = 200 000, d = 8: 32 120 / 20 250.
+constexpr int kDigMinRows = 6144;
 constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 
 }  // namespace
@@ -122,7 +126,7 @@ struct bbmm_ctx {
   Buf Xa, Xb, Xs, X4, sq, Khat, L, delta, U, R, V, Z0, D4, Vp, partial, gpartial, alpha, beta, resid, st,
       tmpA, tmpB, SA, SB, u0v, dkpartial, eig, plan[3], nseg[3], 
       KUU, Gm, Ginv, Kux, AT, A, qdiag, Tp, T4, sgplan[4], sgnseg[4],
-      Ua, Ub, Us, U4, usq, TU, TW, BU, BW, dkops;
+      Ua, Ub, Us, U4, usq, TU, TW, BU, BW, dkops, rec, Pb;
   double* eig_static = nullptr;   // this device's address of `scratch`
   int* h_eig_status = nullptr;    // pinned, BBMM_EIG_NOALLOC_MAX ints
   DevState* h_st = nullptr;   // pinned
@@ -240,6 +244,14 @@ int ensure_vp(bbmm_ctx* c, int slots, int ld) {
   return ensure(c, c->Vp, bytes);
 }
 
+// Records of the block's digit operands (see launch_digits).
+int ensure_records(bbmm_ctx* c, int ng) {
+  size_t bytes = (size_t)c->np / 16 * dig_record_bytes(c->KK, ng);
+  if (bytes <= c->rec.cap) return BBMM_OK;
+  HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still use the old buffer
+  return ensure(c, c->rec, bytes);
+}
+
 // Lays out one plan on the host (bbmm_plan::lay_out_plan, which checks everything the kernel
 // relies on) and uploads it.
 int make_plan(bbmm_ctx* c, int rows_p, int cols_p, int ld, int wgs, int slot_cap, Buf& plan_buf,
@@ -342,6 +354,23 @@ int ensure_sgpr_plans(bbmm_ctx* c) {
   c->sg_tune[0] = c->sgpr_wgs[0];
   c->sg_tune[1] = c->sgpr_wgs[1];
   return BBMM_OK;
+}
+
+// Row chunks of the digit form of the on-the-fly product: one workgroup per compute unit; at most
+// kDigMaxBlocks row blocks per chunk.
+int dig_split_of(const bbmm_ctx* c, int cc) {
+  int nblk = c->np / 16, nj = dig_nj(c->KK, dig_groups(cc));
+  int strips = (nblk + 4 * nj - 1) / (4 * nj);
+  int lo = (nblk + kDigMaxBlocks - 1) / kDigMaxBlocks;
+  int s = c->otf_split > 0 ? (int)std::min<int64_t>(c->otf_split, std::min(kMaxSplit, nblk))
+                           : bbmm_plan::split_by_fill(c->np, c->num_cus, strips, 3 * c->num_cus, 0.97);
+  return std::max(lo, std::max(1, std::min(s, nblk / 4)));
+}
+
+// Whether a product of this mode and block width runs on the 8-bit matrix pipe.
+bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
+  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym != 0 && c->np >= kDigMinRows && c->KK <= 4 &&
+         dig_split_of(c, cc) <= kMaxSplit;
 }
 
 int otf_split_of(const bbmm_ctx* c) {
@@ -543,6 +572,20 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scal
     *shape = VpShape{0, ptr<int>(c->nseg[v]), v == 1 ? 512 : 1024, c->plan_slots[v]};
     *scaleV = 1.0;
     *addD = 0.0;
+  } else if (uses_digits(c, mode, cc)) {
+    int ns = dig_split_of(c, cc), ng = dig_groups(cc);
+    int rc = ensure_vp(c, ns, ld);
+    if (rc) return rc;
+    rc = ensure_records(c, ng);
+    if (rc) return rc;
+    launch_digits(c->stream, ptr<double>(c->D4), ptr<float>(c->Xb), ptr<float>(c->sq), c->np, ld, c->KK, ng,
+                  ptr<DevState>(c->st), c->rec.p);
+    if (launch_mm_otf_dig(c->stream, c->prob.kernel, c->KK, ng, c->rec.p, c->Pb.p, ptr<float>(c->sq),
+                          ptr<double>(c->Vp), c->np, ld, ns, ptr<DevState>(c->st)))
+      return fail(c, BBMM_EINVAL, "unsupported block width or input dimension");
+    *shape = VpShape{ns, nullptr, 1};
+    *scaleV = c->prob.outputscale;
+    *addD = c->prob.noise;
   } else if (mode == BBMM_MODE_ONTHEFLY && (c->otf_sym == 2 || (c->otf_sym == 1 && c->np >= kOtfSymMinRows)) &&
              ld == 16 && c->KK <= 8) {
     // every pair of tiles (I, J), (J, I) evaluated once and used for both contributions (beyond 32
@@ -635,14 +678,15 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
   // wave where n allows it (a trip costs a memory round trip; more waves overlap more of them)
   int nb_zd = std::max(nb, std::min((c->n / 16 + 3) / 4, (c->zd_blocks > 0 ? (int)c->zd_blocks : 16) * c->num_cus));
   size_t blk = (size_t)c->np * ld;
-  // U, D, the coefficient histories and done / iters_run (next to each other at the end of
+  // U, D, the coefficient histories and dmax / dflag / done / iters_run (next to each other in
   // DevState), zeroed by one launch
   {
     size_t hist = (size_t)2 * BBMM_MAXP * BBMM_MAXC;   // words of one history of doubles
-    ZeroSegs z = {{c->U.p, c->D4.p, c->alpha.p, c->beta.p, c->resid.p, &st->done},
-                  {2 * blk, 2 * blk, hist, hist, hist, 2}, 6};
+    ZeroSegs z = {{c->U.p, c->D4.p, c->alpha.p, c->beta.p, c->resid.p, &st->dmax[0]},
+                  {2 * blk, 2 * blk, hist, hist, hist, 2 * BBMM_MAXC + 2}, 6};
     launch_fill_multi0(s, z);
   }
+  int track = uses_digits(c, mode, cc) ? 1 : 0;
   double noise = c->prob.noise;
   int nb_ur = ur_blocks(c, c->n, ld);
   double* pdv = ptr<double>(c->gpartial);
@@ -654,7 +698,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     // Alg. 1/2: r_0 = b - K_hat u_0 for the current solution u_0 -- one more product, of the block
     // [u_init, 0, ..]; the pass above has left |b| (the residuals stay relative to it), the second
     // pass redoes rho_0 for the new residual
-    launch_warm_rhs(s, warm, c->n, ld, ptr<double>(c->D4));
+    launch_warm_rhs(s, warm, c->n, ld, ptr<double>(c->D4), track, st);
     VpShape ns{0, nullptr, 1};
     double scaleV = 1.0, addD = 0.0;
     int rc = stage_mm(c, mode, cc, ld, &ns, &scaleV, &addD);
@@ -667,7 +711,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
               ptr<double>(c->beta), ptr<double>(c->resid));
   }
   launch_zd(s, 1, c->n, ld, c->kp, noise, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4),
-            ptr<double>(c->Z0), st, nb);
+            ptr<double>(c->Z0), track, st, nb);
   // the loop's kernels take noise, tolerance and the (scale, diagonal) pair of the product from the
   // device state, so their launches are the same for any hyperparameter values
   {
@@ -711,7 +755,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
                 ptr<double>(c->U), ptr<double>(c->R), ptr<double>(c->L), st, pdv, nb, pur, nb_ur, j,
                 ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid));
       launch_zd(ls, 0, c->n, ld, c->kp, -1.0, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4),
-                ptr<double>(c->Z0), st, nb_zd);
+                ptr<double>(c->Z0), track, st, nb_zd);
     }
     c->stream = user;
     return rc;
@@ -1006,7 +1050,7 @@ int bbmm_destroy(bbmm_ctx* c) {
                  &c->nseg[1], &c->nseg[2], &c->KUU, &c->Gm, &c->Ginv, &c->Kux, &c->AT, &c->A, &c->qdiag, &c->Tp, &c->T4,
                  &c->sgplan[0], &c->sgplan[1], &c->sgplan[2], &c->sgplan[3], &c->sgnseg[0], &c->sgnseg[1],
                  &c->sgnseg[2], &c->sgnseg[3], &c->Ua, &c->Ub, &c->Us, &c->U4, &c->usq, &c->TU, &c->TW, &c->BU,
-                 &c->BW, &c->dkops};
+                 &c->BW, &c->dkops, &c->rec, &c->Pb};
   for (Buf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
@@ -1128,7 +1172,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
       {&c->gpartial, sizeof(double) * 40 * (BBMM_MAXK * BBMM_MAXK + (BBMM_MAXK + 1) * BBMM_MAXC)},
       {&c->alpha, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->beta, sizeof(double) * BBMM_MAXP * BBMM_MAXC},
       {&c->resid, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->st, sizeof(DevState)},
-      {&c->tmpA, blk}, {&c->tmpB, blk},
+      {&c->tmpA, blk}, {&c->tmpB, blk}, {&c->Pb, c->KK <= 4 ? 4 * opx : 0},
       {&c->SA, np * 64 * sizeof(float)}, {&c->SB, np * 64 * sizeof(float)}, {&c->u0v, np * sizeof(float)},
   };
   for (auto& w : want) {
@@ -1146,6 +1190,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   launch_colmean(s, in->X, c->n, c->d, ptr<DevState>(c->st), ptr<double>(c->partial), ptr<double>(c->gpartial));
   launch_prep_x(s, in->X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st), ptr<float>(c->Xa),
                 ptr<float>(c->Xb), ptr<float>(c->Xs), ptr<float>(c->X4), ptr<float>(c->sq));
+  if (c->KK <= 4) launch_split_x(s, ptr<float>(c->Xb), c->np, c->KK, c->Pb.p);
   HIPCHK(c, hipGetLastError());
   c->is_setup = true;
   return BBMM_OK;
@@ -1203,8 +1248,9 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   if (!M || !V || cc < 1 || cc > BBMM_MAXC) return fail(c, BBMM_EINVAL, "bad block");
   int ld = ld_for((int)cc);
   hipStream_t s = c->stream;
-  launch_fill_bytes0(s, &ptr<DevState>(c->st)->done, 2 * sizeof(int));
-  launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4));
+  launch_fill_bytes0(s, &ptr<DevState>(c->st)->dmax[0], (2 * BBMM_MAXC + 2) * sizeof(int));
+  launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), uses_digits(c, mode, (int)cc) ? 1 : 0,
+                 ptr<DevState>(c->st));
   VpShape ns{0, nullptr, 1};
   double scaleV = 1.0, addD = 0.0;
   rc = stage_mm(c, mode, (int)cc, ld, &ns, &scaleV, &addD);
@@ -1311,7 +1357,7 @@ int bbmm_predict_mean(bbmm_ctx* c, const float* Xstar, int64_t ns, const float* 
     if (!c->sgpr_built) return fail(c, BBMM_EINVAL, "bbmm_sgpr_build must run first");
     launch_fill_bytes0(s, &ptr<DevState>(c->st)->done, sizeof(int));
     launch_fill_f64(s, ptr<double>(c->tmpA), (size_t)c->np * 16, 0.0);
-    launch_warm_rhs(s, u0, c->n, 16, ptr<double>(c->tmpA));
+    launch_warm_rhs(s, u0, c->n, 16, ptr<double>(c->tmpA), 0, ptr<DevState>(c->st));
     VpShape sh{0, nullptr, 1};
     rc = sgpr_first_pass(c, 16, ptr<double>(c->tmpA), &sh);
     if (rc) return rc;

@@ -36,10 +36,13 @@ struct DevState {
   int active[BBMM_MAXC];
   int m_valid[BBMM_MAXC];
   int piv[BBMM_MAXK + 1];
+  unsigned dmax[BBMM_MAXC];   // per column of D: largest high word of |D| (its exponent scales the digits)
+  int dflag[BBMM_MAXC];       // per column of D: 1 = holds +inf, 2 = -inf, 4 = NaN   (zeroed with done)
   int done;         // set when the tolerance test passed; later kernels of the loop exit at once
   int iters_run;
   int status;       // BBMM_* code raised on the device (0 = ok)
   int rank;         // preconditioner rank actually built
+  int xbad;         // a coordinate of X is not finite (the digit products then return NaN throughout)
   unsigned counter[8][40];   // arrival tickets per kernel family: [0] final, [1 + g] group g
 };
 
@@ -78,8 +81,10 @@ void launch_fill_multi0(hipStream_t s, const ZeroSegs& z);
 void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, double* partial,
                     double* gpartial);
 void launch_prep_x(hipStream_t s, const float* X, int n, int d, int np, int KK, HypArgs hyp,
-                   const DevState* st, float* Xa, float* Xb, float* Xs, float* X4, float* sq);
-void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld, double* D4);
+                   DevState* st, float* Xa, float* Xb, float* Xs, float* X4, float* sq);
+// track != 0: leave the columns' magnitudes in st->dmax / st->dflag (zero beforehand), as launch_digits needs
+void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld, double* D4, int track,
+                    DevState* st);
 void launch_unpack_rows(hipStream_t s, const double* src, int ld, int n, int c, float* dst);
 void launch_unpack_rows_f64(hipStream_t s, const double* src, int ld, int n, int c, double* dst);
 void launch_pack_rows(hipStream_t s, const float* src, int n, int c, int ld, double* dst);
@@ -87,7 +92,7 @@ void launch_pack_cols_at(hipStream_t s, const float* src, int n, int c, int ld, 
 // tri: src is the packed upper triangle of a symmetric matrix (see launch_mm_sym)
 void launch_copy_block(hipStream_t s, const float* src, size_t pw, size_t rows_p, int tri, int row0,
                        int nrows, int col0, int ncols, float* dst);
-void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* D4);
+void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* D4, int track, DevState* st);
 void launch_warm_apply(hipStream_t s, const float* u_init, const double* V, int n, int ld, double* U,
                        double* R);
 void launch_vreduce(hipStream_t s, const double* Vp, VpShape shape, int n, int np, int ld, double scaleV,
@@ -115,7 +120,7 @@ void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noi
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
                double* alpha_hist, double* beta_hist, double* resid_hist);
 void launch_zd(hipStream_t s, int init, int n, int ld, int kp, double noise, const double* R,
-               const double* L, double* D4, double* Z0, DevState* st, int nblocks);
+               const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks);
 void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, const double* R,
                          const double* L, double* Z, DevState* st, int nblocks);
 void launch_cross_block(hipStream_t s, const float* X, const float* Xs, int n, int ns, int ld, HypArgs hyp,
@@ -199,6 +204,19 @@ int launch_mm_mat(hipStream_t s, const float* Khat, const double* D4, double* Vp
                   int cols);
 #define BBMM_SGPR_PANEL 512   // column-panel width of the transposed SGPR root
 // c: number of columns really used (<= ld); lets 17..20 columns run one MFMA group plus vector FMAs
+// ---- launchers implemented in kernels_dig.hip: products on the 8-bit matrix pipe ------------
+// The block D (and the coordinates) as digit operands, one record per 16-row block (needs st->dmax / st->dflag
+// of the columns of D); ng = dig_groups(columns in use).
+constexpr int kDigMaxBlocks = 2046;   // 16-row blocks one accumulator may sum without overflow
+int dig_groups(int c);
+int dig_nj(int KK, int ng);
+size_t dig_record_bytes(int KK, int ng);
+void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float* sq, int np, int ld, int KK, int ng,
+                   const DevState* st, void* rec);
+// column-side coordinates (from Xb: MFMA operand order) as bf16 pieces: 16 np * 4 KK bytes
+void launch_split_x(hipStream_t s, const float* Xb, int np, int KK, void* Pb);
+int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec, const void* Pb, const float* sq,
+                      double* Vp, int np, int ld, int nsplit, const DevState* st);
 int launch_mm_otf(hipStream_t s, int kernel, int KK, const float* Xa, const float* Xb, const float* sq,
                   const double* D4, double* Vp, int np, int ld, int c, int nsplit, const DevState* st);
 // The same product with every pair of tiles (I, J), (J, I) evaluated once and used for both of its

@@ -28,6 +28,14 @@ __device__ inline size_t d4_index(int i, int q, int ld) {
   return (size_t)(i >> 2) * (size_t)(4 * ld) + (size_t)q * 4 + (size_t)(i & 3);
 }
 
+// Magnitude of a block's columns for the digit products: largest high word of |D| per column, and
+// which kinds of non-finite value it holds (all in DevState; max and or, so the order is irrelevant).
+__device__ inline unsigned track_hi(double v, unsigned hi, int& flag) {
+  unsigned h = (unsigned)__double2hiint(v) & 0x7fffffffu;
+  if (h >= 0x7ff00000u) flag |= (v != v) ? 4 : (v > 0.0 ? 1 : 2);
+  return max(hi, h);
+}
+
 // Returns true in every thread of exactly one block: the one that arrives last.
 __device__ inline bool last_block_arrives(unsigned* counter) {
   __shared__ int is_last;
@@ -161,13 +169,14 @@ __global__ __launch_bounds__(VT) void k_colmean(const float* __restrict__ X, int
 //   sq[i] = sum_dim xs^2
 // with xs[i][dim] = (X[i][dim] - mean[dim]) * xscale[dim], zero for padding rows / dims.
 __global__ void k_prep_x(const float* __restrict__ X, int n, int d, int np, int KK, HypArgs hyp,
-                         const DevState* __restrict__ st, float* __restrict__ Xa,
+                         DevState* st, float* __restrict__ Xa,
                          float* __restrict__ Xb, float* __restrict__ Xs, float* __restrict__ X4,
                          float* __restrict__ sq) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
   int dp = 4 * KK;
   float acc = 0.f;
+  bool bad = false;
   int b = i >> 4, r16 = i & 15;
   for (int dim = 0; dim < dp; ++dim) {
     float v = 0.f;
@@ -179,19 +188,30 @@ __global__ void k_prep_x(const float* __restrict__ X, int n, int d, int np, int 
     Xs[(size_t)i * dp + dim] = v;
     X4[(size_t)(i >> 2) * (size_t)(4 * dp) + (size_t)dim * 4 + (i & 3)] = v;
     acc = fmaf(v, v, acc);
+    bad |= !(fabsf(v) < 1e38f);
   }
   sq[i] = acc;
+  if (bad || !(acc < 3e38f)) st->xbad = 1;
 }
 
 // Row-major n x c (stride c) -> quad-swizzled D4 with np rows and ld columns, zero padded.
-__global__ void k_pack_d4(const float* __restrict__ M, int n, int c, int np, int ld,
-                          double* __restrict__ D4) {
+// track: the columns' magnitudes are left in st for a digit product (np * ld is a multiple of the
+// block size and the block size of ld, so a thread's column is threadIdx.x % ld).
+__global__ __launch_bounds__(VT) void k_pack_d4(const float* __restrict__ M, int n, int c, int np, int ld,
+                                                 double* __restrict__ D4, int track, DevState* st) {
+  __shared__ unsigned smax[BBMM_MAXC];
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t total = (size_t)np * ld;
-  if (idx >= total) return;
   int i = (int)(idx / ld), q = (int)(idx % ld);
   double v = (i < n && q < c) ? (double)M[(size_t)i * c + q] : 0.0;
   D4[d4_index(i, q, ld)] = v;
+  if (!track) return;
+  if (threadIdx.x < BBMM_MAXC) smax[threadIdx.x] = 0u;
+  __syncthreads();
+  int flag = 0;
+  atomicMax(&smax[q], track_hi(v, 0u, flag));
+  if (flag) atomicOr(&st->dflag[q], flag);
+  __syncthreads();
+  if ((int)threadIdx.x < ld) atomicMax(&st->dmax[threadIdx.x], smax[threadIdx.x]);
 }
 
 // padded row-major (stride ld) -> dense n x c
@@ -269,9 +289,18 @@ __global__ void k_vreduce(const double* __restrict__ Vp, VpShape shape, int n, i
 
 // Warm start of column 0 (Alg. 1/2 take the current solution as input): the quad-swizzled
 // right-hand side gets u_init in column 0 (the rest of the block was zero-filled) ...
-__global__ void k_warm_rhs(const float* __restrict__ u_init, int n, int ld, double* __restrict__ D4) {
+__global__ void k_warm_rhs(const float* __restrict__ u_init, int n, int ld, double* __restrict__ D4,
+                           int track, DevState* st) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) D4[d4_index(i, 0, ld)] = (double)u_init[i];
+  double v = (i < n) ? (double)u_init[i] : 0.0;
+  if (i < n) D4[d4_index(i, 0, ld)] = v;
+  if (!track) return;
+  int flag = 0;
+  unsigned hi = track_hi(v, 0u, flag);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) hi = max(hi, (unsigned)__shfl_xor((int)hi, o, 64));
+  if ((threadIdx.x & 63) == 0) atomicMax(&st->dmax[0], hi);
+  if (flag) atomicOr(&st->dflag[0], flag);
 }
 
 // ... and with V = K_hat [u_init, 0, ..] the iteration starts from U[:,0] = u_init, R[:,0] = b - V[:,0].
@@ -906,6 +935,10 @@ __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double n
     tot[e] = t;
   }
   if (done) return;                     // block-uniform
+  if ((int)threadIdx.x < BBMM_MAXC) {   // the direction update that follows measures the new block
+    st->dmax[threadIdx.x] = 0u;
+    st->dflag[threadIdx.x] = 0;
+  }
   Gs[threadIdx.x] = g_mine;             // G^{-1}, zero outside the leading k x k lower triangle
   __syncthreads();
   // C^{-1} (L^T r) for all columns at once: w = G^{-1} y, quad = w^T w, x = G^{-T} w; thread
@@ -985,10 +1018,11 @@ __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double n
 //     A wave takes 16 rows per step: L Qt is KP / 4 fp64 MFMAs whose result register r holds
 //     row 4 r + lane / 16, column lane % 16 -- rows in which R and the quad-swizzled D are
 //     contiguous across the wave.
+//     track: the columns' magnitudes of the new D are left in st for a digit product.
 template <int KP, int NQ, int MODE>
 __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __restrict__ R,
                                             const double* __restrict__ L, double* __restrict__ D4,
-                                            double* __restrict__ Z, const DevState* __restrict__ st) {
+                                            double* __restrict__ Z, int track, DevState* st) {
   constexpr int LD = 16 * NQ;
   constexpr int KS = KP / 4;
   if (MODE != 2 && st->done) return;
@@ -1005,6 +1039,13 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
   }
   double inv_noise = 1.0 / noise;
   constexpr int NW = VT / 64;
+  unsigned hi[NQ];
+  int flag[NQ];
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) {
+    hi[qb] = 0u;
+    flag[qb] = 0;
+  }
   int gw = blockIdx.x * NW + wave, nw = gridDim.x * NW;
   for (int i0 = 16 * gw; i0 < n; i0 += 16 * nw) {   // wave-uniform bounds: MFMA needs all lanes
     f64x4 acc[NQ];
@@ -1030,15 +1071,32 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
             Z[idx] = z;
           } else {
             size_t di = d4_index(i, col, LD);
-            if (MODE == 1) {
-              Z[idx] = z;
-              D4[di] = z;
-            } else {
-              D4[di] = z + beta[qb] * D4[di];
-            }
+            double d = z;
+            if (MODE == 1) Z[idx] = z;
+            else d = z + beta[qb] * D4[di];
+            D4[di] = d;
+            hi[qb] = track_hi(d, hi[qb], flag[qb]);
           }
         }
       }
+    }
+  }
+  if (MODE != 2 && track) {
+    __shared__ unsigned smax[NW][LD];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      unsigned h = hi[qb];
+      h = max(h, (unsigned)__shfl_xor((int)h, 16, 64));
+      h = max(h, (unsigned)__shfl_xor((int)h, 32, 64));
+      if (g == 0) smax[wave][qb * 16 + q] = h;
+      if (flag[qb]) atomicOr(&st->dflag[qb * 16 + q], flag[qb]);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < LD) {
+      unsigned h = 0u;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) h = max(h, smax[w][threadIdx.x]);
+      atomicMax(&st->dmax[threadIdx.x], h);
     }
   }
 }
@@ -1448,12 +1506,14 @@ void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, d
 }
 
 void launch_prep_x(hipStream_t s, const float* X, int n, int d, int np, int KK, HypArgs hyp,
-                   const DevState* st, float* Xa, float* Xb, float* Xs, float* X4, float* sq) {
+                   DevState* st, float* Xa, float* Xb, float* Xs, float* X4, float* sq) {
   k_prep_x<<<blocks_for(np, 256), 256, 0, s>>>(X, n, d, np, KK, hyp, st, Xa, Xb, Xs, X4, sq);
 }
 
-void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld, double* D4) {
-  k_pack_d4<<<blocks_for((size_t)np * ld, 256), 256, 0, s>>>(M, n, c, np, ld, D4);
+void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld, double* D4, int track,
+                    DevState* st) {
+  // np is a multiple of 256, ld 16 or 32: whole blocks
+  k_pack_d4<<<(int)((size_t)np * ld / VT), VT, 0, s>>>(M, n, c, np, ld, D4, track, st);
 }
 
 void launch_unpack_rows(hipStream_t s, const double* src, int ld, int n, int c, float* dst) {
@@ -1483,8 +1543,8 @@ void launch_vreduce(hipStream_t s, const double* Vp, VpShape shape, int n, int n
   k_vreduce<<<blocks_for((size_t)n * ld, 256), 256, 0, s>>>(Vp, shape, n, np, ld, scaleV, addD, D4, V);
 }
 
-void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* D4) {
-  k_warm_rhs<<<(n + 255) / 256, 256, 0, s>>>(u_init, n, ld, D4);
+void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* D4, int track, DevState* st) {
+  k_warm_rhs<<<(n + 255) / 256, 256, 0, s>>>(u_init, n, ld, D4, track, st);
 }
 
 void launch_warm_apply(hipStream_t s, const float* u_init, const double* V, int n, int ld, double* U,
@@ -1585,15 +1645,15 @@ void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noi
 }
 
 void launch_zd(hipStream_t s, int init, int n, int ld, int kp, double noise, const double* R,
-               const double* L, double* D4, double* Z0, DevState* st, int nblocks) {
+               const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks) {
   int nq = ld / 16;
   if (init) {
 #define ZD_INIT(KP, NQ) k_zd<KP, NQ, 1>
-    DISPATCH_KP_NQ(ZD_INIT, kp, nq, nblocks, VT, n, noise, R, L, D4, Z0, st);
+    DISPATCH_KP_NQ(ZD_INIT, kp, nq, nblocks, VT, n, noise, R, L, D4, Z0, track, st);
 #undef ZD_INIT
   } else {
 #define ZD_ITER(KP, NQ) k_zd<KP, NQ, 0>
-    DISPATCH_KP_NQ(ZD_ITER, kp, nq, nblocks, VT, n, noise, R, L, D4, Z0, st);
+    DISPATCH_KP_NQ(ZD_ITER, kp, nq, nblocks, VT, n, noise, R, L, D4, Z0, track, st);
 #undef ZD_ITER
   }
 }
@@ -1602,7 +1662,7 @@ void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, con
                          const double* L, double* Z, DevState* st, int nblocks) {
   int nq = ld / 16;
 #define ZD_APPLY(KP, NQ) k_zd<KP, NQ, 2>
-  DISPATCH_KP_NQ(ZD_APPLY, kp, nq, nblocks, VT, n, noise, R, L, (double*)nullptr, Z, st);
+  DISPATCH_KP_NQ(ZD_APPLY, kp, nq, nblocks, VT, n, noise, R, L, (double*)nullptr, Z, 0, st);
 #undef ZD_APPLY
 }
 

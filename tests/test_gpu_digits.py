@@ -1,0 +1,125 @@
+"""GPU: the on-the-fly product on the 8-bit matrix pipe (at most 16 input dimensions, from 6144 padded rows
+on) against fp64 kernel rows, over block widths, dimensions and sizes at the edges of its tiles."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import bbmm_oracle as O  # noqa: E402
+from paper_1809_11165_amd import inputs  # noqa: E402
+
+N0 = 6144            # first size of the route; 16-row tiles, workgroups of 4 * (2 .. 6) tiles, pads of 256
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1809_11165_amd import binding
+    c = binding.Context(0)
+    yield c
+    c.close()
+
+
+def _problem(n, d, kernel, X=None, noise=0.1):
+    from paper_1809_11165_amd import binding
+    w = inputs.tiny(n, d, kernel=kernel, ard=d > 1, t=1, k=1, iters=1, noise=noise, seed=3)
+    if X is not None:
+        w.X = X.astype(np.float32)
+    return w, binding.problem_from_workload(w, inputs.ONTHEFLY)
+
+
+def _rows(w, rows, M):
+    """Rows of K_hat M in fp64 and the bound on their error.
+
+    The squared distance is formed in fp32 from |x|^2 + |x'|^2 - 2 x.x' of scaled, centred coordinates rounded to
+    fp32: every one of its roundings is at most 2^-24 of |x|^2 + |x'|^2, and four of them are allowed for (two
+    squared norms, the product, the last addition; longer sums round at random).  The entry moves by what the
+    kernel function makes of that, by 2^-22 of itself in its own evaluation, and by half a unit of the
+    fixed-point scale; the sum over the row is bounded term by term.  The result is rounded to fp32."""
+    X = w.X.astype(np.float64)
+    K = O.kernel_block(w.kernel, X[rows], X, w.lengthscale, w.outputscale)
+    xs = (X - X.mean(axis=0)) / w.lengthscale
+    sq = (xs * xs).sum(axis=1)
+    r2 = np.maximum(sq[rows][:, None] + sq[None, :] - 2.0 * xs[rows] @ xs.T, 0.0)
+    delta = 4 * 2.0 ** -24 * (sq[rows][:, None] + sq[None, :])
+
+    def k(r2):
+        if w.kernel == inputs.RBF:
+            return w.outputscale * np.exp(-0.5 * r2)
+        a = np.sqrt(5.0 * r2)
+        return w.outputscale * (1.0 + a + a * a / 3.0) * np.exp(-a)
+
+    dK = k(np.maximum(r2 - delta, 0.0)) - k(r2 + delta) + 2.0 ** -22 * K + 0.5 * w.outputscale / 2055208960.0
+    dK[np.arange(len(rows)), rows] = 2.0 ** -22 * w.outputscale
+    K[np.arange(len(rows)), rows] = w.outputscale + w.noise
+    ref = K @ M
+    return ref, dK @ np.abs(M) + 2.0 ** -23 * np.abs(ref)
+
+
+def _check(V, ref, bound):
+    err = np.abs(V - ref)
+    assert np.all(err <= bound), float((err / np.maximum(bound, 1e-300)).max())
+
+
+@pytest.mark.parametrize("kernel", [inputs.RBF, inputs.MATERN52])
+@pytest.mark.parametrize("n,d,c", [(N0, 1, 1), (N0 + 1, 3, 4), (N0 - 100, 4, 5), (6400, 4, 8), (6401, 5, 9), (7000, 8, 12),
+                                   (6999, 8, 13), (6656, 9, 16), (6657, 16, 17), (7169, 16, 18), (6300, 2, 19),
+                                   (6200, 13, 24), (6500, 7, 25), (6911, 16, 32), (9000, 16, 11), (8193, 4, 32)])
+def test_digit_product_against_fp64_rows(ctx, kernel, n, d, c):
+    import torch
+    w, prob = _problem(n, d, kernel)
+    rng = np.random.default_rng(n + 31 * c)
+    M = rng.standard_normal((n, c)).astype(np.float32)
+    M[:, -1] *= 1e-25                                   # a scale of its own per column
+    if c > 1:
+        M[:, 0] = 1.0 + 0.1 * M[:, 0]                   # no cancellation
+    if c > 2:
+        M[:, 1] = 0.0
+    if c > 3:
+        M[:, 2] *= np.exp(3.0 * rng.standard_normal(n)) # one entry far above the others
+    ctx.bbmm_setup(prob)
+    V = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, torch.from_numpy(M).cuda()).cpu().numpy().astype(np.float64)
+    rows = np.unique(np.concatenate([[0, 15, 16, n - 1, n - 2, n // 2], rng.integers(0, n, 60)]))
+    M64 = M.astype(np.float64)
+    _check(V[rows], *_rows(w, rows, M64))
+    if c > 2:
+        assert not V[:, 1].any()
+
+
+@pytest.mark.parametrize("kernel", [inputs.RBF, inputs.MATERN52])
+def test_digit_product_with_near_duplicate_points(ctx, kernel):
+    """Entries at and just below one (the largest digits)."""
+    import torch
+    n, d = 6300, 4
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal((n, d))
+    X[1::2] = X[0:n - 1:2] + 1e-3 * rng.standard_normal((n // 2, d)) * (rng.random((n // 2, 1)) < 0.5)
+    w, prob = _problem(n, d, kernel, X=X)
+    M = rng.standard_normal((n, 11)).astype(np.float32)
+    ctx.bbmm_setup(prob)
+    V = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, torch.from_numpy(M).cuda()).cpu().numpy().astype(np.float64)
+    rows = rng.integers(0, n, 80)
+    M64 = M.astype(np.float64)
+    _check(V[rows], *_rows(w, rows, M64))
+
+
+def test_digit_product_of_non_finite_blocks(ctx):
+    """A column with an infinity or a NaN gets what the fp64 form gives; the others are not touched."""
+    import torch
+    w, prob = _problem(6200, 4, inputs.RBF)
+    M = np.random.default_rng(1).standard_normal((6200, 6)).astype(np.float32)
+    M[7, 1], M[9, 2], M[11, 3] = np.inf, -np.inf, np.nan
+    M[3, 4], M[4, 4] = np.inf, -np.inf
+    Md = torch.from_numpy(M).cuda()
+    ctx.bbmm_setup(prob)
+    V = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, Md).cpu().numpy()
+    ctx.bbmm_tune("otf_sym", 0)
+    try:
+        ref = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, Md).cpu().numpy()
+    finally:
+        ctx.bbmm_tune("otf_sym", 1)
+    np.testing.assert_allclose(V[:, [0, 5]], ref[:, [0, 5]], rtol=0, atol=2e-6 * np.abs(ref[:, [0, 5]]).max())
+    np.testing.assert_array_equal(V[:, 1:5], ref[:, 1:5])
+    w.X[5, 2] = np.nan
+    from paper_1809_11165_amd import binding
+    ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+    assert np.isnan(ctx.bbmm_kernel_mm(inputs.ONTHEFLY, Md).cpu().numpy()).all()
