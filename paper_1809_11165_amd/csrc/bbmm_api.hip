@@ -1363,12 +1363,12 @@ int bbmm_predict_mean(bbmm_ctx* c, const float* Xstar, int64_t ns, const float* 
     if (rc) return rc;
     launch_sgpr_mid_rows(s, ptr<double>(c->Tp), sh, c->mp, 16, ptr<double>(c->TU));
     launch_sgpr_bsolve(s, ptr<double>(c->Ginv), ptr<double>(c->TU), c->mp, 16, ptr<double>(c->BU));
-    launch_cross_dot(s, c->prob.Uind, Xstar, c->m, (int)ns, c->hyp, ptr<double>(c->BU), 16, 0, 0.0, 1.0, mean);
+    launch_cross_dot(s, c->prob.Uind, Xstar, c->m, (int)ns, c->hyp, ptr<double>(c->BU), 16, 0, 0.0, 1.0,
+                     ptr<double>(c->partial), mean);
     HIPCHK(c, hipGetLastError());
     return BBMM_OK;
   }
-  launch_pack_rows(s, u0, c->n, 1, 16, ptr<double>(c->tmpB));
-  launch_cross_dot(s, c->prob.X, Xstar, c->n, (int)ns, c->hyp, ptr<double>(c->tmpB), 16, 0, 0.0, 1.0, mean);
+  launch_cross_dot_f32(s, c->prob.X, Xstar, c->n, (int)ns, c->hyp, u0, ptr<double>(c->partial), mean);
   HIPCHK(c, hipGetLastError());
   return BBMM_OK;
 }
@@ -1406,7 +1406,7 @@ int bbmm_predict_var(bbmm_ctx* c, int32_t mode, const float* Xstar, int64_t ns, 
     rc = stage_mbcg(c, mode, (int)ns, ld);
     if (rc) return rc;
     launch_cross_dot(s, c->prob.X, Xstar, c->n, (int)ns, c->hyp, ptr<double>(c->U), ld, 1,
-                     c->prob.outputscale, -1.0, var);
+                     c->prob.outputscale, -1.0, ptr<double>(c->partial), var);
   }
   rc = fetch_state(c, true);
   if (rc) return rc;

@@ -125,8 +125,11 @@ void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, con
                          const double* L, double* Z, DevState* st, int nblocks);
 void launch_cross_block(hipStream_t s, const float* X, const float* Xs, int n, int ns, int ld, HypArgs hyp,
                         double* B);
-void launch_cross_dot(hipStream_t s, const float* X, const float* Xs, int n, int ns, HypArgs hyp,
-                      const double* V, int ldv, int percol, double prior, double sign, float* out);
+// partial: room for at least 512 * 1024 doubles
+void launch_cross_dot(hipStream_t s, const float* X, const float* Xs, int n, int ns, HypArgs hyp, const double* V, int ldv,
+                      int percol, double prior, double sign, double* partial, float* out);
+void launch_cross_dot_f32(hipStream_t s, const float* X, const float* Xs, int n, int ns, HypArgs hyp, const float* v,
+                          double* partial, float* out);
 // sweeps_per_row: trip budget of the tridiagonal eigen-solver per matrix row (sweeps and deflations;
 // about two sweeps per eigenvalue are needed); a matrix that is not reduced within it is reported
 // through st->status / status[] as BBMM_ENOCONV instead of being used.
