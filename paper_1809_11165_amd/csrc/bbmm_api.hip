@@ -48,6 +48,10 @@ constexpr int kOtfSymMinRows = 12288;
 // 41 / 48; 5 000: 58 / 60 (d = 8), 66 / 64 (d = 16); 8 000: 81 / 69, 100 / 81; 20 000: 303 / 203, 358 / 261; 32 000:
 // 687 / 442, 820 / 589.  17 columns, n = 200 000, d = 8: 32 120 / 20 250.
 constexpr int kDigMinRows = 6144;
+// Materialised product by 64-column workgroups (k_mm_mat_small) up to this size, where the matrix (256 MB) still fits
+// the memory-side cache: us per product call with 11 columns, k_mm_mat / k_mm_mat_small: n = 1 000: 28 / 18; 2 500: 35 / 21;
+// 5 000: 48 / 37; 8 000: 70 / 57; 10 000: 95 / 105.  16 columns: 34 / 18; 43 / 22; 55 / 39; 70 / 57; 94 / 105.
+constexpr int kMatSmallMaxRows = 8192;
 constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 
 }  // namespace
@@ -250,6 +254,16 @@ int ensure_records(bbmm_ctx* c, int ng) {
   if (bytes <= c->rec.cap) return BBMM_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still use the old buffer
   return ensure(c, c->rec, bytes);
+}
+
+// Row chunks of a materialised product with a 16-column block on the kernel for small matrices; 0: too large
+// for it, or the number of workgroups is tuned.  About 192 workgroups do best (n = 2 500: 160 workgroups 20.8 us,
+// 280: 27.1, 520: 31.9; n = 5 000: 160: 36.6, 320: 42.5; n = 8 000: 126: 83.1, 378: 57.8): more of them
+// leave more partial results, and every wave should have a step.
+int mat_split_of(const bbmm_ctx* c, int ld) {
+  if (ld != 16 || c->mat_wgs > 0 || c->np > kMatSmallMaxRows) return 0;
+  int groups = c->np / 64, steps = c->np / 16;
+  return std::max(1, std::min((192 + groups / 2) / groups, steps / 8));
 }
 
 // Lays out one plan on the host (bbmm_plan::lay_out_plan, which checks everything the kernel
@@ -557,6 +571,17 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scal
                         ptr<int>(c->sym.first1), c->sym.wgs[1], ptr<int>(c->sym.base), ptr<DevState>(c->st)))
         return fail(c, BBMM_EINVAL, "unsupported block width");
       *shape = VpShape{0, ptr<int>(c->sym.tot), BBMM_SYM_PANEL};
+      *scaleV = 1.0;
+      *addD = 0.0;
+      return BBMM_OK;
+    }
+    if (int ns = mat_split_of(c, ld)) {
+      int rc = ensure_vp(c, ns, ld);
+      if (rc) return rc;
+      if (launch_mm_mat_small(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ns,
+                              ptr<DevState>(c->st), c->khat_pw, c->np, cc))
+        return fail(c, BBMM_EINVAL, "unsupported layout of the stored matrix");
+      *shape = VpShape{ns, nullptr, 1, ns};
       *scaleV = 1.0;
       *addD = 0.0;
       return BBMM_OK;

@@ -206,6 +206,9 @@ int launch_mm_sym(hipStream_t s, const float* Ktri, const double* D4, double* Vp
 int launch_mm_mat(hipStream_t s, const float* Khat, const double* D4, double* Vp, int np, int ld,
                   const MmPlan* plan, int wgs, const DevState* st, int panel_width, int panel_rows,
                   int cols);
+// The same for ld = 16 and a small np (a multiple of 256): nsplit row chunks, one partial result each.
+int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, double* Vp, int np, int nsplit, const DevState* st,
+                        int panel_width, int panel_rows, int cols);
 #define BBMM_SGPR_PANEL 512   // column-panel width of the transposed SGPR root
 // c: number of columns really used (<= ld); lets 17..20 columns run one MFMA group plus vector FMAs
 // ---- launchers implemented in kernels_dig.hip: products on the 8-bit matrix pipe ------------

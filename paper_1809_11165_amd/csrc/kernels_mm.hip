@@ -275,6 +275,91 @@ __global__ __launch_bounds__(256, 2) void k_mm_mat(const float* __restrict__ Kha
   }
 }
 
+// The same product for a small matrix, where k_mm_mat has too few workgroups (one strip of 1024 columns at
+// n = 1 000) and leaves too many partial results.  A workgroup takes 64 columns and a chunk of rows, its MS_NW
+// waves every MS_NW-th 16-row step of it, two steps requested ahead; their sums meet in LDS, so a chunk
+// leaves one partial result.  Bound by latency (n = 1 000) to HBM (n = 12 000).
+// Measured, 11 columns, k_mm_mat and the sum of its partial results -> this and its sum: see mat_split_of.
+constexpr int MS_NW = 8;
+
+template <bool NARROW>
+__global__ __launch_bounds__(64 * MS_NW, 2) void k_mm_mat_small(const float* __restrict__ Khat, const double* __restrict__ D4,
+                                                                 double* __restrict__ Vp, int np, int pw, size_t panel_stride,
+                                                                 int ldk, int nsplit, const DevState* __restrict__ st) {
+  if (st->done) return;
+  constexpr int NA = NARROW ? 12 : 16;                    // accumulator doubles per lane
+  __shared__ double red[MS_NW][NA][64];
+  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int jc = lane & 15, g = lane >> 4;
+  int split = blockIdx.x % nsplit, col0 = (blockIdx.x / nsplit) * 64;
+  int steps = np >> 4;
+  int s0 = (int)((long long)steps * split / nsplit), s1 = (int)((long long)steps * (split + 1) / nsplit);
+  f64x4 acc[1][4][1];
+  double accn[1][4][3];
+#pragma unroll
+  for (int cc = 0; cc < 4; ++cc) {
+    acc[0][cc][0] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) accn[0][cc][q] = 0.0;
+  }
+  const float* kp = Khat + (size_t)(col0 / pw) * panel_stride + (size_t)(g * 4) * ldk + (size_t)(col0 % pw + 4 * jc);
+  constexpr int PF = 3;                                   // steps in flight
+  f32x4 kv[PF][4];
+  f64x4 dop[PF][NARROW ? 3 : 1];
+  auto request = [&](int u, int step) {
+    int sc = min(step, s1 - 1);                           // (past the end: the last step again, not used)
+    mm_mat_load_d<1, NARROW>(D4, sc * 16, jc, g, dop[u]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) kv[u][r] = *(const f32x4*)(kp + (size_t)(sc * 16 + r) * ldk);
+  };
+  int s = s0 + wave;
+  if (s < s1) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) request(u, s + u * MS_NW);
+    for (; s < s1; s += PF * MS_NW) {
+#pragma unroll
+      for (int u = 0; u < PF; ++u) {
+        int su = s + u * MS_NW;
+        if (su < s1) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            double kd[4];
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) kd[cc] = (double)kv[u][r][cc];
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) {
+              if (NARROW) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) accn[0][cc][q] = mfma4d(dop[u][q][r], kd[cc], accn[0][cc][q]);
+              } else {
+                acc[0][cc][0] = mfma16d(dop[u][0][r], kd[cc], acc[0][cc][0]);
+              }
+            }
+          }
+          if (su + PF * MS_NW < s1) request(u, su + PF * MS_NW);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+    for (int q = 0; q < NA / 4; ++q) red[wave][cc * (NA / 4) + q][lane] = NARROW ? accn[0][cc][q < 3 ? q : 0] : acc[0][cc][0][q];
+  __syncthreads();
+  // 64 columns x 16 positions (position 4 g + q of a row: column q of lane group g's four, see perm16)
+  double* vout = Vp + (size_t)split * np * 16 + (size_t)col0 * 16;
+#pragma unroll
+  for (int e = threadIdx.x; e < 1024; e += 64 * MS_NW) {
+    int col = e >> 4, gg = (e >> 2) & 3, q = e & 3;       // column col = 4 jc + cc
+    double t = 0.0;
+    if (q < NA / 4) {
+#pragma unroll
+      for (int w = 0; w < MS_NW; ++w) t += red[w][(col & 3) * (NA / 4) + q][gg * 16 + (col >> 2)];
+    }
+    vout[e] = t;
+  }
+}
+
 // ------------------------------------------------------- product on the fly ---
 // Wave: NJ column blocks (16*NJ output rows of V), a chunk of row blocks to contract over.
 // Distances by fp32 MFMA, kernel function in registers, product with the block by fp64 MFMA.
@@ -859,6 +944,19 @@ int launch_mm_mat(hipStream_t s, const float* Khat, const double* D4, double* Vp
     k_mm_mat<2, 2, false><<<wgs, 256, 0, s>>>(Khat, D4, Vp, np, pw, panel_stride, ldk, plan, st);
   else
     return 1;
+  return 0;
+}
+
+int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, double* Vp, int np, int nsplit, const DevState* st,
+                        int panel_width, int panel_rows, int cols) {
+  int pw = panel_width > 0 ? panel_width : np;
+  size_t panel_stride = panel_width > 0 ? (size_t)panel_rows * panel_width : 0;
+  if (pw % 64 != 0 || np % 64 != 0 || nsplit < 1) return 1;
+  int grid = np / 64 * nsplit;
+  if (cols > 0 && cols <= 12)
+    k_mm_mat_small<true><<<grid, 64 * MS_NW, 0, s>>>(Khat, D4, Vp, np, pw, panel_stride, pw, nsplit, st);
+  else
+    k_mm_mat_small<false><<<grid, 64 * MS_NW, 0, s>>>(Khat, D4, Vp, np, pw, panel_stride, pw, nsplit, st);
   return 0;
 }
 
