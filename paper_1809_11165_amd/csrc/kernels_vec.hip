@@ -642,7 +642,7 @@ __global__ __launch_bounds__(VT) void k_cross_finish(const double* __restrict__ 
 // step a scales column a of C and row a of W (identity at first) by 1 / g_aa and takes their products off the
 // rest, which leaves W = G^{-1} (the iteration applies C^{-1} = G^{-T} G^{-1} as two small dense products;
 // cond(G) = sqrt(cond(C)) <= sqrt(1 + |L|^2 / sigma^2): harmless in fp64).  One barrier per step.
-// n = 50 000, k = 20: 193 us -> 14 us (with the sums by one thread per pair of columns, and factor and
+// n = 50 000, k = 20: 193 us -> 21 + 25 us (with the sums by one thread per pair of columns, and factor and
 // inverse in one thread and one thread per column).
 template <int KP>
 __global__ __launch_bounds__(VT) void k_gram(const double* __restrict__ L, int n, double* __restrict__ partial) {
@@ -743,7 +743,7 @@ __global__ __launch_bounds__(BBMM_MAXK* BBMM_MAXK) void k_pre_setup(const double
 // -------------------------------------------------------------- probes -------
 // R[:,0] = y,  R[:,1+i] = L E1[:,i] + sigma E2[:,i]   (row-major, stride ld, zero padded).  A wave takes 16
 // rows: L E1 is KP / 4 fp64 MFMAs (columns of L beyond the rank built are zero).  Bound by reading L and E2 and
-// writing R; n = 50 000, k = 20, t = 10: 18.7 us with one thread per entry -> 7 us.
+// writing R; n = 50 000, k = 20, t = 10: 18.7 us with one thread per entry -> 9.3 us.
 template <int KP, int NQ>
 __global__ __launch_bounds__(VT) void k_probes(const float* __restrict__ y, const float* __restrict__ E1,
                                                 const float* __restrict__ E2, const double* __restrict__ L, int n, int t,
