@@ -40,6 +40,7 @@ struct TriLists {
 };
 
 constexpr int kMaxVecBlocks = 512;   // at most 32 reduction groups of 16 blocks
+static_assert(kMaxVecBlocks <= kUrMaxRows, "launch_ur's finish sizes its LDS for this many blocks");
 constexpr int kMaxSplit = bbmm_plan::kMaxSplit;
 // More than 16 input dimensions (up to 16 the digit form takes over earlier); product in us (two-use /
 // one-use form, d = 16): n = 5 000: 88 / 60; 10 000: 125 / 121; 20 000: 312 / 331; 30 000: 630 / 696; 50 000: 1950 / 2630.

@@ -42,6 +42,7 @@ struct DevState {
   int iters_run;
   int status;       // BBMM_* code raised on the device (0 = ok)
   int rank;         // preconditioner rank actually built
+  unsigned fin_ticket;   // arrivals of k_ur_fin's blocks (zero between launches)
   int xbad;         // a coordinate of X is not finite (the digit products then return NaN throughout)
   unsigned counter[8][40];   // arrival tickets per kernel family: [0] final, [1 + g] group g
 };
@@ -116,6 +117,7 @@ void launch_set_loop_scalars(hipStream_t s, DevState* st, double noise, double t
 void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, int ld, double scaleV,
                double addD, const double* D4, double* V, const DevState* st, double* partial_dv,
                int nblocks);
+constexpr int kUrMaxRows = 512;   // most blocks of launch_ur
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,

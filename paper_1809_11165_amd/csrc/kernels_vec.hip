@@ -1012,8 +1012,9 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
     }
   }
   // ---- block reduction over the waves, 256 values (16 rows of L^T R x 16 columns) per round ----
-  size_t pstride = (size_t)(KP + 1) * LD;
-  double* pout = partial + (size_t)blockIdx.x * pstride;
+  auto pout = [&](int e, int col) {   // four columns' entries of a block side by side, as k_ur_fin reads them
+    return partial + (((size_t)(col >> 2) * gridDim.x + blockIdx.x) * (KP + 1) + e) * 4 + (col & 3);
+  };
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     double v = rr[qb];
@@ -1026,7 +1027,7 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) t += stage[w][threadIdx.x];
-    pout[threadIdx.x] = t;
+    *pout(0, threadIdx.x) = t;
   }
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
@@ -1042,25 +1043,31 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
           double t = 0.0;
 #pragma unroll
           for (int w = 0; w < NW; ++w) t += stage[w][threadIdx.x];
-          pout[(size_t)(1 + m) * LD + qq] = t;
+          *pout(1 + m, qq) = t;
         }
       }
     }
 }
 
-// (2b) one block: totals of |r|^2 and L^T R, the k x k solves (one wave per column, lanes =
-//      rows of the triangular systems), rho' = (|r|^2 - (L^T r)^T C^{-1} (L^T r)) / sigma^2
-//      (= r^T P^{-1} r by the Woodbury formula), alpha/beta bookkeeping, residual history, stop flag.
+// (2b) one block per four columns: totals of |r|^2 and L^T R, the k x k solves, rho' = (|r|^2 -
+//      (L^T r)^T C^{-1} (L^T r)) / sigma^2 (= r^T P^{-1} r by the Woodbury formula), alpha/beta
+//      bookkeeping, residual history; the last block to arrive sets the stop flag.  What it reads (819 KB of
+//      partial sums at k = 20, 32 columns) took one block the time that one compute unit needs to load it.
+//      n = 20 000, k = 20, 32 columns: 17.3 us in one block -> 6.0; n = 10 000, k = 10, 11 columns: 8.3 -> 5.4.
 template <int KP>
 __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double noise, double tol,
                                                 DevState* st, const double* __restrict__ partial,
                                                 int nb, int iter, double* alpha_hist,
                                                 double* beta_hist, double* resid_hist) {
-  __shared__ double tot[(BBMM_MAXK + 1) * BBMM_MAXC];
-  __shared__ double psum[(BBMM_MAXK + 1) * BBMM_MAXC];   // parts x E, parts * E <= this size
+  constexpr int E = 4 * (KP + 1);                        // entries of a partial row
+  constexpr int RB = 32;                                 // rows that a thread requests at a time
+  constexpr int GROUPS = UT / E;
+  __shared__ double tot[E];
+  __shared__ double bsum[(kUrMaxRows / RB) * E];         // batches of RB rows
+  __shared__ double psum[4 * E];
   __shared__ double Gs[BBMM_MAXK * BBMM_MAXK];
-  __shared__ double quad_s[BBMM_MAXC];
-  __shared__ double rel_s[BBMM_MAXC];
+  __shared__ double quad_s[4];
+  __shared__ double rel_s[4];
   // Everything this block needs from the state is requested first, together with the partial
   // sums, so that the kernel pays one memory round trip instead of one per dependent read.
   int done = st->done;
@@ -1068,114 +1075,132 @@ __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double n
     noise = st->loop_noise;
     tol = st->loop_tol;
   }
-  int tq = (int)threadIdx.x < ld ? (int)threadIdx.x : 0;
+  int q0 = 4 * blockIdx.x;
+  int tq = q0 + ((int)threadIdx.x & 3);
   double s_rho = st->rho[tq], s_bnorm = st->bnorm[tq], s_dv = st->dvtot[tq];
   int s_active = st->active[tq], s_mvalid = st->m_valid[tq];
   double g_mine = st->Ginv[threadIdx.x];   // BBMM_MAXK * BBMM_MAXK == UT entries
-  size_t pstride = (size_t)(KP + 1) * ld;
-  int E = (KP + 1) * ld;
-  // totals over the nb partial rows: `parts` thread groups take every parts-th row
-  int parts = (E <= UT / 4) ? 4 : ((E <= UT / 2) ? 2 : 1);
-  int per = UT / parts;
-  int part = threadIdx.x / per, te = threadIdx.x % per;
-  for (int e = te; e < E; e += per) {
-    // 32 loads are issued before the first is consumed: the sum is latency-, not bandwidth-bound
-    // (a round trip to memory written by other compute units costs ~2.4 us here)
-    double tsum = 0.0;
-    int b = part;
-    for (; b + 31 * parts < nb; b += 32 * parts) {
-      double v[32];
+  const double* prow = partial + (size_t)blockIdx.x * nb * E;
+  // totals over the nb partial rows: `parts` sums over every parts-th row, each in batches of RB rows
+  int all = (KP + 1) * ld;
+  int parts = (all <= UT / 4) ? 4 : ((all <= UT / 2) ? 2 : 1);
+  int batches = nb / (RB * parts);
+  int grp = threadIdx.x / E, te = threadIdx.x % E;
+  if (grp < GROUPS) {
+    for (int u = grp; u < batches * parts; u += GROUPS) {
+      int b = (u / parts) * RB * parts + u % parts;
+      double v[RB];
 #pragma unroll
-      for (int u = 0; u < 32; ++u) v[u] = partial[(size_t)(b + u * parts) * pstride + e];
+      for (int w = 0; w < RB; ++w) v[w] = prow[(size_t)(b + w * parts) * E + te];
 #pragma unroll
-      for (int w = 16; w > 0; w >>= 1)
+      for (int w = RB / 2; w > 0; w >>= 1)
 #pragma unroll
-        for (int u = 0; u < w; ++u) v[u] += v[u + w];
-      tsum += v[0];
+        for (int x = 0; x < w; ++x) v[x] += v[x + w];
+      bsum[u * E + te] = v[0];
     }
-    for (; b < nb; b += parts) tsum += partial[(size_t)b * pstride + e];
-    psum[part * E + e] = tsum;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += UT) {
-    double t = psum[e];
-    for (int pp = 1; pp < parts; ++pp) t += psum[pp * E + e];
-    tot[e] = t;
+  if (grp < GROUPS && grp < parts) {
+    double tsum = 0.0;
+    for (int k = 0; k < batches; ++k) tsum += bsum[(k * parts + grp) * E + te];
+    int b0 = batches * RB * parts + grp;
+    if (b0 < nb) {                         // at most RB rows are left
+      double v[RB];
+#pragma unroll
+      for (int w = 0; w < RB; ++w) {
+        int b = b0 + w * parts;
+        v[w] = (b < nb) ? prow[(size_t)b * E + te] : 0.0;
+      }
+#pragma unroll
+      for (int w = 0; w < RB; ++w) tsum += v[w];
+    }
+    psum[grp * E + te] = tsum;
   }
-  if (done) return;                     // block-uniform
-  if ((int)threadIdx.x < BBMM_MAXC) {   // the direction update that follows measures the new block
-    st->dmax[threadIdx.x] = 0u;
-    st->dflag[threadIdx.x] = 0;
+  __syncthreads();
+  if ((int)threadIdx.x < E) {
+    double t = psum[threadIdx.x];
+    for (int pp = 1; pp < parts; ++pp) t += psum[pp * E + threadIdx.x];
+    tot[threadIdx.x] = t;
+  }
+  if (done) return;                     // the same in every block
+  if (threadIdx.x < 4) {                // the direction update that follows measures the new block
+    st->dmax[tq] = 0u;
+    st->dflag[tq] = 0;
   }
   Gs[threadIdx.x] = g_mine;             // G^{-1}, zero outside the leading k x k lower triangle
   __syncthreads();
-  // C^{-1} (L^T r) for all columns at once: w = G^{-1} y, quad = w^T w, x = G^{-T} w; thread
+  // C^{-1} (L^T r) for the columns at once: w = G^{-1} y, quad = w^T w, x = G^{-T} w; thread
   // (m, qq) owns one entry; sums run over the compiled rank limit (padding is zero)
   {
-    int m = threadIdx.x / ld, qq = threadIdx.x % ld;
+    int m = threadIdx.x / 4, qq = threadIdx.x % 4;
     double wv = 0.0;
     if (m < KP) {
 #pragma unroll
-      for (int a = 0; a < KP; ++a) wv += Gs[m * BBMM_MAXK + a] * tot[(size_t)(1 + a) * ld + qq];
-      psum[m * ld + qq] = wv;
+      for (int a = 0; a < KP; ++a) wv += Gs[m * BBMM_MAXK + a] * tot[(1 + a) * 4 + qq];
+      psum[m * 4 + qq] = wv;
     }
     __syncthreads();
     if (m < KP) {
       double xv = 0.0;
 #pragma unroll
-      for (int a = 0; a < KP; ++a) xv += Gs[a * BBMM_MAXK + m] * psum[a * ld + qq];
-      st->Qt[m * BBMM_MAXC + qq] = xv;
+      for (int a = 0; a < KP; ++a) xv += Gs[a * BBMM_MAXK + m] * psum[a * 4 + qq];
+      st->Qt[m * BBMM_MAXC + tq] = xv;
     }
-    if ((int)threadIdx.x < ld) {
+    if (threadIdx.x < 4) {
       double sq = 0.0;
 #pragma unroll
       for (int a = 0; a < KP; ++a) {
-        double wa = psum[a * ld + threadIdx.x];
+        double wa = psum[a * 4 + threadIdx.x];
         sq += wa * wa;
       }
       quad_s[threadIdx.x] = sq;
     }
   }
   __syncthreads();
-  if ((int)threadIdx.x < ld) {
-    int qq = threadIdx.x;
-    double rrq = tot[qq];
-    double rho_new = (rrq - quad_s[qq]) / noise;
+  if (threadIdx.x < 4) {
+    double rrq = tot[threadIdx.x];
+    double rho_new = (rrq - quad_s[threadIdx.x]) / noise;
     if (init) {
-      int ok = finite_d(rho_new) && rho_new > 0.0 && qq < c;
-      st->rho[qq] = rho_new;
-      st->rho0[qq] = rho_new;
-      if (init != 2) st->bnorm[qq] = sqrt(rrq);   // init == 2: warm start, |b| is already there
-      st->active[qq] = ok;
-      st->m_valid[qq] = 0;
-      st->beta_cur[qq] = 0.0;
-      st->alpha_cur[qq] = 0.0;
+      int ok = finite_d(rho_new) && rho_new > 0.0 && tq < c;
+      st->rho[tq] = rho_new;
+      st->rho0[tq] = rho_new;
+      if (init != 2) st->bnorm[tq] = sqrt(rrq);   // init == 2: warm start, |b| is already there
+      st->active[tq] = ok;
+      st->m_valid[tq] = 0;
+      st->beta_cur[tq] = 0.0;
+      st->alpha_cur[tq] = 0.0;
     } else {
       int ok;
-      double alpha = alpha_from(s_active, s_rho, s_dv, qq, c, &ok);
-      st->alpha_cur[qq] = alpha;
-      st->m_valid[qq] = s_mvalid + ok;
-      alpha_hist[(size_t)iter * BBMM_MAXC + qq] = alpha;
+      double alpha = alpha_from(s_active, s_rho, s_dv, tq, c, &ok);
+      st->alpha_cur[tq] = alpha;
+      st->m_valid[tq] = s_mvalid + ok;
+      alpha_hist[(size_t)iter * BBMM_MAXC + tq] = alpha;
       int ok2 = ok && finite_d(rho_new) && rho_new > 0.0;
       double beta = ok2 ? rho_new / s_rho : 0.0;
-      st->active[qq] = ok2;
-      st->beta_cur[qq] = beta;
-      if (ok2) st->rho[qq] = rho_new;
-      beta_hist[(size_t)iter * BBMM_MAXC + qq] = beta;
+      st->active[tq] = ok2;
+      st->beta_cur[tq] = beta;
+      if (ok2) st->rho[tq] = rho_new;
+      beta_hist[(size_t)iter * BBMM_MAXC + tq] = beta;
       double bn = s_bnorm;
       double rel = sqrt(rrq) / (bn > 0.0 ? bn : 1.0);
-      resid_hist[(size_t)iter * BBMM_MAXC + qq] = rel;
-      rel_s[qq] = rel;
+      resid_hist[(size_t)iter * BBMM_MAXC + tq] = rel;
+      rel_s[threadIdx.x] = rel;
     }
   }
   __syncthreads();
   if (threadIdx.x == 0 && !init) {
-    st->iters_run = iter + 1;
+    if (blockIdx.x == 0) st->iters_run = iter + 1;
     if (tol > 0.0) {
-      int all = 1;
-      for (int qq = 0; qq < c; ++qq)
-        if (!(rel_s[qq] < tol)) all = 0;
-      if (all) st->done = 1;
+      unsigned conv = 1;
+      for (int qq = 0; qq < 4; ++qq)
+        if (q0 + qq < c && !(rel_s[qq] < tol)) conv = 0;
+      // arrivals in the low half, blocks whose columns have all converged in the high half: the ticket holds
+      // all that the last block needs, so no fence is involved
+      unsigned t = atomicAdd(&st->fin_ticket, 1u + (conv << 16)) + 1u + (conv << 16);
+      if ((t & 0xffffu) == gridDim.x) {
+        atomicExch(&st->fin_ticket, 0u);
+        if ((t >> 16) == gridDim.x) st->done = 1;
+      }
     }
   }
 }
@@ -1809,7 +1834,7 @@ void launch_probes(hipStream_t s, const float* y, const float* E1, const float* 
 #undef PROBES
 }
 
-// U, R update + partial sums (nb_ur blocks of 1024 threads), then the one-block finish.
+// U, R update + partial sums (nb_ur <= kUrMaxRows blocks of 1024 threads), then the finish by four columns a block.
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
@@ -1818,7 +1843,7 @@ void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noi
 #define UR_MAIN(KP, NQ) k_ur_main<KP, NQ>
   DISPATCH_KP_NQ(UR_MAIN, kp, nq, nb_ur, UT, init, n, c, D4, V, U, R, L, st, partial_dv, nb_dv, partial);
 #undef UR_MAIN
-  DISPATCH_KP_T(k_ur_fin, kp, 1, UT, init, ld, c, noise, tol, st, partial, nb_ur, iter, alpha_hist,
+  DISPATCH_KP_T(k_ur_fin, kp, ld / 4, UT, init, ld, c, noise, tol, st, partial, nb_ur, iter, alpha_hist,
                 beta_hist, resid_hist);
 }
 
