@@ -46,12 +46,12 @@ constexpr int kMaxSplit = bbmm_plan::kMaxSplit;
 // one-use form, d = 16): n = 5 000: 88 / 60; 10 000: 125 / 121; 20 000: 312 / 331; 30 000: 630 / 696; 50 000: 1950 / 2630.
 constexpr int kOtfSymMinRows = 12288;
 // Product on the fly, 11 columns, us per call (fp64 matrix pipe, the faster of its two forms / digits): n = 3 000:
-// 41 / 48; 5 000: 58 / 60 (d = 8), 66 / 64 (d = 16); 8 000: 81 / 69, 100 / 81; 20 000: 303 / 203, 358 / 261; 32 000:
-// 687 / 442, 820 / 589.  17 columns, n = 200 000, d = 8: 32 120 / 20 250.
+// 41 / 48; 5 000: 58 / 60 (d = 8), 66 / 64 (d = 16); 8 000: 80 / 69, 99 / 79; 20 000: 302 / 211, 358 / 270; 32 000:
+// 687 / 464, 820 / 616.  17 columns, n = 200 000, d = 8: 32 060 / 20 430.
 constexpr int kDigMinRows = 6144;
 // Materialised product by 64-column workgroups (k_mm_mat_small) up to this size, where the matrix (256 MB) still fits
 // the memory-side cache: us per product call with 11 columns, k_mm_mat / k_mm_mat_small: n = 1 000: 28 / 18; 2 500: 35 / 21;
-// 5 000: 48 / 37; 8 000: 70 / 57; 10 000: 95 / 105.  16 columns: 34 / 18; 43 / 22; 55 / 39; 70 / 57; 94 / 105.
+// 5 000: 48 / 36; 8 000: 70 / 55; 10 000: 95 / 105.  16 columns: 34 / 18; 43 / 22; 55 / 39; 70 / 57; 94 / 105.
 constexpr int kMatSmallMaxRows = 8192;
 constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 
@@ -382,9 +382,13 @@ int dig_split_of(const bbmm_ctx* c, int cc) {
   return std::max(lo, std::max(1, std::min(s, nblk / 4)));
 }
 
+// Whether the problem's size and dimensions allow a product on the 8-bit matrix pipe (its split coordinates are
+// laid out with the others then).
+bool may_use_digits(const bbmm_ctx* c) { return c->np >= kDigMinRows && c->KK <= 4; }
+
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.
 bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
-  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym != 0 && c->np >= kDigMinRows && c->KK <= 4 &&
+  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym != 0 && may_use_digits(c) &&
          dig_split_of(c, cc) <= kMaxSplit;
 }
 
@@ -900,7 +904,7 @@ int stage_dk(bbmm_ctx* c, int ld, int t) {
     return fail(c, BBMM_EINVAL, "derivative pass: unsupported configuration");
   int nls = ard ? c->dp : 1;
   launch_noise_terms(s, U, Z0, c->prob.y, c->n, ld, t, nls + 1, ptr<DevState>(c->st), ptr<double>(c->partial),
-                     ptr<double>(c->gpartial), vec_blocks(c->n, ld));
+                     vec_blocks(c->n, ld));
   return BBMM_OK;
 }
 
@@ -951,7 +955,7 @@ int stage_dk_sgpr(bbmm_ctx* c, int ld, int t) {
   launch_dk_finish(s, partial, nb1 + nb2, kDkStride, 2 * nls, st);
   launch_sgpr_sterm(s, tout[0], tout[1], c->mp, ld, t, c->prob.outputscale, nls, st);
   launch_noise_terms(s, U, Z0, c->prob.y, c->n, ld, t, nls + 1, st, ptr<double>(c->partial),
-                     ptr<double>(c->gpartial), vec_blocks(c->n, ld));
+                     vec_blocks(c->n, ld));
   return BBMM_OK;
 }
 
@@ -1200,7 +1204,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
       {&c->gpartial, sizeof(double) * 40 * (BBMM_MAXK * BBMM_MAXK + (BBMM_MAXK + 1) * BBMM_MAXC)},
       {&c->alpha, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->beta, sizeof(double) * BBMM_MAXP * BBMM_MAXC},
       {&c->resid, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->st, sizeof(DevState)},
-      {&c->tmpA, blk}, {&c->tmpB, blk}, {&c->Pb, c->KK <= 4 ? 4 * opx : 0},
+      {&c->tmpA, blk}, {&c->tmpB, blk}, {&c->Pb, may_use_digits(c) ? 4 * opx : 0},
       {&c->SA, np * 64 * sizeof(float)}, {&c->SB, np * 64 * sizeof(float)}, {&c->u0v, np * sizeof(float)},
   };
   for (auto& w : want) {
@@ -1218,7 +1222,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   launch_colmean(s, in->X, c->n, c->d, ptr<DevState>(c->st), ptr<double>(c->partial), ptr<double>(c->gpartial));
   launch_prep_x(s, in->X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st), ptr<float>(c->Xa),
                 ptr<float>(c->Xb), ptr<float>(c->Xs), ptr<float>(c->X4), ptr<float>(c->sq));
-  if (c->KK <= 4) launch_split_x(s, ptr<float>(c->Xb), c->np, c->KK, c->Pb.p);
+  if (may_use_digits(c)) launch_split_x(s, ptr<float>(c->Xb), c->np, c->KK, c->Pb.p);
   HIPCHK(c, hipGetLastError());
   c->is_setup = true;
   return BBMM_OK;

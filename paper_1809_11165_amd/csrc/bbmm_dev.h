@@ -146,7 +146,7 @@ void launch_slq_coeffs(hipStream_t s, const double* alpha, const double* beta, c
 void launch_tridiag_eig(hipStream_t s, const double* diag, const double* off, int m, int batch,
                         int sweeps_per_row, double* eigvals, double* first_row, int* status);
 void launch_noise_terms(hipStream_t s, const double* U, const double* Z0, const float* y, int n, int ld,
-                        int t, int slot, DevState* st, double* partial, double* gpartial, int nblocks);
+                        int t, int slot, DevState* st, double* partial, int nblocks);
 
 // ---- launchers implemented in kernels_sgpr.hip (subset-of-regressors covariance) ----------
 void launch_sgpr_kuu(hipStream_t s, const float* Uind, int m, int mp, HypArgs hyp, double jitter,

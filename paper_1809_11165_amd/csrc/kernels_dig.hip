@@ -257,8 +257,8 @@ __device__ __forceinline__ void wait_vm() {
 // 7.8 ns, of which about 4 keep the vector ALU from issuing; a simple vector instruction 1.3 ns, a conversion
 // 2.3 - 2.9, an exponential or square root 3.6.  A tile (16 x 16, 17 columns, RBF, d = 8) is 11 MFMAs and
 // ~46 ns of vector work, one of Matern-5/2 with 11 columns at d = 16 is 10 and ~75 ns.
-// Per product, n = 200 000, d = 8, 17 columns: 20.3 ms (k_mm_otf, fp64 matrix pipe: 32.1 ms); n = 32 000, d = 16,
-// 11 columns, Matern-5/2: 0.59 ms (k_mm_otf_tri 0.82, k_mm_otf 0.99).
+// Per product, n = 200 000, d = 8, 17 columns: 20.4 ms (k_mm_otf, fp64 matrix pipe: 32.1 ms); n = 32 000, d = 16,
+// 11 columns, Matern-5/2: 0.62 ms (k_mm_otf_tri 0.82, k_mm_otf 0.99).
 template <int KIND, int KK, int NG, int NJ>
 __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ rec, const bf16x8u* __restrict__ Pb,
                                                         const float* __restrict__ sq, double* __restrict__ Vp, int np,
@@ -460,7 +460,8 @@ void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float
 
 // Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles
 // in flight (24) leave room for with two waves per SIMD.  n = 50 000, d = 16, 11 columns: 1433 us with 4,
-// 1597 with 3; n = 100 000, d = 8, 17 columns: 5272 with 4, 5632 with 3.
+// 1597 with 3; n = 100 000, d = 8, 17 columns: 5272 with 4, 5632 with 3 (all with the norms as the MFMA's addend, about
+// 5 % faster than the loop is with symmetric ones).
 int dig_nj(int KK, int ng) {
   if (ng == 2) return KK <= 2 ? 6 : 5;
   if (ng == 4) return KK <= 2 ? 5 : 4;
