@@ -192,17 +192,20 @@ def roofline_mat(n, c, mm_ms, launches, config):
 
 def roofline_otf(n, c, d, mm_ms, launches):
     """Tiles rebuilt from X in every product.  Algorithmic flops per pair: 2 d (distance contraction)
-    + 2 c (multiply by the block).  `frac` prices all of them at the fp32 matrix rate; the second
-    contraction is carried out in fp64, at half that rate on the same pipe, so the floor of the two
-    together is n^2 (2 d / peak32 + 2 c / peak64): `frac_of_mixed_floor` is that floor over the
-    launch time."""
+    + 2 c (multiply by the block).  `frac` prices all of them at the fp32 matrix rate.  With the
+    second contraction in fp64, at half that rate on the same pipe, the floor of the two together is
+    n^2 (2 d / peak32 + 2 c / peak64): `frac_of_mixed_floor` is that floor over the launch time.
+    k_mm_otf_dig uses neither unit (bf16 and 8-bit matrix instructions), so it is not bound by it."""
     alg_flops = (2.0 * d + 2.0 * c) * n * n
+    np_ = -(-n // 256) * 256
     achieved = alg_flops / (mm_ms * 1e-3) / 1e12
     mixed_floor_ms = n * n * (2.0 * d / MFMA_F32_PEAK_TFLOPS + 2.0 * c / MFMA_F64_PEAK_TFLOPS) * 1e-9
     return {"bound": "mfma", "achieved": achieved, "peak": MFMA_F32_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": achieved / MFMA_F32_PEAK_TFLOPS, "traffic": None,
-            "kernel": "k_mm_otf_tri (tiles on and above the diagonal, each used twice; two launches per product)"
-                      if (c <= 16 and d <= 32 and -(-n // 256) * 256 >= 12288) else "k_mm_otf",
+            "kernel": "k_mm_otf_dig (8-bit matrix instructions on fixed-point digits; with k_digits)"
+                      if (d <= 16 and np_ >= 6144) else
+                      "k_mm_otf_tri (tiles on and above the diagonal, each used twice; two launches per product)"
+                      if (c <= 16 and d <= 32 and np_ >= 12288) else "k_mm_otf",
             "avg_launch_ms": mm_ms, "launches": launches,
             "pairs_per_s": n * n / (mm_ms * 1e-3),
             "mixed_floor_ms": mixed_floor_ms, "frac_of_mixed_floor": mixed_floor_ms / mm_ms}

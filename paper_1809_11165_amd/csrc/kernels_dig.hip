@@ -460,8 +460,8 @@ void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float
 
 // Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles
 // in flight (24) leave room for with two waves per SIMD.  n = 50 000, d = 16, 11 columns: 1433 us with 4,
-// 1597 with 3; n = 100 000, d = 8, 17 columns: 5272 with 4, 5632 with 3 (all with the norms as the MFMA's addend, about
-// 5 % faster than the loop is with symmetric ones).
+// 1597 with 3; n = 100 000, d = 8, 17 columns: 5272 with 4, 5632 with 3 (all with the norms as the MFMA's addend, 1 to
+// 5 % faster than the loop with symmetric ones).
 int dig_nj(int KK, int ng) {
   if (ng == 2) return KK <= 2 ? 6 : 5;
   if (ng == 4) return KK <= 2 ? 5 : 4;
