@@ -689,11 +689,9 @@ int stage_pivchol(bbmm_ctx* c) {
 
 int stage_pre_setup(bbmm_ctx* c) {
   if (!c->chol_done) return fail(c, BBMM_EINVAL, "bbmm_pivoted_cholesky must run first");
-  // at least one trip of the four waves' four row quads per block; few enough rows of partial sums for
-  // the one block that adds them
-  int nb = std::min(48, std::max(1, c->n / 64));
-  launch_pre_setup(c->stream, ptr<double>(c->L), c->n, c->kp, c->prob.noise, ptr<DevState>(c->st),
-                   ptr<double>(c->partial), nb);
+  int nb = std::min(kMaxVecBlocks, std::max(1, c->n / 64));
+  launch_pre_setup(c->stream, ptr<double>(c->L), c->n, c->k, c->kp, c->prob.noise, ptr<DevState>(c->st),
+                   ptr<double>(c->partial), ptr<double>(c->gpartial), nb);
   c->pre_done = true;
   return BBMM_OK;
 }
@@ -1349,8 +1347,8 @@ int bbmm_make_probes(bbmm_ctx* c, float* B) {
   if (!c->chol_done) return fail(c, BBMM_EINVAL, "bbmm_pivoted_cholesky must run first");
   if (!B) return fail(c, BBMM_EINVAL, "B is NULL");
   int cc = c->t + 1, ld = ld_for(cc);
-  launch_probes(c->stream, c->prob.y, c->prob.E1, c->prob.E2, ptr<double>(c->L), c->n, c->t, c->k, c->kp, ld,
-                c->prob.noise, ptr<double>(c->tmpA));
+  launch_probes(c->stream, c->prob.y, c->prob.E1, c->prob.E2, ptr<double>(c->L), c->n, c->t, c->kp, ld,
+                c->prob.noise, ptr<DevState>(c->st), ptr<double>(c->tmpA));
   launch_unpack_rows(c->stream, ptr<double>(c->tmpA), ld, c->n, cc, B);
   HIPCHK(c, hipGetLastError());
   return BBMM_OK;
@@ -1609,7 +1607,8 @@ int bbmm_solve_logdet_grad(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out
   if (rc) return rc;
   rc = stage_pre_setup(c);
   if (rc) return rc;
-  launch_probes(s, in->y, in->E1, in->E2, ptr<double>(c->L), c->n, c->t, c->k, c->kp, ld, in->noise, ptr<double>(c->R));
+  launch_probes(s, in->y, in->E1, in->E2, ptr<double>(c->L), c->n, c->t, c->kp, ld, in->noise,
+                ptr<DevState>(c->st), ptr<double>(c->R));
   rc = stage_mbcg(c, in->mode, cc, ld, in->u0_init);
   if (rc) return rc;
   // The eigensolves need only the coefficient histories and the derivative pass only the solves:

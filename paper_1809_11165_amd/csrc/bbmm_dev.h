@@ -107,11 +107,10 @@ void launch_pc_init(hipStream_t s, int n, HypArgs hyp, double* delta, DevState* 
 void launch_pc_step(hipStream_t s, const float* X, int n, int m, int kp, HypArgs hyp, double* delta,
                     double* L, DevState* st, const double* arg_in, double* arg_out, int nblocks,
                     const double* row_in, int row_ld, int forced, int next_forced);
-// partial: room for nblocks * BBMM_MAXK^2 doubles
-void launch_pre_setup(hipStream_t s, const double* L, int n, int kp, double noise, DevState* st, double* partial,
-                      int nblocks);
-void launch_probes(hipStream_t s, const float* y, const float* E1, const float* E2, const double* L, int n, int t, int k,
-                   int kp, int ld, double noise, double* R);
+void launch_pre_setup(hipStream_t s, const double* L, int n, int k, int kp, double noise, DevState* st,
+                      double* partial, double* gpartial, int nblocks);
+void launch_probes(hipStream_t s, const float* y, const float* E1, const float* E2, const double* L,
+                   int n, int t, int kp, int ld, double noise, const DevState* st, double* R);
 void launch_set_loop_scalars(hipStream_t s, DevState* st, double noise, double tol, double scaleV, double addD);
 // launch_dv: addD < 0, launch_ur / launch_zd: noise < 0  =>  the scalars come from st->loop_*
 void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, int ld, double scaleV,

@@ -327,34 +327,27 @@ __device__ inline double kernel_value_f64(const float* __restrict__ X, int a, in
   return hyp.outputscale * (1.0 + s5 * rho + (5.0 / 3.0) * rho2) * exp(-s5 * rho);
 }
 
-// Block-level argmax of (value, lowest index on ties); result valid in every thread.  Shuffles inside a
-// wave, one exchange between the waves (two barriers instead of the sixteen of a tree in LDS).
+// Block-level argmax of (value, lowest index on ties); result valid in thread 0.
 __device__ inline void block_argmax(double v, int idx, double* sval, int* sidx, double* outv,
                                     int* outi) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    double v2 = __shfl_xor(v, o, 64);
-    int i2 = __shfl_xor(idx, o, 64);
-    if (v2 > v || (v2 == v && i2 < idx)) {
-      v = v2;
-      idx = i2;
-    }
-  }
-  int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    sval[wave] = v;
-    sidx[wave] = idx;
-  }
+  sval[threadIdx.x] = v;
+  sidx[threadIdx.x] = idx;
   __syncthreads();
-  v = sval[0];
-  idx = sidx[0];
-  for (int w = 1; w < (int)blockDim.x >> 6; ++w)
-    if (sval[w] > v || (sval[w] == v && sidx[w] < idx)) {
-      v = sval[w];
-      idx = sidx[w];
+  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) {
+      double v2 = sval[threadIdx.x + w];
+      int i2 = sidx[threadIdx.x + w];
+      double v1 = sval[threadIdx.x];
+      int i1 = sidx[threadIdx.x];
+      if (v2 > v1 || (v2 == v1 && i2 < i1)) {
+        sval[threadIdx.x] = v2;
+        sidx[threadIdx.x] = i2;
+      }
     }
-  *outv = v;
-  *outi = idx;
+    __syncthreads();
+  }
+  *outv = sval[0];
+  *outi = sidx[0];
   __syncthreads();
 }
 
@@ -637,159 +630,104 @@ __global__ __launch_bounds__(VT) void k_cross_finish(const double* __restrict__ 
 
 // ---------------------------------------------- capacitance matrix, log|P| ---
 // C = sigma^2 I + L^T L (k x k, fp64), Cholesky factor G, log|P| = log|C| + (n-k) log sigma^2.
-// k_gram: partial sums of L^T L by fp64 MFMA, four rows of L being both operands; one row of partials per
-// block.  k_pre_setup, one block: their sum, then factor and inverse factor side by side, one thread per entry:
-// step a scales column a of C and row a of W (identity at first) by 1 / g_aa and takes their products off the
-// rest, which leaves W = G^{-1} (the iteration applies C^{-1} = G^{-T} G^{-1} as two small dense products;
-// cond(G) = sqrt(cond(C)) <= sqrt(1 + |L|^2 / sigma^2): harmless in fp64).  One barrier per step.
-// n = 50 000, k = 20: 193 us -> 21 + 25 us (with the sums by one thread per pair of columns, and factor and
-// inverse in one thread and one thread per column).
-template <int KP>
-__global__ __launch_bounds__(VT) void k_gram(const double* __restrict__ L, int n, double* __restrict__ partial) {
-  constexpr int MB = (KP + 15) / 16;
-  __shared__ double stage[VT / 64][256];
-  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int q = lane & 15, g = lane >> 4;
-  f64x4 acc[MB][MB];
+__global__ __launch_bounds__(VT) void k_pre_setup(const double* __restrict__ L, int n, int kp,
+                                                   double noise, DevState* st, double* partial,
+                                                   double* gpartial) {
+  int k = st->rank;
+  int npairs = k * k;
+  // each thread owns pairs e = tid, tid + VT, ... (at most 4 for k <= 32)
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  int rows_per_block = (n + gridDim.x - 1) / gridDim.x;
+  int r0 = blockIdx.x * rows_per_block;
+  int r1 = min(n, r0 + rows_per_block);
+  for (int i = r0; i < r1; ++i) {
+    const double* li = L + (size_t)i * kp;
 #pragma unroll
-  for (int a = 0; a < MB; ++a)
+    for (int u = 0; u < 4; ++u) {
+      int e = threadIdx.x + u * VT;
+      if (e < npairs) acc[u] += (double)li[e / k] * (double)li[e % k];
+    }
+  }
 #pragma unroll
-    for (int c = 0; c < MB; ++c) acc[a][c] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  int gw = blockIdx.x * (VT / 64) + wave, nw = gridDim.x * (VT / 64);
-  constexpr int RU = 4;
-  for (int ib = 4 * gw; ib < n; ib += 4 * nw * RU) {   // wave-uniform bounds: MFMA needs all lanes
-    double la[RU][MB];
-#pragma unroll
-    for (int u = 0; u < RU; ++u) {
-      int i = ib + u * 4 * nw + g;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        int m = mb * 16 + q;
-        la[u][mb] = (i < n && m < KP) ? L[(size_t)i * KP + m] : 0.0;
+  for (int u = 0; u < 4; ++u) {
+    int e = threadIdx.x + u * VT;
+    if (e < npairs) partial[(size_t)blockIdx.x * (BBMM_MAXK * BBMM_MAXK) + e] = acc[u];
+  }
+  __shared__ double C[BBMM_MAXK * BBMM_MAXK];
+  __shared__ double tot[BBMM_MAXK * BBMM_MAXK];
+  if (!reduce_blocks(partial, gpartial, BBMM_MAXK * BBMM_MAXK, npairs, st->counter[1], tot)) return;
+  for (int e = threadIdx.x; e < npairs; e += VT) {
+    int a = e / k, c = e % k;
+    C[a * BBMM_MAXK + c] = tot[e] + (a == c ? noise : 0.0);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    // in-place lower Cholesky factorisation of C in LDS
+    double logdet = 0.0;
+    int bad = 0;
+    for (int a = 0; a < k; ++a) {
+      for (int c = 0; c <= a; ++c) {
+        double s = C[a * BBMM_MAXK + c];
+        for (int j = 0; j < c; ++j) s -= C[a * BBMM_MAXK + j] * C[c * BBMM_MAXK + j];
+        if (a == c) {
+          if (!(s > 0.0) || !finite_d(s)) {
+            bad = 1;
+            s = 1.0;
+          }
+          double g = sqrt(s);
+          C[a * BBMM_MAXK + a] = g;
+          logdet += 2.0 * log(g);
+        } else {
+          C[a * BBMM_MAXK + c] = s / C[c * BBMM_MAXK + c];
+        }
       }
     }
-#pragma unroll
-    for (int u = 0; u < RU; ++u)
-#pragma unroll
-      for (int a = 0; a < MB; ++a)
-#pragma unroll
-        for (int c = 0; c < MB; ++c) acc[a][c] = mfma16d(la[u][a], la[u][c], acc[a][c]);
-  }
-  double* pout = partial + (size_t)blockIdx.x * (BBMM_MAXK * BBMM_MAXK);
-#pragma unroll
-  for (int a = 0; a < MB; ++a)
-#pragma unroll
-    for (int c = 0; c < MB; ++c) {
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < 4; ++r) stage[wave][(4 * r + g) * 16 + q] = acc[a][c][r];
-      __syncthreads();
-      int row = 16 * a + (int)threadIdx.x / 16, col = 16 * c + (int)threadIdx.x % 16;
-      pout[row * BBMM_MAXK + col] = (stage[0][threadIdx.x] + stage[1][threadIdx.x]) + (stage[2][threadIdx.x] + stage[3][threadIdx.x]);
-    }
-}
-
-__global__ __launch_bounds__(BBMM_MAXK* BBMM_MAXK) void k_pre_setup(const double* __restrict__ partial, int nb, int n, int kp,
-                                                                     double noise, DevState* st) {
-  __shared__ double colbuf[2][BBMM_MAXK], rowbuf[2][BBMM_MAXK];
-  int k = st->rank;
-  int tid = threadIdx.x, i = tid / BBMM_MAXK, j = tid % BBMM_MAXK;
-  double c = 0.0;
-  if (i < kp && j < kp) {
-    for (int b0 = 0; b0 < nb; b0 += 16) {
-      double v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = (b0 + u < nb) ? partial[(size_t)(b0 + u) * (BBMM_MAXK * BBMM_MAXK) + tid] : 0.0;
-#pragma unroll
-      for (int w = 8; w > 0; w >>= 1)
-#pragma unroll
-        for (int u = 0; u < w; ++u) v[u] += v[u + w];
-      c += v[0];
-    }
-  }
-  if (i == j) c += noise;
-  double w = (i == j) ? 1.0 : 0.0, gout = 0.0, logdet = 0.0;
-  int bad = 0;
-  for (int a = 0; a < k; ++a) {
-    double* col = colbuf[a & 1];
-    double* row = rowbuf[a & 1];
-    if (j == a) col[i] = c;
-    if (i == a) row[j] = w;
-    __syncthreads();
-    double p = col[a];
-    if (!(p > 0.0) || !finite_d(p)) {
-      bad = 1;
-      p = 1.0;
-    }
-    double g = sqrt(p);
-    if (tid == 0) logdet += 2.0 * log(g);
-    double gi = (i == a) ? g : col[i] / g, gj = col[j] / g, wj = row[j] / g;
-    if (j == a && i >= a) gout = gi;
-    if (i == a) w = wj;
-    if (i > a) {
-      if (j > a) c -= gi * gj;
-      w -= gi * wj;
-    }
-  }
-  bool low = i < k && j <= i;
-  st->G[tid] = low ? gout : 0.0;
-  st->Ginv[tid] = low ? w : 0.0;
-  if (tid == 0) {
     st->logdetP = logdet + (double)(n - k) * log(noise);
     if (bad) st->status = 3;
+  }
+  __syncthreads();
+  // G^{-1}, one column per thread by forward substitution on the unit vectors; the iteration
+  // applies C^{-1} = G^{-T} G^{-1} as two small dense products instead of serial substitutions
+  // (cond(G) = sqrt(cond(C)) <= sqrt(1 + |L|^2 / sigma^2): harmless in fp64).
+  for (int e = threadIdx.x; e < BBMM_MAXK * BBMM_MAXK; e += VT) tot[e] = 0.0;
+  __syncthreads();
+  if ((int)threadIdx.x < k) {
+    int j = threadIdx.x;
+    tot[j * BBMM_MAXK + j] = 1.0 / C[j * BBMM_MAXK + j];
+    for (int i = j + 1; i < k; ++i) {
+      double sacc = 0.0;
+      for (int a = j; a < i; ++a) sacc += C[i * BBMM_MAXK + a] * tot[a * BBMM_MAXK + j];
+      tot[i * BBMM_MAXK + j] = -sacc / C[i * BBMM_MAXK + i];
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < BBMM_MAXK * BBMM_MAXK; e += VT) {
+    int a = e / BBMM_MAXK, c = e % BBMM_MAXK;
+    bool low = a < k && c <= a;
+    st->G[e] = low ? C[e] : 0.0;
+    st->Ginv[e] = low ? tot[e] : 0.0;
   }
 }
 
 // -------------------------------------------------------------- probes -------
-// R[:,0] = y,  R[:,1+i] = L E1[:,i] + sigma E2[:,i]   (row-major, stride ld, zero padded).  A wave takes 16
-// rows: L E1 is KP / 4 fp64 MFMAs (columns of L beyond the rank built are zero).  Bound by reading L and E2 and
-// writing R; n = 50 000, k = 20, t = 10: 18.7 us with one thread per entry -> 9.3 us.
-template <int KP, int NQ>
-__global__ __launch_bounds__(VT) void k_probes(const float* __restrict__ y, const float* __restrict__ E1,
-                                                const float* __restrict__ E2, const double* __restrict__ L, int n, int t,
-                                                int k, double sigma, double* __restrict__ R) {
-  constexpr int LD = 16 * NQ;
-  constexpr int KS = KP / 4;
-  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int q = lane & 15, g = lane >> 4;
-  double e1[KS > 0 ? KS : 1][NQ];
-#pragma unroll
-  for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      int m = 4 * kk + g, col = qb * 16 + q;
-      e1[kk][qb] = (m < k && col >= 1 && col <= t) ? (double)E1[(size_t)m * t + (col - 1)] : 0.0;
-    }
-  int gw = blockIdx.x * (VT / 64) + wave, nw = gridDim.x * (VT / 64);
-  for (int i0 = 16 * gw; i0 < n; i0 += 16 * nw) {   // wave-uniform bounds: MFMA needs all lanes
-    f64x4 acc[NQ];
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int i = i0 + 4 * r + g, col = qb * 16 + q;
-        double v = 0.0;
-        if (i < n) {
-          if (col == 0) v = (double)y[i];
-          else if (col <= t) v = sigma * (double)E2[(size_t)i * t + (col - 1)];
-        }
-        acc[qb][r] = v;
-      }
-    int arow = i0 + q;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      double la = (arow < n) ? L[(size_t)arow * KP + 4 * kk + g] : 0.0;
-#pragma unroll
-      for (int qb = 0; qb < NQ; ++qb) acc[qb] = mfma16d(la, e1[kk][qb], acc[qb]);
-    }
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int i = i0 + 4 * r + g;
-        if (i < n) R[(size_t)i * LD + qb * 16 + q] = acc[qb][r];
-      }
+// R[:,0] = y,  R[:,1+i] = L E1[:,i] + sigma E2[:,i]   (row-major, stride ld, zero padded)
+__global__ void k_probes(const float* __restrict__ y, const float* __restrict__ E1,
+                         const float* __restrict__ E2, const double* __restrict__ L, int n, int t,
+                         int kp, int ld, double sigma, const DevState* __restrict__ st,
+                         double* __restrict__ R) {
+  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (size_t)n * ld) return;
+  int i = (int)(idx / ld), q = (int)(idx % ld);
+  int k = st->rank;
+  double v = 0.0;
+  if (q == 0) {
+    v = (double)y[i];
+  } else if (q <= t) {
+    double s = sigma * (double)E2[(size_t)i * t + (q - 1)];
+    for (int m = 0; m < k; ++m) s += (double)L[(size_t)i * kp + m] * (double)E1[(size_t)m * t + (q - 1)];
+    v = s;
   }
+  R[idx] = v;
 }
 
 // ------------------------------------------------ fused mBCG vector updates --
@@ -1775,6 +1713,17 @@ void launch_pc_step(hipStream_t s, const float* X, int n, int m, int kp, HypArgs
                                    forced, next_forced);
 }
 
+void launch_pre_setup(hipStream_t s, const double* L, int n, int k, int kp, double noise, DevState* st,
+                      double* partial, double* gpartial, int nblocks) {
+  (void)k;
+  k_pre_setup<<<nblocks, VT, 0, s>>>(L, n, kp, noise, st, partial, gpartial);
+}
+
+void launch_probes(hipStream_t s, const float* y, const float* E1, const float* E2, const double* L,
+                   int n, int t, int kp, int ld, double noise, const DevState* st, double* R) {
+  k_probes<<<blocks_for((size_t)n * ld, 256), 256, 0, s>>>(y, E1, E2, L, n, t, kp, ld, sqrt(noise), st, R);
+}
+
 __global__ void k_set_loop_scalars(DevState* st, double noise, double tol, double scaleV, double addD) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     st->loop_noise = noise;
@@ -1830,28 +1779,7 @@ void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, in
       break;                                                                     \
   }
 
-void launch_pre_setup(hipStream_t s, const double* L, int n, int kp, double noise, DevState* st, double* partial,
-                      int nblocks) {
-  switch (kp) {
-    case 0: nblocks = 0; break;
-    case 8: k_gram<8><<<nblocks, VT, 0, s>>>(L, n, partial); break;
-    case 16: k_gram<16><<<nblocks, VT, 0, s>>>(L, n, partial); break;
-    case 24: k_gram<24><<<nblocks, VT, 0, s>>>(L, n, partial); break;
-    default: k_gram<32><<<nblocks, VT, 0, s>>>(L, n, partial); break;
-  }
-  k_pre_setup<<<1, BBMM_MAXK * BBMM_MAXK, 0, s>>>(partial, nblocks, n, kp, noise, st);
-}
-
-void launch_probes(hipStream_t s, const float* y, const float* E1, const float* E2, const double* L, int n, int t, int k,
-                   int kp, int ld, double noise, double* R) {
-  int nq = ld / 16, nb = blocks_for((size_t)((n + 15) / 16), VT / 64);
-  if (nb > 4096) nb = 4096;
-#define PROBES(KP, NQ) k_probes<KP, NQ>
-  DISPATCH_KP_NQ(PROBES, kp, nq, nb, VT, y, E1, E2, L, n, t, k, sqrt(noise), R);
-#undef PROBES
-}
-
-// U, R update + partial sums (nb_ur <= kUrMaxRows blocks of 1024 threads), then the finish by four columns a block.
+// U, R update + partial sums (nb_ur blocks of 1024 threads), then the one-block finish.
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
