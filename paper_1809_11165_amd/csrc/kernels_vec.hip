@@ -327,27 +327,34 @@ __device__ inline double kernel_value_f64(const float* __restrict__ X, int a, in
   return hyp.outputscale * (1.0 + s5 * rho + (5.0 / 3.0) * rho2) * exp(-s5 * rho);
 }
 
-// Block-level argmax of (value, lowest index on ties); result valid in thread 0.
+// Block-level argmax of (value, lowest index on ties); result valid in every thread.  Shuffles inside a
+// wave, one exchange between the waves (two barriers instead of the sixteen of a tree in LDS).
 __device__ inline void block_argmax(double v, int idx, double* sval, int* sidx, double* outv,
                                     int* outi) {
-  sval[threadIdx.x] = v;
-  sidx[threadIdx.x] = idx;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      double v2 = sval[threadIdx.x + w];
-      int i2 = sidx[threadIdx.x + w];
-      double v1 = sval[threadIdx.x];
-      int i1 = sidx[threadIdx.x];
-      if (v2 > v1 || (v2 == v1 && i2 < i1)) {
-        sval[threadIdx.x] = v2;
-        sidx[threadIdx.x] = i2;
-      }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    double v2 = __shfl_xor(v, o, 64);
+    int i2 = __shfl_xor(idx, o, 64);
+    if (v2 > v || (v2 == v && i2 < idx)) {
+      v = v2;
+      idx = i2;
     }
-    __syncthreads();
   }
-  *outv = sval[0];
-  *outi = sidx[0];
+  int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    sval[wave] = v;
+    sidx[wave] = idx;
+  }
+  __syncthreads();
+  v = sval[0];
+  idx = sidx[0];
+  for (int w = 1; w < (int)blockDim.x >> 6; ++w)
+    if (sval[w] > v || (sval[w] == v && sidx[w] < idx)) {
+      v = sval[w];
+      idx = sidx[w];
+    }
+  *outv = v;
+  *outi = idx;
   __syncthreads();
 }
 
