@@ -251,7 +251,7 @@ int ensure_vp(bbmm_ctx* c, int slots, int ld) {
 
 // Records of the block's digit operands (see launch_digits).
 int ensure_records(bbmm_ctx* c, int ng) {
-  size_t bytes = (size_t)c->np / 16 * dig_record_bytes(c->KK, ng);
+  size_t bytes = (size_t)bbmm_plan::dig_buffer_bytes(c->np / 16, c->KK, ng);
   if (bytes <= c->rec.cap) return BBMM_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still use the old buffer
   return ensure(c, c->rec, bytes);

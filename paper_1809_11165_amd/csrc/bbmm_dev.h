@@ -218,7 +218,6 @@ int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, doub
 constexpr int kDigMaxBlocks = 2046;   // 16-row blocks one accumulator may sum without overflow
 int dig_groups(int c);
 int dig_nj(int KK, int ng);
-size_t dig_record_bytes(int KK, int ng);
 void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float* sq, int np, int ld, int KK, int ng,
                    const DevState* st, void* rec);
 // column-side coordinates (from Xb: MFMA operand order) as bf16 pieces: 16 np * 4 KK bytes

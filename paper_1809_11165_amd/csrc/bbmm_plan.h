@@ -195,4 +195,24 @@ inline const char* lay_out_triangle(int np, int W, int want, TriHost& L) {
   return nullptr;
 }
 
+// Records of the digit product (see launch_digits): 1 KB pieces, copied into LDS by the four waves of a
+// workgroup in rounds of four pieces.  The last round of a record may run up to three pieces past it and the
+// ring requests a fixed number of records ahead, so both the copies' addresses and the buffer's size are laid
+// out here: whatever a chunk of nk records requests is the chunk's own last record again, and behind the last record of
+// all there is room for its round.  (Nothing rests on the range check of the buffer instruction, whose
+// scalar offset is not part of what it checks.)
+constexpr int kDigPiece = 1024;
+constexpr int dig_pieces(int KK, int ng) { return KK + ng + 1; }
+constexpr int dig_copies(int KK, int ng) { return (dig_pieces(KK, ng) + 3) / 4; }   // per wave and record
+constexpr int dig_record_bytes(int KK, int ng) { return dig_pieces(KK, ng) * kDigPiece; }
+constexpr int dig_slot_bytes(int KK, int ng) { return dig_copies(KK, ng) * 4 * kDigPiece; }   // of a record in the ring
+constexpr int dig_ring(int KK, int ng) { return 5 * dig_slot_bytes(KK, ng) <= 81920 ? 5 : 4; }   // two workgroups per compute unit where it fits
+// Bytes from the chunk's first record to round c of the copy of its record k (a wave adds 1024 times its number).
+constexpr int dig_copy_offset(int KK, int ng, int k, int nk, int c) {
+  return (k < nk ? k : nk - 1) * dig_record_bytes(KK, ng) + c * 4 * kDigPiece;
+}
+constexpr long long dig_buffer_bytes(long long blocks, int KK, int ng) {
+  return blocks * dig_record_bytes(KK, ng) + (dig_slot_bytes(KK, ng) - dig_record_bytes(KK, ng));
+}
+
 }  // namespace bbmm_plan

@@ -220,8 +220,8 @@ __device__ __forceinline__ void dig_store(const i32x4 (&acc)[NG], double* __rest
 }
 
 // A workgroup's ring of records in LDS, shared by its four waves and copied straight from global memory (a
-// wave copies every fourth piece; the last round may run into the next record, hence whole multiples
-// of 4 KB here).  In step k of a chunk record k - 1 feeds the digit MFMAs, k + 1 the distances, and
+// wave copies every fourth piece; the last round may run past the record, hence whole multiples
+// of 4 KB here, see bbmm_plan::dig_copy_offset).  In step k of a chunk record k - 1 feeds the digit MFMAs, k + 1 the distances, and
 // k + kRing - 2 is requested, into the place that record k - 2 has left.
 typedef __attribute__((address_space(3))) char lds_char;
 typedef const __attribute__((address_space(3))) i32x4* lds_i32x4;
@@ -229,11 +229,11 @@ typedef const __attribute__((address_space(3))) f32x4* lds_f32x4;
 
 template <int KK, int NG>
 struct DigRec {
-  static constexpr int kPieces = KK + NG + 1;
-  static constexpr int kBytes = kPieces * 1024;                      // in global memory
-  static constexpr int kCopies = (kPieces + 3) / 4;                  // per wave
-  static constexpr int kSlot = kCopies * 4096;                       // in the ring
-  static constexpr int kRing = 5 * kSlot <= 81920 ? 5 : 4;           // two workgroups per compute unit where it fits
+  static constexpr int kPieces = bbmm_plan::dig_pieces(KK, NG);
+  static constexpr int kBytes = bbmm_plan::dig_record_bytes(KK, NG);   // in global memory
+  static constexpr int kCopies = bbmm_plan::dig_copies(KK, NG);        // per wave
+  static constexpr int kSlot = bbmm_plan::dig_slot_bytes(KK, NG);      // in the ring
+  static constexpr int kRing = bbmm_plan::dig_ring(KK, NG);
 };
 
 // s_waitcnt vmcnt(N) alone
@@ -299,16 +299,16 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
 
   lds_char* L0 = (lds_char*)lds;
   int nk = ib_end - ib_begin;
-  // the records as a raw buffer of this chunk (at most kDigMaxBlocks records of up to 21 KB); what a copy
-  // reads beyond the chunk is not used, beyond the buffer it reads as zero
+  // the records as a raw buffer of this chunk (at most kDigMaxBlocks records of up to 21 KB and the room of
+  // the last copy); past the end the last record comes again (the count of copies stays)
   __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(rec + (size_t)ib_begin * Rec::kBytes), 0,
-                                                                  nk * Rec::kBytes, 0x00020000);
+                                                                  (int)bbmm_plan::dig_buffer_bytes(nk, KK, NG), 0x00020000);
   int voff = wave * 1024 + lane * 16;
-  auto fetch = [&](int k, int slot) {        // past the end: zeros (the count of copies stays)
+  auto fetch = [&](int k, int slot) {
 #pragma unroll
     for (int c = 0; c < Rec::kCopies; ++c)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(L0 + slot + wave * 1024 + c * 4096),
-                                               16, voff, k * Rec::kBytes + c * 4096, 0, 0);
+                                               16, voff, bbmm_plan::dig_copy_offset(KK, NG, k, nk, c), 0, 0);
   };
   // this lane's address in a ring place, opaque so that the constant offsets go into the instructions
   auto base = [&](int slot) {
@@ -451,11 +451,9 @@ int dig_groups(int c) {
   return 16;
 }
 
-size_t dig_record_bytes(int KK, int ng) { return (size_t)(KK + ng + 1) * 1024; }
-
 void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float* sq, int np, int ld, int KK, int ng,
                    const DevState* st, void* rec) {
-  k_digits<<<np / 16, 256, 0, s>>>(D4, Xb, sq, ld, ng, KK, (int)dig_record_bytes(KK, ng), st, (char*)rec);
+  k_digits<<<np / 16, 256, 0, s>>>(D4, Xb, sq, ld, ng, KK, bbmm_plan::dig_record_bytes(KK, ng), st, (char*)rec);
 }
 
 // Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles
