@@ -608,7 +608,7 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scal
     if (rc) return rc;
     rc = ensure_records(c, ng);
     if (rc) return rc;
-    launch_digits(c->stream, ptr<double>(c->D4), ptr<float>(c->Xb), ptr<float>(c->sq), c->np, ld, c->KK, ng,
+    launch_digits(c->stream, ptr<double>(c->D4), ptr<float>(c->Xs), ptr<float>(c->sq), c->np, ld, c->KK, ng,
                   ptr<DevState>(c->st), c->rec.p);
     if (launch_mm_otf_dig(c->stream, c->prob.kernel, c->KK, ng, c->rec.p, c->Pb.p, ptr<float>(c->sq),
                           ptr<double>(c->Vp), c->np, ld, ns, ptr<DevState>(c->st)))
@@ -1220,7 +1220,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   launch_colmean(s, in->X, c->n, c->d, ptr<DevState>(c->st), ptr<double>(c->partial), ptr<double>(c->gpartial));
   launch_prep_x(s, in->X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st), ptr<float>(c->Xa),
                 ptr<float>(c->Xb), ptr<float>(c->Xs), ptr<float>(c->X4), ptr<float>(c->sq));
-  if (may_use_digits(c)) launch_split_x(s, ptr<float>(c->Xb), c->np, c->KK, c->Pb.p);
+  if (may_use_digits(c)) launch_split_x(s, ptr<float>(c->Xs), c->np, c->KK, c->Pb.p);
   HIPCHK(c, hipGetLastError());
   c->is_setup = true;
   return BBMM_OK;

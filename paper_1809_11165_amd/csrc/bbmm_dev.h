@@ -218,10 +218,10 @@ int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, doub
 constexpr int kDigMaxBlocks = 2046;   // 16-row blocks one accumulator may sum without overflow
 int dig_groups(int c);
 int dig_nj(int KK, int ng);
-void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float* sq, int np, int ld, int KK, int ng,
+void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float* sq, int np, int ld, int KK, int ng,
                    const DevState* st, void* rec);
-// column-side coordinates (from Xb: MFMA operand order) as bf16 pieces: 16 np * 4 KK bytes
-void launch_split_x(hipStream_t s, const float* Xb, int np, int KK, void* Pb);
+// column-side coordinates (from Xs: rows of 4 KK) as bf16 pieces: 16 np * 4 KK bytes
+void launch_split_x(hipStream_t s, const float* Xs, int np, int KK, void* Pb);
 int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec, const void* Pb, const float* sq,
                       double* Vp, int np, int ld, int nsplit, const DevState* st);
 int launch_mm_otf(hipStream_t s, int kernel, int KK, const float* Xa, const float* Xb, const float* sq,

@@ -19,8 +19,9 @@
 // entries in extended precision the sums are as good as fp64 ones (1e-16 ... 2e-15 relative, fp64 accumulation
 // 1e-16 ... 8e-16).  The entries are 32-bit numbers either way: in fixed point they are within 2.4e-10 of
 // the largest, where fp32 rounds them to 6e-8 of themselves; what decides their error is their evaluation
-// (3e-7).  Product of 200,000 points, d = 8, 17 columns, distance from the 64-bit result: 6.7e-7, and 6.5e-7
-// with k_mm_otf; 30,011 points, 100 iterations of the solver: 6.1e-7 and 6.0e-7.
+// (3e-7), the rounding of the distance above all.  Product with normal columns, distance from the 64-bit
+// result (this / k_mm_otf): 200,000 points, d = 8, 17 columns 5.3e-7 / 6.3e-7; 50,000, d = 16, 11 columns 3.3e-7 / 4.0e-7;
+// 9,000, d = 4, 16 columns 1.76e-7 / 1.77e-7.
 #include "bbmm_dev.h"
 #include "bbmm_kfun.h"
 
@@ -65,7 +66,7 @@ __device__ __forceinline__ float unit_kernel_x(float r2) {
 }
 
 // The digit words of a tile's four entries per lane in stages of a few vector instructions, so that the
-// caller can place them between MFMAs.  v: -2 x.x' on entry.  The norms are added as (|x|^2 + |x'|^2), never
+// caller can place them between MFMAs.  v: -2 sgn x.x' on entry.  The norms are added as (|x|^2 + |x'|^2), never
 // one after the other: entry (i, j) and entry (j, i) have to come out the same, bit for bit, or the iteration
 // sees a matrix that is not symmetric (13 iterations more on 92 with the norms as the MFMA's addend).
 template <int KIND>
@@ -82,16 +83,16 @@ struct DigEval {
     }
   };
   template <int S>
-  static __device__ __forceinline__ void run(f32x4& v, f32x4& p, f32x4 sqi, float sqj, i32x4& w, const Const& c) {
+  static __device__ __forceinline__ void run(f32x4& v, f32x4& p, f32x4 sqi, float sqj, float sgn, i32x4& w, const Const& c) {
     constexpr int P = S >> 1, lo = 2 * (S & 1);                // half a tile per stage
     constexpr int E = KIND == 0 ? 2 : 4;                       // first stage of the conversion
 #pragma unroll
     for (int r = lo; r < lo + 2; ++r) {
       if (KIND == 0) {
-        if (P == 0) v[r] = __builtin_amdgcn_exp2f(-__builtin_fabsf(v[r] + (sqi[r] + sqj)));
+        if (P == 0) v[r] = __builtin_amdgcn_exp2f(-__builtin_fabsf(fmaf(v[r], sgn, sqi[r] + sqj)));
         if (P == 1) v[r] = fmaf(v[r], c.x, kHalf);
       } else {
-        if (P == 0) v[r] = __builtin_amdgcn_sqrtf(__builtin_fabsf(v[r] + (sqi[r] + sqj)));
+        if (P == 0) v[r] = __builtin_amdgcn_sqrtf(__builtin_fabsf(fmaf(v[r], sgn, sqi[r] + sqj)));
         if (P == 1) p[r] = __builtin_amdgcn_exp2f(-v[r]);
         if (P == 2) v[r] = fmaf(v[r], fmaf(v[r], c.k2, c.k1), c.x);
         if (P == 3) v[r] = fmaf(v[r], p[r], kHalf);
@@ -109,9 +110,15 @@ __device__ inline int dig_exponent(unsigned hi) { return (int)(hi >> 20) - 1022;
 // Coordinates for the distance MFMA.  |x - x'|^2 = |x|^2 + |x'|^2 - 2 x.x'; the fp32 MFMA of the contraction
 // runs on the vector ALU (measured: 14.4 ns a piece, added to the vector instructions around it), the
 // bf16 one does not.  An fp32 coordinate is the sum of three bf16 pieces h + m + l exactly, and of the nine
-// products all but l l' (2^-32) are kept: one v_mfma_f32_16x16x32_bf16 per four dimensions, lane group g
-// holding dimension 4 t + g, halves j = 0..7 the pieces h h m h l m m l of -2 x in one operand and
-// h m h l h m l m of x in the other.
+// products all but l l' (2^-32) are kept: one v_mfma_f32_16x16x32_bf16 per four dimensions.
+// The unit adds eight products (one lane group) at a time to the sum so far, so their order decides the error: the
+// small ones of all dimensions first, m l' + l m', h l' + l h', h m' + m h', m m', and h h' last.  Rounding of
+// 2 x.x', standard normal coordinates, d = 4, 8, 16: 1.5e-7, 1.7e-7, 2.7e-7 (fp32 MFMA 1.6e-7, 3.0e-7, 5.9e-7; all eight
+// products of one dimension after those of another 2.1e-7, 3.6e-7, 6.5e-7).  A product and its mirror image are
+// neighbours in one group, so that (i, j) and (j, i) get the same bits (see DigEval).  The unit aligns what it adds
+// and drops bits downwards: -5e-8 to -7e-8 on average in the sums above, which would shift all entries
+// the same way.  So every second block of 16 points enters with its sign turned: the sum of tile (I, J) is -2 x.x'
+// times (-1)^(I + J), and the shift has either sign equally often.
 __device__ inline unsigned short bf16_round(float v) {
   unsigned u = __float_as_uint(v);
   return (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
@@ -125,34 +132,55 @@ __device__ inline void bf16_pieces(float x, unsigned short (&q)[3]) {
   }
 }
 
+// Operand of lane group g, MFMA t, of one point: eight slots of the sum over (dimension, pair of pieces).  SIDE
+// 0: the row's factors (times -2), 1: the column's.  x: the point's 4 KK coordinates, blk: its 16-row block.
+template <int SIDE>
+__device__ inline bf16x8u split_operand(const float* __restrict__ x, int KK, int blk, int t, int g) {
+  int G = 4 * t + g, part = G / KK, u = G % KK;
+  bf16x8u o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    unsigned short q[3];
+    int k;
+    if (part < 3) {                                // four dimensions, a product and its mirror image each
+      bf16_pieces(x[4 * u + (e >> 1)], q);
+      int a = part == 0 ? 1 : 0, b = part == 2 ? 1 : 2;      // m l, h l, h m
+      k = ((e & 1) != SIDE) ? b : a;
+    } else {                                       // m m of every dimension, then h h
+      int s = 8 * u + e;
+      k = s < 4 * KK ? 1 : 0;
+      bf16_pieces(x[s < 4 * KK ? s : s - 4 * KK], q);
+    }
+    float v = __uint_as_float((unsigned)(k == 0 ? q[0] : (k == 1 ? q[1] : q[2])) << 16);
+    if (SIDE == 0) v *= -2.f;
+    o[e] = bf16_round(blk & 1 ? -v : v);           // (exact)
+  }
+  return o;
+}
+
 // column-side operand: Pb[i / 16][t][lane][8]
-__global__ __launch_bounds__(256) void k_split_x(const float* __restrict__ Xb, int np, int KK, bf16x8u* __restrict__ Pb) {
+__global__ __launch_bounds__(256) void k_split_x(const float* __restrict__ Xs, int np, int KK, bf16x8u* __restrict__ Pb) {
   size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;      // MFMA operand order: [block][t][lane]
   if (idx >= (size_t)np * 4 * KK) return;
-  unsigned short q[3];
-  bf16_pieces(Xb[idx], q);
-  Pb[idx] = (bf16x8u){q[0], q[1], q[0], q[2], q[0], q[1], q[2], q[1]};
+  int lane = (int)(idx & 63), t = (int)((idx >> 6) % KK);
+  size_t row = (idx >> 6) / KK * 16 + (lane & 15);
+  Pb[idx] = split_operand<1>(Xs + row * 4 * KK, KK, (int)(row >> 4), t, lane >> 4);
 }
 
 // One record per 16-row block holds everything a product needs of it, in 1 KB pieces of 16 bytes per lane
-// (m = lane%16, g = lane/16): KK pieces of coordinates (row m), ng of digits, one of norms (rows 4g..4g+3).
+// (m = lane%16, g = lane/16): KK pieces of coordinates (row m, see split_operand), ng of digits, one of norms (rows 4g..4g+3).
 // Digit piece p: for rows 4g..4g+3 the digit window of right-hand side 2 p + m/8, weight m%8.  One
 // workgroup per record, first threads = (row quad, right-hand side).  Bound by the bytes written (128 per
 // value).
-__global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, const float* __restrict__ Xb,
+__global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, const float* __restrict__ Xs,
                                                  const float* __restrict__ sq, int ld, int ng, int KK, int rec_bytes,
                                                  const DevState* __restrict__ st, char* __restrict__ rec) {
   if (st->done) return;
   int nrhs = 2 * ng;
   int rb = blockIdx.x;
   char* R = rec + (size_t)rb * rec_bytes;
-  for (int e = threadIdx.x; e < KK * 64; e += 256) {
-    unsigned short q[3];
-    bf16_pieces(Xb[(size_t)rb * KK * 64 + e], q);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) q[k] = bf16_round(-2.f * __uint_as_float((unsigned)q[k] << 16));   // exact
-    ((bf16x8u*)R)[e] = (bf16x8u){q[0], q[0], q[1], q[0], q[2], q[1], q[1], q[2]};
-  }
+  for (int e = threadIdx.x; e < KK * 64; e += 256)
+    ((bf16x8u*)R)[e] = split_operand<0>(Xs + (size_t)(rb * 16 + (e & 15)) * 4 * KK, KK, rb, e >> 6, (e >> 4) & 3);
   if (threadIdx.x < 64)
     ((f32x4*)(R + (KK + ng) * 1024))[threadIdx.x] = *(const f32x4*)(sq + rb * 16 + (threadIdx.x >> 4) * 4);
   if ((int)threadIdx.x >= 4 * nrhs) return;
@@ -320,6 +348,8 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
   constexpr int kOperands = NG + KK, kM = NJ * kOperands, kB = NG < 4 ? NG : 4;
   constexpr int kS = NJ * DigEval<KIND>::kStages;
   typename DigEval<KIND>::Const cst;
+  // sign of the sum of tile (k, jb): this times (-1)^(k + jb) (a chunk's first block is even)
+  float sgn0 = __int_as_float(__builtin_amdgcn_readfirstlane(0x3f800000 | (int)((unsigned)jb0 << 31)));
   i32x4 op[2][kB];
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   f32x4 da[NJ], db[NJ], nrm;           // nrm: norms of block k's rows
@@ -336,7 +366,7 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
   // slots of records k - 1, k, k + 1 and of the one requested in step k
   int s_prev = 0, s_cur = Rec::kSlot, s_next = 2 * Rec::kSlot, s_new = (kRing - 1) * Rec::kSlot;
   // d: distances of block k (used up), dn: of block k + 1; w: digits of block k - 1, wn: of block k
-  auto step = [&](int k, f32x4 (&d)[NJ], f32x4 (&dn)[NJ], const i32x4 (&w)[NJ], i32x4 (&wn)[NJ]) {
+  auto step = [&](int k, auto odd, f32x4 (&d)[NJ], f32x4 (&dn)[NJ], const i32x4 (&w)[NJ], i32x4 (&wn)[NJ]) {
     wait_vm<(kRing - 4) * Rec::kCopies>();   // this wave's copies of record k + 1 have landed ...
     __builtin_amdgcn_s_barrier();            // ... and everybody's; nobody reads record k - 2 any more
     asm volatile("" ::: "memory");
@@ -356,7 +386,8 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
       }
       static_for<m * kS / kM, (m + 1) * kS / kM>([&](auto SS) {
         constexpr int S = decltype(SS)::value, t = S / DigEval<KIND>::kStages;
-        DigEval<KIND>::template run<S % DigEval<KIND>::kStages>(d[t], p, nrm, sqj[t], wn[t], cst);
+        DigEval<KIND>::template run<S % DigEval<KIND>::kStages>(d[t], p, nrm, sqj[t], (decltype(odd)::value + t) & 1 ? -sgn0 : sgn0,
+                                                                wn[t], cst);
       });
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -391,17 +422,17 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
     }
     static_for<0, kS>([&](auto SS) {
       constexpr int S = decltype(SS)::value, t = S / DigEval<KIND>::kStages;
-      DigEval<KIND>::template run<S % DigEval<KIND>::kStages>(db[t], p, nrm, sqj[t], wa[t], cst);
+      DigEval<KIND>::template run<S % DigEval<KIND>::kStages>(db[t], p, nrm, sqj[t], t & 1 ? -sgn0 : sgn0, wa[t], cst);
     });
     load_batch(std::integral_constant<int, 0>{}, P, P);
     nrm = *(lds_f32x4)(Q + (Rec::kPieces - 1) * 1024);
   }
 #pragma unroll 1
   for (int k = 1; k + 1 < nk; k += 2) {
-    step(k, da, db, wa, wb);
-    step(k + 1, db, da, wb, wa);
+    step(k, std::integral_constant<int, 1>{}, da, db, wa, wb);
+    step(k + 1, std::integral_constant<int, 0>{}, db, da, wb, wa);
   }
-  step(nk - 1, da, db, wa, wb);
+  step(nk - 1, std::integral_constant<int, 1>{}, da, db, wa, wb);
   {
     lds_char* P = base(s_prev);
     static_for<0, NJ * NG>([&](auto MM) {
@@ -425,7 +456,7 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
       i32x4 w;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        int x = (int)unit_kernel_x<KIND>(__builtin_fabsf(d2[r] + (sqi[r] + sqj[jb])));
+        int x = (int)unit_kernel_x<KIND>(__builtin_fabsf(d2[r] + (sqi[r] + sqj[jb])));   // (the sign is (-1)^(2 I) here)
         w[r] = 4 * g + r == jc ? (((int)kX - x + kDigits) ^ kDigits) : 0;
       }
 #pragma unroll
@@ -451,9 +482,9 @@ int dig_groups(int c) {
   return 16;
 }
 
-void launch_digits(hipStream_t s, const double* D4, const float* Xb, const float* sq, int np, int ld, int KK, int ng,
+void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float* sq, int np, int ld, int KK, int ng,
                    const DevState* st, void* rec) {
-  k_digits<<<np / 16, 256, 0, s>>>(D4, Xb, sq, ld, ng, KK, bbmm_plan::dig_record_bytes(KK, ng), st, (char*)rec);
+  k_digits<<<np / 16, 256, 0, s>>>(D4, Xs, sq, ld, ng, KK, bbmm_plan::dig_record_bytes(KK, ng), st, (char*)rec);
 }
 
 // Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles
@@ -468,9 +499,9 @@ int dig_nj(int KK, int ng) {
   return ng == 12 && KK <= 2 ? 3 : 2;
 }
 
-void launch_split_x(hipStream_t s, const float* Xb, int np, int KK, void* Pb) {
+void launch_split_x(hipStream_t s, const float* Xs, int np, int KK, void* Pb) {
   size_t total = (size_t)np * 4 * KK;
-  k_split_x<<<(int)((total + 255) / 256), 256, 0, s>>>(Xb, np, KK, (bf16x8u*)Pb);
+  k_split_x<<<(int)((total + 255) / 256), 256, 0, s>>>(Xs, np, KK, (bf16x8u*)Pb);
 }
 
 int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec, const void* Pb, const float* sq,
