@@ -54,15 +54,19 @@ constexpr int kDigits = 0x00808080;
 // Scale of the entries: below 2^31 less the largest balanced lower digits, and among the multiples of 2^23
 // there the one that the Matern-5/2 coefficients times it round least at (3e-9 and 1e-8).
 constexpr float kX = 2055208960.f;
-constexpr float kHalf = 0.49999997f;   // rounds x to nearest by truncation, and leaves x >= 2^23 as it is
+// Adding kDigits to the scaled entry rounds it to a whole number, to nearest and in the one rounding of the fma (the
+// sum is above 2^23), and is the addition that the digits need.  (Adding 1/2 and truncating rounds twice: entries
+// came out half a unit high, or 4e-8 of themselves below 2^-8; so does any rounding of ties to one side, since the
+// product lies on a grid of halves, quarters, ...)  An entry keeps 23 bits at least from 2^-8 up.
+constexpr float kRound = (float)kDigits;
 
-// kX k / s + 1/2 from the scaled squared distance (see unit_kernel; the scale costs nothing)
+// kX k / s + kDigits, a whole number, from the scaled squared distance (see unit_kernel; the scale costs nothing)
 template <int KIND>
 __device__ __forceinline__ float unit_kernel_x(float r2) {
-  if (KIND == 0) return fmaf(__builtin_amdgcn_exp2f(-r2), kX, kHalf);
+  if (KIND == 0) return fmaf(__builtin_amdgcn_exp2f(-r2), kX, kRound);
   float a = __builtin_amdgcn_sqrtf(r2);
   float e = __builtin_amdgcn_exp2f(-a);
-  return fmaf(fmaf(a, fmaf(a, kMatK2 * kX, kMatK1 * kX), kX), e, kHalf);
+  return fmaf(fmaf(a, fmaf(a, kMatK2 * kX, kMatK1 * kX), kX), e, kRound);
 }
 
 // The digit words of a tile's four entries per lane in stages of a few vector instructions, so that the
@@ -90,15 +94,15 @@ struct DigEval {
     for (int r = lo; r < lo + 2; ++r) {
       if (KIND == 0) {
         if (P == 0) v[r] = __builtin_amdgcn_exp2f(-__builtin_fabsf(fmaf(v[r], sgn, sqi[r] + sqj)));
-        if (P == 1) v[r] = fmaf(v[r], c.x, kHalf);
+        if (P == 1) v[r] = fmaf(v[r], c.x, kRound);
       } else {
         if (P == 0) v[r] = __builtin_amdgcn_sqrtf(__builtin_fabsf(fmaf(v[r], sgn, sqi[r] + sqj)));
         if (P == 1) p[r] = __builtin_amdgcn_exp2f(-v[r]);
         if (P == 2) v[r] = fmaf(v[r], fmaf(v[r], c.k2, c.k1), c.x);
-        if (P == 3) v[r] = fmaf(v[r], p[r], kHalf);
+        if (P == 3) v[r] = fmaf(v[r], p[r], kRound);
       }
       if (P == E) w[r] = (int)v[r];
-      if (P == E + 1) w[r] = (w[r] + c.dig) ^ c.dig;
+      if (P == E + 1) w[r] = w[r] ^ c.dig;
     }
   }
 };
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         int x = (int)unit_kernel_x<KIND>(__builtin_fabsf(d2[r] + (sqi[r] + sqj[jb])));   // (the sign is (-1)^(2 I) here)
-        w[r] = 4 * g + r == jc ? (((int)kX - x + kDigits) ^ kDigits) : 0;
+        w[r] = 4 * g + r == jc ? (((int)kX + kDigits - x + kDigits) ^ kDigits) : 0;
       }
 #pragma unroll
       for (int q = 0; q < NG; ++q) acc[jb][q] = mfma_i8(R[(KK + q) * 64], w, acc[jb][q]);

@@ -167,3 +167,27 @@ def test_digit_product_is_no_further_off_than_the_fp64_form(ctx, kernel, d):
         err.append(np.linalg.norm(V[rows] - ref) / np.linalg.norm(ref))
     print(d, err)
     assert err[0] <= 1.02 * err[1]
+
+
+@pytest.mark.parametrize("d,ell", [(16, 1.5), (16, 2.0), (8, 1.0), (4, 0.8), (4, 0.5)])
+def test_digit_entries_carry_no_systematic_error(ctx, d, ell):
+    """Row sums of K against the fp64 form's, which shares the rounded coordinates: the roundings of distances and entries
+    differ, but their mean over the rows has to vanish within five standard errors.  (Entries 2^-7 ... 2^-14 for the most
+    part at d = 16, l = 1.5, where half a unit per entry would show as 2e-8.)"""
+    import torch
+    n = N0
+    w, _ = _problem(n, d, inputs.RBF)
+    from paper_1809_11165_amd import binding
+    w.X = np.random.default_rng(1).standard_normal((n, d)).astype(np.float32)
+    w.lengthscale, w.outputscale = np.array([ell]), 1.0
+    ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+    one = torch.ones(n, 1, device="cuda")
+    V = []
+    for v in (1, 0):
+        ctx.bbmm_tune("otf_sym", v)
+        try:
+            V.append(ctx.bbmm_kernel_mm(inputs.ONTHEFLY, one).cpu().numpy().astype(np.float64)[:, 0])
+        finally:
+            ctx.bbmm_tune("otf_sym", 1)
+    e = (V[0] - V[1]) / V[1]
+    assert abs(e.mean()) <= 5.0 * e.std() / np.sqrt(n), (e.mean(), e.std() / np.sqrt(n))
