@@ -51,8 +51,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 constexpr int kDigits = 0x00808080;
-// Scale of the entries: below 2^31 less the largest balanced lower digits, and among the multiples of 2^23
-// there the one that the Matern-5/2 coefficients times it round least at (3e-9 and 1e-8).
+// Scale of the entries: below 2^31 less the largest balanced lower digits, and a multiple of 2^23, so that it is exact in fp32.
 constexpr float kX = 2055208960.f;
 // Adding kDigits to the scaled entry rounds it to a whole number, to nearest and in the one rounding of the fma (the
 // sum is above 2^23), and is the addition that the digits need.  (Adding 1/2 and truncating rounds twice: entries
@@ -60,13 +59,15 @@ constexpr float kX = 2055208960.f;
 // product lies on a grid of halves, quarters, ...)  An entry keeps 23 bits at least from 2^-8 up.
 constexpr float kRound = (float)kDigits;
 
-// kX k / s + kDigits, a whole number, from the scaled squared distance (see unit_kernel; the scale costs nothing)
+// kX k / s + kDigits, a whole number, from the scaled squared distance: the fp32 entry that unit_kernel gives, scaled.
+// (The scale in the Matern coefficients would save the product, but overflow from distances of 1e15 on and round
+// the coefficients once more.)
 template <int KIND>
 __device__ __forceinline__ float unit_kernel_x(float r2) {
   if (KIND == 0) return fmaf(__builtin_amdgcn_exp2f(-r2), kX, kRound);
   float a = __builtin_amdgcn_sqrtf(r2);
   float e = __builtin_amdgcn_exp2f(-a);
-  return fmaf(fmaf(a, fmaf(a, kMatK2 * kX, kMatK1 * kX), kX), e, kRound);
+  return fmaf(fmaf(a, fmaf(a, kMatK2, kMatK1), 1.f) * e, kX, kRound);
 }
 
 // The digit words of a tile's four entries per lane in stages of a few vector instructions, so that the
@@ -81,7 +82,7 @@ struct DigEval {
   struct Const {
     int dig;
     float x, k1, k2;
-    __device__ Const() : dig(kDigits), x(kX), k1(kMatK1 * kX), k2(kMatK2 * kX) {
+    __device__ Const() : dig(kDigits), x(kX), k1(kMatK1), k2(kMatK2) {
       asm volatile("" : "+s"(dig), "+s"(x));
       if (KIND == 1) asm volatile("" : "+s"(k1), "+s"(k2));
     }
@@ -98,8 +99,8 @@ struct DigEval {
       } else {
         if (P == 0) v[r] = __builtin_amdgcn_sqrtf(__builtin_fabsf(fmaf(v[r], sgn, sqi[r] + sqj)));
         if (P == 1) p[r] = __builtin_amdgcn_exp2f(-v[r]);
-        if (P == 2) v[r] = fmaf(v[r], fmaf(v[r], c.k2, c.k1), c.x);
-        if (P == 3) v[r] = fmaf(v[r], p[r], kRound);
+        if (P == 2) v[r] = fmaf(v[r], fmaf(v[r], c.k2, c.k1), 1.f);
+        if (P == 3) v[r] = fmaf(v[r] * p[r], c.x, kRound);
       }
       if (P == E) w[r] = (int)v[r];
       if (P == E + 1) w[r] = w[r] ^ c.dig;

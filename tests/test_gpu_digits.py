@@ -169,14 +169,15 @@ def test_digit_product_is_no_further_off_than_the_fp64_form(ctx, kernel, d):
     assert err[0] <= 1.02 * err[1]
 
 
+@pytest.mark.parametrize("kernel", [inputs.RBF, inputs.MATERN52])
 @pytest.mark.parametrize("d,ell", [(16, 1.5), (16, 2.0), (8, 1.0), (4, 0.8), (4, 0.5)])
-def test_digit_entries_carry_no_systematic_error(ctx, d, ell):
+def test_digit_entries_carry_no_systematic_error(ctx, kernel, d, ell):
     """Row sums of K against the fp64 form's, which shares the rounded coordinates: the roundings of distances and entries
-    differ, but their mean over the rows has to vanish within five standard errors.  (Entries 2^-7 ... 2^-14 for the most
+    differ, but their mean over the rows has to vanish within five standard errors.  (RBF entries are 2^-7 ... 2^-14 for the most
     part at d = 16, l = 1.5, where half a unit per entry would show as 2e-8.)"""
     import torch
     n = N0
-    w, _ = _problem(n, d, inputs.RBF)
+    w, _ = _problem(n, d, kernel)
     from paper_1809_11165_amd import binding
     w.X = np.random.default_rng(1).standard_normal((n, d)).astype(np.float32)
     w.lengthscale, w.outputscale = np.array([ell]), 1.0
@@ -191,3 +192,27 @@ def test_digit_entries_carry_no_systematic_error(ctx, d, ell):
             ctx.bbmm_tune("otf_sym", 1)
     e = (V[0] - V[1]) / V[1]
     assert abs(e.mean()) <= 5.0 * e.std() / np.sqrt(n), (e.mean(), e.std() / np.sqrt(n))
+
+
+@pytest.mark.parametrize("kernel", [inputs.RBF, inputs.MATERN52])
+@pytest.mark.parametrize("far", [1e6, 1e13, 1e16, 1e18])
+def test_digit_entries_of_a_far_point(ctx, kernel, far):
+    """One point very far out (its square still in fp32's range): entries with it are zero, as in the fp64 form.  X is
+    centred, so two points on opposite sides keep the others where they are."""
+    import torch
+    n, d = 6200, 3
+    w, _ = _problem(n, d, kernel)
+    w.X[17], w.X[4000] = far, -far
+    from paper_1809_11165_amd import binding
+    ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+    M = torch.from_numpy(np.random.default_rng(2).standard_normal((n, 5)).astype(np.float32)).cuda()
+    V = []
+    for v in (1, 0):
+        ctx.bbmm_tune("otf_sym", v)
+        try:
+            V.append(ctx.bbmm_kernel_mm(inputs.ONTHEFLY, M).cpu().numpy())
+        finally:
+            ctx.bbmm_tune("otf_sym", 1)
+    assert np.isfinite(V[1]).all()
+    np.testing.assert_allclose(V[0][[17, 4000]], (w.outputscale + w.noise) * M.cpu().numpy()[[17, 4000]], rtol=2e-7)
+    np.testing.assert_allclose(V[0], V[1], rtol=0, atol=4e-6 * np.abs(V[1]).max())
