@@ -22,7 +22,8 @@
  *     before they return).  A call
  *     that returns host values synchronises the stream once before it returns.
  *   - Precision: K_hat entries are fp32; inside the library every n x c block of
- *     the iteration, the pivoted-Cholesky factor and all sums are fp64.  float
+ *     the iteration, the pivoted-Cholesky factor and all sums are fp64 (large on-the-fly
+ *     products: integers of that accuracy, see "otf_digits").  float
  *     block arguments are converted on entry and rounded once on exit.
  *   - Every function returns an int status (BBMM_OK == 0).  No exceptions,
  *     no exit().  bbmm_last_error() gives a message for the last failure.
@@ -173,15 +174,24 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                of K_hat)
  *   "otf_split"  number of row chunks an on-the-fly product is split into (with "otf_sym": number
  *                of workgroups of each of its two launches, default two per compute unit)
- *   "otf_sym"    1 (default): an on-the-fly product over at most 16 input dimensions and at least 6144
- *                (padded) rows is formed on the 8-bit matrix pipe from the digits of the entries and of
- *                the block (exact integer sums; entries in 32-bit fixed point, within 2.4e-10 of the
- *                outputscale); otherwise one of at most 16 columns over 17 to 32 dimensions and at least
- *                12288 rows evaluates only the tiles on and above the diagonal and uses each for both of
- *                its contributions (K is symmetric).  2: where the first does not apply, the second for
- *                any number of rows and up to 32 dimensions; 0: every tile is evaluated for the one
- *                contribution, in fp64, as it is for wider blocks and inputs.  Same products to the
- *                rounding of the entries
+ *   "otf_digits" products on the fly over at most 16 input dimensions and at least 6144 (padded) rows, with
+ *                "otf_sym" at its default, are formed on the 8-bit matrix pipe from the digits of the
+ *                entries and of the block: exact integer sums; entries rounded to whole multiples of
+ *                4.9e-10 of the outputscale (to 23 bits at least where that is more), the block to
+ *                62 bits below the largest entry of each column.  Against 64 bits the products of dense
+ *                blocks are nearer than the fp64 form's (the distances are rounded less), but every
+ *                row gets an error of about 1.4e-10 outputscale |column|, also a row that meets
+ *                only small entries.
+ *                1 (default): the products of an mBCG run, whose results are measured by norms; and
+ *                bbmm_kernel_mm where all columns suit it: finite, at most n / 128 entries below
+ *                2^-12 and n / 16384 + 4 below 2^-20 of the largest (decided on the device); any
+ *                other block of bbmm_kernel_mm takes the fp64 form.  2: all of them; 0: none
+ *   "otf_sym"    the form with fp64 sums.  1 (default): a product of at most 16 columns over at most 32 input
+ *                dimensions and at least 12288 (padded) rows evaluates only the tiles on and above
+ *                the diagonal and uses each for both of its contributions (K is symmetric);
+ *                2: the same for any number of rows; 0: every tile is evaluated for the one
+ *                contribution, as it is for wider blocks and inputs.  Same values, fp64 sums in
+ *                another order.  0 and 2 also switch "otf_digits" off
  *   "ur_blocks"  upper limit of the workgroups of the fused U/R update (default 128, at most 512)
  *   "khat_panel" layout of the materialised K_hat: column panels of that width (a multiple of
  *                256; default 1024), each panel row-major; 1 = plain row-major.  Takes effect at
@@ -218,7 +228,7 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                not reduced within it makes the call return BBMM_ENOCONV
  *   "time_mm"    1: record HIP events on the context's stream around every K_hat.M launch of
  *                the next mBCG runs (read back with bbmm_mm_timing); 0: off (default)
- * value <= 0 restores the default (for "khat_sym" and "otf_sym" the value is the setting itself).
+ * value <= 0 restores the default (for "khat_sym", "otf_sym" and "otf_digits" the value is the setting itself).
  * Unknown key: BBMM_EINVAL. */
 int bbmm_tune(bbmm_ctx* ctx, const char* key, int64_t value);
 

@@ -100,6 +100,7 @@ struct bbmm_ctx {
   TriLists sym;                              // ... from the stored triangle (panels of 1024 columns)
   TriLists otft;                             // ... on the fly from X (panels of 512 columns)
   int64_t otf_sym = 1;                       // on-the-fly product with each tile pair evaluated once (<= 16 columns, d <= 32): 0 never, 1 from kOtfSymMinRows rows on, 2 always
+  int64_t otf_digits = 1;                    // digits (needs otf_sym 1): 0 never, 1 in the iteration and for products of blocks that suit them, 2 for all
   // plans of the materialised product: 16- and 32-column blocks (index 0 / 1), 16-column block with at most 12 columns in use (2)
   int plan_np = 0, plan_wgs[3] = {0, 0, 0}, plan_slots[3] = {0, 0, 0};
   int64_t plan_tune = -1;
@@ -131,7 +132,7 @@ struct bbmm_ctx {
   Buf Xa, Xb, Xs, X4, sq, Khat, L, delta, U, R, V, Z0, D4, Vp, partial, gpartial, alpha, beta, resid, st,
       tmpA, tmpB, SA, SB, u0v, dkpartial, eig, plan[3], nseg[3], 
       KUU, Gm, Ginv, Kux, AT, A, qdiag, Tp, T4, sgplan[4], sgnseg[4],
-      Ua, Ub, Us, U4, usq, TU, TW, BU, BW, dkops, rec, Pb;
+      Ua, Ub, Us, U4, usq, TU, TW, BU, BW, dkops, rec, Pb, dcnt;
   double* eig_static = nullptr;   // this device's address of `scratch`
   int* h_eig_status = nullptr;    // pinned, BBMM_EIG_NOALLOC_MAX ints
   DevState* h_st = nullptr;   // pinned
@@ -371,8 +372,8 @@ int ensure_sgpr_plans(bbmm_ctx* c) {
   return BBMM_OK;
 }
 
-// Row chunks of the digit form of the on-the-fly product: one workgroup per compute unit; at most
-// kDigMaxBlocks row blocks per chunk.
+// Row chunks of the digit form of the on-the-fly product: at least three workgroups per compute unit, in whole rounds;
+// at most kDigMaxBlocks row blocks per chunk.
 int dig_split_of(const bbmm_ctx* c, int cc) {
   int nblk = c->np / 16, nj = dig_nj(c->KK, dig_groups(cc));
   int strips = (nblk + 4 * nj - 1) / (4 * nj);
@@ -388,7 +389,7 @@ bool may_use_digits(const bbmm_ctx* c) { return c->np >= kDigMinRows && c->KK <=
 
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.
 bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
-  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym != 0 && may_use_digits(c) &&
+  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym == 1 && c->otf_digits != 0 && may_use_digits(c) &&
          dig_split_of(c, cc) <= kMaxSplit;
 }
 
@@ -547,6 +548,63 @@ int sgpr_first_pass(bbmm_ctx* c, int ld, const double* D4, VpShape* shape, int c
   return BBMM_OK;
 }
 
+// Whether the fp64 form of the on-the-fly product evaluates every pair of tiles (I, J), (J, I) once and uses it for
+// both contributions (beyond 32 input dimensions that form runs out of registers and the one-use form is the
+// faster; so it is for small n, where the pieces of the two-use form are short).
+bool otf64_paired(const bbmm_ctx* c, int ld) {
+  return (c->otf_sym == 2 || (c->otf_sym == 1 && c->np >= kOtfSymMinRows)) && ld == 16 && c->KK <= 8;
+}
+
+// Plan and room for the partial results of stage_otf64.
+int otf64_reserve(bbmm_ctx* c, int ld) {
+  if (!otf64_paired(c, ld)) return ensure_vp(c, otf_split_of(c), ld);
+  int rc = ensure_otf_tri_plan(c);
+  return rc ? rc : ensure_vp(c, c->otft.max_slots, ld);
+}
+
+// On-the-fly product with fp32 entries and fp64 sums.
+int stage_otf64(bbmm_ctx* c, int cc, int ld, VpShape* shape, double* scaleV, double* addD) {
+  int rc = otf64_reserve(c, ld);
+  if (rc) return rc;
+  *scaleV = c->prob.outputscale;
+  *addD = c->prob.noise;
+  if (otf64_paired(c, ld)) {
+    if (launch_mm_otf_tri(c->stream, c->prob.kernel, c->KK, ptr<float>(c->Xa), ptr<float>(c->Xb), ptr<float>(c->sq),
+                          ptr<double>(c->D4), ptr<double>(c->Vp), c->np, cc, ptr<MmPiece>(c->otft.pieces),
+                          ptr<int>(c->otft.first0), c->otft.wgs[0], ptr<int>(c->otft.first1), c->otft.wgs[1],
+                          ptr<int>(c->otft.base), ptr<DevState>(c->st)))
+      return fail(c, BBMM_EINVAL, "unsupported input dimension");
+    *shape = VpShape{0, ptr<int>(c->otft.tot), BBMM_OTF_PANEL};
+    return BBMM_OK;
+  }
+  int ns = otf_split_of(c);
+  if (launch_mm_otf(c->stream, c->prob.kernel, c->KK, ptr<float>(c->Xa), ptr<float>(c->Xb),
+                    ptr<float>(c->sq), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld, cc, ns,
+                    ptr<DevState>(c->st)))
+    return fail(c, BBMM_EINVAL, "unsupported block width or input dimension");
+  *shape = VpShape{ns, nullptr, 1};
+  return BBMM_OK;
+}
+
+// The same on the 8-bit matrix pipe; guard: only if the block suits it (see launch_mm_otf_dig; counts zero beforehand).
+int stage_otf_dig(bbmm_ctx* c, int cc, int ld, bool guard, VpShape* shape, double* scaleV, double* addD) {
+  int ns = dig_split_of(c, cc), ng = dig_groups(cc);
+  int rc = ensure_vp(c, ns, ld);
+  if (rc) return rc;
+  rc = ensure_records(c, ng);
+  if (rc) return rc;
+  unsigned* counts = guard ? ptr<unsigned>(c->dcnt) : nullptr;
+  launch_digits(c->stream, ptr<double>(c->D4), ptr<float>(c->Xs), ptr<float>(c->sq), c->n, c->np, ld, c->KK, ng,
+                ptr<DevState>(c->st), counts, c->rec.p);
+  if (launch_mm_otf_dig(c->stream, c->prob.kernel, c->KK, ng, c->rec.p, c->Pb.p, ptr<float>(c->sq),
+                        ptr<double>(c->Vp), c->n, c->np, ld, ns, counts, ptr<DevState>(c->st)))
+    return fail(c, BBMM_EINVAL, "unsupported block width or input dimension");
+  *shape = VpShape{ns, nullptr, 1};
+  *scaleV = c->prob.outputscale;
+  *addD = c->prob.noise;
+  return BBMM_OK;
+}
+
 // Vp <- partial products of K_hat with the block in D4; returns the split count and the
 // (scale, add) pair that turns the partial sums into K_hat D.
 int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scaleV, double* addD) {
@@ -603,47 +661,9 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scal
     *scaleV = 1.0;
     *addD = 0.0;
   } else if (uses_digits(c, mode, cc)) {
-    int ns = dig_split_of(c, cc), ng = dig_groups(cc);
-    int rc = ensure_vp(c, ns, ld);
-    if (rc) return rc;
-    rc = ensure_records(c, ng);
-    if (rc) return rc;
-    launch_digits(c->stream, ptr<double>(c->D4), ptr<float>(c->Xs), ptr<float>(c->sq), c->np, ld, c->KK, ng,
-                  ptr<DevState>(c->st), c->rec.p);
-    if (launch_mm_otf_dig(c->stream, c->prob.kernel, c->KK, ng, c->rec.p, c->Pb.p, ptr<float>(c->sq),
-                          ptr<double>(c->Vp), c->np, ld, ns, ptr<DevState>(c->st)))
-      return fail(c, BBMM_EINVAL, "unsupported block width or input dimension");
-    *shape = VpShape{ns, nullptr, 1};
-    *scaleV = c->prob.outputscale;
-    *addD = c->prob.noise;
-  } else if (mode == BBMM_MODE_ONTHEFLY && (c->otf_sym == 2 || (c->otf_sym == 1 && c->np >= kOtfSymMinRows)) &&
-             ld == 16 && c->KK <= 8) {
-    // every pair of tiles (I, J), (J, I) evaluated once and used for both contributions (beyond 32
-    // input dimensions the two-use form runs out of registers and the one-use form is the faster;
-    // so it is for small n, where the pieces of the two-use form are short)
-    int rc = ensure_otf_tri_plan(c);
-    if (rc) return rc;
-    rc = ensure_vp(c, c->otft.max_slots, ld);
-    if (rc) return rc;
-    if (launch_mm_otf_tri(c->stream, c->prob.kernel, c->KK, ptr<float>(c->Xa), ptr<float>(c->Xb), ptr<float>(c->sq),
-                          ptr<double>(c->D4), ptr<double>(c->Vp), c->np, cc, ptr<MmPiece>(c->otft.pieces),
-                          ptr<int>(c->otft.first0), c->otft.wgs[0], ptr<int>(c->otft.first1), c->otft.wgs[1],
-                          ptr<int>(c->otft.base), ptr<DevState>(c->st)))
-      return fail(c, BBMM_EINVAL, "unsupported input dimension");
-    *shape = VpShape{0, ptr<int>(c->otft.tot), BBMM_OTF_PANEL};
-    *scaleV = c->prob.outputscale;
-    *addD = c->prob.noise;
+    return stage_otf_dig(c, cc, ld, false, shape, scaleV, addD);
   } else if (mode == BBMM_MODE_ONTHEFLY) {
-    int ns = otf_split_of(c);
-    int rc = ensure_vp(c, ns, ld);
-    if (rc) return rc;
-    if (launch_mm_otf(c->stream, c->prob.kernel, c->KK, ptr<float>(c->Xa), ptr<float>(c->Xb),
-                      ptr<float>(c->sq), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld, cc, ns,
-                      ptr<DevState>(c->st)))
-      return fail(c, BBMM_EINVAL, "unsupported block width or input dimension");
-    *shape = VpShape{ns, nullptr, 1};
-    *scaleV = c->prob.outputscale;
-    *addD = c->prob.noise;
+    return stage_otf64(c, cc, ld, shape, scaleV, addD);
   } else {
     return fail(c, BBMM_EINVAL, "unknown mode");
   }
@@ -670,7 +690,7 @@ int stage_pivchol(bbmm_ctx* c) {
       VpShape sh{0, nullptr, 1};
       int rc = sgpr_second_pass(c, 16, &sh, 1);
       if (rc) return rc;
-      launch_vreduce(s, ptr<double>(c->Vp), sh, c->n, c->np, 16, 1.0, 0.0, ptr<double>(c->D4), ptr<double>(c->V));
+      launch_vreduce(s, ptr<double>(c->Vp), sh, sh, nullptr, c->n, c->np, 16, 1.0, 0.0, ptr<double>(c->D4), ptr<double>(c->V));
       launch_pc_step(s, c->prob.X, c->n, m, c->kp, c->hyp, ptr<double>(c->delta), ptr<double>(c->L), st,
                      arg[m & 1], arg[(m + 1) & 1], nb, ptr<double>(c->V), 16, fpiv(m), fpiv(m + 1));
     }
@@ -733,7 +753,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     double scaleV = 1.0, addD = 0.0;
     int rc = stage_mm(c, mode, cc, ld, &ns, &scaleV, &addD);
     if (rc) return rc;
-    launch_vreduce(s, ptr<double>(c->Vp), ns, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
+    launch_vreduce(s, ptr<double>(c->Vp), ns, ns, nullptr, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
     launch_warm_apply(s, warm, ptr<double>(c->V), c->n, ld, ptr<double>(c->U), ptr<double>(c->R));
     launch_fill_f64(s, ptr<double>(c->D4), blk, 0.0);
     launch_ur(s, 2, c->n, ld, cc, c->kp, noise, 0.0, ptr<double>(c->D4), ptr<double>(c->V), ptr<double>(c->U),
@@ -1080,7 +1100,7 @@ int bbmm_destroy(bbmm_ctx* c) {
                  &c->nseg[1], &c->nseg[2], &c->KUU, &c->Gm, &c->Ginv, &c->Kux, &c->AT, &c->A, &c->qdiag, &c->Tp, &c->T4,
                  &c->sgplan[0], &c->sgplan[1], &c->sgplan[2], &c->sgplan[3], &c->sgnseg[0], &c->sgnseg[1],
                  &c->sgnseg[2], &c->sgnseg[3], &c->Ua, &c->Ub, &c->Us, &c->U4, &c->usq, &c->TU, &c->TW, &c->BU,
-                 &c->BW, &c->dkops, &c->rec, &c->Pb};
+                 &c->BW, &c->dkops, &c->rec, &c->Pb, &c->dcnt};
   for (Buf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
@@ -1102,6 +1122,7 @@ int bbmm_tune(bbmm_ctx* c, const char* key, int64_t value) {
   }
   if (!strcmp(key, "mat_wgs")) c->mat_wgs = value > 0 ? value : 0;
   else if (!strcmp(key, "otf_split")) c->otf_split = value > 0 ? value : 0;
+  else if (!strcmp(key, "otf_digits")) c->otf_digits = value <= 0 ? 0 : (value == 1 ? 1 : 2);   // never / where they suit / always
   else if (!strcmp(key, "otf_sym")) c->otf_sym = value <= 0 ? 0 : (value == 1 ? 1 : 2);   // off / by size / always
   else if (!strcmp(key, "ur_blocks")) c->ur_blocks_cap = value > 0 ? value : 0;
   else if (!strcmp(key, "khat_sym")) {
@@ -1203,6 +1224,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
       {&c->alpha, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->beta, sizeof(double) * BBMM_MAXP * BBMM_MAXC},
       {&c->resid, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->st, sizeof(DevState)},
       {&c->tmpA, blk}, {&c->tmpB, blk}, {&c->Pb, may_use_digits(c) ? 4 * opx : 0},
+      {&c->dcnt, may_use_digits(c) ? kDigCountWords * sizeof(unsigned) : 0},
       {&c->SA, np * 64 * sizeof(float)}, {&c->SB, np * 64 * sizeof(float)}, {&c->u0v, np * sizeof(float)},
   };
   for (auto& w : want) {
@@ -1278,14 +1300,26 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   if (!M || !V || cc < 1 || cc > BBMM_MAXC) return fail(c, BBMM_EINVAL, "bad block");
   int ld = ld_for((int)cc);
   hipStream_t s = c->stream;
-  launch_fill_bytes0(s, &ptr<DevState>(c->st)->dmax[0], (2 * BBMM_MAXC + 2) * sizeof(int));
-  launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), uses_digits(c, mode, (int)cc) ? 1 : 0,
-                 ptr<DevState>(c->st));
-  VpShape ns{0, nullptr, 1};
+  DevState* st = ptr<DevState>(c->st);
+  int digits = uses_digits(c, mode, (int)cc) ? 1 : 0;
+  ZeroSegs z = {{&st->dmax[0], digits ? c->dcnt.p : nullptr}, {2 * BBMM_MAXC + 2, kDigCountWords}, digits ? 2 : 1};
+  launch_fill_multi0(s, z);                     // ... dflag, done, iters_run
+  launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), digits, st);
+  VpShape ns{0, nullptr, 1}, alt{0, nullptr, 1};
   double scaleV = 1.0, addD = 0.0;
-  rc = stage_mm(c, mode, (int)cc, ld, &ns, &scaleV, &addD);
+  const DevState* pick = nullptr;
+  if (digits && c->otf_digits == 1) {
+    // the caller sees the rows of this product, not an iteration's result: the digits only where the block suits them
+    // (decided on the device, with the counts that k_digits leaves), the fp64 form otherwise
+    pick = st;
+    rc = otf64_reserve(c, ld);
+    if (!rc) rc = stage_otf_dig(c, (int)cc, ld, true, &alt, &scaleV, &addD);
+    if (!rc) rc = stage_otf64(c, (int)cc, ld, &ns, &scaleV, &addD);
+  } else {
+    rc = stage_mm(c, mode, (int)cc, ld, &ns, &scaleV, &addD);
+  }
   if (rc) return rc;
-  launch_vreduce(s, ptr<double>(c->Vp), ns, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
+  launch_vreduce(s, ptr<double>(c->Vp), ns, alt, pick, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
   launch_unpack_rows(s, ptr<double>(c->V), ld, c->n, (int)cc, V);
   HIPCHK(c, hipGetLastError());
   return BBMM_OK;
@@ -1426,7 +1460,7 @@ int bbmm_predict_var(bbmm_ctx* c, int32_t mode, const float* Xstar, int64_t ns, 
     rc = sgpr_second_pass(c, ld, &sh);
     if (rc) return rc;
     launch_fill_f64(s, ptr<double>(c->D4), (size_t)c->np * ld, 0.0);
-    launch_vreduce(s, ptr<double>(c->Vp), sh, c->n, c->np, ld, 1.0, 0.0, ptr<double>(c->D4), ptr<double>(c->R));
+    launch_vreduce(s, ptr<double>(c->Vp), sh, sh, nullptr, c->n, c->np, ld, 1.0, 0.0, ptr<double>(c->D4), ptr<double>(c->R));
     HIPCHK(c, hipMemcpyAsync(c->tmpB.p, c->R.p, sizeof(double) * (size_t)c->np * ld, hipMemcpyDeviceToDevice, s));
     rc = stage_mbcg(c, mode, (int)ns, ld);
     if (rc) return rc;

@@ -43,7 +43,7 @@ struct DevState {
   int status;       // BBMM_* code raised on the device (0 = ok)
   int rank;         // preconditioner rank actually built
   unsigned fin_ticket;   // arrivals of k_ur_fin's blocks (zero between launches)
-  int xbad;         // a coordinate of X is not finite (the digit products then return NaN throughout)
+  int xbad;         // 1: one point of X is too far out to be squared, 2 or more: see k_prep_x
   unsigned counter[8][40];   // arrival tickets per kernel family: [0] final, [1 + g] group g
 };
 
@@ -96,7 +96,8 @@ void launch_copy_block(hipStream_t s, const float* src, size_t pw, size_t rows_p
 void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* D4, int track, DevState* st);
 void launch_warm_apply(hipStream_t s, const float* u_init, const double* V, int n, int ld, double* U,
                        double* R);
-void launch_vreduce(hipStream_t s, const double* Vp, VpShape shape, int n, int np, int ld, double scaleV,
+// pick (may be null): with pick->done set the partial results have the shape `alt`
+void launch_vreduce(hipStream_t s, const double* Vp, VpShape shape, VpShape alt, const DevState* pick, int n, int np, int ld, double scaleV,
                     double addD, const double* D4, double* V);
 // diag_in / row_in: NULL for a plain kernel matrix of X (constant diagonal, rows evaluated from X);
 // otherwise the matrix diagonal (n) and, per step, the pivot's row at row_in[i * row_ld].
@@ -218,12 +219,17 @@ int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, doub
 constexpr int kDigMaxBlocks = 2046;   // 16-row blocks one accumulator may sum without overflow
 int dig_groups(int c);
 int dig_nj(int KK, int ng);
-void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float* sq, int np, int ld, int KK, int ng,
-                   const DevState* st, void* rec);
+// counts (may be null; kDigCountWords words, zero beforehand): receives the entries that decide whether the block suits the digits.
+constexpr int kDigCountRows = 32;                            // copies of the counts, against contention
+constexpr int kDigCountWords = kDigCountRows * 2 * BBMM_MAXC;
+void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float* sq, int n, int np, int ld, int KK, int ng,
+                   const DevState* st, unsigned* counts, void* rec);
 // column-side coordinates (from Xs: rows of 4 KK) as bf16 pieces: 16 np * 4 KK bytes
 void launch_split_x(hipStream_t s, const float* Xs, int np, int KK, void* Pb);
+// counts (may be null): does nothing for a block that does not suit the digits (or unusual X), and sets st->done otherwise, so that a
+// fp64 product launched behind it does the work or none.
 int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec, const void* Pb, const float* sq,
-                      double* Vp, int np, int ld, int nsplit, const DevState* st);
+                      double* Vp, int n, int np, int ld, int nsplit, const unsigned* counts, DevState* st);
 int launch_mm_otf(hipStream_t s, int kernel, int KK, const float* Xa, const float* Xb, const float* sq,
                   const double* D4, double* Vp, int np, int ld, int c, int nsplit, const DevState* st);
 // The same product with every pair of tiles (I, J), (J, I) evaluated once and used for both of its

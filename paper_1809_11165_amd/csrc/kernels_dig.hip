@@ -172,14 +172,28 @@ __global__ __launch_bounds__(256) void k_split_x(const float* __restrict__ Xs, i
   Pb[idx] = split_operand<1>(Xs + row * 4 * KK, KK, (int)(row >> 4), t, lane >> 4);
 }
 
+// Whether a block suits the digits, for a caller who sees the product itself.  Fixed point leaves an error of 1.4e-10 of the
+// outputscale times the norm of the block's column in every row of the product: nothing beside the rounding of the entries
+// where the column's entries are of a size, and too much in rows that meet only small entries of K or of the column.
+// So at most n / 128 entries of a column may lie below 2^-12 of its largest power of two, and n / 16384 + 4 below 2^-20
+// (a column of 200 000 normal values has 2e-3 n and about one); everything must be finite.
+__device__ inline bool dig_dense(const DevState* st, const unsigned* __restrict__ counts, int n) {
+  int lane = threadIdx.x & 63, q = lane & (BBMM_MAXC - 1);   // lanes 0..31: small entries, 32..63: tiny ones
+  unsigned sum = 0, hi = st->dmax[q];
+#pragma unroll
+  for (int r = 0; r < kDigCountRows; ++r) sum += counts[r * 2 * BBMM_MAXC + lane];
+  bool bad = hi >= 0x7ff00000u || (hi != 0u && sum > (unsigned)(lane < BBMM_MAXC ? n / 128 : n / 16384 + 4));
+  return !__any(bad) && st->xbad == 0;
+}
+
 // One record per 16-row block holds everything a product needs of it, in 1 KB pieces of 16 bytes per lane
 // (m = lane%16, g = lane/16): KK pieces of coordinates (row m, see split_operand), ng of digits, one of norms (rows 4g..4g+3).
 // Digit piece p: for rows 4g..4g+3 the digit window of right-hand side 2 p + m/8, weight m%8.  One
 // workgroup per record, first threads = (row quad, right-hand side).  Bound by the bytes written (128 per
 // value).
 __global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, const float* __restrict__ Xs,
-                                                 const float* __restrict__ sq, int ld, int ng, int KK, int rec_bytes,
-                                                 const DevState* __restrict__ st, char* __restrict__ rec) {
+                                                 const float* __restrict__ sq, int n, int ld, int ng, int KK, int rec_bytes,
+                                                 const DevState* __restrict__ st, unsigned* counts, char* __restrict__ rec) {
   if (st->done) return;
   int nrhs = 2 * ng;
   int rb = blockIdx.x;
@@ -195,11 +209,20 @@ __global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, c
   int e = dig_exponent(hi);
   bool use = hi >= 0x00100000u && hi < 0x7ff00000u;   // neither zero nor non-finite
   unsigned long long str[4];
+  unsigned small = 0, tiny = 0;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     long long i = llrint(use ? ldexp(d[r], 62 - e) : 0.0);
+    bool live = rb * 16 + 4 * g + r < n;
+    small += live && llabs(i) < (1ll << 50);
+    tiny += live && llabs(i) < (1ll << 42);
     constexpr long long C = 0x0080808080808080ll;
     str[r] = __builtin_bswap64((unsigned long long)((i + C) ^ C));   // most significant digit in byte 0
+  }
+  if (counts && small) {
+    unsigned* c = counts + (rb % kDigCountRows) * 2 * BBMM_MAXC + q;
+    atomicAdd(c, small);
+    if (tiny) atomicAdd(c + BBMM_MAXC, tiny);
   }
   i32x4* out = (i32x4*)(R + (KK + (q >> 1)) * 1024) + g * 16 + (q & 1) * 8;
 #pragma unroll
@@ -295,10 +318,15 @@ __device__ __forceinline__ void wait_vm() {
 template <int KIND, int KK, int NG, int NJ>
 __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ rec, const bf16x8u* __restrict__ Pb,
                                                         const float* __restrict__ sq, double* __restrict__ Vp, int np,
-                                                        int ld, int nsplit, int blocks_per_split,
-                                                        const DevState* __restrict__ st) {
+                                                        int ld, int nsplit, int blocks_per_split, int n,
+                                                        const unsigned* __restrict__ counts, DevState* st) {
 #ifdef __HIP_DEVICE_COMPILE__   // (the buffer resource type exists on the device only)
-  if (st->done) return;
+  if (counts) {                 // done is zero on entry and tells the kernels behind this one who did it
+    if (!dig_dense(st, counts, n)) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->done = 1;
+  } else if (st->done) {
+    return;
+  }
   constexpr int LD = NG <= 8 ? 16 : 32;
   using Rec = DigRec<KK, NG>;
   constexpr int kRing = Rec::kRing;
@@ -350,7 +378,9 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
     return q;
   };
   auto next = [](int slot) { return slot + Rec::kSlot == kRing * Rec::kSlot ? 0 : slot + Rec::kSlot; };
-  constexpr int kOperands = NG + KK, kM = NJ * kOperands, kB = NG < 4 ? NG : 4;
+  // (operands per batch: 16 kB registers; 17 and 18 columns fill the file otherwise, and the compiler then spills up to 48
+  // registers inside the loop: n = 50 000, d = 8, 17 columns 1.65 ms, 1.30 without)
+  constexpr int kOperands = NG + KK, kM = NJ * kOperands, kB = NG < 4 ? NG : (NG == 9 ? 3 : 4);
   constexpr int kS = NJ * DigEval<KIND>::kStages;
   typename DigEval<KIND>::Const cst;
   // sign of the sum of tile (k, jb): this times (-1)^(k + jb) (a chunk's first block is even)
@@ -487,9 +517,9 @@ int dig_groups(int c) {
   return 16;
 }
 
-void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float* sq, int np, int ld, int KK, int ng,
-                   const DevState* st, void* rec) {
-  k_digits<<<np / 16, 256, 0, s>>>(D4, Xs, sq, ld, ng, KK, bbmm_plan::dig_record_bytes(KK, ng), st, (char*)rec);
+void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float* sq, int n, int np, int ld, int KK, int ng,
+                   const DevState* st, unsigned* counts, void* rec) {
+  k_digits<<<np / 16, 256, 0, s>>>(D4, Xs, sq, n, ld, ng, KK, bbmm_plan::dig_record_bytes(KK, ng), st, counts, (char*)rec);
 }
 
 // Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles
@@ -510,7 +540,7 @@ void launch_split_x(hipStream_t s, const float* Xs, int np, int KK, void* Pb) {
 }
 
 int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec, const void* Pb, const float* sq,
-                      double* Vp, int np, int ld, int nsplit, const DevState* st) {
+                      double* Vp, int n, int np, int ld, int nsplit, const unsigned* counts, DevState* st) {
   int nblk = np / 16;
   int bps = (nblk + nsplit - 1) / nsplit;
   bps += bps & 1;
@@ -519,9 +549,9 @@ int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec
   int grid = ((nblk + 4 * nj - 1) / (4 * nj)) * nsplit;
 #define DIG(K, G, J)                                                                                           \
   if (kernel == 0)                                                                                             \
-    k_mm_otf_dig<0, K, G, J><<<grid, 256, 0, s>>>((const char*)rec, (const bf16x8u*)Pb, sq, Vp, np, ld, nsplit, bps, st); \
+    k_mm_otf_dig<0, K, G, J><<<grid, 256, 0, s>>>((const char*)rec, (const bf16x8u*)Pb, sq, Vp, np, ld, nsplit, bps, n, counts, st); \
   else                                                                                                         \
-    k_mm_otf_dig<1, K, G, J><<<grid, 256, 0, s>>>((const char*)rec, (const bf16x8u*)Pb, sq, Vp, np, ld, nsplit, bps, st)
+    k_mm_otf_dig<1, K, G, J><<<grid, 256, 0, s>>>((const char*)rec, (const bf16x8u*)Pb, sq, Vp, np, ld, nsplit, bps, n, counts, st)
 #define DIG_G(K, TWO, FOUR, NINE, TWELVE)  \
   switch (ng) {                            \
     case 2: DIG(K, 2, TWO); break;         \

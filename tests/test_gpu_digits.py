@@ -15,6 +15,7 @@ N0 = 6144            # first size of the route; 16-row tiles, workgroups of 4 * 
 def ctx():
     from paper_1809_11165_amd import binding
     c = binding.Context(0)
+    c.bbmm_tune("otf_digits", 2)         # whatever the block
     yield c
     c.close()
 
@@ -216,3 +217,67 @@ def test_digit_entries_of_a_far_point(ctx, kernel, far):
     assert np.isfinite(V[1]).all()
     np.testing.assert_allclose(V[0][[17, 4000]], (w.outputscale + w.noise) * M.cpu().numpy()[[17, 4000]], rtol=2e-7)
     np.testing.assert_allclose(V[0], V[1], rtol=0, atol=4e-6 * np.abs(V[1]).max())
+
+
+def _blocks(n):
+    """Name, column, whether it suits the digits."""
+    rng = np.random.default_rng(n)
+    g = rng.standard_normal(n).astype(np.float32)
+    one = np.zeros(n, dtype=np.float32)
+    one[n // 3] = 1.0
+    half = g.copy()
+    half[n // 2:] = 0.0
+    spike = g.copy()
+    spike[5] = 1e12
+    few = g.copy()
+    few[:n // 16384 + 40] = 0.0
+    inf = one.copy()
+    inf[n // 3] = np.inf
+    nan = g.copy()
+    nan[3] = np.nan
+    return [("normal", g, True), ("signs", np.sign(g), True), ("zero", 0.0 * one, True), ("uniform", rng.random(n).astype(np.float32), True),
+            ("indicator", one, False), ("half zero", half, False), ("one entry far above", spike, False),
+            ("lognormal", np.exp(3.0 * g), False), ("a few zeros", few, False), ("infinity", inf, False), ("NaN", nan, False)]
+
+
+@pytest.mark.parametrize("n,c", [(6200, 5), (6144, 17), (12500, 9), (12500, 17)])
+def test_product_takes_the_digits_only_for_blocks_that_suit_them(n, c):
+    """By default a block with a column that is not of one size (or a point too far out to be squared) gets the fp64
+    product to the bit, and so keeps the accuracy of each row; a dense one gets the digits."""
+    import torch
+    from paper_1809_11165_amd import binding
+    ctx = binding.Context(0)
+
+    def mm(M, **tune):
+        for k, v in tune.items():
+            ctx.bbmm_tune(k, v)
+        try:
+            return ctx.bbmm_kernel_mm(inputs.ONTHEFLY, M).cpu().numpy()
+        finally:
+            for k in tune:
+                ctx.bbmm_tune(k, 1)
+
+    w, _ = _problem(n, 6, inputs.RBF)
+    w.lengthscale = 0.5 * w.lengthscale
+    ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+    fp64 = {"otf_sym": 2 if n >= 12288 and c <= 16 else 0}
+    dense = np.random.default_rng(1).standard_normal((n, c)).astype(np.float32)
+    for name, col, suits in _blocks(n):
+        M = dense.copy()
+        M[:, c - 2] = col
+        Md = torch.from_numpy(M).cuda()
+        V, V64, Vd = mm(Md), mm(Md, **fp64), mm(Md, otf_digits=2)
+        np.testing.assert_array_equal(V, Vd if suits else V64, err_msg=name)
+        assert not np.array_equal(Vd, V64), name
+        if name == "indicator":       # entries of K themselves: seven digits of the smallest as of the largest
+            K = O.kernel_block(w.kernel, w.X.astype(np.float64), w.X[n // 3:n // 3 + 1].astype(np.float64), w.lengthscale,
+                               w.outputscale)[:, 0]
+            small = (K > 1e-12) & (K < 1e-8)
+            assert small.sum() > 50 and np.all(np.abs(V[small, c - 2] / K[small] - 1.0) < 1e-4)
+    w.X[7] = 1e25                     # its square overflows: infinitely far from the others
+    w.X[9] = -1e25
+    w.X[9, 0] = 0.0
+    ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+    Md = torch.from_numpy(dense).cuda()
+    np.testing.assert_array_equal(mm(Md), mm(Md, **fp64))
+    ctx.close()

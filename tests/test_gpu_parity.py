@@ -870,27 +870,33 @@ def test_onthefly_tile_pairs_once_over_input_dimensions(ctx, kernel, d):
 
 
 def test_onthefly_default_form_depends_on_the_size(ctx):
-    # by default the paired form runs from 12288 (padded) rows on: there the default must be the forced
-    # paired product bit for bit, below it the plain one; sampled rows against the oracle's kernel rows
-    for n, paired in ((4000, False), (12500, True)):
-        w = _case(inputs.MATERN52, True, n, 6)
+    # beyond 16 input dimensions (up to 16 the digit form takes over earlier) the paired form runs by default from
+    # 12288 (padded) rows on, below it the plain one.  Rounded to fp32 the two products are mostly the same bits, so
+    # the form that ran is told by the (fp64) coefficients of the iteration, which the order of the sums changes;
+    # sampled rows of the products against the oracle's kernel rows
+    for n, d, paired in ((4000, 6, False), (4000, 18, False), (12500, 18, True), (12500, 32, True)):
+        w = _case(inputs.MATERN52, True, n, d)
         rng = np.random.default_rng(n)
         M = _dev(rng.standard_normal((n, 11)))
         ctx.bbmm_setup(_problem(w, inputs.ONTHEFLY))
+        ctx.bbmm_pivoted_cholesky()
+        ctx.bbmm_precond_setup()
+        V, alpha = {}, {}
         try:
-            Vd = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, M)
-            ctx.bbmm_tune("otf_sym", 0)
-            V0 = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, M)
-            ctx.bbmm_tune("otf_sym", 2)
-            V2 = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, M)
+            for form in (1, 0, 2):
+                ctx.bbmm_tune("otf_sym", form)
+                V[form] = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, M)
+                alpha[form] = ctx.bbmm_mbcg(inputs.ONTHEFLY, M)[1]
         finally:
             ctx.bbmm_tune("otf_sym", 1)
-        assert torch.equal(Vd, V2 if paired else V0), n
+        same, other = (2, 0) if paired else (0, 2)
+        assert torch.equal(V[1], V[same]) and np.array_equal(alpha[1], alpha[same]), (n, d)
+        assert not np.array_equal(alpha[1], alpha[other]), (n, d)
         rows = rng.choice(n, size=48, replace=False)
         Krows = O.kernel_block(w.kernel, w.X[rows], w.X, w.lengthscale, w.outputscale)
         ref = Krows @ _host(M) + w.noise * _host(M)[rows]
-        for V in (V0, V2):
-            got = _host(V)[rows]
+        for form in (0, 2):
+            got = _host(V[form])[rows]
             assert np.max(np.abs(got - ref)) < 1e-4 * np.max(np.abs(ref)), n
 
 
