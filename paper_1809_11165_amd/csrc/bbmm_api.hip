@@ -60,11 +60,11 @@ constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 // Everything the launch sequence of the iteration loop depends on.
 struct LoopKey {
   uint64_t alloc_epoch, tune_epoch;
-  int mode, kernel, n, d, cc, ld, kp, maxit, m, tri, nls;
+  int mode, kernel, n, d, cc, ld, kp, maxit, m, tri, nls, dig;
   bool operator==(const LoopKey& o) const {
     return alloc_epoch == o.alloc_epoch && tune_epoch == o.tune_epoch && mode == o.mode && kernel == o.kernel &&
            n == o.n && d == o.d && cc == o.cc && ld == o.ld && kp == o.kp && maxit == o.maxit && m == o.m &&
-           tri == o.tri && nls == o.nls;
+           tri == o.tri && nls == o.nls && dig == o.dig;
   }
 };
 
@@ -86,6 +86,7 @@ struct bbmm_ctx {
   HypArgs hyp{};
   bool khat_built = false, chol_done = false, pre_done = false, mbcg_done = false;
   bool sgpr = false, sgpr_built = false;
+  bool far_x = false;                       // X is known to hold points too far out for the digit products
   int last_c = 0, last_ld = 0, last_t = 0;   // shape of the last mBCG run
 
   int64_t mat_wgs = 0, otf_split = 0;        // 0 = default
@@ -389,8 +390,20 @@ bool may_use_digits(const bbmm_ctx* c) { return c->np >= kDigMinRows && c->KK <=
 
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.
 bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
-  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym == 1 && c->otf_digits != 0 && may_use_digits(c) &&
+  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym == 1 && c->otf_digits != 0 && !c->far_x && may_use_digits(c) &&
          dig_split_of(c, cc) <= kMaxSplit;
+}
+
+// A point whose coordinates or their square overflow fp32 is infinitely far from the others (or not a number); the fp64
+// form keeps that to the rows concerned, the digits cannot.  The device knows (DevState::xbad), the host does when it
+// has fetched the state: such a run leaves the caller's buffers alone and is repeated with the fp64 form.
+const DevState* unless_far(const bbmm_ctx* c, int mode, int cc) {
+  return uses_digits(c, mode, cc) ? (const DevState*)c->st.p : nullptr;
+}
+bool again_without_digits(bbmm_ctx* c, int mode, int cc) {
+  if (!c->h_st->xbad || !uses_digits(c, mode, cc)) return false;
+  c->far_x = true;
+  return true;
 }
 
 int otf_split_of(const bbmm_ctx* c) {
@@ -813,7 +826,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
   bool replayed = false;
   if (c->use_graph && !c->time_mm && c->cap) {
     LoopKey key{c->alloc_epoch, c->tune_epoch, mode, c->prob.kernel, c->n, c->d, cc, ld, c->kp, c->maxit, c->m,
-                c->khat_tri ? 1 : 0, (int)c->prob.n_lengthscale};
+                c->khat_tri ? 1 : 0, (int)c->prob.n_lengthscale, track};
     // graphs recorded against buffers or tuning values that are gone can never be replayed again
     for (size_t i = 0; i < c->graphs.size();) {
       if (c->graphs[i].key.alloc_epoch != c->alloc_epoch || c->graphs[i].key.tune_epoch != c->tune_epoch) {
@@ -1197,6 +1210,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   c->khat_built = c->chol_done = c->pre_done = c->mbcg_done = false;
   c->sgpr = (in->mode == BBMM_MODE_SGPR);
   c->sgpr_built = false;
+  c->far_x = false;
   c->m = c->sgpr ? (int)in->m : 0;
   c->mp = ((c->m + 255) / 256) * 256;
 
@@ -1394,12 +1408,14 @@ int bbmm_mbcg(bbmm_ctx* c, int32_t mode, const float* B, int64_t cc, float* U, d
   if (rc) return rc;
   if (!B || !U || cc < 1 || cc > BBMM_MAXC) return fail(c, BBMM_EINVAL, "bad block");
   int ld = ld_for((int)cc);
-  launch_pack_rows(c->stream, B, c->n, (int)cc, ld, ptr<double>(c->R));
-  rc = stage_mbcg(c, mode, (int)cc, ld, c->prob.u0_init);
-  if (rc) return rc;
-  launch_unpack_rows(c->stream, ptr<double>(c->U), ld, c->n, (int)cc, U);
-  rc = fetch_state(c, true);
-  if (rc) return rc;
+  do {
+    launch_pack_rows(c->stream, B, c->n, (int)cc, ld, ptr<double>(c->R));
+    rc = stage_mbcg(c, mode, (int)cc, ld, c->prob.u0_init);
+    if (rc) return rc;
+    launch_unpack_rows(c->stream, ptr<double>(c->U), ld, c->n, (int)cc, U, unless_far(c, mode, (int)cc));
+    rc = fetch_state(c, true);
+    if (rc) return rc;
+  } while (again_without_digits(c, mode, (int)cc));
   int it = c->h_st->iters_run;
   if (iters_run) *iters_run = it;
   double* dst[3] = {alpha, beta, resid};
@@ -1466,13 +1482,17 @@ int bbmm_predict_var(bbmm_ctx* c, int32_t mode, const float* Xstar, int64_t ns, 
     if (rc) return rc;
     launch_coldot_var(s, ptr<double>(c->tmpB), ptr<double>(c->U), c->n, ld, (int)ns, ptr<double>(c->TW), var);
   } else {
-    launch_cross_block(s, c->prob.X, Xstar, c->n, (int)ns, ld, c->hyp, ptr<double>(c->R));
-    rc = stage_mbcg(c, mode, (int)ns, ld);
-    if (rc) return rc;
-    launch_cross_dot(s, c->prob.X, Xstar, c->n, (int)ns, c->hyp, ptr<double>(c->U), ld, 1,
-                     c->prob.outputscale, -1.0, ptr<double>(c->partial), var);
+    do {
+      launch_cross_block(s, c->prob.X, Xstar, c->n, (int)ns, ld, c->hyp, ptr<double>(c->R));
+      rc = stage_mbcg(c, mode, (int)ns, ld);
+      if (rc) return rc;
+      launch_cross_dot(s, c->prob.X, Xstar, c->n, (int)ns, c->hyp, ptr<double>(c->U), ld, 1,
+                       c->prob.outputscale, -1.0, ptr<double>(c->partial), var);
+      rc = fetch_state(c, true);
+      if (rc) return rc;
+    } while (again_without_digits(c, mode, (int)ns));
   }
-  rc = fetch_state(c, true);
+  if (c->sgpr) rc = fetch_state(c, true);
   if (rc) return rc;
   rc = device_status(c);
   if (rc) return rc;
@@ -1622,12 +1642,12 @@ int bbmm_dk_traces(bbmm_ctx* c, const float* U, const float* W, double* trace, d
   return BBMM_OK;
 }
 
-int bbmm_solve_logdet_grad(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out) {
-  if (!c) return BBMM_EINVAL;
-  if (!out || !out->u0 || !out->trace || !out->quad || !out->grad_nlml)
-    return fail(c, BBMM_EINVAL, "result struct, u0, trace, quad and grad_nlml are required");
+// *again: nothing has been returned, the call has to be made once more with far_x set.
+static int solve_call(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out, bool far_x, bool* again) {
+  *again = false;
   int rc = bbmm_setup(c, in);
   if (rc) return rc;
+  c->far_x = far_x;
   hipStream_t s = c->stream;
   int cc = c->t + 1, ld = ld_for(cc);
   if (in->mode == BBMM_MODE_MATERIALISED) {
@@ -1655,12 +1675,15 @@ int bbmm_solve_logdet_grad(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out
   HIPCHK(c, hipEventRecord(c->ev_join, c->side));
   rc = stage_dk(c, ld, c->t);
   if (rc) return rc;
-  launch_extract_col(s, ptr<double>(c->U), ld, c->n, c->n, 0, out->u0);
-  if (out->U) launch_unpack_rows(s, ptr<double>(c->U), ld, c->n, cc, out->U);
+  const DevState* keep = unless_far(c, in->mode, cc);
+  launch_extract_col(s, ptr<double>(c->U), ld, c->n, c->n, 0, out->u0, keep);
+  if (out->U) launch_unpack_rows(s, ptr<double>(c->U), ld, c->n, cc, out->U, keep);
   HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
   c->side_busy = false;
   rc = fetch_state(c, true);
   if (rc) return rc;
+  *again = again_without_digits(c, in->mode, cc);
+  if (*again) return BBMM_OK;
   rc = device_status(c);
   if (rc) return rc;
 
@@ -1686,6 +1709,15 @@ int bbmm_solve_logdet_grad(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out
   if (out->slq_terms)
     for (int i = 0; i < c->t; ++i) out->slq_terms[i] = st->slq_terms[i];
   return BBMM_OK;
+}
+
+int bbmm_solve_logdet_grad(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out) {
+  if (!c) return BBMM_EINVAL;
+  if (!out || !out->u0 || !out->trace || !out->quad || !out->grad_nlml)
+    return fail(c, BBMM_EINVAL, "result struct, u0, trace, quad and grad_nlml are required");
+  bool again = false;
+  int rc = solve_call(c, in, out, false, &again);
+  return again ? solve_call(c, in, out, true, &again) : rc;
 }
 
 }  // extern "C"

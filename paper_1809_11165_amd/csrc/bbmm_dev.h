@@ -43,7 +43,7 @@ struct DevState {
   int status;       // BBMM_* code raised on the device (0 = ok)
   int rank;         // preconditioner rank actually built
   unsigned fin_ticket;   // arrivals of k_ur_fin's blocks (zero between launches)
-  int xbad;         // 1: one point of X is too far out to be squared, 2 or more: see k_prep_x
+  int xbad;         // a coordinate of X or its square is not finite in fp32: no X for the digit products (they return NaN)
   unsigned counter[8][40];   // arrival tickets per kernel family: [0] final, [1 + g] group g
 };
 
@@ -86,7 +86,8 @@ void launch_prep_x(hipStream_t s, const float* X, int n, int d, int np, int KK, 
 // track != 0: leave the columns' magnitudes in st->dmax / st->dflag (zero beforehand), as launch_digits needs
 void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld, double* D4, int track,
                     DevState* st);
-void launch_unpack_rows(hipStream_t s, const double* src, int ld, int n, int c, float* dst);
+// unless_far (may be null): dst is left alone if that state's X holds points too far out for the digit products
+void launch_unpack_rows(hipStream_t s, const double* src, int ld, int n, int c, float* dst, const DevState* unless_far = nullptr);
 void launch_unpack_rows_f64(hipStream_t s, const double* src, int ld, int n, int c, double* dst);
 void launch_pack_rows(hipStream_t s, const float* src, int n, int c, int ld, double* dst);
 void launch_pack_cols_at(hipStream_t s, const float* src, int n, int c, int ld, int dstcol0, double* dst);
@@ -251,4 +252,5 @@ void launch_dk_finish(hipStream_t s, const double* partial, int nrows, int pstri
                       DevState* st);
 void launch_swizzle_cols(hipStream_t s, const double* src, int ld, int n, int np, int col0, int ncols,
                          int TS, int dstcol0, float scale, float* dst);
-void launch_extract_col(hipStream_t s, const double* src, int ld, int n, int np, int col, float* dst);
+void launch_extract_col(hipStream_t s, const double* src, int ld, int n, int np, int col, float* dst,
+                        const DevState* unless_far = nullptr);

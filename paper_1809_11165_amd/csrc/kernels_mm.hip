@@ -919,9 +919,9 @@ __global__ void k_swizzle_cols(const double* __restrict__ src, int ld, int n, in
 }
 
 __global__ void k_extract_col(const double* __restrict__ src, int ld, int n, int np, int col,
-                              float* __restrict__ dst) {
+                              float* __restrict__ dst, const DevState* __restrict__ unless_far) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= np) return;
+  if (i >= np || (unless_far && unless_far->xbad)) return;
   dst[i] = (i < n) ? (float)src[(size_t)i * ld + col] : 0.f;
 }
 
@@ -1098,6 +1098,7 @@ void launch_swizzle_cols(hipStream_t s, const double* src, int ld, int n, int np
                                                             scale, dst);
 }
 
-void launch_extract_col(hipStream_t s, const double* src, int ld, int n, int np, int col, float* dst) {
-  k_extract_col<<<(np + 255) / 256, 256, 0, s>>>(src, ld, n, np, col, dst);
+void launch_extract_col(hipStream_t s, const double* src, int ld, int n, int np, int col, float* dst,
+                        const DevState* unless_far) {
+  k_extract_col<<<(np + 255) / 256, 256, 0, s>>>(src, ld, n, np, col, dst, unless_far);
 }

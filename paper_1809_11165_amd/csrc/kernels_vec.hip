@@ -222,7 +222,8 @@ __global__ __launch_bounds__(VT) void k_pack_d4(const float* __restrict__ M, int
 
 // padded row-major (stride ld) -> dense n x c
 __global__ void k_unpack_rows(const double* __restrict__ src, int ld, int n, int c,
-                              float* __restrict__ dst) {
+                              float* __restrict__ dst, const DevState* __restrict__ unless_far) {
+  if (unless_far && unless_far->xbad) return;
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)n * c) return;
   int i = (int)(idx / c), q = (int)(idx % c);
@@ -1679,8 +1680,8 @@ void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld,
   k_pack_d4<<<track && blocks > kPackTrackBlocks ? kPackTrackBlocks : blocks, VT, 0, s>>>(M, n, c, np, ld, D4, track, st);
 }
 
-void launch_unpack_rows(hipStream_t s, const double* src, int ld, int n, int c, float* dst) {
-  k_unpack_rows<<<blocks_for((size_t)n * c, 256), 256, 0, s>>>(src, ld, n, c, dst);
+void launch_unpack_rows(hipStream_t s, const double* src, int ld, int n, int c, float* dst, const DevState* unless_far) {
+  k_unpack_rows<<<blocks_for((size_t)n * c, 256), 256, 0, s>>>(src, ld, n, c, dst, unless_far);
 }
 
 void launch_unpack_rows_f64(hipStream_t s, const double* src, int ld, int n, int c, double* dst) {

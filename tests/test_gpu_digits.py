@@ -274,10 +274,58 @@ def test_product_takes_the_digits_only_for_blocks_that_suit_them(n, c):
                                w.outputscale)[:, 0]
             small = (K > 1e-12) & (K < 1e-8)
             assert small.sum() > 50 and np.all(np.abs(V[small, c - 2] / K[small] - 1.0) < 1e-4)
-    w.X[7] = 1e25                     # its square overflows: infinitely far from the others
-    w.X[9] = -1e25
-    w.X[9, 0] = 0.0
+    w.X[7], w.X[9] = 1e25, -1e25      # squares overflow: infinitely far from the others
     ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
     Md = torch.from_numpy(dense).cuda()
-    np.testing.assert_array_equal(mm(Md), mm(Md, **fp64))
+    V = mm(Md)
+    assert np.isfinite(V).all()
+    np.testing.assert_array_equal(V, mm(Md, **fp64))
     ctx.close()
+
+
+@pytest.mark.parametrize("loop_graph", [0, 1])
+@pytest.mark.parametrize("kernel", [inputs.RBF, inputs.MATERN52])
+def test_calls_with_points_too_far_out_are_those_of_the_fp64_form(kernel, loop_graph):
+    """Two points whose squares overflow fp32, on either side of the rest: infinitely far from all others (RBF) or not a
+    number (Matern-5/2: infinity times zero).  Whole calls, solves and variances are those of the fp64 form, and
+    the next problem has the digits again."""
+    import torch
+    from paper_1809_11165_amd import binding
+    w = inputs.tiny(6300, 3, kernel=kernel, t=4, k=3, iters=12, noise=0.3, seed=4)
+    near = w.X.copy()
+    far = w.X.copy()
+    far[7], far[9] = 1e25, -1e25
+    rng = np.random.default_rng(0)
+    B = torch.from_numpy(rng.standard_normal((w.n, 6)).astype(np.float32)).cuda()
+    Xs = torch.from_numpy(rng.standard_normal((5, 3)).astype(np.float32)).cuda()
+
+    def results(digits, X):
+        w.X = X
+        ctx = binding.Context(0)
+        ctx.bbmm_tune("otf_digits", digits)
+        ctx.bbmm_tune("loop_graph", loop_graph)
+        out = []
+        for _ in range(3):
+            ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+            ctx.bbmm_pivoted_cholesky()
+            ctx.bbmm_precond_setup()
+            U, alpha, beta, resid, iters = ctx.bbmm_mbcg(inputs.ONTHEFLY, B)
+            var = ctx.bbmm_predict_var(inputs.ONTHEFLY, Xs)[0]
+            out.append([U.cpu().numpy(), alpha, beta, resid, iters, var.cpu().numpy()])
+            try:
+                r = ctx.bbmm_solve_logdet_grad(binding.problem_from_workload(w, inputs.ONTHEFLY))
+                out[-1] += [r.U.cpu().numpy(), r.u0.cpu().numpy(), r.logdet, r.trace, r.quad]
+            except RuntimeError as e:
+                out[-1].append(str(e))
+        ctx.close()
+        return out
+
+    for a, b in zip(results(1, far), results(0, far)):
+        assert len(a) == len(b)
+        if kernel == inputs.RBF:
+            assert np.isfinite(a[0]).all() and np.isfinite(a[5]).all()
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+    a, b = results(1, near)[0], results(0, near)[0]
+    assert not np.array_equal(a[1], b[1])
+    np.testing.assert_allclose(a[0], b[0], rtol=0, atol=1e-5 * np.abs(b[0]).max())
