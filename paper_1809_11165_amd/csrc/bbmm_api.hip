@@ -386,11 +386,11 @@ int dig_split_of(const bbmm_ctx* c, int cc) {
 
 // Whether the problem's size and dimensions allow a product on the 8-bit matrix pipe (its split coordinates are
 // laid out with the others then).
-bool may_use_digits(const bbmm_ctx* c) { return c->np >= kDigMinRows && c->KK <= 4; }
+bool may_use_digits(const bbmm_ctx* c) { return !c->sgpr && c->np >= kDigMinRows && c->KK <= 4; }
 
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.
 bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
-  return mode == BBMM_MODE_ONTHEFLY && !c->sgpr && c->otf_sym == 1 && c->otf_digits != 0 && !c->far_x && may_use_digits(c) &&
+  return mode == BBMM_MODE_ONTHEFLY && c->otf_sym == 1 && c->otf_digits != 0 && !c->far_x && may_use_digits(c) &&
          dig_split_of(c, cc) <= kMaxSplit;
 }
 

@@ -329,3 +329,20 @@ def test_calls_with_points_too_far_out_are_those_of_the_fp64_form(kernel, loop_g
     a, b = results(1, near)[0], results(0, near)[0]
     assert not np.array_equal(a[1], b[1])
     np.testing.assert_allclose(a[0], b[0], rtol=0, atol=1e-5 * np.abs(b[0]).max())
+
+
+def test_a_sparse_problem_keeps_no_split_coordinates():
+    """Only an exact problem can reach the digit product: 128 bytes per point at d = 8 that an SGPR problem does without."""
+    import torch
+    from paper_1809_11165_amd import binding
+    n = 1 << 19
+    w = inputs.tiny_sgpr(n, 8, 16, t=1, k=2, iters=1)
+    used = []
+    for mode in (inputs.ONTHEFLY, inputs.SGPR):
+        ctx = binding.Context(0)
+        free = torch.cuda.mem_get_info()[0]
+        ctx.bbmm_setup(binding.problem_from_workload(w, mode))
+        torch.cuda.synchronize()
+        used.append(free - torch.cuda.mem_get_info()[0])
+        ctx.close()
+    assert used[0] - used[1] >= 120 * n, used
