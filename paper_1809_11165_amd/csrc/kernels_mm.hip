@@ -635,18 +635,22 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_tri(const float* __restrict__
 //               tile as  sum_j [ xs_jd^2 c_j + Y2_jd - 2 xs_jd Y_jd ],  c_j = sum_i T_ij,
 //               Y_jd = sum_i T_ij xs_id,  Y2_jd = sum_i T_ij xs_id^2  (two MFMA contractions).
 //               Only the sum of Y2 over j is needed: the wave's DK_NJ tiles of a row block are added first
-//               and share one contraction.  T = g u0_i u0_j of the quad terms: u0_i goes into the row
-//               operand, u0_j into the epilogue, so the tile itself is g.
+//               and share one contraction.  c, Y and Y2 cancel, so all three see the same rounded T, and
+//               sums run in fp32 over DK_RUN row blocks only; the wave's fp64 row takes them from there.
 // Bound by the vector ALU, which the fp32 MFMAs block (14.4 ns each, nothing beside them).  The derivative call,
-// n = 50 000, d = 16, ARD: 3.27 ms with a Y2 contraction per tile -> 2.76.
+// n = 50 000, d = 16, ARD: 3.40 ms with a Y2 contraction per tile -> 2.85 -> 3.05 with the sums in runs.  Error of all terms
+// against 64 bits, rms of four problems there (trace, quad): 2.9e-6, 4.5e-8 -> 1.4e-6, 2.2e-8; of 96 problems with n = 9 000:
+// 3.0e-6, 5.5e-8 -> 3.0e-6, 5.3e-8 (in one fp32 run, with u0_i in the row operand: 3.5e-6, 6.3e-8).
 // Every summand is symmetric in (i, j), so only tiles with row block <= column block are
 // evaluated: weight 1 above the diagonal, 1/2 on it, and the total is doubled at the end.
 // Partial results: one row of `pstride` doubles per wave: [2*h] trace-type, [2*h+1] quad-type,
 // h = lengthscale slots (1 or 4*KK) then the outputscale slot.
 constexpr int DK_NJ = 4;
+constexpr int DK_RUN = 32;   // row blocks per fp32 sum
 constexpr int DK_TSMAX = 16;
 
-__device__ inline float wave_sum(float v) {
+template <typename T>
+__device__ inline T wave_sum(T v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
@@ -657,9 +661,9 @@ struct DkAcc {
   static constexpr int MB = (4 * KK + 15) / 16;
   float es_tr = 0.f, el_tr = 0.f;
   float es_q[DK_NJ], el_q[DK_NJ];                 // without the factor u0_j
-  f32x4 ytr[DK_NJ][ARD ? MB : 1], yq[DK_NJ][ARD ? MB : 1];   // yq: without the factor u0_j
+  f32x4 ytr[DK_NJ][ARD ? MB : 1], yq[DK_NJ][ARD ? MB : 1];
   f32x4 y2tr[ARD ? MB : 1], y2q[ARD ? MB : 1];
-  float ctr[DK_NJ], cq[DK_NJ];                    // cq: without the factor u0_j
+  float ctr[DK_NJ], cq[DK_NJ];
 };
 
 // One row block ib against the wave's DK_NJ column blocks.  NEAR: the row block lies inside the
@@ -680,15 +684,15 @@ __device__ __forceinline__ void dk_step(int ib, int jb0, int lane, int TS, const
   for (int kk = 0; kk < KK; ++kk) a[kk] = Xa[((size_t)ib * KK + kk) * 64 + lane];
   f32x4 sqi = *(const f32x4*)(sq + ib * 16 + g * 4);
   f32x4 u0i = *(const f32x4*)(u0 + ib * 16 + g * 4);
-  f32x4 xop[ARD ? MB : 1], xopu[ARD ? MB : 1];
-  f32x4 tsum = {0.f, 0.f, 0.f, 0.f}, qsum = {0.f, 0.f, 0.f, 0.f};
+  f32x4 xop[ARD ? MB : 1], xop2[ARD ? MB : 1];
+  f32x4 ts[NJ], tq[NJ];
   if (ARD) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       int dim = mb * 16 + jc;
       xop[mb] = (dim < DP) ? *(const f32x4*)(X4 + ((size_t)(ib * 4 + g) * DP + dim) * 4)
                            : (f32x4){0.f, 0.f, 0.f, 0.f};
-      xopu[mb] = xop[mb] * u0i;
+      xop2[mb] = xop[mb] * xop[mb];
     }
   }
   // S tiles for all column blocks: contraction over the probe index, TS chunks of 4
@@ -712,7 +716,6 @@ __device__ __forceinline__ void dk_step(int ib, int jb0, int lane, int TS, const
     }
     f32x4 r2 = tile_r2<KK>(a, b[jb], sqi, sqj[jb]);
     if (NEAR) r2 = fix_diag_if(ib == jb0 + jb, r2, lane);
-    f32x4 ts, tg;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float e, gw;
@@ -724,12 +727,8 @@ __device__ __forceinline__ void dk_step(int ib, int jb0, int lane, int TS, const
       A.es_tr = fmaf(e, S[jb][r], A.es_tr);
       A.es_q[jb] = fmaf(e, u0i[r], A.es_q[jb]);
       if (ARD) {
-        ts[r] = gw * S[jb][r];
-        tg[r] = gw;
-        A.ctr[jb] += ts[r];
-        A.cq[jb] = fmaf(gw, u0i[r], A.cq[jb]);
-        tsum[r] += ts[r];
-        qsum[r] = fmaf(gw, u0j[jb], qsum[r]);
+        ts[jb][r] = gw * S[jb][r];
+        tq[jb][r] = gw * (u0i[r] * u0j[jb]);
       } else {
         float w = gw * r2[r];
         A.el_tr = fmaf(w, S[jb][r], A.el_tr);
@@ -737,23 +736,30 @@ __device__ __forceinline__ void dk_step(int ib, int jb0, int lane, int TS, const
       }
     }
     if (ARD) {
+      A.ctr[jb] += (ts[jb][0] + ts[jb][1]) + (ts[jb][2] + ts[jb][3]);
+      A.cq[jb] += (tq[jb][0] + tq[jb][1]) + (tq[jb][2] + tq[jb][3]);
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          A.ytr[jb][mb] = mfma16(xop[mb][r], ts[r], A.ytr[jb][mb]);
-          A.yq[jb][mb] = mfma16(xopu[mb][r], tg[r], A.yq[jb][mb]);
+          A.ytr[jb][mb] = mfma16(xop[mb][r], ts[jb][r], A.ytr[jb][mb]);
+          A.yq[jb][mb] = mfma16(xop[mb][r], tq[jb][r], A.yq[jb][mb]);
         }
     }
   }
   if (ARD) {
+    f32x4 tsum = (ts[0] + ts[1]) + (ts[2] + ts[3]), qsum = (tq[0] + tq[1]) + (tq[2] + tq[3]);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb) {
+      f32x4 y1 = {0.f, 0.f, 0.f, 0.f}, y2 = y1;   // (this block's sums first: fewer roundings of the long ones)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        A.y2tr[mb] = mfma16(xop[mb][r] * xop[mb][r], tsum[r], A.y2tr[mb]);
-        A.y2q[mb] = mfma16(xopu[mb][r] * xop[mb][r], qsum[r], A.y2q[mb]);
+        y1 = mfma16(xop2[mb][r], tsum[r], y1);
+        y2 = mfma16(xop2[mb][r], qsum[r], y2);
       }
+      A.y2tr[mb] += y1;
+      A.y2q[mb] += y2;
+    }
   }
 }
 
@@ -798,94 +804,89 @@ __global__ __launch_bounds__(256) void k_dk(const float* __restrict__ Xa,
     sqj[jb] = sq[(jb0 + jb) * 16 + jc];
     u0j[jb] = u0[(jb0 + jb) * 16 + jc];
   }
-  DkAcc<KK, ARD> A;
-#pragma unroll
-  for (int jb = 0; jb < NJ; ++jb) {
-    A.ctr[jb] = 0.f;
-    A.cq[jb] = 0.f;
-    A.es_q[jb] = 0.f;
-    A.el_q[jb] = 0.f;
-#pragma unroll
-    for (int mb = 0; mb < (ARD ? MB : 1); ++mb) {
-      A.ytr[jb][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      A.yq[jb][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    }
-  }
-#pragma unroll
-  for (int mb = 0; mb < (ARD ? MB : 1); ++mb) {
-    A.y2tr[mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    A.y2q[mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  }
-  int ib = ib_begin;
+  // DK_RUN row blocks at a time in fp32; their sums go into the wave's fp64 row (the factor 2 restores the tiles below
+  // the diagonal)
+  constexpr int nls = ARD ? DP : 1;
   int far_end = min(ib_end, jb0);
-  for (; ib < far_end; ++ib)
-    dk_step<KIND, KK, ARD, false>(ib, jb0, lane, TS, Xa, sq, X4, SA, u0, sb_lds, b, sqj, u0j, A);
-  for (; ib < ib_end; ++ib)
-    dk_step<KIND, KK, ARD, true>(ib, jb0, lane, TS, Xa, sq, X4, SA, u0, sb_lds, b, sqj, u0j, A);
-
-  // ---- wave-level epilogue (the factor 2 restores the tiles below the diagonal) -------
-  int nls = ARD ? DP : 1;
-  if (ARD) {
-    float dtr[MB][4], dq[MB][4];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        dtr[mb][rr] = A.y2tr[mb][rr];
-        dq[mb][rr] = A.y2q[mb][rr];
-      }
+  for (int ib0 = ib_begin; ib0 < ib_end; ib0 += DK_RUN) {
+    DkAcc<KK, ARD> A;
 #pragma unroll
     for (int jb = 0; jb < NJ; ++jb) {
-      float c1 = A.ctr[jb], c2 = A.cq[jb];
-      c1 += __shfl_xor(c1, 16, 64);
-      c1 += __shfl_xor(c1, 32, 64);
-      c2 += __shfl_xor(c2, 16, 64);
-      c2 += __shfl_xor(c2, 32, 64);
-      int j = (jb0 + jb) * 16 + jc;
+      A.ctr[jb] = 0.f;
+      A.cq[jb] = 0.f;
+      A.es_q[jb] = 0.f;
+      A.el_q[jb] = 0.f;
+#pragma unroll
+      for (int mb = 0; mb < (ARD ? MB : 1); ++mb) {
+        A.ytr[jb][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        A.yq[jb][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int mb = 0; mb < (ARD ? MB : 1); ++mb) {
+      A.y2tr[mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      A.y2q[mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    int ib = ib0, ib1 = min(ib0 + DK_RUN, ib_end);
+    for (; ib < min(ib1, far_end); ++ib)
+      dk_step<KIND, KK, ARD, false>(ib, jb0, lane, TS, Xa, sq, X4, SA, u0, sb_lds, b, sqj, u0j, A);
+    for (; ib < ib1; ++ib)
+      dk_step<KIND, KK, ARD, true>(ib, jb0, lane, TS, Xa, sq, X4, SA, u0, sb_lds, b, sqj, u0j, A);
+
+    auto add = [&](int e, double v) { pout[e] = (ib0 == ib_begin ? 0.0 : pout[e]) + 2.0 * v; };
+    if (ARD) {
+      double c1[NJ], c2[NJ];
+#pragma unroll
+      for (int jb = 0; jb < NJ; ++jb) {
+        c1[jb] = A.ctr[jb];
+        c2[jb] = A.cq[jb];
+#pragma unroll
+        for (int o = 16; o < 64; o *= 2) {
+          c1[jb] += __shfl_xor(c1[jb], o, 64);
+          c2[jb] += __shfl_xor(c2[jb], o, 64);
+        }
+      }
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
           int dim = mb * 16 + g * 4 + rr;
-          float xj = (dim < DP) ? Xs[(size_t)j * DP + dim] : 0.f;
-          dtr[mb][rr] += xj * (xj * c1 - 2.f * A.ytr[jb][mb][rr]);
-          dq[mb][rr] += u0j[jb] * (xj * (xj * c2 - 2.f * A.yq[jb][mb][rr]));
-        }
-    }
-    // sum over the 16 columns held by lanes with the same l/16
+          double v1 = A.y2tr[mb][rr], v2 = A.y2q[mb][rr];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+          for (int jb = 0; jb < NJ; ++jb) {
+            double xj = (dim < DP) ? (double)Xs[(size_t)((jb0 + jb) * 16 + jc) * DP + dim] : 0.0;
+            v1 += xj * (xj * c1[jb] - 2.0 * (double)A.ytr[jb][mb][rr]);
+            v2 += xj * (xj * c2[jb] - 2.0 * (double)A.yq[jb][mb][rr]);
+          }
+          // sum over the 16 columns held by lanes with the same l/16
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        float v1 = dtr[mb][rr], v2 = dq[mb][rr];
+          for (int o = 8; o > 0; o >>= 1) {
+            v1 += __shfl_xor(v1, o, 64);
+            v2 += __shfl_xor(v2, o, 64);
+          }
+          if (jc == 0 && dim < DP) {
+            add(2 * dim, v1);
+            add(2 * dim + 1, v2);
+          }
+        }
+    } else {
+      double elq = 0.0;
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-          v1 += __shfl_xor(v1, o, 64);
-          v2 += __shfl_xor(v2, o, 64);
-        }
-        int dim = mb * 16 + g * 4 + rr;
-        if (jc == 0 && dim < DP) {
-          pout[2 * dim] = 2.0 * (double)v1;
-          pout[2 * dim + 1] = 2.0 * (double)v2;
-        }
+      for (int jb = 0; jb < NJ; ++jb) elq += (double)A.el_q[jb] * (double)u0j[jb];
+      double v1 = wave_sum((double)A.el_tr), v2 = wave_sum(elq);
+      if (lane == 0) {
+        add(0, v1);
+        add(1, v2);
       }
-  } else {
-    float elq = 0.f;
-#pragma unroll
-    for (int jb = 0; jb < NJ; ++jb) elq = fmaf(A.el_q[jb], u0j[jb], elq);
-    float v1 = wave_sum(A.el_tr), v2 = wave_sum(elq);
-    if (lane == 0) {
-      pout[0] = 2.0 * (double)v1;
-      pout[1] = 2.0 * (double)v2;
     }
-  }
-  float esq = 0.f;
+    double esq = 0.0;
 #pragma unroll
-  for (int jb = 0; jb < NJ; ++jb) esq = fmaf(A.es_q[jb], u0j[jb], esq);
-  float s1 = wave_sum(A.es_tr), s2 = wave_sum(esq);
-  if (lane == 0) {
-    pout[2 * nls] = 2.0 * (double)s1;
-    pout[2 * nls + 1] = 2.0 * (double)s2;
+    for (int jb = 0; jb < NJ; ++jb) esq += (double)A.es_q[jb] * (double)u0j[jb];
+    double s1 = wave_sum((double)A.es_tr), s2 = wave_sum(esq);
+    if (lane == 0) {
+      add(2 * nls, s1);
+      add(2 * nls + 1, s2);
+    }
   }
 }
 
