@@ -516,20 +516,20 @@ __global__ void k_cross_block(const float* __restrict__ X, const float* __restri
 
 // out[a] = prior + sign * sum_j k(x*_a, x_j) V[j * ldv + (percol ? a : 0)] in fp64 from the raw inputs.
 // Mean: V = K_hat^{-1} y, prior 0, sign +1.  Variance: V = the solves of the block above, prior
-// k(x*, x*) = s (both kernels are stationary), sign -1.  Bound by the fp64 vector ALU (2 d + ~45
-// instructions a pair).  Two splits of the pairs, each leaving partial[chunk][a] for k_cross_finish, fixed order:
+// k(x*, x*) = s (both kernels are stationary), sign -1.  Inputs are subtracted first, which is
+// exact, and then scaled, as in cross_value_f64.  Bound by the fp64 vector ALU (3 d + ~45 instructions a pair).  Two splits of the pairs, each leaving partial[chunk][a] for k_cross_finish, fixed order:
 //   k_cross_lanes  a lane is a test point and walks a chunk of the training points, which all lanes read
 //                  from LDS (no reduction but that over the four waves).  Many test points.
 //   k_cross_rows   a thread is a training point and walks a group of CR_A test points; sums over the block.
 //                  Few test points (a wave's lanes could not be filled with them).
 // n = 50 000, d = 16, one block per test point (each reading X with a stride of d floats) -> now: 1024 test
-// points 1 467 -> 179 us, one test point 467 -> 10 us.
+// points 1 467 -> 194 us, one test point 467 -> 10 us.
 template <int DP>
 __device__ inline double cross_kernel(const double (&x)[DP], const double* __restrict__ z, const HypArgs& hyp) {
   double rho2 = 0.0;
 #pragma unroll
   for (int dim = 0; dim < DP; ++dim) {
-    double df = x[dim] - z[dim];
+    double df = (x[dim] - z[dim]) * hyp.inv_ls[dim];   // (the difference is exact)
     rho2 = fma(df, df, rho2);
   }
   if (hyp.kernel == 0) return exp(-0.5 * rho2);
@@ -538,12 +538,12 @@ __device__ inline double cross_kernel(const double (&x)[DP], const double* __res
   return (1.0 + s5 * rho + (5.0 / 3.0) * rho2) * exp(-s5 * rho);
 }
 
-// one input row times 1 / l, in fp64, zero beyond d dimensions
+// one input row in fp64, zero beyond d dimensions
 template <int DP>
 __device__ inline void cross_row(const float* __restrict__ X, size_t i, bool live, const HypArgs& hyp, double (&x)[DP]) {
 #pragma unroll
   for (int dim = 0; dim < DP; ++dim)
-    x[dim] = (live && dim < hyp.d) ? (double)X[i * hyp.d + dim] * hyp.inv_ls[dim] : 0.0;
+    x[dim] = (live && dim < hyp.d) ? (double)X[i * hyp.d + dim] : 0.0;
 }
 
 constexpr int CL_J = 64;     // training points staged per round (16 per wave)
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(VT) void k_cross_lanes(const float* __restrict__ X,
     __syncthreads();
     for (int e = threadIdx.x; e < CL_J * DP; e += VT) {
       int r = e / DP, dim = e % DP;
-      zx[r][dim] = (jb + r < j1 && dim < hyp.d) ? (double)X[(size_t)(jb + r) * hyp.d + dim] * hyp.inv_ls[dim] : 0.0;
+      zx[r][dim] = (jb + r < j1 && dim < hyp.d) ? (double)X[(size_t)(jb + r) * hyp.d + dim] : 0.0;
     }
     if (threadIdx.x < CL_J) zv[threadIdx.x] = (jb + (int)threadIdx.x < j1) ? (double)V[(size_t)(jb + threadIdx.x) * ldv] : 0.0;
     __syncthreads();
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(VT) void k_cross_rows(const float* __restrict__ X, 
   int a0 = blockIdx.y * CR_A, na = min(CR_A, ns - a0);
   for (int e = threadIdx.x; e < CR_A * DP; e += VT) {
     int r = e / DP, dim = e % DP;
-    zx[r][dim] = (r < na && dim < hyp.d) ? (double)Xs[(size_t)(a0 + r) * hyp.d + dim] * hyp.inv_ls[dim] : 0.0;
+    zx[r][dim] = (r < na && dim < hyp.d) ? (double)Xs[(size_t)(a0 + r) * hyp.d + dim] : 0.0;
   }
   __syncthreads();
   double acc[CR_A];
@@ -1839,8 +1839,8 @@ void launch_cross_block(hipStream_t s, const float* X, const float* Xs, int n, i
 template <typename VT_>
 static void cross_dot(hipStream_t s, const float* X, const float* Xs, int n, int ns, const HypArgs& hyp, const VT_* V, int ldv,
                       int percol, double prior, double sign, double* partial, float* out) {
-  // Where the two cross (n = 50 000, d = 16): by rows 1, 16, 32, 47 test points take 14, 22, 37, 43 us, by lanes
-  // 48 and 64 take 29 and 31 (the lanes that no test point fills cost the same).  Enough chunks for four
+  // Where the two cross (n = 50 000, d = 16): by rows 1, 8, 16, 23 test points take 10, 12, 20, 27 us, by lanes 24,
+  // 48 and 64 take 26, 28 and 30 (the lanes that no test point fills cost the same).  Enough chunks for four
   // waves per SIMD, none below 64 points.
   bool lanes = !percol && ns >= 24;
   int bx, chunks;
