@@ -45,9 +45,13 @@ constexpr int kMaxSplit = bbmm_plan::kMaxSplit;
 // More than 16 input dimensions (up to 16 the digit form takes over earlier); product in us (two-use /
 // one-use form, d = 16): n = 5 000: 88 / 60; 10 000: 125 / 121; 20 000: 312 / 331; 30 000: 630 / 696; 50 000: 1950 / 2630.
 constexpr int kOtfSymMinRows = 12288;
-// Product on the fly, 11 columns, us per call (fp64 matrix pipe, the faster of its two forms / digits): n = 3 000:
-// 41 / 48; 5 000: 58 / 60 (d = 8), 66 / 64 (d = 16); 8 000: 80 / 69, 99 / 79; 20 000: 302 / 211, 358 / 270; 32 000:
-// 687 / 464, 820 / 616.  17 columns, n = 200 000, d = 8: 32 060 / 20 430.
+// Product on the fly with the digits, us per call, fp64 form (the faster of its two) / digits / digits where they suit
+// (kernel_mm's default: the fp64 form's launch behind them is idle).  RBF, 11 columns, d = 4: n = 6 144: 62 / 59 / 62;
+// 8 000: 75 / 68 / 71; 12 000: 125 / 98 / 102; 20 000: 286 / 187 / 193; 50 000: 1540 / 937 / 964.  d = 16: 68 / 62 / 65;
+// 88 / 75 / 78; 156 / 115 / 119; 325 / 227 / 233; 1753 / 1161 / 1174.  Matern-5/2, d = 16: 72 / 66 / 69; 97 / 83 / 87;
+// 176 / 130 / 134; 357 / 272 / 278; 1929 / 1424 / 1440.  32 columns, d = 16, RBF: 96 / 93 / 97; 136 / 124 / 128;
+// 264 / 233 / 238; 620 / 499 / 503; 3487 / 2793 / 2816.  1 to 32 columns, d = 4, 8, 16, both kernels: the digits are
+// faster throughout from 8 000 rows on, and within 3 us of the fp64 form at 6 144.  Below, the fp64 form: n = 3 000: 41 / 48.
 constexpr int kDigMinRows = 6144;
 // Materialised product by 64-column workgroups (k_mm_mat_small) up to this size, where the matrix (256 MB) still fits
 // the memory-side cache: us per product call with 11 columns, k_mm_mat / k_mm_mat_small: n = 1 000: 28 / 18; 2 500: 35 / 21;

@@ -15,10 +15,12 @@
 // holds, for output pair (right-hand side q, weight w), the four digits w-3 .. w of D[i][q] (zero outside
 // 0..7): digit a of the entry meets digit w - a of the block, so accumulator (q, w) collects every digit
 // product of weight 256^-w, w = 0..7, exactly.  16 pairs share an MFMA: ceil(c / 2) of them per tile for
-// c columns.  What is left out is below 2^-62 of max|K| max|D| per term: against a product of the same
+// c columns.  What is left out: three digit products of at most 2^14 at weight 8, so below 2^-60 of max|K| max|D| per
+// term (2^e <= 2 max|D|, kX above 2^30), and D's rounding, 2^-62 max|D|.  Against a product of the same
 // entries in extended precision the sums are as good as fp64 ones (1e-16 ... 2e-15 relative, fp64 accumulation
 // 1e-16 ... 8e-16).  The entries are 32-bit numbers either way: in fixed point they are within 2.4e-10 of
-// the largest, where fp32 rounds them to 6e-8 of themselves; what decides their error is their evaluation
+// the largest or 2^-24 of themselves, whichever is more, where fp32 rounds them to 6e-8 of themselves: that suits dense
+// blocks (see dig_dense).  What decides their error is their evaluation
 // (3e-7), the rounding of the distance above all.  Product with normal columns, distance from the 64-bit
 // result (this / k_mm_otf): 200,000 points, d = 8, 17 columns 5.3e-7 / 6.3e-7; 50,000, d = 16, 11 columns 3.3e-7 / 4.0e-7;
 // 9,000, d = 4, 16 columns 1.76e-7 / 1.77e-7.
@@ -510,7 +512,8 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
 
 }  // namespace
 
-// column pairs per product, rounded up to a compiled count
+// Column pairs per product, rounded up to a compiled count.  A pair is one MFMA more per tile; n = 20 000, d = 8, RBF, 4,
+// 8, 12, 16, 18, 24, 32 columns: 155, 172, 202, 226, 258, 310, 385 us.
 int dig_groups(int c) {
   for (int g : {2, 4, 6, 8, 9, 12, 16})
     if (c <= 2 * g) return g;
@@ -522,10 +525,10 @@ void launch_digits(hipStream_t s, const double* D4, const float* Xs, const float
   k_digits<<<np / 16, 256, 0, s>>>(D4, Xs, sq, n, ld, ng, KK, bbmm_plan::dig_record_bytes(KK, ng), st, counts, (char*)rec);
 }
 
-// Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles
-// in flight (24) leave room for with two waves per SIMD.  n = 50 000, d = 16, 11 columns: 1433 us with 4,
-// 1597 with 3; n = 100 000, d = 8, 17 columns: 5272 with 4, 5632 with 3 (all with the norms as the MFMA's addend, 1 to
-// 5 % faster than the loop with symmetric ones).
+// Column blocks per wave: what the accumulators (4 ng registers a block), the coordinates (4 KK) and the tiles in flight
+// (24) leave room for in the 256 registers that two waves per SIMD have, without spills inside the loop
+// (n = 50 000, d = 16, 11 columns: 1433 us with 4, 1597 with 3; n = 100 000, d = 8, 17 columns: 5272 with 4, 5632 with 3).
+// The widest records (9 to 16 dimensions, 25 to 32 columns) leave LDS for one workgroup and so one wave per SIMD.
 int dig_nj(int KK, int ng) {
   if (ng == 2) return KK <= 2 ? 6 : 5;
   if (ng == 4) return KK <= 2 ? 5 : 4;

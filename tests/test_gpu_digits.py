@@ -346,3 +346,31 @@ def test_a_sparse_problem_keeps_no_split_coordinates():
         used.append(free - torch.cuda.mem_get_info()[0])
         ctx.close()
     assert used[0] - used[1] >= 120 * n, used
+
+
+@pytest.mark.parametrize("kernel", [inputs.RBF, inputs.MATERN52])
+@pytest.mark.parametrize("c", [3, 18])
+@pytest.mark.parametrize("scale", [0, 8, 16, 24, 32, 40])
+def test_small_entries_beside_large_ones_that_cancel(ctx, kernel, c, scale):
+    """Every weight of the digits counts.  Pairs of equal points carry +1 and -1 times the same value and cancel to the last
+    digit; what is left of a row outside them are 600 entries 2^-scale as large, known to the rounding of the entries
+    of K as if they stood alone, and to half a unit 2^-62 of the column's largest power of two (4) each.  Without
+    the digits of weight 256^-w a row would be off by up to 2^(scale - 8 w) of itself."""
+    import torch
+    n, d = 6400, 3
+    w, _ = _problem(n, d, kernel)
+    w.X[1:4000:2] = w.X[0:4000:2]
+    from paper_1809_11165_amd import binding
+    ctx.bbmm_setup(binding.problem_from_workload(w, inputs.ONTHEFLY))
+    rng = np.random.default_rng(scale)
+    small = np.zeros((n, c), dtype=np.float32)
+    small[4000:4600] = 1.0 + rng.random((600, c), dtype=np.float32)
+    small *= np.float32(2.0 ** -scale)
+    M = small.copy()
+    M[0:4000:2] = (1.0 + rng.random((2000, c))) * np.sign(rng.standard_normal((2000, c)))
+    M[1:4000:2] = -M[0:4000:2]
+    V = ctx.bbmm_kernel_mm(inputs.ONTHEFLY, torch.from_numpy(M).cuda()).cpu().numpy().astype(np.float64)
+    rows = 4600 + rng.choice(n - 4600, size=100, replace=False)
+    ref, bound = _rows(w, rows, small.astype(np.float64))
+    _check(V[rows], ref, bound + 600 * w.outputscale * 4.0 * 2.0 ** -63)
+    assert bound.max() < 1e-4 * np.abs(ref).min()
