@@ -1320,8 +1320,12 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   hipStream_t s = c->stream;
   DevState* st = ptr<DevState>(c->st);
   int digits = uses_digits(c, mode, (int)cc) ? 1 : 0;
-  ZeroSegs z = {{&st->dmax[0], digits ? c->dcnt.p : nullptr}, {2 * BBMM_MAXC + 2, kDigCountWords}, digits ? 2 : 1};
-  launch_fill_multi0(s, z);                     // ... dflag, done, iters_run
+  if (digits) {                                 // dmax, dflag, done, iters_run; the counts
+    ZeroSegs z = {{&st->dmax[0], c->dcnt.p}, {2 * BBMM_MAXC + 2, kDigCountWords}, 2};
+    launch_fill_multi0(s, z);
+  } else {
+    launch_fill_bytes0(s, &st->done, 2 * sizeof(int));
+  }
   launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), digits, st);
   VpShape ns{0, nullptr, 1}, alt{0, nullptr, 1};
   double scaleV = 1.0, addD = 0.0;

@@ -1164,11 +1164,13 @@ __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double n
 //     A wave takes 16 rows per step: L Qt is KP / 4 fp64 MFMAs whose result register r holds
 //     row 4 r + lane / 16, column lane % 16 -- rows in which R and the quad-swizzled D are
 //     contiguous across the wave.
-//     track: the columns' magnitudes of the new D are left in st for a digit product.
-template <int KP, int NQ, int MODE>
+//     TRACK: the columns' magnitudes of the new D are left in dmax / dflag for a digit product (a variant of its own
+//     and not a flag, whose code every product paid for: n = 1 500, k = 2, 32 columns 6.3 us, 4.6 without).
+template <int KP, int NQ, int MODE, bool TRACK>
 __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __restrict__ R,
                                             const double* __restrict__ L, double* __restrict__ D4,
-                                            double* __restrict__ Z, int track, DevState* st) {
+                                            double* __restrict__ Z, const DevState* __restrict__ st,
+                                            unsigned* __restrict__ dmax, int* __restrict__ dflag) {
   constexpr int LD = 16 * NQ;
   constexpr int KS = KP / 4;
   if (MODE != 2 && st->done) return;
@@ -1221,13 +1223,13 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
             if (MODE == 1) Z[idx] = z;
             else d = z + beta[qb] * D4[di];
             D4[di] = d;
-            hi[qb] = track_hi(d, hi[qb], flag[qb]);
+            if (TRACK) hi[qb] = track_hi(d, hi[qb], flag[qb]);
           }
         }
       }
     }
   }
-  if (MODE != 2 && track) {
+  if (TRACK) {
     __shared__ unsigned smax[NW][LD];
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
@@ -1235,14 +1237,14 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
       h = max(h, (unsigned)__shfl_xor((int)h, 16, 64));
       h = max(h, (unsigned)__shfl_xor((int)h, 32, 64));
       if (g == 0) smax[wave][qb * 16 + q] = h;
-      if (flag[qb]) atomicOr(&st->dflag[qb * 16 + q], flag[qb]);
+      if (flag[qb]) atomicOr(&dflag[qb * 16 + q], flag[qb]);
     }
     __syncthreads();
     if ((int)threadIdx.x < LD) {
       unsigned h = 0u;
 #pragma unroll
       for (int w = 0; w < NW; ++w) h = max(h, smax[w][threadIdx.x]);
-      atomicMax(&st->dmax[threadIdx.x], h);
+      atomicMax(&dmax[threadIdx.x], h);
     }
   }
 }
@@ -1808,25 +1810,27 @@ void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noi
                 beta_hist, resid_hist);
 }
 
+template <int MODE, bool TRACK>
+static void zd(hipStream_t s, int n, int ld, int kp, double noise, const double* R, const double* L, double* D4,
+               double* Z0, DevState* st, int nblocks) {
+#define ZD(KP, NQ) k_zd<KP, NQ, MODE, TRACK>
+  DISPATCH_KP_NQ(ZD, kp, ld / 16, nblocks, VT, n, noise, R, L, D4, Z0, st, st->dmax, st->dflag);
+#undef ZD
+}
+
 void launch_zd(hipStream_t s, int init, int n, int ld, int kp, double noise, const double* R,
                const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks) {
-  int nq = ld / 16;
-  if (init) {
-#define ZD_INIT(KP, NQ) k_zd<KP, NQ, 1>
-    DISPATCH_KP_NQ(ZD_INIT, kp, nq, nblocks, VT, n, noise, R, L, D4, Z0, track, st);
-#undef ZD_INIT
-  } else {
-#define ZD_ITER(KP, NQ) k_zd<KP, NQ, 0>
-    DISPATCH_KP_NQ(ZD_ITER, kp, nq, nblocks, VT, n, noise, R, L, D4, Z0, track, st);
-#undef ZD_ITER
-  }
+  if (init && track) zd<1, true>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
+  else if (init) zd<1, false>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
+  else if (track) zd<0, true>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
+  else zd<0, false>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
 }
 
 void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, const double* R,
                          const double* L, double* Z, DevState* st, int nblocks) {
   int nq = ld / 16;
-#define ZD_APPLY(KP, NQ) k_zd<KP, NQ, 2>
-  DISPATCH_KP_NQ(ZD_APPLY, kp, nq, nblocks, VT, n, noise, R, L, (double*)nullptr, Z, 0, st);
+#define ZD_APPLY(KP, NQ) k_zd<KP, NQ, 2, false>
+  DISPATCH_KP_NQ(ZD_APPLY, kp, nq, nblocks, VT, n, noise, R, L, (double*)nullptr, Z, st, (unsigned*)nullptr, (int*)nullptr);
 #undef ZD_APPLY
 }
 
