@@ -32,6 +32,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_F32_PEAK_TFLOPS = 157.3   # MI355X dense fp32 matrix, published
 MFMA_F64_PEAK_TFLOPS = 78.6    # MI355X dense fp64 matrix, published
+MFMA_I8_OPS = 2.0 * 16 * 16 * 64     # of one v_mfma_i32_16x16x64_i8
+MFMA_I8_PEAK_TOPS = MFMA_I8_OPS / 16 * 1024 * 2.4e9 / 1e12   # 16 cycles each, 1024 SIMDs, 2.4 GHz: 5 033
 FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X fp64 vector, published
 # HBM bytes per k_mm_mat launch at n = 50000 from rocprofv3 FETCH_SIZE / WRITE_SIZE, each scaled by a
 # 1 GiB copy (profiles/k_mm_mat_cfg3_n50000_hbm_counters.txt); only valid for that workload.
@@ -190,25 +192,43 @@ def roofline_mat(n, c, mm_ms, launches, config):
             "kernel": "k_mm_mat", "avg_launch_ms": mm_ms, "launches": launches}
 
 
+def otf_uses_digits(n, d):
+    """Whether the library's default on-the-fly product runs on the 8-bit matrix pipe."""
+    return d <= 16 and -(-n // 256) * 256 >= 6144
+
+
 def roofline_otf(n, c, d, mm_ms, launches):
     """Tiles rebuilt from X in every product.  Algorithmic flops per pair: 2 d (distance contraction)
-    + 2 c (multiply by the block).  `frac` prices all of them at the fp32 matrix rate.  With the
-    second contraction in fp64, at half that rate on the same pipe, the floor of the two together is
-    n^2 (2 d / peak32 + 2 c / peak64): `frac_of_mixed_floor` is that floor over the launch time.
-    k_mm_otf_dig uses neither unit (bf16 and 8-bit matrix instructions), so it is not bound by it."""
+    + 2 c (multiply by the block).
+
+    On the 8-bit matrix pipe (k_mm_otf_dig) a 16 x 16 tile takes ceil(c / 2) v_mfma_i32_16x16x64_i8 for the block's
+    digits and one v_mfma_f32_16x16x32_bf16 per four (padded) dimensions for the distances, 16 cycles each: `frac` is
+    the 8-bit operations of the former over the dense 8-bit peak, `issue_floor_ms` the time in which the
+    matrix pipes can take all of them.
+
+    Otherwise `frac` prices the algorithmic flops at the fp32 matrix rate; the second contraction is carried out in fp64,
+    at half that rate on the same pipe, so the floor of the two together is n^2 (2 d / peak32 + 2 c / peak64):
+    `frac_of_mixed_floor` is that floor over the launch time."""
     alg_flops = (2.0 * d + 2.0 * c) * n * n
     np_ = -(-n // 256) * 256
+    out = {"bound": "mfma", "traffic": None, "avg_launch_ms": mm_ms, "launches": launches, "pairs_per_s": n * n / (mm_ms * 1e-3)}
+    if otf_uses_digits(n, d):
+        tiles, kk = (np_ / 16.0) ** 2, 1 if d <= 4 else (2 if d <= 8 else 4)
+        pairs = -(-c // 2)
+        achieved = tiles * pairs * MFMA_I8_OPS / (mm_ms * 1e-3) / 1e12
+        floor_ms = tiles * (pairs + kk) * MFMA_I8_OPS / MFMA_I8_PEAK_TOPS * 1e-9
+        out.update({"achieved": achieved, "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (8-bit)", "frac": achieved / MFMA_I8_PEAK_TOPS,
+                    "kernel": "k_mm_otf_dig (8-bit matrix instructions on fixed-point digits; with k_digits)",
+                    "algorithmic_TFLOPs": alg_flops / (mm_ms * 1e-3) / 1e12,
+                    "issue_floor_ms": floor_ms, "frac_of_issue_floor": floor_ms / mm_ms})
+        return out
     achieved = alg_flops / (mm_ms * 1e-3) / 1e12
     mixed_floor_ms = n * n * (2.0 * d / MFMA_F32_PEAK_TFLOPS + 2.0 * c / MFMA_F64_PEAK_TFLOPS) * 1e-9
-    return {"bound": "mfma", "achieved": achieved, "peak": MFMA_F32_PEAK_TFLOPS,
-            "unit": "TFLOP/s", "frac": achieved / MFMA_F32_PEAK_TFLOPS, "traffic": None,
-            "kernel": "k_mm_otf_dig (8-bit matrix instructions on fixed-point digits; with k_digits)"
-                      if (d <= 16 and np_ >= 6144) else
-                      "k_mm_otf_tri (tiles on and above the diagonal, each used twice; two launches per product)"
-                      if (c <= 16 and d <= 32 and np_ >= 12288) else "k_mm_otf",
-            "avg_launch_ms": mm_ms, "launches": launches,
-            "pairs_per_s": n * n / (mm_ms * 1e-3),
-            "mixed_floor_ms": mixed_floor_ms, "frac_of_mixed_floor": mixed_floor_ms / mm_ms}
+    out.update({"achieved": achieved, "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_F32_PEAK_TFLOPS,
+                "kernel": "k_mm_otf_tri (tiles on and above the diagonal, each used twice; two launches per product)"
+                          if (c <= 16 and d <= 32 and np_ >= 12288) else "k_mm_otf",
+                "mixed_floor_ms": mixed_floor_ms, "frac_of_mixed_floor": mixed_floor_ms / mm_ms})
+    return out
 
 
 def time_calls(ctx, prob, warmup, steps):
@@ -324,8 +344,11 @@ def main():
         "vs_baseline": None, "dtype": "f64", "data": "synthetic",
         "config": {"workload": workload,
                    "mode": mode_name,
-                   "arithmetic": "kernel-matrix entries fp32 (stored or generated), products, sums and all "
-                                 "n x c blocks fp64",
+                   "arithmetic": ("kernel-matrix entries evaluated in fp32 and multiplied in 31-bit fixed point with 62-bit "
+                                  "blocks, exact integer sums; all other sums and the n x c blocks fp64"
+                                  if mode == inputs.ONTHEFLY and otf_uses_digits(n, d) else
+                                  "kernel-matrix entries fp32 (stored or generated), products, sums and all "
+                                  "n x c blocks fp64"),
                    "iters_run": res.iters_run, "ms_per_iteration": ms_per_step / max(res.iters_run, 1),
                    "mm_ms_per_iteration": mm_ms,
                    "logdet": res.logdet, "nlml": res.nlml},
