@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, c
 // Accumulators of one 16-column block -> partial results of (K/s) D.  acc[q][r]: lane (jc, g) holds pair
 // 16 q + 4 g + r, i.e. right-hand side 2 q + g / 2, weight 4 (g % 2) + r, of output column jc.  T: LDS,
 // 16 x (LD + 1) doubles of the wave.  A block column with a non-finite entry gets what the sum of K D is
-// for K > 0; non-finite coordinates (xbad) make every entry one.
+// for K > 0; an X that is none for the digits (xbad) makes everything NaN.
 template <int NG, int LD>
 __device__ __forceinline__ void dig_store(const i32x4 (&acc)[NG], double* __restrict__ T, int jc, int g,
                                           const DevState* __restrict__ st, double* __restrict__ vrow) {

@@ -638,7 +638,7 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_tri(const float* __restrict__
 //               and share one contraction.  c, Y and Y2 cancel, so all three see the same rounded T, and
 //               sums run in fp32 over DK_RUN row blocks only; the wave's fp64 row takes them from there.
 // Bound by the vector ALU, which the fp32 MFMAs block (14.4 ns each, nothing beside them).  The derivative call,
-// n = 50 000, d = 16, ARD: 3.40 ms with a Y2 contraction per tile -> 2.85 -> 3.05 with the sums in runs.  Error of all terms
+// n = 50 000, d = 16, ARD: 3.26 ms with a Y2 contraction per tile -> 2.71 -> 2.84 with the sums in runs.  Error of all terms
 // against 64 bits, rms of four problems there (trace, quad): 2.9e-6, 4.5e-8 -> 1.4e-6, 2.2e-8; of 96 problems with n = 9 000:
 // 3.0e-6, 5.5e-8 -> 3.0e-6, 5.3e-8 (in one fp32 run, with u0_i in the row operand: 3.5e-6, 6.3e-8).
 // Every summand is symmetric in (i, j), so only tiles with row block <= column block are

@@ -104,7 +104,8 @@ def test_digit_product_with_near_duplicate_points(ctx, kernel):
 
 
 def test_digit_product_of_non_finite_blocks(ctx):
-    """A column with an infinity or a NaN gets what the fp64 form gives; the others are not touched."""
+    """A column with an infinity or a NaN gets what the fp64 form gives where no entry of K vanishes; the others are not
+    touched.  (otf_digits = 1 takes the fp64 form for such a block.)"""
     import torch
     w, prob = _problem(6200, 4, inputs.RBF)
     M = np.random.default_rng(1).standard_normal((6200, 6)).astype(np.float32)
