@@ -185,7 +185,9 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                1 (default): the products of an mBCG run, whose results are measured by norms; and
  *                bbmm_kernel_mm where all columns suit it: finite, at most n / 128 entries below
  *                2^-12 and n / 16384 + 4 below 2^-20 of the largest (decided on the device); any
- *                other block of bbmm_kernel_mm takes the fp64 form.  2: all of them; 0: none
+ *                other block of bbmm_kernel_mm takes the fp64 form.  Points of X whose scaled square
+ *                overflows fp32 call for the fp64 form in both (an mBCG run is then made twice).
+ *                2: all products (NaN for such X in bbmm_kernel_mm); 0: none
  *   "otf_sym"    the form with fp64 sums.  1 (default): a product of at most 16 columns over at most 32 input
  *                dimensions and at least 12288 (padded) rows evaluates only the tiles on and above
  *                the diagonal and uses each for both of its contributions (K is symmetric);
