@@ -35,15 +35,9 @@ MFMA_F64_PEAK_TFLOPS = 78.6    # MI355X dense fp64 matrix, published
 MFMA_I8_OPS = 2.0 * 16 * 16 * 64     # of one v_mfma_i32_16x16x64_i8
 MFMA_I8_PEAK_TOPS = MFMA_I8_OPS / 16 * 1024 * 2.4e9 / 1e12   # 16 cycles each, 1024 SIMDs, 2.4 GHz: 5 033
 FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X fp64 vector, published
-# HBM bytes per k_mm_mat launch at n = 50000 from rocprofv3 FETCH_SIZE / WRITE_SIZE, each scaled by a
-# 1 GiB copy (profiles/k_mm_mat_cfg3_n50000_hbm_counters.txt); only valid for that workload.
-MEASURED_TRAFFIC_MAT_N50000 = 10.141e9
-# HBM bytes per SGPR product (both k_mm_mat launches) at n = 500000, m = 1024, measured the same way
-# (profiles/k_mm_mat_cfg5_n500000_sgpr_hbm_counters.txt); only valid for that workload.
+# HBM bytes per SGPR product (both k_mm_mat launches) at n = 500000, m = 1024, from rocprofv3 FETCH_SIZE / WRITE_SIZE, each
+# scaled by a 1 GiB copy (profiles/k_mm_mat_cfg5_n500000_sgpr_hbm_counters.txt); only valid for that workload.
 MEASURED_TRAFFIC_SGPR_N500000_M1024 = 4.261e9
-# HBM bytes per product from the upper triangle at n = 50000 (both launches), measured the same way
-# (profiles/k_mm_sym_cfg3_n50000_counters.txt); only valid for that workload.
-MEASURED_TRAFFIC_SYM_N50000 = 5.527e9
 
 
 def _cores():
@@ -160,21 +154,45 @@ TRAFFIC_NOTE = ("HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SI
                 "workload (profiles/%s), not counted in this run")
 
 
+def words_of(n, c, sym):
+    """Whether the library's default materialised products of an iteration run on digit words (8-bit matrix pipe)."""
+    return c <= 12 and -(-n // 256) * 256 > (8192 if sym else 10239)
+
+
+def roofline_words(n, c, mm_ms, launches):
+    """Product from K_hat as digit words (k_mm_words): the upper triangle (with whole 512-column blocks on the diagonal), 4 bytes an
+    entry, is read once, and every 16 x 16 tile takes ceil(c / 2), compiled for 2, 4 or 6, v_mfma_i32_16x16x64_i8 for each of its two
+    uses.  `frac` prices those operations at the dense 8-bit peak; the bytes are given beside it."""
+    np_ = -(-n // 256) * 256
+    tiles = sum(min(np_, 512 * (p + 1)) // 16 * (min(512, np_ - 512 * p) // 16) for p in range(-(-np_ // 512)))
+    groups = next(g for g in (2, 4, 6) if c <= 2 * g)
+    achieved = 2.0 * tiles * groups * MFMA_I8_OPS / (mm_ms * 1e-3) / 1e12
+    return {"bound": "mfma", "achieved": achieved, "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (8-bit)",
+            "frac": achieved / MFMA_I8_PEAK_TOPS, "traffic": None, "kernel": "k_mm_words (with k_digits)",
+            "avg_launch_ms": mm_ms, "launches": launches, "matrix_GBs": tiles * 1024.0 / (mm_ms * 1e-3) / 1e9,
+            "algorithmic_TFLOPs": 2.0 * c * n * n / (mm_ms * 1e-3) / 1e12}
+
+
 def roofline_sym(n, c, mm_ms, launches, config):
     """Product from the stored upper triangle.  The triangle is read once (2 n^2 + 4 n W bytes,
     W = 1024: the diagonal blocks are whole), which no longer binds; every stored 16 x 16 tile still
     takes its fp64 MFMAs for both of its uses, so the product is bound by the fp64 matrix rate.
     Algorithmic flops of one product: 2 c per pair of points (c = t + 1 columns really used).
     Executed: per pair 16 columns on the row-side use and 12 or 16 on the column-side use (12 when at
-    most 12 columns of a 16-column group are in use), each on half the pairs; reported beside it."""
+    most 12 columns of a 16-column group are in use), each on half the pairs; reported beside it.
+
+    Up to 12 columns an iteration's products come from digit words instead, and up to 8192 rows a call keeps the whole matrix."""
+    if words_of(n, c, True):
+        return roofline_words(n, c, mm_ms, launches)
+    if -(-n // 256) * 256 <= 8192 and c <= 16:
+        return roofline_mat(n, c, mm_ms, launches, config)
     alg_flops = 2.0 * c * n * n
     achieved = alg_flops / (mm_ms * 1e-3) / 1e12
     wide = sum(16 + (12 if min(16, c - 16 * q) <= 12 else 16) for q in range((c + 15) // 16))
     executed = wide * n * n / (mm_ms * 1e-3) / 1e12
     return {"bound": "mfma", "achieved": achieved, "peak": MFMA_F64_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": achieved / MFMA_F64_PEAK_TFLOPS,
-            "traffic": MEASURED_TRAFFIC_SYM_N50000 if (n, config) == (50000, 3) else None,
-            "traffic_source": TRAFFIC_NOTE % "k_mm_sym_cfg3_n50000_counters.txt" if (n, config) == (50000, 3) else None,
+            "traffic": None, "traffic_source": None,
             "kernel": "k_mm_sym (one launch per product for c <= 12, else a second one for the diagonal blocks)",
             "avg_launch_ms": mm_ms, "launches": launches,
             "executed_TFLOPs_with_padding": executed,
@@ -182,14 +200,16 @@ def roofline_sym(n, c, mm_ms, launches, config):
 
 
 def roofline_mat(n, c, mm_ms, launches, config):
-    """Whole K_hat streamed once per product: algorithmic bytes 4 n^2 (K_hat) + 8 n c (block in and out)."""
+    """Whole K_hat streamed once per product: algorithmic bytes 4 n^2 (K_hat) + 8 n c (block in and out); beyond 10 240 rows and up
+    to 12 columns an iteration reads half of that (digit words), which the bytes per second of the whole then count too."""
+    words = words_of(n, c, False)
     alg_bytes = 4.0 * n * n + 8.0 * n * c
     achieved = alg_bytes / (mm_ms * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": MEASURED_TRAFFIC_MAT_N50000 if (n, config) == (50000, 3) else None,
-            "traffic_source": TRAFFIC_NOTE % "k_mm_mat_cfg3_n50000_hbm_counters.txt" if (n, config) == (50000, 3) else None,
-            "kernel": "k_mm_mat", "avg_launch_ms": mm_ms, "launches": launches}
+            "traffic": None, "traffic_source": None,
+            "kernel": "k_mm_words (8-bit matrix pipe; the triangle is read)" if words else
+                      ("k_mm_mat" if n > 8192 or c > 16 else "k_mm_mat_small"), "avg_launch_ms": mm_ms, "launches": launches}
 
 
 def otf_uses_digits(n, d):

@@ -22,8 +22,8 @@
  *     before they return).  A call
  *     that returns host values synchronises the stream once before it returns.
  *   - Precision: K_hat entries are fp32; inside the library every n x c block of
- *     the iteration, the pivoted-Cholesky factor and all sums are fp64 (large on-the-fly
- *     products: integers of that accuracy, see "otf_digits").  float
+ *     the iteration, the pivoted-Cholesky factor and all sums are fp64 (large products
+ *     of an iteration: integers of that accuracy, see "otf_digits").  float
  *     block arguments are converted on entry and rounded once on exit.
  *   - Every function returns an int status (BBMM_OK == 0).  No exceptions,
  *     no exit().  bbmm_last_error() gives a message for the last failure.
@@ -187,7 +187,12 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                2^-12 and n / 16384 + 4 below 2^-20 of the largest (decided on the device); any
  *                other block of bbmm_kernel_mm takes the fp64 form.  Points of X whose scaled square
  *                overflows fp32 call for the fp64 form in both (an mBCG run is then made twice).
- *                2: all products (NaN for such X in bbmm_kernel_mm); 0: none
+ *                2: all products (NaN for such X in bbmm_kernel_mm); 0: none.
+ *                The same for BBMM_MODE_MATERIALISED: an mBCG run of at least 8 iterations on at most 12 columns takes its
+ *                products from the entries as fixed-point words, half of the matrix, from 10240 rows on, and from
+ *                1024 on where the triangle is kept ("khat_sym").  bbmm_solve_logdet_grad then evaluates the words from X
+ *                (fp64 distances) and builds the fp32 matrix only when a later call asks for it; a matrix built by
+ *                bbmm_build_khat is converted, and stays.  bbmm_kernel_mm uses the fp32 matrix (2: the words)
  *   "otf_sym"    the form with fp64 sums.  1 (default): a product of at most 16 columns over at most 32 input
  *                dimensions and at least 12288 (padded) rows evaluates only the tiles on and above
  *                the diagonal and uses each for both of its contributions (K is symmetric);
@@ -207,7 +212,8 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                "mat_wgs" then counts the workgroups of each of its two launches.  A block of
  *                more than 16 columns takes one pass over the triangle per group of 16 columns
  *                (the whole-matrix product takes one pass for up to 32), so beyond 16 columns
- *                the whole matrix is the faster storage
+ *                the whole matrix is the faster storage.  bbmm_solve_logdet_grad
+ *                keeps the whole matrix up to 8192 rows and 16 columns, where that is the faster one
  *   "zd_blocks"  workgroups per compute unit of the direction update (default 16, at most 64)
  *   "sgpr_wgs1", "sgpr_wgs2"  workgroups of the two streaming products of an SGPR product
  *                (A^T M, then A (.)); clamped like "mat_wgs"; takes effect at the next bbmm_sgpr_build

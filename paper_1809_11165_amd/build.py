@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libbbmm.so")
 SOURCES = ["kernels_vec.hip", "kernels_mm.hip", "kernels_sym.hip", "kernels_sgpr.hip", "kernels_dig.hip",
-           "bbmm_api.hip"]
+           "kernels_words.hip", "bbmm_api.hip"]
 # packed fp32 VALU ops are switched off for all device code
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -23,7 +23,8 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
 # ordinary registers the accumulator-register moves go (config 4 product 34.0 -> 32.3 ms; the other
 # kernels of the file time the same).  The triangle kernel needs the accumulation registers and stays as it is.
 EXTRA_FLAGS = {"kernels_mm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-               "kernels_dig.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+               "kernels_dig.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "kernels_words.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _run(cmd):

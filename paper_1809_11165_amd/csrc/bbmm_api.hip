@@ -57,6 +57,12 @@ constexpr int kDigMinRows = 6144;
 // the memory-side cache: us per product call with 11 columns, k_mm_mat / k_mm_mat_small: n = 1 000: 28 / 18; 2 500: 35 / 21;
 // 5 000: 48 / 36; 8 000: 70 / 55; 10 000: 95 / 105.  16 columns: 34 / 18; 43 / 22; 55 / 39; 70 / 57; 94 / 105.
 constexpr int kMatSmallMaxRows = 8192;
+// Iterations of the materialised mode with K_hat as digit words (k_mm_words, up to 12 columns).  Whole calls of 50 iterations, 11
+// columns, ms, fp64 products from the whole matrix / from its triangle / words, RBF d = 8: n = 1 100: 1.90 / 3.38 / 3.01; 2 500: 2.04 / 4.79 / 3.51;
+// 6 000: 3.22 / 5.40 / 3.99; 8 500: 4.68 / 6.06 / 4.78; 12 000: 6.72 / 7.62 / 6.41; 16 000: 10.1 / 10.5 / 9.1; 24 000: 19.6 / 18.7 / 16.2;
+// 40 000: 53.2 / 45.9 / 40.2; Matern-5/2 d = 16 and 2 to 12 columns alike.  So the words take over from the triangle at any size that has
+// two panels, and from the whole matrix at 10 240 rows.  Building them costs two products or so.
+constexpr int kWordsTriMinRows = 1024, kWordsMinRows = 10240, kWordsMinIters = 8;
 constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 
 }  // namespace
@@ -101,9 +107,12 @@ struct bbmm_ctx {
   int khat_pw = 0;                           // layout of the K_hat currently in memory
   int64_t khat_sym = 0;                      // 1: keep only the upper triangle of K_hat (packed panels)
   bool khat_tri = false;                     // the K_hat currently in memory is such a triangle
+  bool khat_mem = false;                     // khat_built is what a caller may use; whether the fp32 matrix is in memory
+  bool words_built = false;                  // K_hat is in memory as digit words (the iteration's products, see kernels_words.hip)
   // work list of the product from the triangle
   TriLists sym;                              // ... from the stored triangle (panels of 1024 columns)
   TriLists otft;                             // ... on the fly from X (panels of 512 columns)
+  TriLists wrd;                              // ... from the digit words (panels of 512 columns)
   int64_t otf_sym = 1;                       // on-the-fly product with each tile pair evaluated once (<= 16 columns, d <= 32): 0 never, 1 from kOtfSymMinRows rows on, 2 always
   int64_t otf_digits = 1;                    // digits (needs otf_sym 1): 0 never, 1 in the iteration and for products of blocks that suit them, 2 for all
   // plans of the materialised product: 16- and 32-column blocks (index 0 / 1), 16-column block with at most 12 columns in use (2)
@@ -137,7 +146,7 @@ struct bbmm_ctx {
   Buf Xa, Xb, Xs, X4, sq, Khat, L, delta, U, R, V, Z0, D4, Vp, partial, gpartial, alpha, beta, resid, st,
       tmpA, tmpB, SA, SB, u0v, dkpartial, eig, plan[3], nseg[3], 
       KUU, Gm, Ginv, Kux, AT, A, qdiag, Tp, T4, sgplan[4], sgnseg[4],
-      Ua, Ub, Us, U4, usq, TU, TW, BU, BW, dkops, rec, Pb, dcnt;
+      Ua, Ub, Us, U4, usq, TU, TW, BU, BW, dkops, rec, Pb, dcnt, words, Xo, sqo;
   double* eig_static = nullptr;   // this device's address of `scratch`
   int* h_eig_status = nullptr;    // pinned, BBMM_EIG_NOALLOC_MAX ints
   DevState* h_st = nullptr;   // pinned
@@ -256,8 +265,8 @@ int ensure_vp(bbmm_ctx* c, int slots, int ld) {
 }
 
 // Records of the block's digit operands (see launch_digits).
-int ensure_records(bbmm_ctx* c, int ng) {
-  size_t bytes = (size_t)bbmm_plan::dig_buffer_bytes(c->np / 16, c->KK, ng);
+int ensure_records(bbmm_ctx* c, int KK, int ng) {
+  size_t bytes = (size_t)bbmm_plan::dig_buffer_bytes(c->np / 16, KK, ng);
   if (bytes <= c->rec.cap) return BBMM_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still use the old buffer
   return ensure(c, c->rec, bytes);
@@ -309,11 +318,11 @@ int ensure_mat_plans(bbmm_ctx* c) {
 
 // Work lists of a product that visits only the panels (W columns each) on and above the diagonal
 // (bbmm_plan::lay_out_triangle), uploaded.
-int build_tri_lists(bbmm_ctx* c, int W, int want, int64_t tune, TriLists& L) {
+int build_tri_lists(bbmm_ctx* c, int W, int want, int64_t tune, TriLists& L, int max_steps = 1 << 30, bool whole = false) {
   if (L.np == c->np && L.tune == tune) return BBMM_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still read the old lists
   bbmm_plan::TriHost H;
-  if (const char* what = bbmm_plan::lay_out_triangle(c->np, W, want, H)) return fail(c, BBMM_EINVAL, what);
+  if (const char* what = bbmm_plan::lay_out_triangle(c->np, W, want, H, max_steps, whole)) return fail(c, BBMM_EINVAL, what);
   struct Up {
     Buf* b;
     const void* src;
@@ -338,6 +347,10 @@ int build_tri_lists(bbmm_ctx* c, int W, int want, int64_t tune, TriLists& L) {
 
 int ensure_sym_plan(bbmm_ctx* c) {
   return build_tri_lists(c, BBMM_SYM_PANEL, c->mat_wgs > 0 ? (int)c->mat_wgs : c->num_cus, c->mat_wgs, c->sym);
+}
+
+int ensure_words_plan(bbmm_ctx* c) {
+  return build_tri_lists(c, BBMM_WORDS_PANEL, c->mat_wgs > 0 ? (int)c->mat_wgs : c->num_cus, c->mat_wgs, c->wrd, kDigMaxBlocks, true);
 }
 
 // two workgroups of the on-the-fly triangle kernel fit a compute unit
@@ -392,8 +405,15 @@ int dig_split_of(const bbmm_ctx* c, int cc) {
 // laid out with the others then).
 bool may_use_digits(const bbmm_ctx* c) { return !c->sgpr && c->np >= kDigMinRows && c->KK <= 4; }
 
+// Whether an iteration of the materialised mode takes its products from digit words.
+bool wants_words(const bbmm_ctx* c, int cc) {
+  return !c->sgpr && c->otf_digits != 0 && !c->far_x && cc <= 12 && c->maxit >= kWordsMinIters &&
+         c->np >= (c->khat_tri ? kWordsTriMinRows : kWordsMinRows);
+}
+
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.
 bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
+  if (mode == BBMM_MODE_MATERIALISED) return c->words_built && wants_words(c, cc);
   return mode == BBMM_MODE_ONTHEFLY && c->otf_sym == 1 && c->otf_digits != 0 && !c->far_x && may_use_digits(c) &&
          dig_split_of(c, cc) <= kMaxSplit;
 }
@@ -459,11 +479,10 @@ int device_status(bbmm_ctx* c) {
 }
 
 // ---- stages on internal buffers -------------------------------------------------------------
-int stage_build_khat(bbmm_ctx* c) {
+int stage_build_khat(bbmm_ctx* c, bool tri) {
   // column panels of 1024 (one 16-row step of a workgroup is then 64 KB of contiguous memory:
   // 1.515 -> 1.498 ms per product at n = 50,000); "khat_panel" = 1 keeps plain row-major
   int pw = c->khat_panel == 0 ? 1024 : (c->khat_panel == 1 ? 0 : (int)c->khat_panel);
-  bool tri = c->khat_sym != 0;
   size_t cols_alloc = pw > 0 ? (size_t)((c->np + pw - 1) / pw) * pw : (size_t)c->np;
   size_t bytes = (size_t)c->np * cols_alloc * sizeof(float);
   if (tri) {
@@ -480,8 +499,46 @@ int stage_build_khat(bbmm_ctx* c) {
                         ptr<float>(c->sq), c->n, c->np, pw, tri ? 1 : 0, c->prob.outputscale, c->prob.noise,
                         ptr<float>(c->Khat)))
     return fail(c, BBMM_EINVAL, "unsupported input dimension");
-  c->khat_built = true;
+  c->khat_built = c->khat_mem = true;
+  c->words_built = false;                   // (an iteration on it takes its entries)
   return BBMM_OK;
+}
+
+// K_hat as digit words, for an iteration.  No room for them: c->words_built stays false and the fp32 matrix serves.
+int stage_build_words(bbmm_ctx* c) {
+  if (c->words_built) return BBMM_OK;
+  size_t np = (size_t)c->np;
+  struct { Buf* b; size_t bytes; } want[] = {
+      {&c->words, words_bytes(c->np)}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
+  for (auto& w : want) {
+    int rc = ensure(c, *w.b, w.bytes);
+    if (rc == BBMM_ENOMEM) {
+      c->err.clear();
+      return BBMM_OK;
+    }
+    if (rc) return rc;
+  }
+  if (c->khat_mem)                          // the matrix that the caller has had built
+    launch_words_of(c->stream, ptr<float>(c->Khat), (size_t)(c->khat_pw > 0 ? c->khat_pw : c->np), c->khat_tri ? 1 : 0,
+                    c->prob.outputscale, c->n, c->np, ptr<int>(c->words));
+  else
+    launch_build_words(c->stream, c->prob.kernel, c->prob.X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st),
+                       ptr<double>(c->Xo), ptr<double>(c->sqo), ptr<int>(c->words));
+  c->words_built = true;
+  return BBMM_OK;
+}
+
+// The fp32 matrix, where a call has done without it so far.
+int need_khat(bbmm_ctx* c) {
+  if (c->khat_mem) return BBMM_OK;
+  int rc = stage_build_khat(c, c->khat_tri);
+  if (rc != BBMM_ENOMEM || !c->words.p) return rc;
+  HIPCHK(c, hipStreamSynchronize(c->stream));   // no room for both
+  c->words_built = false;
+  HIPCHK(c, hipFree(c->words.p));
+  c->words = Buf{};
+  ++c->alloc_epoch;
+  return stage_build_khat(c, c->khat_tri);
 }
 
 // SGPR: K_UU (fp64) -> Cholesky factor G -> G^{-1}; K_UX (fp64); A^T = G^{-1} K_UX rounded to fp32,
@@ -608,7 +665,7 @@ int stage_otf_dig(bbmm_ctx* c, int cc, int ld, bool guard, VpShape* shape, doubl
   int ns = dig_split_of(c, cc), ng = dig_groups(cc);
   int rc = ensure_vp(c, ns, ld);
   if (rc) return rc;
-  rc = ensure_records(c, ng);
+  rc = ensure_records(c, c->KK, ng);
   if (rc) return rc;
   unsigned* counts = guard ? ptr<unsigned>(c->dcnt) : nullptr;
   launch_digits(c->stream, ptr<double>(c->D4), ptr<float>(c->Xs), ptr<float>(c->sq), c->n, c->np, ld, c->KK, ng,
@@ -622,9 +679,69 @@ int stage_otf_dig(bbmm_ctx* c, int cc, int ld, bool guard, VpShape* shape, doubl
   return BBMM_OK;
 }
 
+// Plan and room for the partial results of stage_mat64.
+int mat64_reserve(bbmm_ctx* c, int cc, int ld) {
+  if (c->khat_tri) {
+    int rc = ensure_sym_plan(c);
+    return rc ? rc : ensure_vp(c, c->sym.max_slots, ld);
+  }
+  if (int ns = mat_split_of(c, ld)) return ensure_vp(c, ns, ld);
+  int rc = ensure_mat_plans(c);
+  return rc ? rc : ensure_vp(c, c->plan_slots[(ld == 32) ? 1 : (cc <= 12 ? 2 : 0)], ld);
+}
+
+// Product with the stored matrix on the fp64 matrix pipe.
+int stage_mat64(bbmm_ctx* c, int cc, int ld, VpShape* shape) {
+  int rc = need_khat(c);
+  if (rc) return rc;
+  rc = mat64_reserve(c, cc, ld);
+  if (rc) return rc;
+  if (c->khat_tri) {
+    if (launch_mm_sym(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld, cc,
+                      ptr<MmPiece>(c->sym.pieces), ptr<int>(c->sym.first0), c->sym.wgs[0],
+                      ptr<int>(c->sym.first1), c->sym.wgs[1], ptr<int>(c->sym.base), ptr<DevState>(c->st)))
+      return fail(c, BBMM_EINVAL, "unsupported block width");
+    *shape = VpShape{0, ptr<int>(c->sym.tot), BBMM_SYM_PANEL};
+    return BBMM_OK;
+  }
+  if (int ns = mat_split_of(c, ld)) {
+    if (launch_mm_mat_small(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ns,
+                            ptr<DevState>(c->st), c->khat_pw, c->np, cc))
+      return fail(c, BBMM_EINVAL, "unsupported layout of the stored matrix");
+    *shape = VpShape{ns, nullptr, 1, ns};
+    return BBMM_OK;
+  }
+  int v = (ld == 32) ? 1 : (cc <= 12 ? 2 : 0);
+  if (launch_mm_mat(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld,
+                    ptr<MmPlan>(c->plan[v]), c->plan_wgs[v], ptr<DevState>(c->st), c->khat_pw, c->np, cc))
+    return fail(c, BBMM_EINVAL, "unsupported block width");
+  *shape = VpShape{0, ptr<int>(c->nseg[v]), v == 1 ? 512 : 1024, c->plan_slots[v]};
+  return BBMM_OK;
+}
+
+// Partial sums of (K/s) D less the diagonal from the digit words.
+int stage_mm_words(bbmm_ctx* c, int cc, int ld, VpShape* shape, double* scaleV, double* addD) {
+  int ng = dig_groups(cc);
+  int rc = ensure_words_plan(c);
+  if (rc) return rc;
+  rc = ensure_vp(c, c->wrd.max_slots, ld);
+  if (rc) return rc;
+  rc = ensure_records(c, 0, ng);
+  if (rc) return rc;
+  launch_digits(c->stream, ptr<double>(c->D4), nullptr, nullptr, c->n, c->np, ld, 0, ng, ptr<DevState>(c->st), nullptr, c->rec.p);
+  if (launch_mm_words(c->stream, ptr<int>(c->words), c->rec.p, ng, ptr<double>(c->Vp), c->np, ld, ptr<MmPiece>(c->wrd.pieces),
+                      ptr<int>(c->wrd.first0), c->wrd.wgs[0], ptr<int>(c->wrd.base), ptr<DevState>(c->st)))
+    return fail(c, BBMM_EINVAL, "unsupported block width");
+  *shape = VpShape{0, ptr<int>(c->wrd.tot), BBMM_WORDS_PANEL};
+  *scaleV = c->prob.outputscale;
+  *addD = c->prob.outputscale + c->prob.noise;
+  return BBMM_OK;
+}
+
 // Vp <- partial products of K_hat with the block in D4; returns the split count and the
 // (scale, add) pair that turns the partial sums into K_hat D.
-int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scaleV, double* addD) {
+// digits: on the 8-bit matrix pipe (see uses_digits)
+int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, int digits, VpShape* shape, double* scaleV, double* addD) {
   if ((mode == BBMM_MODE_SGPR) != c->sgpr)
     return fail(c, BBMM_EINVAL, "an SGPR problem takes mode SGPR, and only an SGPR problem does");
   if (mode == BBMM_MODE_SGPR) {
@@ -641,43 +758,10 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, VpShape* shape, double* scal
   } else if (mode == BBMM_MODE_MATERIALISED) {
     if (!c->khat_built) return fail(c, BBMM_EINVAL, "materialised product needs bbmm_build_khat first");
     if (ld != 16 && ld != 32) return fail(c, BBMM_EINVAL, "unsupported block width");
-    if (c->khat_tri) {
-      int rc = ensure_sym_plan(c);
-      if (rc) return rc;
-      rc = ensure_vp(c, c->sym.max_slots, ld);
-      if (rc) return rc;
-      if (launch_mm_sym(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld, cc,
-                        ptr<MmPiece>(c->sym.pieces), ptr<int>(c->sym.first0), c->sym.wgs[0],
-                        ptr<int>(c->sym.first1), c->sym.wgs[1], ptr<int>(c->sym.base), ptr<DevState>(c->st)))
-        return fail(c, BBMM_EINVAL, "unsupported block width");
-      *shape = VpShape{0, ptr<int>(c->sym.tot), BBMM_SYM_PANEL};
-      *scaleV = 1.0;
-      *addD = 0.0;
-      return BBMM_OK;
-    }
-    if (int ns = mat_split_of(c, ld)) {
-      int rc = ensure_vp(c, ns, ld);
-      if (rc) return rc;
-      if (launch_mm_mat_small(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ns,
-                              ptr<DevState>(c->st), c->khat_pw, c->np, cc))
-        return fail(c, BBMM_EINVAL, "unsupported layout of the stored matrix");
-      *shape = VpShape{ns, nullptr, 1, ns};
-      *scaleV = 1.0;
-      *addD = 0.0;
-      return BBMM_OK;
-    }
-    int rc = ensure_mat_plans(c);
-    if (rc) return rc;
-    int v = (ld == 32) ? 1 : (cc <= 12 ? 2 : 0);
-    rc = ensure_vp(c, c->plan_slots[v], ld);
-    if (rc) return rc;
-    if (launch_mm_mat(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld,
-                      ptr<MmPlan>(c->plan[v]), c->plan_wgs[v], ptr<DevState>(c->st), c->khat_pw, c->np, cc))
-      return fail(c, BBMM_EINVAL, "unsupported block width");
-    *shape = VpShape{0, ptr<int>(c->nseg[v]), v == 1 ? 512 : 1024, c->plan_slots[v]};
     *scaleV = 1.0;
     *addD = 0.0;
-  } else if (uses_digits(c, mode, cc)) {
+    return digits ? stage_mm_words(c, cc, ld, shape, scaleV, addD) : stage_mat64(c, cc, ld, shape);
+  } else if (digits) {
     return stage_otf_dig(c, cc, ld, false, shape, scaleV, addD);
   } else if (mode == BBMM_MODE_ONTHEFLY) {
     return stage_otf64(c, cc, ld, shape, scaleV, addD);
@@ -753,6 +837,10 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
                   {2 * blk, 2 * blk, hist, hist, hist, 2 * BBMM_MAXC + 2}, 6};
     launch_fill_multi0(s, z);
   }
+  if (mode == BBMM_MODE_MATERIALISED && c->khat_built && wants_words(c, cc)) {
+    int rc = stage_build_words(c);
+    if (rc) return rc;
+  }
   int track = uses_digits(c, mode, cc) ? 1 : 0;
   double noise = c->prob.noise;
   int nb_ur = ur_blocks(c, c->n, ld);
@@ -768,7 +856,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     launch_warm_rhs(s, warm, c->n, ld, ptr<double>(c->D4), track, st);
     VpShape ns{0, nullptr, 1};
     double scaleV = 1.0, addD = 0.0;
-    int rc = stage_mm(c, mode, cc, ld, &ns, &scaleV, &addD);
+    int rc = stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
     if (rc) return rc;
     launch_vreduce(s, ptr<double>(c->Vp), ns, ns, nullptr, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
     launch_warm_apply(s, warm, ptr<double>(c->V), c->n, ld, ptr<double>(c->U), ptr<double>(c->R));
@@ -787,6 +875,9 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     else if (mode == BBMM_MODE_ONTHEFLY) {
       scaleV = c->prob.outputscale;
       addD = noise;
+    } else if (track) {
+      scaleV = c->prob.outputscale;
+      addD = c->prob.outputscale + noise;
     }
     launch_set_loop_scalars(s, st, noise, c->prob.tol, scaleV, addD);
   }
@@ -807,7 +898,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
       VpShape ns{0, nullptr, 1};
       double scaleV = 1.0, addD = 0.0;
       if (timed && hipEventRecord(c->ev[2 * j], ls) != hipSuccess) rc = fail(c, BBMM_EHIP, "hipEventRecord failed");
-      if (rc == BBMM_OK) rc = stage_mm(c, mode, cc, ld, &ns, &scaleV, &addD);
+      if (rc == BBMM_OK) rc = stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
       if (rc) break;
       if (timed) {
         if (hipEventRecord(c->ev[2 * j + 1], ls) != hipSuccess) {
@@ -1111,13 +1202,14 @@ int bbmm_destroy(bbmm_ctx* c) {
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
   Buf* bufs[] = {&c->Xa, &c->Xb, &c->Xs, &c->X4, &c->sq, &c->Khat, &c->L, &c->delta, &c->U, &c->R, &c->V,
-                 &c->Z0, &c->D4, &c->Vp, &c->partial, &c->gpartial, &c->alpha, &c->beta, &c->resid, &c->st, &c->sym.pieces, &c->sym.first0, &c->sym.first1, &c->sym.base, &c->sym.tot, &c->otft.pieces, &c->otft.first0,
+                 &c->Z0, &c->D4, &c->Vp, &c->partial, &c->gpartial, &c->alpha, &c->beta, &c->resid, &c->st, &c->sym.pieces, &c->sym.first0, &c->sym.first1, &c->sym.base, &c->sym.tot,
+                 &c->wrd.pieces, &c->wrd.first0, &c->wrd.first1, &c->wrd.base, &c->wrd.tot, &c->otft.pieces, &c->otft.first0,
                  &c->otft.first1, &c->otft.base, &c->otft.tot, &c->tmpA,
                  &c->tmpB, &c->SA, &c->SB, &c->u0v, &c->dkpartial, &c->eig, &c->plan[0], &c->plan[1], &c->plan[2], &c->nseg[0],
                  &c->nseg[1], &c->nseg[2], &c->KUU, &c->Gm, &c->Ginv, &c->Kux, &c->AT, &c->A, &c->qdiag, &c->Tp, &c->T4,
                  &c->sgplan[0], &c->sgplan[1], &c->sgplan[2], &c->sgplan[3], &c->sgnseg[0], &c->sgnseg[1],
                  &c->sgnseg[2], &c->sgnseg[3], &c->Ua, &c->Ub, &c->Us, &c->U4, &c->usq, &c->TU, &c->TW, &c->BU,
-                 &c->BW, &c->dkops, &c->rec, &c->Pb, &c->dcnt};
+                 &c->BW, &c->dkops, &c->rec, &c->Pb, &c->dcnt, &c->words, &c->Xo, &c->sqo};
   for (Buf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
@@ -1144,12 +1236,12 @@ int bbmm_tune(bbmm_ctx* c, const char* key, int64_t value) {
   else if (!strcmp(key, "ur_blocks")) c->ur_blocks_cap = value > 0 ? value : 0;
   else if (!strcmp(key, "khat_sym")) {
     if (value != 0 && value != 1) return fail(c, BBMM_EINVAL, "khat_sym must be 0 or 1");
-    if (c->khat_sym != value) c->khat_built = false;   // the stored matrix has the other layout
+    if (c->khat_sym != value) c->khat_built = c->khat_mem = false;   // the stored matrix has the other layout
     c->khat_sym = value;
   } else if (!strcmp(key, "khat_panel")) {
     if (value > 1 && value % 256 != 0) return fail(c, BBMM_EINVAL, "khat_panel must be 1 or a multiple of 256");
     c->khat_panel = value > 0 ? value : 0;
-    c->khat_built = false;
+    c->khat_built = c->khat_mem = false;
   } else if (!strcmp(key, "zd_blocks")) c->zd_blocks = value > 0 ? std::min<int64_t>(value, 64) : 0;
   else if (!strcmp(key, "sgpr_wgs1")) c->sgpr_wgs[0] = value > 0 ? value : 0;
   else if (!strcmp(key, "sgpr_wgs2")) c->sgpr_wgs[1] = value > 0 ? value : 0;
@@ -1211,6 +1303,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   while (4 * KK < c->d) KK *= 2;
   c->KK = KK;
   c->dp = 4 * KK;
+  c->khat_mem = c->words_built = false;
   c->khat_built = c->chol_done = c->pre_done = c->mbcg_done = false;
   c->sgpr = (in->mode == BBMM_MODE_SGPR);
   c->sgpr_built = false;
@@ -1242,7 +1335,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
       {&c->alpha, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->beta, sizeof(double) * BBMM_MAXP * BBMM_MAXC},
       {&c->resid, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->st, sizeof(DevState)},
       {&c->tmpA, blk}, {&c->tmpB, blk}, {&c->Pb, may_use_digits(c) ? 4 * opx : 0},
-      {&c->dcnt, may_use_digits(c) ? kDigCountWords * sizeof(unsigned) : 0},
+      {&c->dcnt, c->sgpr ? 0 : kDigCountWords * sizeof(unsigned)},
       {&c->SA, np * 64 * sizeof(float)}, {&c->SB, np * 64 * sizeof(float)}, {&c->u0v, np * sizeof(float)},
   };
   for (auto& w : want) {
@@ -1269,7 +1362,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
 int bbmm_build_khat(bbmm_ctx* c) {
   int rc = check_ready(c);
   if (rc) return rc;
-  rc = stage_build_khat(c);
+  rc = stage_build_khat(c, c->khat_sym != 0);
   if (rc) return rc;
   HIPCHK(c, hipGetLastError());
   return BBMM_OK;
@@ -1302,6 +1395,8 @@ int bbmm_khat_block(bbmm_ctx* c, int64_t row0, int64_t nrows, int64_t col0, int6
   int rc = check_ready(c);
   if (rc) return rc;
   if (!c->khat_built) return fail(c, BBMM_EINVAL, "bbmm_build_khat must run first");
+  rc = need_khat(c);
+  if (rc) return rc;
   if (!out || row0 < 0 || col0 < 0 || nrows < 0 || ncols < 0 || row0 + nrows > c->n || col0 + ncols > c->n ||
       nrows * ncols > (int64_t)1 << 31)
     return fail(c, BBMM_EINVAL, "block out of range");
@@ -1319,7 +1414,12 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   int ld = ld_for((int)cc);
   hipStream_t s = c->stream;
   DevState* st = ptr<DevState>(c->st);
-  int digits = uses_digits(c, mode, (int)cc) ? 1 : 0;
+  // (a product with the stored matrix is that of its fp32 entries, unless otf_digits says otherwise)
+  if (mode == BBMM_MODE_MATERIALISED && c->otf_digits == 2 && c->khat_built && wants_words(c, (int)cc)) {
+    rc = stage_build_words(c);
+    if (rc) return rc;
+  }
+  int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || c->otf_digits == 2) ? 1 : 0;
   if (digits) {                                 // dmax, dflag, done, iters_run; the counts
     ZeroSegs z = {{&st->dmax[0], c->dcnt.p}, {2 * BBMM_MAXC + 2, kDigCountWords}, 2};
     launch_fill_multi0(s, z);
@@ -1338,7 +1438,7 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
     if (!rc) rc = stage_otf_dig(c, (int)cc, ld, true, &alt, &scaleV, &addD);
     if (!rc) rc = stage_otf64(c, (int)cc, ld, &ns, &scaleV, &addD);
   } else {
-    rc = stage_mm(c, mode, (int)cc, ld, &ns, &scaleV, &addD);
+    rc = stage_mm(c, mode, (int)cc, ld, digits, &ns, &scaleV, &addD);
   }
   if (rc) return rc;
   launch_vreduce(s, ptr<double>(c->Vp), ns, alt, pick, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
@@ -1659,8 +1759,14 @@ static int solve_call(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out, boo
   hipStream_t s = c->stream;
   int cc = c->t + 1, ld = ld_for(cc);
   if (in->mode == BBMM_MODE_MATERIALISED) {
-    rc = stage_build_khat(c);
+    // A triangle asked for is worth having where the whole matrix is large; up to kMatSmallMaxRows the whole one (at most 256 MB, this
+    // call's own) makes the faster product: 50 iterations at n = 2 500 2.0 ms, 3.5 with words, 4.8 with the triangle.  The fp32
+    // matrix is built only if something asks for it (see need_khat).
+    c->khat_tri = c->khat_sym != 0 && mat_split_of(c, ld) == 0;
+    if (wants_words(c, cc)) rc = stage_build_words(c);
+    if (!rc && !c->words_built) rc = stage_build_khat(c, c->khat_tri);
     if (rc) return rc;
+    c->khat_built = true;
   } else if (in->mode == BBMM_MODE_SGPR) {
     rc = stage_sgpr_build(c);
     if (rc) return rc;

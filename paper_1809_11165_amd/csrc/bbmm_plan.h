@@ -137,7 +137,8 @@ inline const char* lay_out_plan(int rows_p, int cols_p, int ld, int wgs, int slo
 // into runs of equal length for `want` workgroups of its own list (first[kind][w] .. first[kind][w + 1]
 // are workgroup w's pieces).  Output panel s then has cnt[s] column-side partial results (one per
 // piece of panel s) followed by one row-side partial result from every panel right of it:
-// tot[s] = cnt[s] + (S - 1 - s) slots.
+// tot[s] = cnt[s] + (S - 1 - s) slots.  No piece is longer than max_steps.  whole: the first
+// kind takes the blocks on the diagonal too, and there is no second.
 struct TriHost {
   std::vector<MmPiece> pieces;
   std::vector<int> first[2], cnt, tot;
@@ -145,7 +146,7 @@ struct TriHost {
   int max_slots = 0;
 };
 
-inline const char* lay_out_triangle(int np, int W, int want, TriHost& L) {
+inline const char* lay_out_triangle(int np, int W, int want, TriHost& L, int max_steps = 1 << 30, bool whole = false) {
   const int S = (np + W - 1) / W;
   struct Seg {
     int strip, row_begin, steps;
@@ -158,6 +159,7 @@ inline const char* lay_out_triangle(int np, int W, int want, TriHost& L) {
     long long total = 0;
     for (int P = 0; P < S; ++P) {
       Seg g = kind == 0 ? Seg{P, 0, P * W / 16} : Seg{P, P * W, (std::min(np, (P + 1) * W) - P * W) / 16};
+      if (whole) g = Seg{P, 0, kind == 0 ? std::min(np, (P + 1) * W) / 16 : 0};
       if (g.steps > 0) segs.push_back(g);
       total += g.steps;
     }
@@ -172,7 +174,7 @@ inline const char* lay_out_triangle(int np, int W, int want, TriHost& L) {
       long long target = total * (w + 1) / nw;
       while (si < segs.size() && done < target) {
         const Seg& g = segs[si];
-        int take = (int)std::min<long long>(g.steps - off, target - done);
+        int take = (int)std::min<long long>(std::min(g.steps - off, max_steps), target - done);
         L.pieces.push_back(MmPiece{g.strip, g.row_begin + off * 16, g.row_begin + (off + take) * 16,
                                    L.cnt[(size_t)g.strip]++});
         done += take;
@@ -202,7 +204,7 @@ inline const char* lay_out_triangle(int np, int W, int want, TriHost& L) {
 // all there is room for its round.  (Nothing rests on the range check of the buffer instruction, whose
 // scalar offset is not part of what it checks.)
 constexpr int kDigPiece = 1024;
-constexpr int dig_pieces(int KK, int ng) { return KK + ng + 1; }
+constexpr int dig_pieces(int KK, int ng) { return KK > 0 ? KK + ng + 1 : ng; }   // KK = 0: digits only (products from a stored matrix)
 constexpr int dig_copies(int KK, int ng) { return (dig_pieces(KK, ng) + 3) / 4; }   // per wave and record
 constexpr int dig_record_bytes(int KK, int ng) { return dig_pieces(KK, ng) * kDigPiece; }
 constexpr int dig_slot_bytes(int KK, int ng) { return dig_copies(KK, ng) * 4 * kDigPiece; }   // of a record in the ring

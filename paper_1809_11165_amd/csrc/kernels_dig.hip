@@ -24,42 +24,16 @@
 // (3e-7), the rounding of the distance above all.  Product with normal columns, distance from the 64-bit
 // result (this / k_mm_otf): 200,000 points, d = 8, 17 columns 5.3e-7 / 6.3e-7; 50,000, d = 16, 11 columns 3.3e-7 / 4.0e-7;
 // 9,000, d = 4, 16 columns 1.76e-7 / 1.77e-7.
-#include "bbmm_dev.h"
+#include "bbmm_dig.h"
 #include "bbmm_kfun.h"
 
-#include <type_traits>
-
-
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short bf16x8u __attribute__((ext_vector_type(8)));
 
 namespace {
 
-// A[m = lane%16][k = 16 (lane/16) + byte], B[k][n = lane%16]; register r of the result holds
-// C[m = 4 (lane/16) + r][n = lane%16] (layout checked against A B on the device).
-__device__ inline i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 // the same with k = 8 (lane/16) + element, fp32 sums
 __device__ inline f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
-constexpr int kDigits = 0x00808080;
-// Scale of the entries: below 2^31 less the largest balanced lower digits, and a multiple of 2^23, so that it is exact in fp32.
-constexpr float kX = 2055208960.f;
-// Adding kDigits to the scaled entry rounds it to a whole number, to nearest and in the one rounding of the fma (the
-// sum is above 2^23), and is the addition that the digits need.  (Adding 1/2 and truncating rounds twice: entries
-// came out half a unit high, or 4e-8 of themselves below 2^-8; so does any rounding of ties to one side, since the
-// product lies on a grid of halves, quarters, ...)  An entry keeps 23 bits at least from 2^-8 up.
-constexpr float kRound = (float)kDigits;
 
 // kX k / s + kDigits, a whole number, from the scaled squared distance: the fp32 entry that unit_kernel gives, scaled.
 // (The scale in the Matern coefficients would save the product, but overflow from distances of 1e15 on and round
@@ -109,10 +83,6 @@ struct DigEval {
     }
   }
 };
-
-// Scale exponent of a column from the largest high word of |D|: 2^e > max |D|; E == 0: the column is
-// zero (to fp64 underflow) and has no digits.
-__device__ inline int dig_exponent(unsigned hi) { return (int)(hi >> 20) - 1022; }
 
 // Coordinates for the distance MFMA.  |x - x'|^2 = |x|^2 + |x'|^2 - 2 x.x'; the fp32 MFMA of the contraction
 // runs on the vector ALU (measured: 14.4 ns a piece, added to the vector instructions around it), the
@@ -174,20 +144,6 @@ __global__ __launch_bounds__(256) void k_split_x(const float* __restrict__ Xs, i
   Pb[idx] = split_operand<1>(Xs + row * 4 * KK, KK, (int)(row >> 4), t, lane >> 4);
 }
 
-// Whether a block suits the digits, for a caller who sees the product itself.  Fixed point leaves an error of 1.4e-10 of the
-// outputscale times the norm of the block's column in every row of the product: nothing beside the rounding of the entries
-// where the column's entries are of a size, and too much in rows that meet only small entries of K or of the column.
-// So at most n / 128 entries of a column may lie below 2^-12 of its largest power of two, and n / 16384 + 4 below 2^-20
-// (a column of 200 000 normal values has 2e-3 n and about one); everything must be finite.
-__device__ inline bool dig_dense(const DevState* st, const unsigned* __restrict__ counts, int n) {
-  int lane = threadIdx.x & 63, q = lane & (BBMM_MAXC - 1);   // lanes 0..31: small entries, 32..63: tiny ones
-  unsigned sum = 0, hi = st->dmax[q];
-#pragma unroll
-  for (int r = 0; r < kDigCountRows; ++r) sum += counts[r * 2 * BBMM_MAXC + lane];
-  bool bad = hi >= 0x7ff00000u || (hi != 0u && sum > (unsigned)(lane < BBMM_MAXC ? n / 128 : n / 16384 + 4));
-  return !__any(bad) && st->xbad == 0;
-}
-
 // One record per 16-row block holds everything a product needs of it, in 1 KB pieces of 16 bytes per lane
 // (m = lane%16, g = lane/16): KK pieces of coordinates (row m, see split_operand), ng of digits, one of norms (rows 4g..4g+3).
 // Digit piece p: for rows 4g..4g+3 the digit window of right-hand side 2 p + m/8, weight m%8.  One
@@ -202,7 +158,7 @@ __global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, c
   char* R = rec + (size_t)rb * rec_bytes;
   for (int e = threadIdx.x; e < KK * 64; e += 256)
     ((bf16x8u*)R)[e] = split_operand<0>(Xs + (size_t)(rb * 16 + (e & 15)) * 4 * KK, KK, rb, e >> 6, (e >> 4) & 3);
-  if (threadIdx.x < 64)
+  if (KK > 0 && threadIdx.x < 64)
     ((f32x4*)(R + (KK + ng) * 1024))[threadIdx.x] = *(const f32x4*)(sq + rb * 16 + (threadIdx.x >> 4) * 4);
   if ((int)threadIdx.x >= 4 * nrhs) return;
   int g = threadIdx.x / nrhs, q = threadIdx.x % nrhs;
@@ -236,55 +192,10 @@ __global__ __launch_bounds__(256) void k_digits(const double* __restrict__ D4, c
   }
 }
 
-// Accumulators of one 16-column block -> partial results of (K/s) D.  acc[q][r]: lane (jc, g) holds pair
-// 16 q + 4 g + r, i.e. right-hand side 2 q + g / 2, weight 4 (g % 2) + r, of output column jc.  T: LDS,
-// 16 x (LD + 1) doubles of the wave.  A block column with a non-finite entry gets what the sum of K D is
-// for K > 0; an X that is none for the digits (xbad) makes everything NaN.
-template <int NG, int LD>
-__device__ __forceinline__ void dig_store(const i32x4 (&acc)[NG], double* __restrict__ T, int jc, int g,
-                                          const DevState* __restrict__ st, double* __restrict__ vrow) {
-  constexpr int TP = LD + 1;
-#pragma unroll
-  for (int q = 0; q < LD / 2; ++q) {
-    double t = 0.0;
-    if (q < NG) {
-      const i32x4& a = acc[q < NG ? q : 0];
-      t = (double)a[0] + 0x1p-8 * (double)a[1] + 0x1p-16 * (double)a[2] + 0x1p-24 * (double)a[3];
-      if (g & 1) t *= 0x1p-32;
-      t += __shfl_xor(t, 16, 64);
-    }
-    if (!(g & 1)) T[jc * TP + 2 * q + (g >> 1)] = t;
-  }
-  __builtin_amdgcn_wave_barrier();
-  int xbad = st->xbad;
-#pragma unroll
-  for (int nq = 0; nq < LD / 16; ++nq) {
-    f64x4 v;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      int q = 16 * nq + 4 * r + g;
-      unsigned hi = st->dmax[q];
-      double x = (hi < 0x00100000u) ? 0.0 : ldexp(T[jc * TP + q] * (1.0 / (double)kX), dig_exponent(hi) + 18);
-      if (hi >= 0x7ff00000u) {
-        int f = st->dflag[q];
-        x = (f & 4) || f == 3 ? __builtin_nan("") : (f == 1 ? __builtin_inf() : -__builtin_inf());
-      }
-      if (xbad) x = __builtin_nan("");
-      v[r] = x;
-    }
-    *(f64x4*)(vrow + nq * 16 + g * 4) = v;
-  }
-  __builtin_amdgcn_wave_barrier();
-}
-
 // A workgroup's ring of records in LDS, shared by its four waves and copied straight from global memory (a
 // wave copies every fourth piece; the last round may run past the record, hence whole multiples
 // of 4 KB here, see bbmm_plan::dig_copy_offset).  In step k of a chunk record k - 1 feeds the digit MFMAs, k + 1 the distances, and
 // k + kRing - 2 is requested, into the place that record k - 2 has left.
-typedef __attribute__((address_space(3))) char lds_char;
-typedef const __attribute__((address_space(3))) i32x4* lds_i32x4;
-typedef const __attribute__((address_space(3))) f32x4* lds_f32x4;
-
 template <int KK, int NG>
 struct DigRec {
   static constexpr int kPieces = bbmm_plan::dig_pieces(KK, NG);
@@ -293,12 +204,6 @@ struct DigRec {
   static constexpr int kSlot = bbmm_plan::dig_slot_bytes(KK, NG);      // in the ring
   static constexpr int kRing = bbmm_plan::dig_ring(KK, NG);
 };
-
-// s_waitcnt vmcnt(N) alone
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
 
 // Workgroup: 4 NJ column blocks (NJ per wave), a chunk of row blocks (an even number, at most
 // kDigMaxBlocks: an accumulator grows by at most 2^20 per row block).  Partial sums of (K/s) D as
@@ -506,7 +411,7 @@ __global__ __launch_bounds__(256, 2) void k_mm_otf_dig(const char* __restrict__ 
 #pragma unroll
   for (int jb = 0; jb < NJ; ++jb)
     if (jb0 + jb < nblk)
-      dig_store<NG, LD>(acc[jb], T, jc, g, st, vout + (size_t)((jb0 + jb) * 16 + jc) * ld);
+      dig_store<NG, LD>(acc[jb], 1.0 / (double)kX, T, jc, g, st, vout + (size_t)((jb0 + jb) * 16 + jc) * ld);
 #endif
 }
 
