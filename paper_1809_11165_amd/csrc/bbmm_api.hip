@@ -773,7 +773,7 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, int digits, VpShape* shape, 
 
 int stage_pivchol(bbmm_ctx* c) {
   hipStream_t s = c->stream;
-  int nb = vec_blocks(c->n, 16);
+  int nb = std::min(kMaxVecBlocks, (c->n + BBMM_VEC_THREADS - 1) / BBMM_VEC_THREADS);   // a row per thread, no candidates without rows
   if (c->kp > 0) launch_fill_f64(s, ptr<double>(c->L), (size_t)c->np * c->kp, 0.0);
   // pivot candidates alternate between two buffers (a step reads one and writes the other)
   double* arg[2] = {ptr<double>(c->partial), ptr<double>(c->partial) + 2 * kMaxVecBlocks};
@@ -1350,7 +1350,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
 
   hipStream_t s = c->stream;
   launch_fill_bytes0(s, c->st.p, sizeof(DevState));
-  launch_colmean(s, in->X, c->n, c->d, ptr<DevState>(c->st), ptr<double>(c->partial), ptr<double>(c->gpartial));
+  launch_colmean(s, in->X, c->n, c->d, ptr<DevState>(c->st), ptr<double>(c->partial));
   launch_prep_x(s, in->X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st), ptr<float>(c->Xa),
                 ptr<float>(c->Xb), ptr<float>(c->Xs), ptr<float>(c->X4), ptr<float>(c->sq));
   if (may_use_digits(c)) launch_split_x(s, ptr<float>(c->Xs), c->np, c->KK, c->Pb.p);

@@ -79,8 +79,7 @@ struct ZeroSegs {
   int n;
 };
 void launch_fill_multi0(hipStream_t s, const ZeroSegs& z);
-void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, double* partial,
-                    double* gpartial);
+void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, double* partial);
 void launch_prep_x(hipStream_t s, const float* X, int n, int d, int np, int KK, HypArgs hyp,
                    DevState* st, float* Xa, float* Xb, float* Xs, float* X4, float* sq);
 // track != 0: leave the columns' magnitudes in st->dmax / st->dflag (zero beforehand), as launch_digits needs

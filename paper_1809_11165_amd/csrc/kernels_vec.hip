@@ -57,57 +57,9 @@ __device__ inline bool finite_d(double x) { return x == x && fabs(x) < 1.0e300; 
 // lane/16, 4 + lane/16, 8 + lane/16, 12 + lane/16, stored contiguously.
 __device__ inline int perm16(int q) { return (q & ~15) | ((q & 3) << 2) | ((q >> 2) & 3); }
 
-// Deterministic two-level sum of per-block partial vectors (the latency of a single block adding
+// Per-block partial sums are added in groups of this many blocks, then over the groups (the latency of a single block adding
 // hundreds of partial rows one after the other would dominate these small kernels).
-// Every block has written partial[blockIdx.x * stride + e], e < E.  Blocks are grouped by
-// RGROUP: the last block of a group to arrive adds its group's rows into gpartial[group], the
-// last group to finish adds the group rows into tot (LDS).  Returns true, in every thread, only
-// in that final block.  counters: 1 + number of groups tickets, all zero on entry, reset on exit.
 constexpr int RGROUP = 16;
-__device__ inline bool reduce_blocks(const double* __restrict__ partial, double* __restrict__ gpartial,
-                                     size_t stride, int E, unsigned* counters, double* tot) {
-  __shared__ int flag;
-  int nb = gridDim.x, ng = (nb + RGROUP - 1) / RGROUP;
-  int grp = blockIdx.x / RGROUP;
-  int gsize = min(RGROUP, nb - grp * RGROUP);
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) flag = (atomicAdd(&counters[1 + grp], 1u) == (unsigned)(gsize - 1));
-  __syncthreads();
-  if (!flag) return false;
-  __threadfence();
-  const double* base = partial + (size_t)grp * RGROUP * stride;
-  for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    double v[RGROUP];
-#pragma unroll
-    for (int b = 0; b < RGROUP; ++b) v[b] = (b < gsize) ? base[(size_t)b * stride + e] : 0.0;
-    double s = 0.0;
-#pragma unroll
-    for (int b = 0; b < RGROUP; ++b) s += v[b];
-    gpartial[(size_t)grp * stride + e] = s;
-  }
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) flag = (atomicAdd(&counters[0], 1u) == (unsigned)(ng - 1));
-  __syncthreads();
-  if (!flag) return false;
-  __threadfence();
-  for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int g = 0;
-    for (; g + 3 < ng; g += 4) {
-      s0 += gpartial[(size_t)g * stride + e];
-      s1 += gpartial[(size_t)(g + 1) * stride + e];
-      s2 += gpartial[(size_t)(g + 2) * stride + e];
-      s3 += gpartial[(size_t)(g + 3) * stride + e];
-    }
-    for (; g < ng; ++g) s0 += gpartial[(size_t)g * stride + e];
-    tot[e] = (s0 + s1) + (s2 + s3);
-  }
-  __syncthreads();
-  if ((int)threadIdx.x <= ng) counters[threadIdx.x] = 0u;
-  return true;
-}
 
 // ------------------------------------------------------------------ fills ----
 __global__ void k_fill_f64(double* p, size_t count, double v) {
@@ -135,31 +87,62 @@ __global__ void k_fill_multi0(ZeroSegs z) {
 }
 
 // ------------------------------------------------------- input preparation ---
-// Column means of X (fp64): per-block partial sums, last block finishes.
-__global__ __launch_bounds__(VT) void k_colmean(const float* __restrict__ X, int n, int d,
-                                                 DevState* st, double* partial, double* gpartial) {
+// Column means of X (fp64): per-block partial sums, one wave per dimension, then one block (two launches: the device-wide fences
+// of one launch that finishes itself, and a barrier per level and dimension, cost more: n = 50 000, d = 16 40 -> 24 us).
+__global__ __launch_bounds__(VT) void k_colmean(const float* __restrict__ X, int n, int d, double* __restrict__ partial) {
   __shared__ double red[VT];
-  __shared__ double tot[BBMM_MAXD];
   // thread -> (row slot, dim): consecutive threads read consecutive floats of X
   size_t total = (size_t)n * d;
   size_t start = (size_t)blockIdx.x * VT + threadIdx.x;
   size_t stride = (size_t)gridDim.x * VT;
   // stride is kept a multiple of d so that a thread always sees the same dimension
-  int dim = (int)(start % d);
   double acc = 0.0;
+#pragma unroll 8
   for (size_t e = start; e < total; e += stride) acc += (double)X[e];
-  for (int dd = 0; dd < d; ++dd) {
-    red[threadIdx.x] = (dim == dd) ? acc : 0.0;
-    __syncthreads();
-    for (int w = VT / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-      __syncthreads();
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  int lane = threadIdx.x & 63;
+  int dim0 = (int)(((size_t)blockIdx.x * VT + lane) % d), s64 = 64 % d;
+  for (int dd = threadIdx.x >> 6; dd < d; dd += VT / 64) {
+    double v[VT / 64];
+    int dim = dim0;
+#pragma unroll
+    for (int u = 0; u < VT / 64; ++u) {
+      v[u] = dim == dd ? red[64 * u + lane] : 0.0;
+      dim += s64;
+      if (dim >= d) dim -= d;
     }
-    if (threadIdx.x == 0) partial[(size_t)blockIdx.x * BBMM_MAXD + dd] = red[0];
-    __syncthreads();
+    double t = (v[0] + v[2]) + (v[1] + v[3]);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) t += __shfl_down(t, w, 64);
+    if (lane == 0) partial[(size_t)blockIdx.x * BBMM_MAXD + dd] = t;
   }
-  if (!reduce_blocks(partial, gpartial, BBMM_MAXD, d, st->counter[5], tot)) return;
-  if ((int)threadIdx.x < d) st->xmean[threadIdx.x] = tot[threadIdx.x] / (double)n;
+}
+
+__global__ __launch_bounds__(1024) void k_colmean_fin(const double* __restrict__ partial, int nb, int n, int d, DevState* st) {
+  __shared__ double grp[8][BBMM_MAXD];
+  int ng = (nb + RGROUP - 1) / RGROUP;                       // at most 8: nb < 64 + d
+  for (int e = threadIdx.x; e < ng * d; e += 1024) {
+    int g = e / d, dd = e % d;
+    double v[RGROUP], s = 0.0;
+#pragma unroll
+    for (int b = 0; b < RGROUP; ++b) v[b] = g * RGROUP + b < nb ? partial[(size_t)(g * RGROUP + b) * BBMM_MAXD + dd] : 0.0;
+#pragma unroll
+    for (int b = 0; b < RGROUP; ++b) s += v[b];
+    grp[g][dd] = s;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x >= d) return;
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  int g = 0;
+  for (; g + 3 < ng; g += 4) {
+    s0 += grp[g][threadIdx.x];
+    s1 += grp[g + 1][threadIdx.x];
+    s2 += grp[g + 2][threadIdx.x];
+    s3 += grp[g + 3][threadIdx.x];
+  }
+  for (; g < ng; ++g) s0 += grp[g][threadIdx.x];
+  st->xmean[threadIdx.x] = ((s0 + s1) + (s2 + s3)) / (double)n;
 }
 
 // Scaled, centred copies of X in the layouts the tile kernels read:
@@ -321,6 +304,13 @@ __global__ void k_warm_apply(const float* __restrict__ u_init, const double* __r
 }
 
 // ------------------------------------------------------- pivoted Cholesky ----
+__device__ inline double kernel_of_rho2(double rho2, const HypArgs& hyp) {
+  if (hyp.kernel == 0) return hyp.outputscale * exp(-0.5 * rho2);
+  double rho = sqrt(rho2);
+  const double s5 = 2.23606797749978969;
+  return hyp.outputscale * (1.0 + s5 * rho + (5.0 / 3.0) * rho2) * exp(-s5 * rho);
+}
+
 __device__ inline double kernel_value_f64(const float* __restrict__ X, int a, int b,
                                           const HypArgs& hyp) {
   double rho2 = 0.0;
@@ -329,10 +319,7 @@ __device__ inline double kernel_value_f64(const float* __restrict__ X, int a, in
                 hyp.inv_ls[dim];
     rho2 += df * df;
   }
-  if (hyp.kernel == 0) return hyp.outputscale * exp(-0.5 * rho2);
-  double rho = sqrt(rho2);
-  const double s5 = 2.23606797749978969;
-  return hyp.outputscale * (1.0 + s5 * rho + (5.0 / 3.0) * rho2) * exp(-s5 * rho);
+  return kernel_of_rho2(rho2, hyp);
 }
 
 // Block-level argmax of (value, lowest index on ties); result valid in every thread.  Shuffles inside a
@@ -422,9 +409,13 @@ __global__ __launch_bounds__(VT) void k_pc_init(int n, HypArgs hyp, double* __re
 // step (and every later one, which sees the same candidates) does nothing.
 // The pivot's row of the matrix is evaluated in fp64 from X, or read from row_in[i * row_ld]
 // when the caller has formed it (a covariance that is not a plain kernel matrix of X).
+// A step is a chain of three memory round trips (candidates, the pivot's rows, nothing else): a thread's own rows of X
+// and L are requested before the first, and the pivot's go through LDS (n = 50 000, d = 16, k = 20: 9.4 -> 9.0 us, and
+// no candidates of blocks without rows).
+template <int DP>
 __global__ __launch_bounds__(VT) void k_pc_step(const float* __restrict__ X, int n, int m, int kp,
                                                  HypArgs hyp, double* __restrict__ delta,
-                                                 double* __restrict__ L, DevState* st,
+                                                 double* L, DevState* st,
                                                  const double* __restrict__ arg_in,
                                                  double* __restrict__ arg_out, double stop_thresh,
                                                  const double* __restrict__ row_in, int row_ld,
@@ -432,6 +423,31 @@ __global__ __launch_bounds__(VT) void k_pc_step(const float* __restrict__ X, int
   __shared__ double sval[VT];
   __shared__ int sidx[VT];
   __shared__ double lpiv[BBMM_MAXK];
+  __shared__ double xpiv[BBMM_MAXD];
+  constexpr int QD = DP / 4, QL = BBMM_MAXK / 4;
+  double di, row = 0.0, lr[BBMM_MAXK];
+  float xr[DP];
+  auto request = [&](int i) {
+    di = delta[i];
+    if (row_in) {
+      row = row_in[(size_t)i * row_ld];
+    } else {
+#pragma unroll
+      for (int q = 0; q < QD; ++q)
+        if (4 * q < hyp.d) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) xr[4 * q + e] = X[(size_t)i * hyp.d + min(4 * q + e, hyp.d - 1)];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < QL; ++q)
+      if (4 * q < m) {                     // (kp is a multiple of 8; the columns from m on are zero so far)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lr[4 * q + e] = L[(size_t)i * kp + 4 * q + e];
+      }
+  };
+  int i0 = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i0 < n) request(i0);
   double dpiv;
   int piv;
   reduce_argmax(arg_in, gridDim.x, sval, sidx, &dpiv, &piv);
@@ -452,13 +468,15 @@ __global__ __launch_bounds__(VT) void k_pc_step(const float* __restrict__ X, int
     st->pivdmax[m] = dpiv;
     st->rank = m + 1;
   }
+  if ((int)threadIdx.x < m) lpiv[threadIdx.x] = L[(size_t)piv * kp + threadIdx.x];
+  int xd = (int)threadIdx.x - 64;          // (another wave's threads)
+  if (!row_in && xd >= 0 && xd < hyp.d) xpiv[xd] = (double)X[(size_t)piv * hyp.d + xd];
   double root = sqrt(dpiv);
-  if ((int)threadIdx.x < m) lpiv[threadIdx.x] = (double)L[(size_t)piv * kp + threadIdx.x];
   __syncthreads();
   double bv = -1.0e300;
   int bi = 0x7fffffff;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    double di = delta[i];
+  for (int i = i0; i < n; i += gridDim.x * blockDim.x) {
+    if (i != i0) request(i);
     double lval;
     if (i == piv) {
       lval = root;
@@ -466,8 +484,20 @@ __global__ __launch_bounds__(VT) void k_pc_step(const float* __restrict__ X, int
     } else if (di < 0.0) {
       lval = 0.0;                  // already picked
     } else {
-      double kv = row_in ? row_in[(size_t)i * row_ld] : kernel_value_f64(X, piv, i, hyp);
-      for (int j = 0; j < m; ++j) kv -= lpiv[j] * (double)L[(size_t)i * kp + j];
+      double kv = row;
+      if (!row_in) {               // kernel_value_f64 of the two rows
+        double rho2 = 0.0;
+#pragma unroll
+        for (int dim = 0; dim < DP; ++dim)
+          if (dim < hyp.d) {
+            double df = (xpiv[dim] - (double)xr[dim]) * hyp.inv_ls[dim];
+            rho2 += df * df;
+          }
+        kv = kernel_of_rho2(rho2, hyp);
+      }
+#pragma unroll
+      for (int j = 0; j < BBMM_MAXK; ++j)
+        if (j < m) kv -= lpiv[j] * lr[j];
       lval = kv / root;
       di = di - lval * lval;
       if (di < 0.0) di = 0.0;
@@ -644,105 +674,189 @@ __global__ __launch_bounds__(VT) void k_cross_finish(const double* __restrict__ 
 }
 
 // ---------------------------------------------- capacitance matrix, log|P| ---
-// C = sigma^2 I + L^T L (k x k, fp64), Cholesky factor G, log|P| = log|C| + (n-k) log sigma^2.
-__global__ __launch_bounds__(VT) void k_pre_setup(const double* __restrict__ L, int n, int kp,
-                                                   double noise, DevState* st, double* partial,
-                                                   double* gpartial) {
-  int k = st->rank;
-  int npairs = k * k;
-  // each thread owns pairs e = tid, tid + VT, ... (at most 4 for k <= 32)
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  int rows_per_block = (n + gridDim.x - 1) / gridDim.x;
-  int r0 = blockIdx.x * rows_per_block;
-  int r1 = min(n, r0 + rows_per_block);
-  for (int i = r0; i < r1; ++i) {
-    const double* li = L + (size_t)i * kp;
+// C = sigma^2 I + L^T L (k x k, fp64), Cholesky factor G, log|P| = log|C| + (n-k) log sigma^2, in three launches: sums over the
+// rows of a block, over 16 blocks, and the rest in one wave.  (One launch whose last blocks finish the sums and whose one
+// thread factors C: n = 50 000, k = 20 187 us; now 11 + 5 + 19.)
+// Entry e of a partial sum is the e-th pair (a, c), c <= a, of the lower triangle.
+constexpr int kPairs = BBMM_MAXK * (BBMM_MAXK + 1) / 2;
+constexpr int kGramRows = 128;                               // rows staged in LDS at a time (a block has 98 at n = 50 000)
+
+__device__ inline int pair_row(int e) {
+  int a = 0;
+  while ((a + 1) * (a + 2) / 2 <= e) ++a;
+  return a;
+}
+
+__global__ __launch_bounds__(VT) void k_pre_gram(const double* __restrict__ L, int n, int kp, const DevState* __restrict__ st,
+                                                  double* __restrict__ partial) {
+  __shared__ double rows[kGramRows * BBMM_MAXK];
+  int k = st->rank, npairs = k * (k + 1) / 2;
+  constexpr int NU = (kPairs + VT - 1) / VT;
+  double acc[NU];
+  int pa[NU], pc[NU];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      int e = threadIdx.x + u * VT;
-      if (e < npairs) acc[u] += (double)li[e / k] * (double)li[e % k];
-    }
+  for (int u = 0; u < NU; ++u) {
+    acc[u] = 0.0;
+    pa[u] = pair_row(min((int)threadIdx.x + u * VT, kPairs - 1));
+    pc[u] = min((int)threadIdx.x + u * VT, kPairs - 1) - pa[u] * (pa[u] + 1) / 2;
+  }
+  int per = (n + gridDim.x - 1) / gridDim.x;
+  int r0 = blockIdx.x * per, r1 = min(n, r0 + per);
+  for (int i0 = r0; i0 < r1; i0 += kGramRows) {
+    int nr = min(kGramRows, r1 - i0);
+    __syncthreads();
+    for (int e = threadIdx.x; e < nr * kp; e += VT) rows[e] = L[(size_t)i0 * kp + e];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if ((int)threadIdx.x + u * VT < npairs)
+#pragma unroll 8
+        for (int i = 0; i < nr; ++i) acc[u] += rows[i * kp + pa[u]] * rows[i * kp + pc[u]];
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < NU; ++u) {
     int e = threadIdx.x + u * VT;
-    if (e < npairs) partial[(size_t)blockIdx.x * (BBMM_MAXK * BBMM_MAXK) + e] = acc[u];
+    if (e < npairs) partial[(size_t)blockIdx.x * kPairs + e] = acc[u];
   }
-  __shared__ double C[BBMM_MAXK * BBMM_MAXK];
-  __shared__ double tot[BBMM_MAXK * BBMM_MAXK];
-  if (!reduce_blocks(partial, gpartial, BBMM_MAXK * BBMM_MAXK, npairs, st->counter[1], tot)) return;
+}
+
+__global__ __launch_bounds__(VT) void k_pre_group(const double* __restrict__ partial, int nb, const DevState* __restrict__ st,
+                                                   double* __restrict__ gpartial) {
+  int k = st->rank, npairs = k * (k + 1) / 2;
+  const double* base = partial + (size_t)blockIdx.x * RGROUP * kPairs;
+  int gsize = min(RGROUP, nb - (int)blockIdx.x * RGROUP);
   for (int e = threadIdx.x; e < npairs; e += VT) {
-    int a = e / k, c = e % k;
-    C[a * BBMM_MAXK + c] = tot[e] + (a == c ? noise : 0.0);
+    double v[RGROUP];
+#pragma unroll
+    for (int b = 0; b < RGROUP; ++b) v[b] = (b < gsize) ? base[(size_t)b * kPairs + e] : 0.0;
+    double s = 0.0;
+#pragma unroll
+    for (int b = 0; b < RGROUP; ++b) s += v[b];
+    gpartial[(size_t)blockIdx.x * kPairs + e] = s;
+  }
+}
+
+// v of lane `l` (the same in all lanes)
+__device__ inline double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// One block adds the ng group sums; its first wave then factors C with row a in the registers of lane a (right-looking: every entry
+// takes its subtractions in the order of the columns) and forms G^{-1} with column j in lane j, by forward substitution on the unit
+// vectors.  The iteration applies C^{-1} = G^{-T} G^{-1} as two small dense products instead of serial substitutions
+// (cond(G) = sqrt(cond(C)) <= sqrt(1 + |L|^2 / sigma^2): harmless in fp64).
+template <int KP>
+__global__ __launch_bounds__(VT) void k_pre_fin(const double* __restrict__ gpartial, int ng, int n, double noise, DevState* st) {
+  __shared__ double tot[kPairs];
+  int k = st->rank, npairs = k * (k + 1) / 2;
+  for (int e = threadIdx.x; e < npairs; e += VT) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int g = 0;
+#pragma unroll 4
+    for (; g + 3 < ng; g += 4) {
+      s0 += gpartial[(size_t)g * kPairs + e];
+      s1 += gpartial[(size_t)(g + 1) * kPairs + e];
+      s2 += gpartial[(size_t)(g + 2) * kPairs + e];
+      s3 += gpartial[(size_t)(g + 3) * kPairs + e];
+    }
+    for (; g < ng; ++g) s0 += gpartial[(size_t)g * kPairs + e];
+    tot[e] = (s0 + s1) + (s2 + s3);
+  }
+  for (int e = threadIdx.x; e < BBMM_MAXK * BBMM_MAXK; e += VT) {
+    int a = e / BBMM_MAXK, c = e % BBMM_MAXK;
+    if (a >= k || c > a) st->G[e] = st->Ginv[e] = 0.0;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    // in-place lower Cholesky factorisation of C in LDS
-    double logdet = 0.0;
-    int bad = 0;
-    for (int a = 0; a < k; ++a) {
-      for (int c = 0; c <= a; ++c) {
-        double s = C[a * BBMM_MAXK + c];
-        for (int j = 0; j < c; ++j) s -= C[a * BBMM_MAXK + j] * C[c * BBMM_MAXK + j];
-        if (a == c) {
-          if (!(s > 0.0) || !finite_d(s)) {
-            bad = 1;
-            s = 1.0;
-          }
-          double g = sqrt(s);
-          C[a * BBMM_MAXK + a] = g;
-          logdet += 2.0 * log(g);
-        } else {
-          C[a * BBMM_MAXK + c] = s / C[c * BBMM_MAXK + c];
-        }
+  if (threadIdx.x >= 64) return;
+  int lane = threadIdx.x;
+  constexpr int R = KP > 0 ? KP : 1;
+  double row[R], col[R];
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    bool in = lane < k && c <= lane;
+    row[c] = in ? tot[lane * (lane + 1) / 2 + c] : 0.0;
+    if (lane == c) row[c] += noise;
+    col[c] = 0.0;
+  }
+  double diag = 1.0;                       // of this lane's row
+  int bad = 0;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    if (j < k) {
+      double s = lane_value(row[j], j);
+      if (!(s > 0.0) || !finite_d(s)) {
+        bad = 1;
+        s = 1.0;
       }
+      double g = sqrt(s);
+      if (lane == j) diag = g;
+      row[j] = lane == j ? g : row[j] / g;
+#pragma unroll
+      for (int c = j + 1; c < R; ++c)
+        if (c < k) row[c] -= row[j] * lane_value(row[j], c);
     }
+  }
+  double logdet = 0.0, lg = log(diag);
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+    if (j < k) logdet += 2.0 * lane_value(lg, j);
+  if (lane == 0) {
     st->logdetP = logdet + (double)(n - k) * log(noise);
     if (bad) st->status = 3;
   }
-  __syncthreads();
-  // G^{-1}, one column per thread by forward substitution on the unit vectors; the iteration
-  // applies C^{-1} = G^{-T} G^{-1} as two small dense products instead of serial substitutions
-  // (cond(G) = sqrt(cond(C)) <= sqrt(1 + |L|^2 / sigma^2): harmless in fp64).
-  for (int e = threadIdx.x; e < BBMM_MAXK * BBMM_MAXK; e += VT) tot[e] = 0.0;
-  __syncthreads();
-  if ((int)threadIdx.x < k) {
-    int j = threadIdx.x;
-    tot[j * BBMM_MAXK + j] = 1.0 / C[j * BBMM_MAXK + j];
-    for (int i = j + 1; i < k; ++i) {
-      double sacc = 0.0;
-      for (int a = j; a < i; ++a) sacc += C[i * BBMM_MAXK + a] * tot[a * BBMM_MAXK + j];
-      tot[i * BBMM_MAXK + j] = -sacc / C[i * BBMM_MAXK + i];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (i < k) {
+      double g = lane_value(row[i], i), sacc = 0.0;
+#pragma unroll
+      for (int a = 0; a < i; ++a) sacc += lane_value(row[a], i) * col[a];      // (col[a] is zero above the diagonal)
+      col[i] = lane == i ? 1.0 / g : (lane < i ? -sacc / g : 0.0);
     }
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < BBMM_MAXK * BBMM_MAXK; e += VT) {
-    int a = e / BBMM_MAXK, c = e % BBMM_MAXK;
-    bool low = a < k && c <= a;
-    st->G[e] = low ? C[e] : 0.0;
-    st->Ginv[e] = low ? tot[e] : 0.0;
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    if (lane < k && c <= lane) st->G[lane * BBMM_MAXK + c] = row[c];
+    if (lane < k && lane <= c && c < k) st->Ginv[c * BBMM_MAXK + lane] = col[c];
   }
 }
 
 // -------------------------------------------------------------- probes -------
 // R[:,0] = y,  R[:,1+i] = L E1[:,i] + sigma E2[:,i]   (row-major, stride ld, zero padded)
-__global__ void k_probes(const float* __restrict__ y, const float* __restrict__ E1,
+// A thread keeps its column of E1 and takes every PR-th row: the loads of a row are what bounds this (a thread per entry, each with
+// its own 2 k loads: n = 50 000, k = 20, t = 10 18.6 us; now 14).
+constexpr int kProbeRows = 32;             // rows per block
+template <int KP>
+__global__ __launch_bounds__(256) void k_probes(const float* __restrict__ y, const float* __restrict__ E1,
                          const float* __restrict__ E2, const double* __restrict__ L, int n, int t,
                          int kp, int ld, double sigma, const DevState* __restrict__ st,
                          double* __restrict__ R) {
-  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)n * ld) return;
-  int i = (int)(idx / ld), q = (int)(idx % ld);
+  int q = threadIdx.x % ld, step = 256 / ld, i0 = blockIdx.x * kProbeRows;
   int k = st->rank;
-  double v = 0.0;
-  if (q == 0) {
-    v = (double)y[i];
-  } else if (q <= t) {
-    double s = sigma * (double)E2[(size_t)i * t + (q - 1)];
-    for (int m = 0; m < k; ++m) s += (double)L[(size_t)i * kp + m] * (double)E1[(size_t)m * t + (q - 1)];
-    v = s;
+  bool probe = q >= 1 && q <= t;
+  constexpr int KR = KP > 0 ? KP : 1;
+  float e1[KR];
+#pragma unroll
+  for (int m = 0; m < KP; ++m) e1[m] = (probe && m < k) ? E1[(size_t)m * t + (q - 1)] : 0.f;
+#pragma unroll 2
+  for (int i = i0 + (int)threadIdx.x / ld; i < min(n, i0 + kProbeRows); i += step) {
+    double v = 0.0;
+    if (q == 0) {
+      v = (double)y[i];
+    } else if (probe) {
+      double l[KR];
+#pragma unroll
+      for (int m = 0; m < KP; m += 2) {
+        double2 w = *(const double2*)(L + (size_t)i * kp + m);
+        l[m] = w.x;
+        l[m + 1] = w.y;
+      }
+      v = sigma * (double)E2[(size_t)i * t + (q - 1)];
+#pragma unroll
+      for (int m = 0; m < KP; ++m)
+        if (m < k) v += l[m] * (double)e1[m];
+    }
+    R[(size_t)i * ld + q] = v;
   }
-  R[idx] = v;
 }
 
 // ------------------------------------------------ fused mBCG vector updates --
@@ -1662,12 +1776,12 @@ void launch_fill_multi0(hipStream_t s, const ZeroSegs& z) {
   k_fill_multi0<<<nb, 256, 0, s>>>(z);
 }
 
-void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, double* partial,
-                    double* gpartial) {
+void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, double* partial) {
   // grid stride must be a multiple of d: use nb blocks with nb * 256 % d == 0
   int nb = 64;
   while (((size_t)nb * VT) % d != 0) ++nb;      // d <= 64, terminates within d steps
-  k_colmean<<<nb, VT, 0, s>>>(X, n, d, st, partial, gpartial);
+  k_colmean<<<nb, VT, 0, s>>>(X, n, d, partial);
+  k_colmean_fin<<<1, 1024, 0, s>>>(partial, nb, n, d, st);
 }
 
 void launch_prep_x(hipStream_t s, const float* X, int n, int d, int np, int KK, HypArgs hyp,
@@ -1727,19 +1841,39 @@ void launch_pc_step(hipStream_t s, const float* X, int n, int m, int kp, HypArgs
                     double* L, DevState* st, const double* arg_in, double* arg_out, int nblocks,
                     const double* row_in, int row_ld, int forced, int next_forced) {
   double thresh = 1e-12 * hyp.outputscale;
-  k_pc_step<<<nblocks, VT, 0, s>>>(X, n, m, kp, hyp, delta, L, st, arg_in, arg_out, thresh, row_in, row_ld,
-                                   forced, next_forced);
+#define PC_STEP(DP) \
+  k_pc_step<DP><<<nblocks, VT, 0, s>>>(X, n, m, kp, hyp, delta, L, st, arg_in, arg_out, thresh, row_in, row_ld, forced, next_forced)
+  if (hyp.d <= 4) PC_STEP(4);
+  else if (hyp.d <= 8) PC_STEP(8);
+  else if (hyp.d <= 16) PC_STEP(16);
+  else if (hyp.d <= 32) PC_STEP(32);
+  else PC_STEP(64);
+#undef PC_STEP
 }
+
+#define DISPATCH_KP_T(KERNEL, kp, grid, threads, ...)                        \
+  switch (kp) {                                                             \
+    case 0: KERNEL<0><<<grid, threads, 0, s>>>(__VA_ARGS__); break;         \
+    case 8: KERNEL<8><<<grid, threads, 0, s>>>(__VA_ARGS__); break;         \
+    case 16: KERNEL<16><<<grid, threads, 0, s>>>(__VA_ARGS__); break;       \
+    case 24: KERNEL<24><<<grid, threads, 0, s>>>(__VA_ARGS__); break;       \
+    default: KERNEL<32><<<grid, threads, 0, s>>>(__VA_ARGS__); break;       \
+  }
 
 void launch_pre_setup(hipStream_t s, const double* L, int n, int k, int kp, double noise, DevState* st,
                       double* partial, double* gpartial, int nblocks) {
   (void)k;
-  k_pre_setup<<<nblocks, VT, 0, s>>>(L, n, kp, noise, st, partial, gpartial);
+  int groups = (nblocks + RGROUP - 1) / RGROUP;
+  if (kp > 0) {
+    k_pre_gram<<<nblocks, VT, 0, s>>>(L, n, kp, st, partial);
+    k_pre_group<<<groups, VT, 0, s>>>(partial, nblocks, st, gpartial);
+  }
+  DISPATCH_KP_T(k_pre_fin, kp, 1, VT, gpartial, groups, n, noise, st)
 }
 
 void launch_probes(hipStream_t s, const float* y, const float* E1, const float* E2, const double* L,
                    int n, int t, int kp, int ld, double noise, const DevState* st, double* R) {
-  k_probes<<<blocks_for((size_t)n * ld, 256), 256, 0, s>>>(y, E1, E2, L, n, t, kp, ld, sqrt(noise), st, R);
+  DISPATCH_KP_T(k_probes, kp, (n + kProbeRows - 1) / kProbeRows, 256, y, E1, E2, L, n, t, kp, ld, sqrt(noise), st, R)
 }
 
 __global__ void k_set_loop_scalars(DevState* st, double noise, double tol, double scaleV, double addD) {
@@ -1764,14 +1898,6 @@ void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, in
     k_dv<3, 8><<<nblocks, VT, 0, s>>>(Vp, shape, n, np, ld, scaleV, addD, D4, V, st, partial_dv);
 }
 
-#define DISPATCH_KP_T(KERNEL, kp, grid, threads, ...)                        \
-  switch (kp) {                                                             \
-    case 0: KERNEL<0><<<grid, threads, 0, s>>>(__VA_ARGS__); break;         \
-    case 8: KERNEL<8><<<grid, threads, 0, s>>>(__VA_ARGS__); break;         \
-    case 16: KERNEL<16><<<grid, threads, 0, s>>>(__VA_ARGS__); break;       \
-    case 24: KERNEL<24><<<grid, threads, 0, s>>>(__VA_ARGS__); break;       \
-    default: KERNEL<32><<<grid, threads, 0, s>>>(__VA_ARGS__); break;       \
-  }
 // kernels templated on the rank limit and on the block width in units of 16 columns
 #define DISPATCH_KP_NQ(KERNEL, kp, nq, grid, threads, ...)                        \
   switch (kp) {                                                                  \
