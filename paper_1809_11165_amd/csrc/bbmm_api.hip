@@ -282,6 +282,14 @@ int mat_split_of(const bbmm_ctx* c, int ld) {
   return std::max(1, std::min((192 + groups / 2) / groups, steps / 8));
 }
 
+// Whether a product with the whole matrix and at most 16 columns takes k_mm_rows.  50 iterations, us, with k_mm_mat_small / with it, 11 columns:
+// n = 600: 1 779 / 1 353; 1 000: 1 803 / 1 401; 2 500: 2 007 / 1 757; 3 500: 2 359 / 2 005; 5 000: 2 825 / 3 074.  The product on its own: 19.8 /
+// 7.6; 19.8 / 9.5; from 2 048 rows on the block is better packed first, 21.7 / 20; 26.4 / 24; 35.6 / 66.
+constexpr int kMatRowsMax = 4096, kMatRowsUnpackedMax = 2048;
+bool mat_rows(const bbmm_ctx* c, int ld) {
+  return c->khat_built && !c->sgpr && !c->khat_tri && ld == 16 && c->mat_wgs == 0 && c->np <= kMatRowsMax;
+}
+
 // Lays out one plan on the host (bbmm_plan::lay_out_plan, which checks everything the kernel
 // relies on) and uploads it.
 int make_plan(bbmm_ctx* c, int rows_p, int cols_p, int ld, int wgs, int slot_cap, Buf& plan_buf,
@@ -771,6 +779,16 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, int digits, VpShape* shape, 
   return BBMM_OK;
 }
 
+// By k_mm_rows: V <- K_hat D and the partial sums of d^T v, or the caller's fp32 block from M or D4.
+int stage_mm_rows(bbmm_ctx* c, const float* M, int cc, float* out) {
+  int rc = need_khat(c);
+  if (rc) return rc;
+  if (launch_mm_rows(c->stream, ptr<float>(c->Khat), c->np, c->n, c->khat_pw, ptr<double>(c->D4), M, cc, ptr<double>(c->V),
+                     ptr<double>(c->gpartial), out, ptr<DevState>(c->st)))
+    return fail(c, BBMM_EINVAL, "unsupported layout of the stored matrix");
+  return BBMM_OK;
+}
+
 int stage_pivchol(bbmm_ctx* c) {
   hipStream_t s = c->stream;
   int nb = std::min(kMaxVecBlocks, (c->n + BBMM_VEC_THREADS - 1) / BBMM_VEC_THREADS);   // a row per thread, no candidates without rows
@@ -842,6 +860,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     if (rc) return rc;
   }
   int track = uses_digits(c, mode, cc) ? 1 : 0;
+  const bool by_rows = mode == BBMM_MODE_MATERIALISED && !track && mat_rows(c, ld);
   double noise = c->prob.noise;
   int nb_ur = ur_blocks(c, c->n, ld);
   double* pdv = ptr<double>(c->gpartial);
@@ -856,9 +875,9 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     launch_warm_rhs(s, warm, c->n, ld, ptr<double>(c->D4), track, st);
     VpShape ns{0, nullptr, 1};
     double scaleV = 1.0, addD = 0.0;
-    int rc = stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
+    int rc = by_rows ? stage_mm_rows(c, nullptr, cc, nullptr) : stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
     if (rc) return rc;
-    launch_vreduce(s, ptr<double>(c->Vp), ns, ns, nullptr, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
+    if (!by_rows) launch_vreduce(s, ptr<double>(c->Vp), ns, ns, nullptr, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
     launch_warm_apply(s, warm, ptr<double>(c->V), c->n, ld, ptr<double>(c->U), ptr<double>(c->R));
     launch_fill_f64(s, ptr<double>(c->D4), blk, 0.0);
     launch_ur(s, 2, c->n, ld, cc, c->kp, noise, 0.0, ptr<double>(c->D4), ptr<double>(c->V), ptr<double>(c->U),
@@ -889,6 +908,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     }
   }
   c->ev_iters = 0;
+  const bool fin_zd = !track && ld == 16 && nb_ur <= kFinZdRowsMax;
   // one pass over the maxit iterations on stream `ls`, kernel by kernel
   auto launch_loop = [&](hipStream_t ls, bool timed) -> int {
     hipStream_t user = c->stream;
@@ -898,7 +918,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
       VpShape ns{0, nullptr, 1};
       double scaleV = 1.0, addD = 0.0;
       if (timed && hipEventRecord(c->ev[2 * j], ls) != hipSuccess) rc = fail(c, BBMM_EHIP, "hipEventRecord failed");
-      if (rc == BBMM_OK) rc = stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
+      if (rc == BBMM_OK) rc = by_rows ? stage_mm_rows(c, nullptr, cc, nullptr) : stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
       if (rc) break;
       if (timed) {
         if (hipEventRecord(c->ev[2 * j + 1], ls) != hipSuccess) {
@@ -907,13 +927,18 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
         }
         c->ev_iters = j + 1;
       }
-      launch_dv(ls, ptr<double>(c->Vp), ns, c->n, c->np, ld, scaleV, -1.0, ptr<double>(c->D4),
-                ptr<double>(c->V), st, pdv, nb);
+      if (!by_rows)
+        launch_dv(ls, ptr<double>(c->Vp), ns, c->n, c->np, ld, scaleV, -1.0, ptr<double>(c->D4),
+                  ptr<double>(c->V), st, pdv, nb);
       launch_ur(ls, 0, c->n, ld, cc, c->kp, -1.0, 0.0, ptr<double>(c->D4), ptr<double>(c->V),
-                ptr<double>(c->U), ptr<double>(c->R), ptr<double>(c->L), st, pdv, nb, pur, nb_ur, j,
-                ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid));
-      launch_zd(ls, 0, c->n, ld, c->kp, -1.0, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4),
-                ptr<double>(c->Z0), track, st, nb_zd);
+                ptr<double>(c->U), ptr<double>(c->R), ptr<double>(c->L), st, pdv, by_rows ? c->np / 16 : nb, pur, nb_ur, j,
+                ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid), !fin_zd);
+      if (fin_zd)
+        launch_fin_zd(ls, c->n, cc, c->kp, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4), st, pur, nb_ur, j,
+                      ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid), nb_zd);
+      else
+        launch_zd(ls, 0, c->n, ld, c->kp, -1.0, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4),
+                  ptr<double>(c->Z0), track, st, nb_zd);
     }
     c->stream = user;
     return rc;
@@ -1335,7 +1360,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
       {&c->alpha, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->beta, sizeof(double) * BBMM_MAXP * BBMM_MAXC},
       {&c->resid, sizeof(double) * BBMM_MAXP * BBMM_MAXC}, {&c->st, sizeof(DevState)},
       {&c->tmpA, blk}, {&c->tmpB, blk}, {&c->Pb, may_use_digits(c) ? 4 * opx : 0},
-      {&c->dcnt, c->sgpr ? 0 : kDigCountWords * sizeof(unsigned)},
+      {&c->dcnt, may_use_digits(c) ? kDigCountWords * sizeof(unsigned) : 0},
       {&c->SA, np * 64 * sizeof(float)}, {&c->SB, np * 64 * sizeof(float)}, {&c->u0v, np * sizeof(float)},
   };
   for (auto& w : want) {
@@ -1420,11 +1445,17 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
     if (rc) return rc;
   }
   int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || c->otf_digits == 2) ? 1 : 0;
+  if (mode == BBMM_MODE_MATERIALISED && !digits && mat_rows(c, ld)) {
+    bool packed = c->np > kMatRowsUnpackedMax;
+    if (packed) launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), 0, st);
+    rc = stage_mm_rows(c, packed ? nullptr : M, (int)cc, V);
+    if (rc) return rc;
+    HIPCHK(c, hipGetLastError());
+    return BBMM_OK;
+  }
   if (digits) {                                 // dmax, dflag, done, iters_run; the counts
-    ZeroSegs z = {{&st->dmax[0], c->dcnt.p}, {2 * BBMM_MAXC + 2, kDigCountWords}, 2};
+    ZeroSegs z = {{&st->dmax[0], c->dcnt.p}, {2 * BBMM_MAXC + 2, kDigCountWords}, mode == BBMM_MODE_ONTHEFLY ? 2 : 1};
     launch_fill_multi0(s, z);
-  } else {
-    launch_fill_bytes0(s, &st->done, 2 * sizeof(int));
   }
   launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), digits, st);
   VpShape ns{0, nullptr, 1}, alt{0, nullptr, 1};
@@ -1441,8 +1472,7 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
     rc = stage_mm(c, mode, (int)cc, ld, digits, &ns, &scaleV, &addD);
   }
   if (rc) return rc;
-  launch_vreduce(s, ptr<double>(c->Vp), ns, alt, pick, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), ptr<double>(c->V));
-  launch_unpack_rows(s, ptr<double>(c->V), ld, c->n, (int)cc, V);
+  launch_vreduce(s, ptr<double>(c->Vp), ns, alt, pick, c->n, c->np, ld, scaleV, addD, ptr<double>(c->D4), nullptr, V, (int)cc);
   HIPCHK(c, hipGetLastError());
   return BBMM_OK;
 }

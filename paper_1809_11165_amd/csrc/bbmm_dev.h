@@ -20,6 +20,7 @@ struct DevState {
   double alpha_cur[BBMM_MAXC];
   double beta_cur[BBMM_MAXC];
   double dvtot[BBMM_MAXC];      // d^T K_hat d of the current iteration, per column
+  double rho_prev[BBMM_MAXC];   // rho, active and m_valid as k_ur_main met them (for k_fin_zd)
   double Qt[BBMM_MAXK * BBMM_MAXC];   // C^{-1} L^T R, [m][q]
   double G[BBMM_MAXK * BBMM_MAXK];    // lower Cholesky factor of C = sigma^2 I + L^T L, [a][b]
   double Ginv[BBMM_MAXK * BBMM_MAXK]; // G^{-1} (lower triangular, zero padded), [a][b]
@@ -35,6 +36,7 @@ struct DevState {
   double loop_noise, loop_tol, loop_scaleV, loop_addD;
   int active[BBMM_MAXC];
   int m_valid[BBMM_MAXC];
+  int active_prev[BBMM_MAXC], m_valid_prev[BBMM_MAXC];
   int piv[BBMM_MAXK + 1];
   unsigned dmax[BBMM_MAXC];   // per column of D: largest high word of |D| (its exponent scales the digits)
   int dflag[BBMM_MAXC];       // per column of D: 1 = holds +inf, 2 = -inf, 4 = NaN   (zeroed with done)
@@ -83,6 +85,7 @@ void launch_colmean(hipStream_t s, const float* X, int n, int d, DevState* st, d
 void launch_prep_x(hipStream_t s, const float* X, int n, int d, int np, int KK, HypArgs hyp,
                    DevState* st, float* Xa, float* Xb, float* Xs, float* X4, float* sq);
 // track != 0: leave the columns' magnitudes in st->dmax / st->dflag (zero beforehand), as launch_digits needs
+// (track == 0: clears the stop flag and the iteration count)
 void launch_pack_d4(hipStream_t s, const float* M, int n, int c, int np, int ld, double* D4, int track,
                     DevState* st);
 // unless_far (may be null): dst is left alone if that state's X holds points too far out for the digit products
@@ -97,8 +100,9 @@ void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* 
 void launch_warm_apply(hipStream_t s, const float* u_init, const double* V, int n, int ld, double* U,
                        double* R);
 // pick (may be null): with pick->done set the partial results have the shape `alt`
+// out (may be null): the result as the caller's fp32 n x c block instead
 void launch_vreduce(hipStream_t s, const double* Vp, VpShape shape, VpShape alt, const DevState* pick, int n, int np, int ld, double scaleV,
-                    double addD, const double* D4, double* V);
+                    double addD, const double* D4, double* V, float* out = nullptr, int c = 0);
 // diag_in / row_in: NULL for a plain kernel matrix of X (constant diagonal, rows evaluated from X);
 // otherwise the matrix diagonal (n) and, per step, the pivot's row at row_in[i * row_ld].
 // forced / next_forced: -1 for the greedy rule; otherwise the pivot this step must take and the
@@ -118,10 +122,14 @@ void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, in
                double addD, const double* D4, double* V, const DevState* st, double* partial_dv,
                int nblocks);
 constexpr int kUrMaxRows = 512;   // most blocks of launch_ur
+// finish: with k_ur_fin; without, launch_fin_zd has to follow (ld = 16, nb_ur <= kFinZdRowsMax, not in the initial pass, no digits behind it)
+constexpr int kFinZdRowsMax = 16;
+void launch_fin_zd(hipStream_t s, int n, int c, int kp, const double* R, const double* L, double* D4, DevState* st, const double* partial,
+                   int nb_ur, int iter, double* alpha_hist, double* beta_hist, double* resid_hist, int nblocks);
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
-               double* alpha_hist, double* beta_hist, double* resid_hist);
+               double* alpha_hist, double* beta_hist, double* resid_hist, bool finish = true);
 void launch_zd(hipStream_t s, int init, int n, int ld, int kp, double noise, const double* R,
                const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks);
 void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, const double* R,
@@ -211,6 +219,10 @@ int launch_mm_mat(hipStream_t s, const float* Khat, const double* D4, double* Vp
 // The same for ld = 16 and a small np (a multiple of 256): nsplit row chunks, one partial result each.
 int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, double* Vp, int np, int nsplit, const DevState* st,
                         int panel_width, int panel_rows, int cols);
+// The same for at most 16 columns, by rows of a small symmetric matrix: D4 -> V (stride 16) and np / 16 partial sums of d^T v; or, with out
+// (n x c, fp32), D4 or M (n x c, fp32; may be null) -> out, whatever the state's stop flag says.
+int launch_mm_rows(hipStream_t s, const float* Khat, int np, int n, int panel_width, const double* D4, const float* M, int c, double* V,
+                   double* partial_dv, float* out, const DevState* st);
 #define BBMM_SGPR_PANEL 512   // column-panel width of the transposed SGPR root
 // c: number of columns really used (<= ld); lets 17..20 columns run one MFMA group plus vector FMAs
 // ---- launchers implemented in kernels_dig.hip: products on the 8-bit matrix pipe ------------

@@ -360,6 +360,86 @@ __global__ __launch_bounds__(64 * MS_NW, 2) void k_mm_mat_small(const float* __r
   }
 }
 
+// The same for at most 16 columns and an even smaller matrix, where partial results cost as much as the product: K_hat is symmetric,
+// so a workgroup takes 16 of its rows whole, its MR_NW waves every MR_NW-th 16 columns of them, their sums meet in LDS, and the
+// result is final.
+//   MR_ITER    the block is D4; V (fp64) and the workgroup's share of d^T v, as k_dv leaves them (one launch per iteration less)
+//   MR_PACKED  the block is D4, the result the caller's fp32 one (n x c)
+//   MR_CALL    both are the caller's (nothing is packed)
+// Bound by latency (n = 1 000: 7.1 us, k_mm_mat_small 8.0 and k_dv 5.4), and from 4 096 rows on by every workgroup's reading the
+// whole block.  Sizes: see mat_rows.
+constexpr int MR_NW = 8;
+enum { MR_ITER, MR_PACKED, MR_CALL };
+
+template <int SRC>
+__global__ __launch_bounds__(64 * MR_NW) void k_mm_rows(const float* __restrict__ Khat, int np, int n, int pw, size_t panel_stride,
+                                                         const double* __restrict__ D4, const float* __restrict__ M, int c,
+                                                         double* __restrict__ V, double* __restrict__ partial_dv,
+                                                         float* __restrict__ out, const DevState* __restrict__ st) {
+  if (SRC == MR_ITER && st->done) return;
+  __shared__ double red[MR_NW][16][17];
+  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int jc = lane & 15, g = lane >> 4;
+  int row0 = blockIdx.x * 16, steps = np >> 4;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  constexpr int PF = 4;                                   // steps in flight
+  f32x4 kv[PF];
+  f64x4 dop[PF];
+  auto request = [&](int u, int s) {
+    if (s >= steps) return;                               // (uniform over the wave)
+    int i0 = 16 * s;
+    const float* kp = Khat + (size_t)(i0 / pw) * panel_stride + (size_t)(row0 + jc) * pw + (size_t)(i0 % pw + 4 * g);
+    kv[u] = *(const f32x4*)kp;
+    if (SRC != MR_CALL) {
+      dop[u] = *(const f64x4*)(D4 + ((size_t)(i0 / 4 + g) * 16 + jc) * 4);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int i = i0 + 4 * g + r;
+        dop[u][r] = (i < n && jc < c) ? (double)M[(size_t)i * c + jc] : 0.0;
+      }
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < PF; ++u) request(u, wave + u * MR_NW);
+  for (int s = wave; s < steps; s += PF * MR_NW) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      if (s + u * MR_NW < steps) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc = mfma16d(dop[u][r], (double)kv[u][r], acc);
+        request(u, s + (u + PF) * MR_NW);
+      }
+    }
+  }
+  // lane (jc, g) holds out[row0 + jc][column 4 r + g]
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][jc][4 * r + g] = acc[r];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 256; e += 64 * MR_NW) {
+    int row = e >> 4, q = e & 15, i = row0 + row;
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < MR_NW; w += 4) v += (red[w][row][q] + red[w + 1][row][q]) + (red[w + 2][row][q] + red[w + 3][row][q]);
+    if (SRC == MR_ITER) {
+      double d = D4[((size_t)(i >> 2) * 16 + q) * 4 + (i & 3)];
+      if (i < n) V[(size_t)i * 16 + q] = v;
+      red[0][row][q] = i < n ? d * v : 0.0;               // (read by this thread alone above)
+    } else if (i < n && q < c) {
+      out[(size_t)i * c + q] = (float)v;
+    }
+  }
+  if (SRC == MR_ITER) {
+    __syncthreads();
+    if (threadIdx.x < 16) {
+      double t = 0.0;
+#pragma unroll 16
+      for (int row = 0; row < 16; ++row) t += red[0][row][threadIdx.x];
+      partial_dv[(size_t)blockIdx.x * 16 + threadIdx.x] = t;
+    }
+  }
+}
+
 // ------------------------------------------------------- product on the fly ---
 // Wave: NJ column blocks (16*NJ output rows of V), a chunk of row blocks to contract over.
 // Distances by fp32 MFMA, kernel function in registers, product with the block by fp64 MFMA.
@@ -984,6 +1064,18 @@ int launch_mm_mat_small(hipStream_t s, const float* Khat, const double* D4, doub
     k_mm_mat_small<true><<<grid, 64 * MS_NW, 0, s>>>(Khat, D4, Vp, np, pw, panel_stride, pw, nsplit, st);
   else
     k_mm_mat_small<false><<<grid, 64 * MS_NW, 0, s>>>(Khat, D4, Vp, np, pw, panel_stride, pw, nsplit, st);
+  return 0;
+}
+
+int launch_mm_rows(hipStream_t s, const float* Khat, int np, int n, int panel_width, const double* D4, const float* M, int c, double* V,
+                   double* partial_dv, float* out, const DevState* st) {
+  int pw = panel_width > 0 ? panel_width : np;
+  size_t panel_stride = panel_width > 0 ? (size_t)np * panel_width : 0;
+  if (pw % 16 != 0 || np % 16 != 0) return 1;
+  int grid = np / 16;
+  if (M) k_mm_rows<MR_CALL><<<grid, 64 * MR_NW, 0, s>>>(Khat, np, n, pw, panel_stride, D4, M, c, V, partial_dv, out, st);
+  else if (out) k_mm_rows<MR_PACKED><<<grid, 64 * MR_NW, 0, s>>>(Khat, np, n, pw, panel_stride, D4, M, c, V, partial_dv, out, st);
+  else k_mm_rows<MR_ITER><<<grid, 64 * MR_NW, 0, s>>>(Khat, np, n, pw, panel_stride, D4, M, c, V, partial_dv, out, st);
   return 0;
 }
 

@@ -188,6 +188,7 @@ __global__ __launch_bounds__(VT) void k_pack_d4(const float* __restrict__ M, int
   size_t total = (size_t)np * ld, step = (size_t)gridDim.x * VT;
   int q = threadIdx.x % ld, flag = 0;
   unsigned hi = 0u;
+  if (!track && blockIdx.x == 0 && threadIdx.x == 0) st->done = st->iters_run = 0;
   for (size_t idx = (size_t)blockIdx.x * VT + threadIdx.x; idx < total; idx += step) {
     int i = (int)(idx / ld);
     double v = (i < n && q < c) ? (double)M[(size_t)i * c + q] : 0.0;
@@ -266,16 +267,19 @@ __global__ void k_copy_block(const float* __restrict__ src, size_t pw, size_t ro
 // V = scaleV * sum_s Vp[s] + addD * D  (no dot product; used by the stand-alone product call)
 __global__ void k_vreduce(const double* __restrict__ Vp, VpShape shape, VpShape alt, const DevState* __restrict__ pick, int n, int np, int ld,
                           double scaleV, double addD, const double* __restrict__ D4,
-                          double* __restrict__ V) {
+                          double* __restrict__ V, float* __restrict__ out, int c) {
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)n * ld) return;
   int i = (int)(idx / ld), q = (int)(idx % ld);
+  if (out && q >= c) return;
   size_t pidx = (size_t)i * ld + perm16(q);
   if (pick && pick->done) shape = alt;
   int nsplit = shape.nseg ? shape.nseg[i / shape.seg_cols] : shape.nsplit;
   double s = 0.0;
   for (int sp = 0; sp < nsplit; ++sp) s += Vp[(size_t)sp * np * ld + pidx];
-  V[idx] = scaleV * s + addD * D4[d4_index(i, q, ld)];
+  double v = scaleV * s + addD * D4[d4_index(i, q, ld)];
+  if (out) out[(size_t)i * c + q] = (float)v;
+  else V[idx] = v;
 }
 
 // Warm start of column 0 (Alg. 1/2 take the current solution as input): the quad-swizzled
@@ -1018,6 +1022,12 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
     }
   }
   if (done) return;                                   // block-uniform
+  if (!init && blockIdx.x == 0 && (int)threadIdx.x < LD) {   // as k_fin_zd reads them (its first block writes the new ones)
+    int cq = threadIdx.x;
+    st->rho_prev[cq] = st->rho[cq];
+    st->active_prev[cq] = st->active[cq];
+    st->m_valid_prev[cq] = st->m_valid[cq];
+  }
   double rr[NQ];
   f64x4 acc[MB > 0 ? MB : 1][NQ];
 #pragma unroll
@@ -1359,6 +1369,112 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
 #pragma unroll
       for (int w = 0; w < NW; ++w) h = max(h, smax[w][threadIdx.x]);
       atomicMax(&dmax[threadIdx.x], h);
+    }
+  }
+}
+
+// (2b) and (3) in one launch, for at most 16 columns and so few partial rows that every block can add them up for itself (the small
+// solves and the bookkeeping too; the first block writes that down).  Same sums in the same order as k_ur_fin and k_zd.
+// n = 1 000, k = 5: 4.3 + 4.0 us and a launch -> 6.2.
+constexpr int kFinZdRows = 16;
+template <int KP>
+__global__ __launch_bounds__(VT) void k_fin_zd(int n, int c, const double* __restrict__ R, const double* __restrict__ L,
+                                                double* __restrict__ D4, DevState* st, const double* __restrict__ partial, int nb, int iter,
+                                                double* alpha_hist, double* beta_hist, double* resid_hist) {
+  constexpr int LD = 16, KS = KP / 4, E = (KP + 1) * LD, NW = VT / 64;
+  __shared__ double tot[E];                                  // [entry][column]
+  __shared__ double Gs[BBMM_MAXK * BBMM_MAXK];
+  __shared__ double ws[KP > 0 ? KP * LD : 1], xs[KP > 0 ? KP * LD : 1];
+  __shared__ double beta_s[LD];
+  __shared__ int conv_s[LD];
+  if (st->done) return;
+  double noise = st->loop_noise, tol = st->loop_tol;
+  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int tq = threadIdx.x & (LD - 1);
+  double s_rho = st->rho_prev[tq], s_bnorm = st->bnorm[tq], s_dv = st->dvtot[tq];
+  int s_active = st->active_prev[tq], s_mvalid = st->m_valid_prev[tq];
+  constexpr int parts = E <= UT / 4 ? 4 : (E <= UT / 2 ? 2 : 1);
+  for (int e = threadIdx.x; e < E; e += VT) {                // entry e / 16 of column e % 16
+    int q = e & (LD - 1);
+    const double* p = partial + ((size_t)(q >> 2) * nb * (KP + 1) + (e >> 4)) * 4 + (q & 3);
+    double v[kFinZdRows];
+#pragma unroll
+    for (int b = 0; b < kFinZdRows; ++b) v[b] = b < nb ? p[(size_t)b * (KP + 1) * 4] : 0.0;
+    double t = 0.0;
+#pragma unroll
+    for (int pp = 0; pp < parts; ++pp) {
+      double u = 0.0;
+#pragma unroll
+      for (int b = pp; b < kFinZdRows; b += parts) u += v[b];
+      t = pp == 0 ? u : t + u;
+    }
+    tot[e] = t;
+  }
+  for (int e = threadIdx.x; e < KP * BBMM_MAXK; e += VT) Gs[e] = st->Ginv[e];
+  __syncthreads();
+  for (int e = threadIdx.x; e < KP * LD; e += VT) {
+    int m = e >> 4, q = e & (LD - 1);
+    double wv = 0.0;
+#pragma unroll
+    for (int a = 0; a < KP; ++a) wv += Gs[m * BBMM_MAXK + a] * tot[(1 + a) * LD + q];
+    ws[e] = wv;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < KP * LD; e += VT) {
+    int m = e >> 4, q = e & (LD - 1);
+    double xv = 0.0;
+#pragma unroll
+    for (int a = 0; a < KP; ++a) xv += Gs[a * BBMM_MAXK + m] * ws[a * LD + q];
+    xs[e] = xv;
+  }
+  if ((int)threadIdx.x < LD) {
+    double sq = 0.0;
+#pragma unroll
+    for (int a = 0; a < KP; ++a) sq += ws[a * LD + tq] * ws[a * LD + tq];
+    double rrq = tot[tq];
+    double rho_new = (rrq - sq) / noise;
+    int ok;
+    double alpha = alpha_from(s_active, s_rho, s_dv, tq, c, &ok);
+    int ok2 = ok && finite_d(rho_new) && rho_new > 0.0;
+    double beta = ok2 ? rho_new / s_rho : 0.0;
+    double rel = sqrt(rrq) / (s_bnorm > 0.0 ? s_bnorm : 1.0);
+    beta_s[tq] = beta;
+    conv_s[tq] = tq >= c || rel < tol;
+    if (blockIdx.x == 0) {
+      st->alpha_cur[tq] = alpha;
+      st->m_valid[tq] = s_mvalid + ok;
+      st->active[tq] = ok2;
+      st->beta_cur[tq] = beta;
+      if (ok2) st->rho[tq] = rho_new;
+      alpha_hist[(size_t)iter * BBMM_MAXC + tq] = alpha;
+      beta_hist[(size_t)iter * BBMM_MAXC + tq] = beta;
+      resid_hist[(size_t)iter * BBMM_MAXC + tq] = rel;
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->iters_run = iter + 1;
+    int conv = 1;
+    for (int q = 0; q < LD; ++q) conv &= conv_s[q];
+    if (tol > 0.0 && conv) st->done = 1;                     // (a block that has not started yet leaves its rows of D, which nobody reads then)
+  }
+  int q = lane & 15, g = lane >> 4;
+  double beta = beta_s[q], inv_noise = 1.0 / noise;
+  double qtb[KS > 0 ? KS : 1];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) qtb[kk] = xs[(4 * kk + g) * LD + q];
+  for (int i0 = 16 * (blockIdx.x * NW + wave); i0 < n; i0 += 16 * gridDim.x * NW) {   // wave-uniform bounds: MFMA needs all lanes
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    int arow = i0 + q;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) acc = mfma16d((arow < n) ? L[(size_t)arow * KP + 4 * kk + g] : 0.0, qtb[kk], acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int i = i0 + 4 * r + g;
+      if (i < n) {
+        size_t di = d4_index(i, q, LD);
+        D4[di] = (R[(size_t)i * LD + q] - acc[r]) * inv_noise + beta * D4[di];
+      }
     }
   }
 }
@@ -1819,8 +1935,8 @@ void launch_copy_block(hipStream_t s, const float* src, size_t pw, size_t rows_p
 }
 
 void launch_vreduce(hipStream_t s, const double* Vp, VpShape shape, VpShape alt, const DevState* pick, int n, int np, int ld, double scaleV,
-                    double addD, const double* D4, double* V) {
-  k_vreduce<<<blocks_for((size_t)n * ld, 256), 256, 0, s>>>(Vp, shape, alt, pick, n, np, ld, scaleV, addD, D4, V);
+                    double addD, const double* D4, double* V, float* out, int c) {
+  k_vreduce<<<blocks_for((size_t)n * ld, 256), 256, 0, s>>>(Vp, shape, alt, pick, n, np, ld, scaleV, addD, D4, V, out, c);
 }
 
 void launch_warm_rhs(hipStream_t s, const float* u_init, int n, int ld, double* D4, int track, DevState* st) {
@@ -1927,13 +2043,20 @@ void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, in
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
-               double* alpha_hist, double* beta_hist, double* resid_hist) {
+               double* alpha_hist, double* beta_hist, double* resid_hist, bool finish) {
   int nq = ld / 16;
 #define UR_MAIN(KP, NQ) k_ur_main<KP, NQ>
   DISPATCH_KP_NQ(UR_MAIN, kp, nq, nb_ur, UT, init, n, c, D4, V, U, R, L, st, partial_dv, nb_dv, partial);
 #undef UR_MAIN
+  if (!finish) return;
   DISPATCH_KP_T(k_ur_fin, kp, ld / 4, UT, init, ld, c, noise, tol, st, partial, nb_ur, iter, alpha_hist,
                 beta_hist, resid_hist);
+}
+
+static_assert(kFinZdRows == kFinZdRowsMax, "");
+void launch_fin_zd(hipStream_t s, int n, int c, int kp, const double* R, const double* L, double* D4, DevState* st, const double* partial,
+                   int nb_ur, int iter, double* alpha_hist, double* beta_hist, double* resid_hist, int nblocks) {
+  DISPATCH_KP_T(k_fin_zd, kp, nblocks, VT, n, c, R, L, D4, st, partial, nb_ur, iter, alpha_hist, beta_hist, resid_hist)
 }
 
 template <int MODE, bool TRACK>

@@ -1,0 +1,71 @@
+"""GPU: iterations of small problems, whose product, finish and direction update are three launches (at most 4096 rows for the product by
+rows, 2048 for the joint finish), at the edges of both, of the compiled ranks and of the block widths, against the fp64 oracle's
+iteration on the very operands of the GPU."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import bbmm_oracle as O  # noqa: E402
+from paper_1809_11165_amd import inputs  # noqa: E402
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("n,k,c", [(1, 0, 1), (17, 5, 3), (129, 8, 16), (1000, 9, 11), (2048, 16, 15), (2049, 24, 16), (2049, 17, 1), (4096, 32, 12),
+                                   (4097, 25, 16)])
+@pytest.mark.parametrize("mode", [inputs.MATERIALISED, inputs.ONTHEFLY])
+def test_first_iterations_against_the_oracle(n, k, c, mode):
+    """Coefficients of the first five iterations: on the stored matrix only the order of fp64 sums differs (1e-9 leaves it a
+    thousand times the 1e-12 that five iterations make of 2^-53 here), on the fly the evaluation of the entries too."""
+    from paper_1809_11165_amd import binding
+    w = inputs.tiny(n, 3, kernel=inputs.RBF, ard=True, t=max(1, c - 1), k=k, iters=8, noise=0.5, seed=11)
+    ctx = binding.Context(0)
+    try:
+        ctx.bbmm_setup(binding.problem_from_workload(w, mode))
+        if mode == inputs.MATERIALISED:
+            ctx.bbmm_build_khat()
+            K = ctx.bbmm_khat_block(0, n, 0, n).cpu().numpy().astype(np.float64)
+        else:
+            K = O.kernel_matrix(w.kernel, w.X.astype(np.float64), w.lengthscale, w.outputscale) + w.noise * np.eye(n)
+        L = ctx.bbmm_pivoted_cholesky()[0].cpu().numpy().astype(np.float64)[:, :k]
+        ctx.bbmm_precond_setup()
+        B = np.random.default_rng(n + c).standard_normal((n, c)).astype(np.float32)
+        U, alpha, beta, resid, iters = ctx.bbmm_mbcg(mode, torch.from_numpy(B).cuda())
+        U = U.cpu().numpy().astype(np.float64)
+    finally:
+        ctx.close()
+    P = O.make_preconditioner(L, w.noise)
+    it = min(5, n)
+    ref = O.mbcg(lambda M: K @ M, B.astype(np.float64), P.solve, 8)
+    tol = 1e-9 if mode == inputs.MATERIALISED else 1e-4
+    assert iters == 8
+    if n > 16:                                    # (one point is solved exactly by the first step; what follows is noise)
+        assert np.allclose(alpha[:it], ref.alpha[:it], rtol=tol)
+        assert np.allclose(beta[:it], ref.beta[:it], rtol=tol)
+        assert np.linalg.norm(U - ref.U) < 1e-3 * np.linalg.norm(ref.U)
+    else:
+        assert np.allclose(U, B / K, rtol=1e-6)
+
+
+def test_a_tolerance_stops_a_small_iteration_where_the_oracle_stops():
+    from paper_1809_11165_amd import binding
+    w = inputs.tiny(900, 3, kernel=inputs.RBF, ard=True, t=4, k=6, iters=60, noise=0.5, seed=12)
+    w.tol = 1e-3
+    ctx = binding.Context(0)
+    try:
+        ctx.bbmm_setup(binding.problem_from_workload(w, inputs.MATERIALISED))
+        ctx.bbmm_build_khat()
+        K = ctx.bbmm_khat_block(0, 900, 0, 900).cpu().numpy().astype(np.float64)
+        L = ctx.bbmm_pivoted_cholesky()[0].cpu().numpy().astype(np.float64)[:, :6]
+        ctx.bbmm_precond_setup()
+        B = ctx.bbmm_make_probes()
+        U, alpha, beta, resid, iters = ctx.bbmm_mbcg(inputs.MATERIALISED, B)
+    finally:
+        ctx.close()
+    assert 3 < iters < 60
+    rel = np.asarray(resid)
+    assert rel[iters - 1].max() < 1e-3 and rel[iters - 2].max() >= 1e-3
+    P = O.make_preconditioner(L, w.noise)
+    ref = O.mbcg(lambda M: K @ M, B.cpu().numpy().astype(np.float64), P.solve, iters)
+    assert np.linalg.norm(U.cpu().numpy() - ref.U) < 1e-5 * np.linalg.norm(ref.U)
