@@ -96,6 +96,7 @@ struct bbmm_ctx {
   HypArgs hyp{};
   bool khat_built = false, chol_done = false, pre_done = false, mbcg_done = false;
   bool sgpr = false, sgpr_built = false;
+  bool gram_built = false;                   // A^T A of the root in memory (where the Cholesky work matrix was)
   bool far_x = false;                       // X is known to hold points too far out for the digit products
   int last_c = 0, last_ld = 0, last_t = 0;   // shape of the last mBCG run
 
@@ -239,11 +240,12 @@ int vec_blocks(int n, int ld) {
 }
 
 // blocks of the 1024-thread update kernel: at least two 4-row steps per wave, at most 128 partial rows
-int ur_blocks(const bbmm_ctx* c, int n, int ld) {
+// (proj: 256, beside the blocks for H; n = 500 000, m = 1024, a whole call 95.0 ms with 128, 91.7 with 256, 92.8 with 512)
+int ur_blocks(const bbmm_ctx* c, int n, int ld, bool proj = false) {
   (void)ld;
   int rows_per_step = 16 * 4;               // 16 waves, 4 rows each
   int nb = (n + rows_per_step * 2 - 1) / (rows_per_step * 2);
-  int cap = c->ur_blocks_cap > 0 ? (int)std::min<int64_t>(c->ur_blocks_cap, kMaxVecBlocks) : 128;
+  int cap = c->ur_blocks_cap > 0 ? (int)std::min<int64_t>(c->ur_blocks_cap, kMaxVecBlocks) : proj ? 256 : 128;
   return std::max(1, std::min(nb, cap));
 }
 
@@ -371,6 +373,8 @@ int rect_wgs_of(const bbmm_ctx* c, int rows_p, int cols_p, int ld, int slot_cap,
   return bbmm_plan::rect_wgs_of(c->num_cus, rows_p, cols_p, ld, slot_cap, tuned);
 }
 
+constexpr int kProjZdBlocks = 1024;          // blocks of its direction update (they leave partial sums)
+constexpr int kProjMinRows = 2304, kProjMaxInducing = 8192;   // (gpartial: kProjZdBlocks + mp ld / 256 rows of ld)
 constexpr int kSgprSlotCap = 1024;   // partial results of A^T D: one per workgroup when m <= 1024
 
 int ensure_sgpr_plans(bbmm_ctx* c) {
@@ -602,6 +606,7 @@ int stage_sgpr_build(bbmm_ctx* c) {
   launch_prep_x(s, c->prob.Uind, c->m, c->d, c->mp, c->KK, c->hyp, st, ptr<float>(c->Ua), ptr<float>(c->Ub),
                 ptr<float>(c->Us), ptr<float>(c->U4), ptr<float>(c->usq));
   c->sgpr_built = true;
+  c->gram_built = false;
   c->chol_done = c->pre_done = c->mbcg_done = false;
   return BBMM_OK;
 }
@@ -627,6 +632,37 @@ int sgpr_first_pass(bbmm_ctx* c, int ld, const double* D4, VpShape* shape, int c
                     ptr<MmPlan>(c->sgplan[v]), c->sg_wgs[v], ptr<DevState>(c->st), 0, 0, cols))
     return fail(c, BBMM_EINVAL, "unsupported block width");
   *shape = VpShape{0, ptr<int>(c->sgnseg[v]), v ? 512 : 1024};
+  return BBMM_OK;
+}
+
+// Whether the iteration carries T = A^T D and S = A^T R along (their recurrences need A^T A, mp x mp, once) instead of
+// streaming A for A^T D in every product.
+// Measured, m = 1024, n = 500 000: see kernels_sgpr.hip.  A^T A costs what mp / 32 such passes do (n mp^2 at
+// 50 TFLOP/s against 4 n mp bytes at 6.3 TB/s), so it is formed where at least twice as many iterations are certain: no
+// tolerance to stop at.
+// (The partial sums of A^T A have K_UX's memory: eight of its upper triangle fit from 4 mp + 512 points on.)
+bool sgpr_projected(const bbmm_ctx* c) {
+  return c->prob.tol <= 0.0 && c->np >= std::max(kProjMinRows, 4 * c->mp + 512) && c->mp <= kProjMaxInducing &&
+         c->maxit >= std::max(16, c->mp / 16);
+}
+
+// A^T A and A^T L.  The Cholesky work matrix and K_UX have served their purpose and are the memory for it.
+int stage_sgpr_project(bbmm_ctx* c, int nb_zd, SgprLoop* pj) {
+  hipStream_t s = c->stream;
+  if (!c->gram_built) {
+    launch_sgpr_gram(s, ptr<float>(c->A), c->np, c->mp, c->num_cus, ptr<double>(c->Kux), ptr<double>(c->KUU));
+    c->gram_built = true;
+  }
+  int ldw = c->kp > 16 ? 32 : 16;
+  if (c->kp > 0) {
+    launch_cols_to_d4(s, ptr<double>(c->L), c->n, c->np, c->kp, ldw, ptr<double>(c->tmpA));
+    VpShape sh{0, nullptr, 1};
+    int rc = sgpr_first_pass(c, ldw, ptr<double>(c->tmpA), &sh, c->kp);
+    if (rc) return rc;
+    launch_sgpr_mid(s, ptr<double>(c->Tp), sh, c->mp, ldw, ptr<DevState>(c->st), ptr<double>(c->BW));
+  }
+  *pj = SgprLoop{nullptr, VpShape{0, nullptr, 1}, c->np, c->mp, ptr<double>(c->KUU), ptr<double>(c->T4), ptr<double>(c->TU),
+                 ptr<double>(c->BU), ptr<double>(c->BW), ldw, ptr<double>(c->gpartial), 0, nb_zd};
   return BBMM_OK;
 }
 
@@ -861,8 +897,15 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
   }
   int track = uses_digits(c, mode, cc) ? 1 : 0;
   const bool by_rows = mode == BBMM_MODE_MATERIALISED && !track && mat_rows(c, ld);
+  const bool proj = mode == BBMM_MODE_SGPR && sgpr_projected(c);
+  SgprLoop pj = {};
+  if (proj) {
+    nb_zd = std::min(nb_zd, kProjZdBlocks);
+    int rc = stage_sgpr_project(c, nb_zd, &pj);
+    if (rc) return rc;
+  }
   double noise = c->prob.noise;
-  int nb_ur = ur_blocks(c, c->n, ld);
+  int nb_ur = ur_blocks(c, c->n, ld, proj);
   double* pdv = ptr<double>(c->gpartial);
   double* pur = ptr<double>(c->partial);
   launch_ur(s, 1, c->n, ld, cc, c->kp, noise, 0.0, ptr<double>(c->D4), ptr<double>(c->V), ptr<double>(c->U),
@@ -885,7 +928,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
               ptr<double>(c->beta), ptr<double>(c->resid));
   }
   launch_zd(s, 1, c->n, ld, c->kp, noise, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4),
-            ptr<double>(c->Z0), track, st, nb);
+            ptr<double>(c->Z0), track, st, proj ? nb_zd : nb, proj ? &pj : nullptr);
   // the loop's kernels take noise, tolerance and the (scale, diagonal) pair of the product from the
   // device state, so their launches are the same for any hyperparameter values
   {
@@ -900,6 +943,13 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     }
     launch_set_loop_scalars(s, st, noise, c->prob.tol, scaleV, addD);
   }
+  if (proj) {
+    VpShape sh{0, nullptr, 1};
+    int rc = sgpr_first_pass(c, ld, ptr<double>(c->D4), &sh, cc);
+    if (rc) return rc;
+    launch_sgpr_mid(s, ptr<double>(c->Tp), sh, c->mp, ld, st, pj.T4);
+    launch_sgpr_first(s, ld, c->kp, pj, st);
+  }
   if (c->time_mm) {
     while ((int)c->ev.size() < 2 * c->maxit) {
       hipEvent_t e;
@@ -908,7 +958,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     }
   }
   c->ev_iters = 0;
-  const bool fin_zd = !track && ld == 16 && nb_ur <= kFinZdRowsMax;
+  const bool fin_zd = !track && !proj && ld == 16 && nb_ur <= kFinZdRowsMax;
   // one pass over the maxit iterations on stream `ls`, kernel by kernel
   auto launch_loop = [&](hipStream_t ls, bool timed) -> int {
     hipStream_t user = c->stream;
@@ -918,7 +968,10 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
       VpShape ns{0, nullptr, 1};
       double scaleV = 1.0, addD = 0.0;
       if (timed && hipEventRecord(c->ev[2 * j], ls) != hipSuccess) rc = fail(c, BBMM_EHIP, "hipEventRecord failed");
-      if (rc == BBMM_OK) rc = by_rows ? stage_mm_rows(c, nullptr, cc, nullptr) : stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
+      if (rc == BBMM_OK)
+        rc = by_rows ? stage_mm_rows(c, nullptr, cc, nullptr)
+             : proj  ? sgpr_second_pass(c, ld, &ns, cc)
+                     : stage_mm(c, mode, cc, ld, track, &ns, &scaleV, &addD);
       if (rc) break;
       if (timed) {
         if (hipEventRecord(c->ev[2 * j + 1], ls) != hipSuccess) {
@@ -927,18 +980,22 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
         }
         c->ev_iters = j + 1;
       }
-      if (!by_rows)
+      if (proj) {
+        pj.Vp = ptr<double>(c->Vp);
+        pj.shape = ns;
+      } else if (!by_rows)
         launch_dv(ls, ptr<double>(c->Vp), ns, c->n, c->np, ld, scaleV, -1.0, ptr<double>(c->D4),
                   ptr<double>(c->V), st, pdv, nb);
       launch_ur(ls, 0, c->n, ld, cc, c->kp, -1.0, 0.0, ptr<double>(c->D4), ptr<double>(c->V),
-                ptr<double>(c->U), ptr<double>(c->R), ptr<double>(c->L), st, pdv, by_rows ? c->np / 16 : nb, pur, nb_ur, j,
-                ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid), !fin_zd);
+                ptr<double>(c->U), ptr<double>(c->R), ptr<double>(c->L), st, pdv,
+                by_rows ? c->np / 16 : proj ? nb_zd + c->mp * ld / BBMM_VEC_THREADS : nb, pur, nb_ur, j,
+                ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid), !fin_zd, proj ? &pj : nullptr);
       if (fin_zd)
         launch_fin_zd(ls, c->n, cc, c->kp, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4), st, pur, nb_ur, j,
                       ptr<double>(c->alpha), ptr<double>(c->beta), ptr<double>(c->resid), nb_zd);
       else
         launch_zd(ls, 0, c->n, ld, c->kp, -1.0, ptr<double>(c->R), ptr<double>(c->L), ptr<double>(c->D4),
-                  ptr<double>(c->Z0), track, st, nb_zd);
+                  ptr<double>(c->Z0), track, st, nb_zd, proj ? &pj : nullptr);
     }
     c->stream = user;
     return rc;
@@ -946,7 +1003,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
   bool replayed = false;
   if (c->use_graph && !c->time_mm && c->cap) {
     LoopKey key{c->alloc_epoch, c->tune_epoch, mode, c->prob.kernel, c->n, c->d, cc, ld, c->kp, c->maxit, c->m,
-                c->khat_tri ? 1 : 0, (int)c->prob.n_lengthscale, track};
+                c->khat_tri ? 1 : 0, (int)c->prob.n_lengthscale, proj ? 2 : track};
     // graphs recorded against buffers or tuning values that are gone can never be replayed again
     for (size_t i = 0; i < c->graphs.size();) {
       if (c->graphs[i].key.alloc_epoch != c->alloc_epoch || c->graphs[i].key.tune_epoch != c->tune_epoch) {
@@ -1331,7 +1388,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   c->khat_mem = c->words_built = false;
   c->khat_built = c->chol_done = c->pre_done = c->mbcg_done = false;
   c->sgpr = (in->mode == BBMM_MODE_SGPR);
-  c->sgpr_built = false;
+  c->sgpr_built = c->gram_built = false;
   c->far_x = false;
   c->m = c->sgpr ? (int)in->m : 0;
   c->mp = ((c->m + 255) / 256) * 256;

@@ -70,6 +70,20 @@ struct VpShape {
   int max_slots;   // host-side knowledge: the largest slot count of any row (0 = not known)
 };
 
+// The projected form of an SGPR iteration (see kernels_sgpr.hip): what its update kernels take besides the blocks.
+// T = A^T D and S = A^T R are carried along with D and R, H = (A^T A) T.
+struct SgprLoop {
+  const double* Vp;      // partial sums of A T
+  VpShape shape;
+  int np, mp;
+  const double* gram;    // A^T A (mp x mp)
+  double *T4, *S, *H;    // T quad-swizzled, S and H row-major (mp x ld)
+  const double* W4;      // A^T L, quad-swizzled, ldw columns
+  int ldw;
+  double* pdv;           // partial rows of d^T K_hat d = sigma^2 |d|^2 + |T|^2
+  int nb_ur, nb_zd;      // blocks on the n x c blocks; the ones after them work on the mp rows
+};
+
 // ---- launchers implemented in kernels_vec.hip ---------------------------------------------
 // n x c blocks (U, R, V, Z0, D4, Vp) and the factor L are fp64; kernel matrix and X copies are fp32.
 void launch_fill_f64(hipStream_t s, double* p, size_t count, double v);
@@ -129,9 +143,11 @@ void launch_fin_zd(hipStream_t s, int n, int c, int kp, const double* R, const d
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
-               double* alpha_hist, double* beta_hist, double* resid_hist, bool finish = true);
+               double* alpha_hist, double* beta_hist, double* resid_hist, bool finish = true, const SgprLoop* proj = nullptr);
 void launch_zd(hipStream_t s, int init, int n, int ld, int kp, double noise, const double* R,
-               const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks);
+               const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks, const SgprLoop* proj = nullptr);
+// S and the first |T|^2 from T = A^T z (proj.nb_zd as launch_zd's nblocks)
+void launch_sgpr_first(hipStream_t s, int ld, int kp, const SgprLoop& proj, const DevState* st);
 void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, const double* R,
                          const double* L, double* Z, DevState* st, int nblocks);
 void launch_cross_block(hipStream_t s, const float* X, const float* Xs, int n, int ns, int ld, HypArgs hyp,
@@ -170,6 +186,8 @@ void launch_sgpr_qdiag(hipStream_t s, const float* A, int n, int mp, double* qdi
 void launch_sgpr_mid(hipStream_t s, const double* Tp, VpShape shape, int mp, int ld, const DevState* st,
                      double* T4);
 void launch_sgpr_mid_rows(hipStream_t s, const double* Tp, VpShape shape, int mp, int ld, double* T);
+void launch_cols_to_d4(hipStream_t s, const double* src, int n, int np, int cols, int ld, double* D4);
+void launch_sgpr_gram(hipStream_t s, const float* A, int np, int mp, int num_cus, double* scratch, double* gram);
 void launch_sgpr_pick(hipStream_t s, const float* A, int mp, const double* arg_in, int npart,
                       double* T4, int forced);
 

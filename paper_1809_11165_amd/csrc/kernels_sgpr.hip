@@ -495,6 +495,97 @@ __global__ void k_rows_to_d4(const double* __restrict__ src, int n, int np, int 
   D4[d4_index(i, q, ld)] = (i < n) ? src[idx] : 0.0;
 }
 
+// The first `cols` columns of a row-major block with that stride, quad-swizzled, zero where nothing is.
+__global__ void k_cols_to_d4(const double* __restrict__ src, int n, int np, int cols, int ld, double* __restrict__ D4) {
+  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (size_t)np * ld) return;
+  int i = (int)(idx / ld), q = (int)(idx % ld);
+  D4[d4_index(i, q, ld)] = (i < n && q < cols) ? src[(size_t)i * cols + q] : 0.0;
+}
+
+// ------------------------------------------------------------------- A^T A ---
+// A^T A in fp64 from the fp32 root (products of two entries are exact), for the projected iteration.
+// Workgroup: 128 x 128 columns of one slab of points, 64 x 64 per wave; pairs of column blocks bi <= bj only (the
+// wave below the diagonal of a diagonal block has nothing to do).  A lane loads four adjacent columns of one
+// point: they are the operands of four 16 x 16 tiles, tile u taking the columns 4 m + u.  Bound by the fp64
+// matrix pipe (16 MFMAs of 64 cycles per 2 KB of loads), so no LDS; a slab is dealt to one XCD with all its
+// pairs, which walk it together and share it in that XCD's L2.
+constexpr int kGramPf = 4;       // steps of four points requested ahead
+
+__global__ __launch_bounds__(256, 2) void k_sgpr_gram(const float* __restrict__ A, int np, int mp, int nslab,
+                                                      double* __restrict__ part) {
+  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, jc = lane & 15;
+  int nb = mp / 128, pairs = nb * (nb + 1) / 2;
+  int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+  int slab = (seq / pairs) * 8 + xcd, pair = seq % pairs;
+  int bi = 0, left = pair;
+  while (left >= nb - bi) {
+    left -= nb - bi;
+    ++bi;
+  }
+  int bj = bi + left, wi = wave >> 1, wj = wave & 1;
+  if (bi == bj && wi > wj) return;
+  int steps = np / 4;                                    // np is a multiple of 256
+  int s0 = (int)((long long)(steps / kGramPf) * slab / nslab) * kGramPf;
+  int s1 = (int)((long long)(steps / kGramPf) * (slab + 1) / nslab) * kGramPf;
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[u][v] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  const float* pa = A + (size_t)g * mp + bi * 128 + wi * 64 + 4 * jc;
+  const float* pb = A + (size_t)g * mp + bj * 128 + wj * 64 + 4 * jc;
+  float4 av[kGramPf], bv[kGramPf];
+#pragma unroll
+  for (int p = 0; p < kGramPf; ++p) {
+    size_t row = (size_t)4 * min(s0 + p, steps - 1) * mp;
+    av[p] = *(const float4*)(pa + row);
+    bv[p] = *(const float4*)(pb + row);
+  }
+  for (int sb = s0; sb < s1; sb += kGramPf) {
+#pragma unroll
+    for (int p = 0; p < kGramPf; ++p) {
+      double a[4] = {av[p].x, av[p].y, av[p].z, av[p].w}, b[4] = {bv[p].x, bv[p].y, bv[p].z, bv[p].w};
+      size_t row = (size_t)4 * min(sb + p + kGramPf, steps - 1) * mp;
+      av[p] = *(const float4*)(pa + row);
+      bv[p] = *(const float4*)(pb + row);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[u][v] = mfma16d(a[u], b[v], acc[u][v]);
+    }
+  }
+  double* out = part + ((size_t)slab * pairs + pair) * (128 * 128);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      *(f64x4*)(out + (size_t)(wi * 64 + 4 * (4 * r + g) + u) * 128 + wj * 64 + 4 * jc) =
+          (f64x4){acc[u][0][r], acc[u][1][r], acc[u][2][r], acc[u][3][r]};
+}
+
+// The slabs' sums, both triangles.
+__global__ __launch_bounds__(256) void k_sgpr_gram_sum(const double* __restrict__ part, int mp, int nslab, double* __restrict__ gram) {
+  int nb = mp / 128, pairs = nb * (nb + 1) / 2;
+  int pair = blockIdx.x / 64, e = (blockIdx.x % 64) * 256 + threadIdx.x;
+  int bi = 0, left = pair;
+  while (left >= nb - bi) {
+    left -= nb - bi;
+    ++bi;
+  }
+  int bj = bi + left, a = bi * 128 + e / 128, b = bj * 128 + e % 128;
+  if (bi == bj && (e / 128) / 64 > (e % 128) / 64) return;   // (not computed: the mirror writes it)
+  double s = 0.0;
+  for (int sl = 0; sl < nslab; sl += 8) {                    // nslab is a multiple of 8
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[((size_t)(sl + u) * pairs + pair) * (128 * 128) + e];
+    s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+  }
+  gram[(size_t)a * mp + b] = s;
+  gram[(size_t)b * mp + a] = s;
+}
+
 // forward: B = G^{-1} T,  B[a][q] = sum_{b <= a} Ginv[a][b] T[b][q]   (mp x ld, row-major)
 __global__ void k_sgpr_fsolve(const double* __restrict__ Ginv, const double* __restrict__ T, int mp,
                               int ld, double* __restrict__ B) {
@@ -817,6 +908,30 @@ void launch_sgpr_pick(hipStream_t s, const float* A, int mp, const double* arg_i
 void launch_rows_to_d4(hipStream_t s, const double* src, int n, int np, int ld, double* D4) {
   size_t total = (size_t)np * ld;
   k_rows_to_d4<<<(int)((total + 255) / 256), 256, 0, s>>>(src, n, np, ld, D4);
+}
+
+void launch_cols_to_d4(hipStream_t s, const double* src, int n, int np, int cols, int ld, double* D4) {
+  size_t total = (size_t)np * ld;
+  k_cols_to_d4<<<(int)((total + 255) / 256), 256, 0, s>>>(src, n, np, cols, ld, D4);
+}
+
+// scratch: room for mp x np doubles.  Slabs per XCD so that its workgroups (two per compute unit) come in whole rounds,
+// none below 256 points.
+void launch_sgpr_gram(hipStream_t s, const float* A, int np, int mp, int num_cus, double* scratch, double* gram) {
+  int nb = mp / 128, pairs = nb * (nb + 1) / 2, slots = num_cus / 4;
+  int most = np / 2048, best = 1;
+  while (most > 1 && (size_t)most * 8 * pairs * (128 * 128) > (size_t)mp * np) --most;
+  double best_fill = 0.0;
+  for (int k = 1; k <= most && k * pairs <= 16 * slots; ++k) {
+    int rounds = (k * pairs + slots - 1) / slots;
+    double fill = (double)(k * pairs) / ((double)rounds * slots);
+    if (fill > best_fill + 0.01) {
+      best_fill = fill;
+      best = k;
+    }
+  }
+  k_sgpr_gram<<<best * 8 * pairs, 256, 0, s>>>(A, np, mp, best * 8, scratch);
+  k_sgpr_gram_sum<<<pairs * 64, 256, 0, s>>>(scratch, mp, best * 8, gram);
 }
 
 void launch_sgpr_bsolve(hipStream_t s, const double* Ginv, const double* T, int mp, int ld, double* B) {

@@ -962,14 +962,46 @@ __device__ inline double alpha_from(int active, double rho, double dv, int q, in
 //      A wave takes 4 rows per step: lane l holds element (row l/16, column l%16 [+16]) of the
 //      blocks, which is exactly the B operand of an fp64 MFMA whose A operand is the same four
 //      rows of L, so L^T R costs one load of L per 16 columns of L instead of one per entry.
-template <int KP, int NQ>
+//      PROJ (projected SGPR iteration): V = A T + sigma^2 D comes straight from the partial sums of A T (one or two
+//      per row), and the blocks after the first proj.nb_ur leave H = (A^T A) T, a tile of 16 rows each, its terms
+//      split over the waves: 8 MB of A^T A from the caches beside a pass over 450 MB, in compute units that pass
+//      leaves free.
+__device__ inline void sgpr_gram_rows(const SgprLoop& pj, int tile, int nq, double (*stage)[256]) {
+  int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane & 15, g = lane >> 4, ld = 16 * nq;
+  int share = pj.mp / 16, k0 = wave * share;             // mp is a multiple of 256: whole chunks of 16 rows
+  for (int qb = 0; qb < nq; ++qb) {
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int kc = k0; kc < k0 + share; kc += 16) {
+      double a[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        int k = kc + 4 * u;
+        a[u] = pj.gram[(size_t)(k + g) * pj.mp + tile * 16 + q];   // = (A^T A)[tile * 16 + q][k + g]
+        b[u] = pj.T4[d4_index(k + g, qb * 16 + q, ld)];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = mfma16d(a[u], b[u], acc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) stage[wave][(4 * r + g) * 16 + q] = acc[r];
+    __syncthreads();
+    if ((int)threadIdx.x < 256) {
+      double t = 0.0;
+      for (int w = 0; w < UT / 64; ++w) t += stage[w][threadIdx.x];
+      pj.H[(size_t)(tile * 16 + (int)threadIdx.x / 16) * ld + qb * 16 + (int)threadIdx.x % 16] = t;
+    }
+  }
+}
+
+template <int KP, int NQ, bool PROJ>
 __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
                                                  const double* __restrict__ D4,
                                                  const double* __restrict__ V,
                                                  double* __restrict__ U, double* __restrict__ R,
                                                  const double* __restrict__ L, DevState* st,
                                                  const double* __restrict__ partial_dv, int nb_dv,
-                                                 double* __restrict__ partial) {
+                                                 double* __restrict__ partial, SgprLoop proj) {
   constexpr int LD = 16 * NQ;
   constexpr int MB = (KP + 15) / 16;
   constexpr int NW = UT / 64;
@@ -979,6 +1011,13 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
   int q = lane & 15, g = lane >> 4;
   // state reads are requested together with the first partial sums (one memory round trip)
   int done = st->done;
+  const int nb_main = PROJ ? proj.nb_ur : (int)gridDim.x;
+  if (PROJ && (int)blockIdx.x >= nb_main) {
+    if (!done) sgpr_gram_rows(proj, (int)blockIdx.x - nb_main, NQ, stage);
+    return;
+  }
+  double addD = 0.0;
+  if (PROJ) addD = st->loop_addD;
   double alpha[NQ], s_rho[NQ];
   int s_active[NQ];
 #pragma unroll
@@ -1038,10 +1077,19 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
   }
   // RU row quads per loop trip, all their loads requested before the first use
   constexpr int RU = (NQ == 1) ? 4 : 2;
-  int gw = blockIdx.x * NW + wave, nw = gridDim.x * NW;
+  int gw = blockIdx.x * NW + wave, nw = nb_main * NW;
   for (int ib = 4 * gw; ib < n; ib += 4 * nw * RU) {   // wave-uniform bounds: MFMA needs all lanes
     double dd[RU][NQ], uu[RU][NQ], vv[RU][NQ], rv[RU][NQ], la[RU][MB > 0 ? MB : 1];
+    double v2[PROJ ? RU : 1][NQ];
+    int ns[PROJ ? RU : 1];
     bool ok[RU];
+    if (PROJ) {
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        int i = ib + u * 4 * nw + g;
+        ns[u] = i < n ? proj.shape.nseg[i / proj.shape.seg_cols] : 0;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < RU; ++u) {
       int i = ib + u * 4 * nw + g;
@@ -1056,7 +1104,13 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
           if (!init) {
             dd[u][qb] = D4[d4_index(i, col, LD)];
             uu[u][qb] = U[idx];
-            vv[u][qb] = V[idx];
+            if (PROJ) {
+              const double* vp = proj.Vp + (size_t)i * LD + perm16(col);
+              vv[u][qb] = vp[0];
+              v2[u][qb] = ns[u] > 1 ? vp[(size_t)proj.np * LD] : 0.0;
+            } else {
+              vv[u][qb] = V[idx];
+            }
           }
         }
       }
@@ -1076,6 +1130,12 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
         double v = rv[u][qb];
         if (!init && ok[u]) {
           U[idx] = uu[u][qb] + alpha[qb] * dd[u][qb];
+          if (PROJ) {
+            vv[u][qb] += v2[u][qb];
+            for (int sl = 2; sl < ns[u]; ++sl)
+              vv[u][qb] += proj.Vp[((size_t)sl * proj.np + i) * LD + perm16(qb * 16 + q)];
+            vv[u][qb] += addD * dd[u][qb];
+          }
           v = v - alpha[qb] * vv[u][qb];
           R[idx] = v;
         }
@@ -1090,7 +1150,7 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
   }
   // ---- block reduction over the waves, 256 values (16 rows of L^T R x 16 columns) per round ----
   auto pout = [&](int e, int col) {   // four columns' entries of a block side by side, as k_ur_fin reads them
-    return partial + (((size_t)(col >> 2) * gridDim.x + blockIdx.x) * (KP + 1) + e) * 4 + (col & 3);
+    return partial + (((size_t)(col >> 2) * nb_main + blockIdx.x) * (KP + 1) + e) * 4 + (col & 3);
   };
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
@@ -1288,17 +1348,65 @@ __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double n
 //     A wave takes 16 rows per step: L Qt is KP / 4 fp64 MFMAs whose result register r holds
 //     row 4 r + lane / 16, column lane % 16 -- rows in which R and the quad-swizzled D are
 //     contiguous across the wave.
-//     TRACK: the columns' magnitudes of the new D are left in dmax / dflag for a digit product (a variant of its own
+//     EXTRA 1: the columns' magnitudes of the new D are left in dmax / dflag for a digit product (a variant of its own
 //     and not a flag, whose code every product paid for: n = 1 500, k = 2, 32 columns 6.3 us, 4.6 without).
-template <int KP, int NQ, int MODE, bool TRACK>
+//     EXTRA 2 (projected SGPR iteration): the partial sums of sigma^2 |d|^2 go to proj.pdv, and in the loop the blocks
+//     after the first proj.nb_zd carry T = A^T D along with D (sgpr_direction).
+
+// One entry of S = A^T R and T = A^T D per thread, 256 / ld rows of them per block:
+//   S -= alpha (H + sigma^2 T),  T <- (S - (A^T L) C^{-1} L^T r) / sigma^2 + beta T,
+// the images under A^T of R -= alpha K_hat D and D <- z + beta D (A^T K_hat D = (A^T A + sigma^2 I) T).
+// FIRST: S from T = A^T z instead.  Either way a partial row of |T|^2, after the nb_zd of sigma^2 |d|^2.
+template <int KP, int NQ, bool FIRST>
+__device__ inline void sgpr_direction(const SgprLoop& pj, const DevState* st, double noise, int block) {
+  constexpr int LD = 16 * NQ;
+  __shared__ double sq[VT];
+  int col = threadIdx.x % LD, a = block * (VT / LD) + (int)threadIdx.x / LD;
+  size_t si = (size_t)a * LD + col, ti = d4_index(a, col, LD);
+  double t = pj.T4[ti], w = 0.0;
+#pragma unroll
+  for (int m = 0; m < KP; ++m) w += pj.W4[d4_index(a, m, pj.ldw)] * st->Qt[m * BBMM_MAXC + col];
+  if (FIRST) {
+    pj.S[si] = noise * t + w;
+  } else {
+    double s = pj.S[si] - st->alpha_cur[col] * (pj.H[si] + noise * t);
+    pj.S[si] = s;
+    t = (s - w) / noise + st->beta_cur[col] * t;
+    pj.T4[ti] = t;
+  }
+  sq[threadIdx.x] = t * t;
+  __syncthreads();
+  if ((int)threadIdx.x < LD) {
+    double v = 0.0;
+    for (int r = 0; r < VT / LD; ++r) v += sq[r * LD + threadIdx.x];
+    pj.pdv[(size_t)(pj.nb_zd + block) * LD + threadIdx.x] = v;
+  }
+}
+
+template <int KP, int NQ>
+__global__ __launch_bounds__(VT) void k_sgpr_first(SgprLoop proj, const DevState* __restrict__ st) {
+  if (st->done) return;
+  sgpr_direction<KP, NQ, true>(proj, st, st->loop_noise, blockIdx.x);
+}
+
+template <int KP, int NQ, int MODE, int EXTRA>
 __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __restrict__ R,
                                             const double* __restrict__ L, double* __restrict__ D4,
                                             double* __restrict__ Z, const DevState* __restrict__ st,
-                                            unsigned* __restrict__ dmax, int* __restrict__ dflag) {
+                                            unsigned* __restrict__ dmax, int* __restrict__ dflag, SgprLoop proj) {
   constexpr int LD = 16 * NQ;
   constexpr int KS = KP / 4;
+  constexpr bool TRACK = EXTRA == 1, PROJ = EXTRA == 2;
   if (MODE != 2 && st->done) return;
   if (noise < 0.0) noise = st->loop_noise;
+  const int nblk = PROJ ? proj.nb_zd : (int)gridDim.x;
+  if (PROJ && MODE == 0 && (int)blockIdx.x >= nblk) {
+    sgpr_direction<KP, NQ, false>(proj, st, noise, (int)blockIdx.x - nblk);
+    return;
+  }
+  double dd[NQ];
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) dd[qb] = 0.0;
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int q = lane & 15, g = lane >> 4;
   double beta[NQ];
@@ -1318,7 +1426,7 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
     hi[qb] = 0u;
     flag[qb] = 0;
   }
-  int gw = blockIdx.x * NW + wave, nw = gridDim.x * NW;
+  int gw = blockIdx.x * NW + wave, nw = nblk * NW;
   for (int i0 = 16 * gw; i0 < n; i0 += 16 * nw) {   // wave-uniform bounds: MFMA needs all lanes
     f64x4 acc[NQ];
 #pragma unroll
@@ -1348,9 +1456,27 @@ __global__ __launch_bounds__(VT) void k_zd(int n, double noise, const double* __
             else d = z + beta[qb] * D4[di];
             D4[di] = d;
             if (TRACK) hi[qb] = track_hi(d, hi[qb], flag[qb]);
+            if (PROJ) dd[qb] += d * d;
           }
         }
       }
+    }
+  }
+  if (PROJ) {
+    __shared__ double sdd[NW][LD];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      double v = dd[qb];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (g == 0) sdd[wave][qb * 16 + q] = v;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < LD) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v += sdd[w][threadIdx.x];
+      proj.pdv[(size_t)blockIdx.x * LD + threadIdx.x] = noise * v;
     }
   }
   if (TRACK) {
@@ -2043,11 +2169,19 @@ void launch_dv(hipStream_t s, const double* Vp, VpShape shape, int n, int np, in
 void launch_ur(hipStream_t s, int init, int n, int ld, int c, int kp, double noise, double tol,
                const double* D4, const double* V, double* U, double* R, const double* L, DevState* st,
                const double* partial_dv, int nb_dv, double* partial, int nb_ur, int iter,
-               double* alpha_hist, double* beta_hist, double* resid_hist, bool finish) {
+               double* alpha_hist, double* beta_hist, double* resid_hist, bool finish, const SgprLoop* proj) {
   int nq = ld / 16;
-#define UR_MAIN(KP, NQ) k_ur_main<KP, NQ>
-  DISPATCH_KP_NQ(UR_MAIN, kp, nq, nb_ur, UT, init, n, c, D4, V, U, R, L, st, partial_dv, nb_dv, partial);
+#define UR_MAIN(KP, NQ) k_ur_main<KP, NQ, false>
+#define UR_PROJ(KP, NQ) k_ur_main<KP, NQ, true>
+  if (proj) {
+    SgprLoop pj = *proj;
+    pj.nb_ur = nb_ur;
+    DISPATCH_KP_NQ(UR_PROJ, kp, nq, nb_ur + pj.mp / 16, UT, init, n, c, D4, V, U, R, L, st, partial_dv, nb_dv, partial, pj);
+  } else {
+    DISPATCH_KP_NQ(UR_MAIN, kp, nq, nb_ur, UT, init, n, c, D4, V, U, R, L, st, partial_dv, nb_dv, partial, SgprLoop{});
+  }
 #undef UR_MAIN
+#undef UR_PROJ
   if (!finish) return;
   DISPATCH_KP_T(k_ur_fin, kp, ld / 4, UT, init, ld, c, noise, tol, st, partial, nb_ur, iter, alpha_hist,
                 beta_hist, resid_hist);
@@ -2059,27 +2193,39 @@ void launch_fin_zd(hipStream_t s, int n, int c, int kp, const double* R, const d
   DISPATCH_KP_T(k_fin_zd, kp, nblocks, VT, n, c, R, L, D4, st, partial, nb_ur, iter, alpha_hist, beta_hist, resid_hist)
 }
 
-template <int MODE, bool TRACK>
+template <int MODE, int EXTRA>
 static void zd(hipStream_t s, int n, int ld, int kp, double noise, const double* R, const double* L, double* D4,
-               double* Z0, DevState* st, int nblocks) {
-#define ZD(KP, NQ) k_zd<KP, NQ, MODE, TRACK>
-  DISPATCH_KP_NQ(ZD, kp, ld / 16, nblocks, VT, n, noise, R, L, D4, Z0, st, st->dmax, st->dflag);
+               double* Z0, DevState* st, int nblocks, const SgprLoop& pj) {
+#define ZD(KP, NQ) k_zd<KP, NQ, MODE, EXTRA>
+  DISPATCH_KP_NQ(ZD, kp, ld / 16, nblocks, VT, n, noise, R, L, D4, Z0, st, st->dmax, st->dflag, pj);
 #undef ZD
 }
 
 void launch_zd(hipStream_t s, int init, int n, int ld, int kp, double noise, const double* R,
-               const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks) {
-  if (init && track) zd<1, true>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
-  else if (init) zd<1, false>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
-  else if (track) zd<0, true>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
-  else zd<0, false>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks);
+               const double* L, double* D4, double* Z0, int track, DevState* st, int nblocks, const SgprLoop* proj) {
+  SgprLoop pj = proj ? *proj : SgprLoop{};
+  if (proj) {
+    pj.nb_zd = nblocks;
+    if (init) zd<1, 2>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks, pj);
+    else zd<0, 2>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks + pj.mp * ld / VT, pj);
+  } else if (init && track) zd<1, 1>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks, pj);
+  else if (init) zd<1, 0>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks, pj);
+  else if (track) zd<0, 1>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks, pj);
+  else zd<0, 0>(s, n, ld, kp, noise, R, L, D4, Z0, st, nblocks, pj);
+}
+
+void launch_sgpr_first(hipStream_t s, int ld, int kp, const SgprLoop& proj, const DevState* st) {
+#define FIRST(KP, NQ) k_sgpr_first<KP, NQ>
+  DISPATCH_KP_NQ(FIRST, kp, ld / 16, proj.mp * ld / VT, VT, proj, st);
+#undef FIRST
 }
 
 void launch_psolve_apply(hipStream_t s, int n, int ld, int kp, double noise, const double* R,
                          const double* L, double* Z, DevState* st, int nblocks) {
   int nq = ld / 16;
-#define ZD_APPLY(KP, NQ) k_zd<KP, NQ, 2, false>
-  DISPATCH_KP_NQ(ZD_APPLY, kp, nq, nblocks, VT, n, noise, R, L, (double*)nullptr, Z, st, (unsigned*)nullptr, (int*)nullptr);
+#define ZD_APPLY(KP, NQ) k_zd<KP, NQ, 2, 0>
+  DISPATCH_KP_NQ(ZD_APPLY, kp, nq, nblocks, VT, n, noise, R, L, (double*)nullptr, Z, st, (unsigned*)nullptr, (int*)nullptr,
+                 SgprLoop{});
 #undef ZD_APPLY
 }
 
