@@ -188,9 +188,10 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                other block of bbmm_kernel_mm takes the fp64 form.  Points of X whose scaled square
  *                overflows fp32 call for the fp64 form in both (an mBCG run is then made twice).
  *                2: all products (NaN for such X in bbmm_kernel_mm); 0: none.
- *                The same for BBMM_MODE_MATERIALISED: an mBCG run of at least 8 iterations on at most 12 columns takes its
- *                products from the entries as fixed-point words, half of the matrix, from 10240 rows on, and from
- *                1024 on where the triangle is kept ("khat_sym").  bbmm_solve_logdet_grad then evaluates the words from X
+ *                The same for BBMM_MODE_MATERIALISED: an mBCG run of at least 8 iterations takes its products from the entries as
+ *                fixed-point words: on at most 12 columns half of the matrix, from 11264 rows on, and from
+ *                1024 on where the triangle is kept ("khat_sym"); on 17 to 24 columns (25 to 32) the whole matrix, from 8192
+ *                (16384) rows on, unless the triangle is kept.  bbmm_solve_logdet_grad then evaluates the words from X
  *                (fp64 distances) and builds the fp32 matrix only when a later call asks for it; a matrix built by
  *                bbmm_build_khat is converted, and stays.  bbmm_kernel_mm uses the fp32 matrix (2: the words)
  *   "otf_sym"    the form with fp64 sums.  1 (default): a product of at most 16 columns over at most 32 input

@@ -61,8 +61,15 @@ constexpr int kMatSmallMaxRows = 8192;
 // columns, ms, fp64 products from the whole matrix / from its triangle / words, RBF d = 8: n = 1 100: 1.90 / 3.38 / 3.01; 2 500: 2.04 / 4.79 / 3.51;
 // 6 000: 3.22 / 5.40 / 3.99; 8 500: 4.68 / 6.06 / 4.78; 12 000: 6.72 / 7.62 / 6.41; 16 000: 10.1 / 10.5 / 9.1; 24 000: 19.6 / 18.7 / 16.2;
 // 40 000: 53.2 / 45.9 / 40.2; Matern-5/2 d = 16 and 2 to 12 columns alike.  So the words take over from the triangle at any size that has
-// two panels, and from the whole matrix at 10 240 rows.  Building them costs two products or so.
-constexpr int kWordsTriMinRows = 1024, kWordsMinRows = 10240, kWordsMinIters = 8;
+// two panels, and from the whole matrix at 11 264 rows (at 10 240, 160 iterations, 16.6 / 16.5: not worth other roundings).  Building
+// them costs two products or so.
+// 17 to 32 columns from the whole matrix as words (k_mm_words_wide), 60 iterations, ms, fp64 / words, Matern-5/2 d = 16: 17 columns, n = 6 000:
+// 4.86 / 4.68; 8 000: 6.28 / 5.71; 11 000: 9.79 / 8.73; 14 000: 14.2 / 13.2; 20 000: 26.1 / 19.7; 28 000: 47.4 / 40.4.  24 columns: 4.85 / 4.78;
+// 6.28 / 5.92; 9.73 / 8.99; 14.3 / 13.5; 26.0 / 20.2; 47.4 / 40.5.  32: 4.86 / 4.96; 6.31 / 6.03; 9.81 / 9.99; 14.3 / 14.0; 26.2 / 22.4;
+// 49.0 / 43.1.  13 to 16 columns: the fp64 product is bound by reading the matrix, as that from words would be.
+constexpr int kWordsTriMinRows = 1024, kWordsMinRows = 11264, kWordsMinIters = 8;
+constexpr int kWordsTri = 1, kWordsWhole = 2;
+constexpr int kWordsWholeMinRows = 8192, kWordsWhole32MinRows = 16384;   // up to 24 columns, above
 constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 
 }  // namespace
@@ -109,7 +116,7 @@ struct bbmm_ctx {
   int64_t khat_sym = 0;                      // 1: keep only the upper triangle of K_hat (packed panels)
   bool khat_tri = false;                     // the K_hat currently in memory is such a triangle
   bool khat_mem = false;                     // khat_built is what a caller may use; whether the fp32 matrix is in memory
-  bool words_built = false;                  // K_hat is in memory as digit words (the iteration's products, see kernels_words.hip)
+  int words_built = 0;                       // K_hat is in memory as digit words (kWordsTri / kWordsWhole; the iteration's products, see kernels_words.hip)
   // work list of the product from the triangle
   TriLists sym;                              // ... from the stored triangle (panels of 1024 columns)
   TriLists otft;                             // ... on the fly from X (panels of 512 columns)
@@ -417,15 +424,18 @@ int dig_split_of(const bbmm_ctx* c, int cc) {
 // laid out with the others then).
 bool may_use_digits(const bbmm_ctx* c) { return !c->sgpr && c->np >= kDigMinRows && c->KK <= 4; }
 
-// Whether an iteration of the materialised mode takes its products from digit words.
-bool wants_words(const bbmm_ctx* c, int cc) {
-  return !c->sgpr && c->otf_digits != 0 && !c->far_x && cc <= 12 && c->maxit >= kWordsMinIters &&
-         c->np >= (c->khat_tri ? kWordsTriMinRows : kWordsMinRows);
+// Digit words that an iteration of the materialised mode takes its products from (0: none).
+int wants_words(const bbmm_ctx* c, int cc) {
+  if (c->sgpr || c->otf_digits == 0 || c->far_x || c->maxit < kWordsMinIters) return 0;
+  if (cc <= 12) return c->np >= (c->khat_tri ? kWordsTriMinRows : kWordsMinRows) ? kWordsTri : 0;
+  if (cc <= 16 || c->khat_tri) return 0;
+  int from = c->otf_digits == 2 ? kWordsTriMinRows : cc <= 24 ? kWordsWholeMinRows : kWordsWhole32MinRows;
+  return c->np >= from ? kWordsWhole : 0;
 }
 
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.
 bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
-  if (mode == BBMM_MODE_MATERIALISED) return c->words_built && wants_words(c, cc);
+  if (mode == BBMM_MODE_MATERIALISED) return c->words_built != 0 && c->words_built == wants_words(c, cc);
   return mode == BBMM_MODE_ONTHEFLY && c->otf_sym == 1 && c->otf_digits != 0 && !c->far_x && may_use_digits(c) &&
          dig_split_of(c, cc) <= kMaxSplit;
 }
@@ -512,16 +522,35 @@ int stage_build_khat(bbmm_ctx* c, bool tri) {
                         ptr<float>(c->Khat)))
     return fail(c, BBMM_EINVAL, "unsupported input dimension");
   c->khat_built = c->khat_mem = true;
-  c->words_built = false;                   // (an iteration on it takes its entries)
+  c->words_built = 0;                       // (an iteration on it takes its entries)
   return BBMM_OK;
 }
 
-// K_hat as digit words, for an iteration.  No room for them: c->words_built stays false and the fp32 matrix serves.
-int stage_build_words(bbmm_ctx* c) {
-  if (c->words_built) return BBMM_OK;
+// The fp32 matrix, where a call has done without it so far.
+int need_khat(bbmm_ctx* c) {
+  if (c->khat_mem) return BBMM_OK;
+  int rc = stage_build_khat(c, c->khat_tri);
+  if (rc != BBMM_ENOMEM || !c->words.p) return rc;
+  HIPCHK(c, hipStreamSynchronize(c->stream));   // no room for both
+  c->words_built = 0;
+  HIPCHK(c, hipFree(c->words.p));
+  c->words = Buf{};
+  ++c->alloc_epoch;
+  return stage_build_khat(c, c->khat_tri);
+}
+
+// K_hat as digit words, for an iteration.  No room for them: c->words_built is 0 and the fp32 matrix serves.
+int stage_build_words(bbmm_ctx* c, int kind) {
+  if (c->words_built == kind) return BBMM_OK;
+  if (c->words_built) {                     // the other form, from a call whose X may be gone: by way of the fp32 matrix
+    int rc = need_khat(c);
+    if (rc) return rc;
+    c->words_built = 0;
+  }
+  const bool whole = kind == kWordsWhole;
   size_t np = (size_t)c->np;
   struct { Buf* b; size_t bytes; } want[] = {
-      {&c->words, words_bytes(c->np)}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
+      {&c->words, words_bytes(c->np, whole)}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
   for (auto& w : want) {
     int rc = ensure(c, *w.b, w.bytes);
     if (rc == BBMM_ENOMEM) {
@@ -532,25 +561,12 @@ int stage_build_words(bbmm_ctx* c) {
   }
   if (c->khat_mem)                          // the matrix that the caller has had built
     launch_words_of(c->stream, ptr<float>(c->Khat), (size_t)(c->khat_pw > 0 ? c->khat_pw : c->np), c->khat_tri ? 1 : 0,
-                    c->prob.outputscale, c->n, c->np, ptr<int>(c->words));
+                    c->prob.outputscale, c->n, c->np, whole, ptr<int>(c->words));
   else
-    launch_build_words(c->stream, c->prob.kernel, c->prob.X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st),
+    launch_build_words(c->stream, c->prob.kernel, c->prob.X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st), whole,
                        ptr<double>(c->Xo), ptr<double>(c->sqo), ptr<int>(c->words));
-  c->words_built = true;
+  c->words_built = kind;
   return BBMM_OK;
-}
-
-// The fp32 matrix, where a call has done without it so far.
-int need_khat(bbmm_ctx* c) {
-  if (c->khat_mem) return BBMM_OK;
-  int rc = stage_build_khat(c, c->khat_tri);
-  if (rc != BBMM_ENOMEM || !c->words.p) return rc;
-  HIPCHK(c, hipStreamSynchronize(c->stream));   // no room for both
-  c->words_built = false;
-  HIPCHK(c, hipFree(c->words.p));
-  c->words = Buf{};
-  ++c->alloc_epoch;
-  return stage_build_khat(c, c->khat_tri);
 }
 
 // SGPR: K_UU (fp64) -> Cholesky factor G -> G^{-1}; K_UX (fp64); A^T = G^{-1} K_UX rounded to fp32,
@@ -765,20 +781,32 @@ int stage_mat64(bbmm_ctx* c, int cc, int ld, VpShape* shape) {
 
 // Partial sums of (K/s) D less the diagonal from the digit words.
 int stage_mm_words(bbmm_ctx* c, int cc, int ld, VpShape* shape, double* scaleV, double* addD) {
-  int ng = dig_groups(cc);
-  int rc = ensure_words_plan(c);
-  if (rc) return rc;
-  rc = ensure_vp(c, c->wrd.max_slots, ld);
+  int ng = dig_groups(cc), ns = 0;
+  int rc = BBMM_OK;
+  if (c->words_built == kWordsWhole) {
+    ns = bbmm_plan::wide_split(c->np, c->num_cus, kDigMaxBlocks);
+    rc = ensure_vp(c, ns, ld);
+  } else {
+    rc = ensure_words_plan(c);
+    if (rc) return rc;
+    rc = ensure_vp(c, c->wrd.max_slots, ld);
+  }
   if (rc) return rc;
   rc = ensure_records(c, 0, ng);
   if (rc) return rc;
   launch_digits(c->stream, ptr<double>(c->D4), nullptr, nullptr, c->n, c->np, ld, 0, ng, ptr<DevState>(c->st), nullptr, c->rec.p);
+  *scaleV = c->prob.outputscale;
+  *addD = c->prob.outputscale + c->prob.noise;
+  if (c->words_built == kWordsWhole) {
+    if (launch_mm_words_wide(c->stream, ptr<int>(c->words), c->rec.p, ng, ptr<double>(c->Vp), c->np, ld, ns, ptr<DevState>(c->st)))
+      return fail(c, BBMM_EINVAL, "unsupported block width");
+    *shape = VpShape{ns, nullptr, 1};
+    return BBMM_OK;
+  }
   if (launch_mm_words(c->stream, ptr<int>(c->words), c->rec.p, ng, ptr<double>(c->Vp), c->np, ld, ptr<MmPiece>(c->wrd.pieces),
                       ptr<int>(c->wrd.first0), c->wrd.wgs[0], ptr<int>(c->wrd.base), ptr<DevState>(c->st)))
     return fail(c, BBMM_EINVAL, "unsupported block width");
   *shape = VpShape{0, ptr<int>(c->wrd.tot), BBMM_WORDS_PANEL};
-  *scaleV = c->prob.outputscale;
-  *addD = c->prob.outputscale + c->prob.noise;
   return BBMM_OK;
 }
 
@@ -892,7 +920,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     launch_fill_multi0(s, z);
   }
   if (mode == BBMM_MODE_MATERIALISED && c->khat_built && wants_words(c, cc)) {
-    int rc = stage_build_words(c);
+    int rc = stage_build_words(c, wants_words(c, cc));
     if (rc) return rc;
   }
   int track = uses_digits(c, mode, cc) ? 1 : 0;
@@ -1385,7 +1413,8 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
   while (4 * KK < c->d) KK *= 2;
   c->KK = KK;
   c->dp = 4 * KK;
-  c->khat_mem = c->words_built = false;
+  c->khat_mem = false;
+  c->words_built = 0;
   c->khat_built = c->chol_done = c->pre_done = c->mbcg_done = false;
   c->sgpr = (in->mode == BBMM_MODE_SGPR);
   c->sgpr_built = c->gram_built = false;
@@ -1498,7 +1527,7 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   DevState* st = ptr<DevState>(c->st);
   // (a product with the stored matrix is that of its fp32 entries, unless otf_digits says otherwise)
   if (mode == BBMM_MODE_MATERIALISED && c->otf_digits == 2 && c->khat_built && wants_words(c, (int)cc)) {
-    rc = stage_build_words(c);
+    rc = stage_build_words(c, wants_words(c, (int)cc));
     if (rc) return rc;
   }
   int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || c->otf_digits == 2) ? 1 : 0;
@@ -1850,7 +1879,7 @@ static int solve_call(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out, boo
     // call's own) makes the faster product: 50 iterations at n = 2 500 2.0 ms, 3.5 with words, 4.8 with the triangle.  The fp32
     // matrix is built only if something asks for it (see need_khat).
     c->khat_tri = c->khat_sym != 0 && mat_split_of(c, ld) == 0;
-    if (wants_words(c, cc)) rc = stage_build_words(c);
+    if (int kind = wants_words(c, cc)) rc = stage_build_words(c, kind);
     if (!rc && !c->words_built) rc = stage_build_khat(c, c->khat_tri);
     if (rc) return rc;
     c->khat_built = true;

@@ -262,17 +262,21 @@ int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec
                       double* Vp, int n, int np, int ld, int nsplit, const unsigned* counts, DevState* st);
 // ---- launchers implemented in kernels_words.hip: K_hat as digit words -------------------------
 #define BBMM_WORDS_PANEL 512
-size_t words_bytes(int np);
-// Xo: np * 4 KK doubles, sqo: np doubles (work space); Kw: words_bytes(np)
+// whole: all rows of every panel (for launch_mm_words_wide); otherwise the upper triangle (for launch_mm_words)
+size_t words_bytes(int np, bool whole);
+// Xo: np * 4 KK doubles, sqo: np doubles (work space); Kw: words_bytes(np, whole)
 void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, const DevState* st,
-                        double* Xo, double* sqo, int* Kw);
-// the same from the stored fp32 matrix (layout as for launch_copy_block)
-void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, int* Kw);
+                        bool whole, double* Xo, double* sqo, int* Kw);
+// the same from the stored fp32 matrix (layout as for launch_copy_block; whole: not from a triangle)
+void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, bool whole, int* Kw);
 // Partial sums of (K/s) D without the diagonal of K, up to 12 columns (ld = 16); rec: the digits of D alone (launch_digits with
 // KK = 0, ng = dig_groups(columns) <= 6).  Work list: lay_out_triangle with panels of BBMM_WORDS_PANEL columns, whole, at
 // most kDigMaxBlocks steps per piece.
 int launch_mm_words(hipStream_t s, const int* Kw, const void* rec, int ng, double* Vp, int np, int ld, const MmPiece* pieces,
                     const int* first, int wgs, const int* slot_base, const DevState* st);
+// The same sums for 17 to 32 columns (ld = 32, ng = dig_groups(columns)) from whole words: nsplit row chunks of at most
+// kDigMaxBlocks steps, one partial result each.
+int launch_mm_words_wide(hipStream_t s, const int* Kw, const void* rec, int ng, double* Vp, int np, int ld, int nsplit, const DevState* st);
 int launch_mm_otf(hipStream_t s, int kernel, int KK, const float* Xa, const float* Xb, const float* sq,
                   const double* D4, double* Vp, int np, int ld, int c, int nsplit, const DevState* st);
 // The same product with every pair of tiles (I, J), (J, I) evaluated once and used for both of its

@@ -70,10 +70,10 @@ __device__ __forceinline__ double dig_value(double t, double inv_x, int q, int x
 
 // Accumulators of 16 output columns -> partial results.  acc[q][r]: lane (jc, g) holds pair
 // 16 q + 4 g + r, i.e. right-hand side 2 q + g / 2, weight 4 (g % 2) + r, of output column jc.  T: LDS,
-// 16 x (LD + 1) doubles of the wave.
+// 16 x (LD + 1) doubles of the wave.  q0: block column of the first.
 template <int NG, int LD>
 __device__ __forceinline__ void dig_store(const i32x4 (&acc)[NG], double inv_x, double* __restrict__ T, int jc, int g,
-                                          const DevState* __restrict__ st, double* __restrict__ vrow) {
+                                          const DevState* __restrict__ st, double* __restrict__ vrow, int q0 = 0) {
   constexpr int TP = LD + 1;
 #pragma unroll
   for (int q = 0; q < LD / 2; ++q) {
@@ -94,7 +94,7 @@ __device__ __forceinline__ void dig_store(const i32x4 (&acc)[NG], double inv_x, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       int q = 16 * nq + 4 * r + g;
-      v[r] = dig_value(T[jc * TP + q], inv_x, q, xbad, st);
+      v[r] = dig_value(T[jc * TP + q], inv_x, q0 + q, xbad, st);
     }
     *(f64x4*)(vrow + nq * 16 + g * 4) = v;
   }

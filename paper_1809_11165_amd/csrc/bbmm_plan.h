@@ -44,6 +44,22 @@ inline int split_by_fill(int np, int num_cus, int strips, int want_wgs, double m
   return best;
 }
 
+// Row chunks of the product from whole digit words (strips of 256 columns, one workgroup per compute unit), chunks of at most max_steps
+// 16-row steps: the count with the least time, in steps (0.65 us) -- the rounds' own, about 12 to fill and empty a workgroup's pipeline,
+// and the partial results, which are written and read again (512 bytes a row at 5 TB/s).
+inline int wide_split(int np, int num_cus, int max_steps) {
+  int strips = np / 256, steps = np / 16, best = (steps + max_steps - 1) / max_steps;
+  double least = 0.0;
+  for (int s = best; s <= std::min(kMaxSplit, steps); ++s) {
+    double t = (double)((strips * s + num_cus - 1) / num_cus) * ((steps + s - 1) / s + 12) + (double)s * np / 6400;
+    if (least == 0.0 || t < least) {
+      least = t;
+      best = s;
+    }
+  }
+  return best;
+}
+
 // Workgroups of the materialised product of an np x np matrix (tuned: "mat_wgs", 0 = default).
 // The kernel keeps its own loads in flight, so one workgroup per compute unit already saturates
 // that unit's share of HBM; the plan deals the (strip, row step) units out evenly, so whole rounds

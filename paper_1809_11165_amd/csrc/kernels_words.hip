@@ -9,7 +9,8 @@
 //
 // Layout: panels of BBMM_WORDS_PANEL columns, panel P keeping rows [0, (P + 1) * BBMM_WORDS_PANEL) (the upper triangle, blocks
 // on the diagonal whole); 16-row steps of 32 tiles, a tile (16 x 16) being 1 KB: rows 4 a .. 4 a + 3 of column c are the 16
-// bytes in place (c ^ a) of the tile's a-th 256 bytes.  A column quadruple is then one 16-byte read per lane, and
+// bytes in place (c ^ a) of the tile's a-th 256 bytes.  For blocks of more than 16 columns (k_mm_words_wide) every panel keeps all
+// rows ("whole").  A column quadruple is then one 16-byte read per lane, and
 // a row's four words of a column quadruple four 4-byte reads, both without bank conflicts.  The diagonal is zero here and
 // added afterwards (addD), which keeps it exact.
 #include "bbmm_dig.h"
@@ -20,8 +21,9 @@ namespace {
 constexpr int kWP = BBMM_WORDS_PANEL;
 constexpr int kWTiles = kWP / 16;                            // tiles per 16-row step
 
-// first step of panel P
+// first step of panel P (whole: of np rows each)
 __host__ __device__ inline size_t words_panel_step(int P) { return (size_t)(kWP / 16) * ((size_t)P * (P + 1) / 2); }
+__host__ __device__ inline size_t words_panel_step(int P, int np, int whole) { return whole ? (size_t)(np / 16) * P : words_panel_step(P); }
 
 __device__ inline f64x4 mfma16d(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
@@ -46,17 +48,17 @@ __device__ inline int entry_word(double k) { return ((int)rint(k * (double)kX) +
 // that a lane's four results are four consecutive rows), the kernel function in fp32.  Bound by the stores.
 template <int KIND>
 __global__ __launch_bounds__(256) void k_build_words(const double* __restrict__ Xo, const double* __restrict__ sqo, int n, int np,
-                                                      int KK, int* __restrict__ Kw) {
+                                                      int KK, int whole, int* __restrict__ Kw) {
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int jc = lane & 15, g = lane >> 4;
   int P = blockIdx.x, step = blockIdx.y * 4 + wave;
-  if (step * 16 >= min(np, (P + 1) * kWP)) return;
+  if (step * 16 >= (whole ? np : min(np, (P + 1) * kWP))) return;
   const double* Ar = Xo + (size_t)step * KK * 64 + g * 16 + 4 * (jc & 3) + (jc >> 2);
   double si[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) si[r] = sqo[step * 16 + 4 * g + r];
   int ntiles = min(kWTiles, (np - P * kWP) / 16);
-  int* out = Kw + ((words_panel_step(P) + step) * kWTiles) * 256 + (g * 16 + (jc ^ g)) * 4;
+  int* out = Kw + ((words_panel_step(P, np, whole) + step) * kWTiles) * 256 + (g * 16 + (jc ^ g)) * 4;
   for (int t = 0; t < ntiles; ++t) {
     int cb = P * kWTiles + t;
     const double* Br = Xo + (size_t)cb * KK * 64 + lane;
@@ -81,13 +83,13 @@ __global__ __launch_bounds__(256) void k_build_words(const double* __restrict__ 
 // The same from a stored fp32 matrix (layout as for launch_copy_block), whose entries are s K: an iteration started on a matrix
 // that its caller has had built runs on the entries of that matrix.
 __global__ __launch_bounds__(256) void k_words_of(const float* __restrict__ K, size_t pw, int tri, double inv_s, int n, int np,
-                                                   int* __restrict__ Kw) {
+                                                   int whole, int* __restrict__ Kw) {
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int jc = lane & 15, g = lane >> 4;
   int P = blockIdx.x, step = blockIdx.y * 4 + wave;
-  if (step * 16 >= min(np, (P + 1) * kWP)) return;
+  if (step * 16 >= (whole ? np : min(np, (P + 1) * kWP))) return;
   int ntiles = min(kWTiles, (np - P * kWP) / 16);
-  int* out = Kw + ((words_panel_step(P) + step) * kWTiles) * 256 + (g * 16 + (jc ^ g)) * 4;
+  int* out = Kw + ((words_panel_step(P, np, whole) + step) * kWTiles) * 256 + (g * 16 + (jc ^ g)) * 4;
   for (int t = 0; t < ntiles; ++t) {
     int j = (P * kWTiles + t) * 16 + jc;
     size_t q = (size_t)j / pw;                               // (the panels of a triangle are 1 024 wide: rows up to this step are there)
@@ -406,21 +408,143 @@ __global__ __launch_bounds__(256, 1) void k_mm_words(const int* __restrict__ Kw,
 #endif
 }
 
-}  // namespace
+// Geometry of the product for blocks of 17 to 2 NG columns: a wave owns 64 matrix columns, four waves 256.  H = 2: eight waves, each
+// with half of the block's columns (one wave with all 16 pairs needs 420 registers, of which half are accumulation registers that every
+// matrix instruction's operands have to be copied from: n = 20 000, 32 columns 420 us a product, 332 with two).
+template <int NG, int H>
+struct WideMM {
+  static constexpr int kNJ = 4, kNW = NG / H;                // tiles and pairs per wave
+  static constexpr int kThreads = 256 * H;
+  static constexpr int kSlotK = 4 * kNJ * 1024;              // a 16-row step of the matrix
+  static constexpr int kCopiesK = kNJ / H;
+  static constexpr int kRounds = (NG + 4 * H - 1) / (4 * H);
+  static constexpr int kSlot = kSlotK + kRounds * 4 * H * 1024;   // and the step's digit record
+  static constexpr int kRing = 5;
+  static constexpr int kCopies = kCopiesK + kRounds;         // per wave and step
+  static constexpr int kFirst = kNW / 4 * kNJ;               // matrix instructions of a step ahead of its barrier
+  static_assert(kRing * kSlot <= 160 * 1024 && NG % H == 0 && (H == 1 || kNW == 8), "");
+  static_assert(kRounds * 4 * H * 1024 == bbmm_plan::dig_slot_bytes(0, NG), "the last copy of a record may run past it by this much");
+};
 
-size_t words_bytes(int np) { return words_panel_step((np + kWP - 1) / kWP) * kWTiles * 1024; }
-
-void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, const DevState* st,
-                        double* Xo, double* sqo, int* Kw) {
-  k_prep_words<<<(np + 255) / 256, 256, 0, s>>>(X, n, d, np, KK, hyp, st, Xo, sqo);
-  dim3 grid((np + kWP - 1) / kWP, (np / 16 + 3) / 4);
-  if (kernel == 0) k_build_words<0><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, Kw);
-  else k_build_words<1><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, Kw);
+// out[J] += T^T D[I] for every tile T of the whole matrix, blocks of 17 to 32 columns: 2 NG accumulators a tile for both uses of a tile
+// do not fit the registers.  On the fp64 matrix pipe (k_mm_mat, 32 columns) the product is bound by that pipe: 0.45 ms at
+// n = 20 000, where reading the matrix takes 0.25.  On words the product takes 0.28 ms with 17 to 24 columns, bound by the reading, and 0.33
+// with 32, where a step's reads from LDS (96 KB and 32 KB written) take as long as its matrix instructions.  (Neither a ring of four
+// in place of five nor another pitch of the panels changes these.)
+// A workgroup takes one strip of 256 columns and one chunk of at most kDigMaxBlocks 16-row steps; sums stay in registers.  Matrix and
+// records are copied straight into LDS, four steps ahead.  Behind the first quarter of a step's matrix instructions stand its one
+// barrier and then, dealt out behind single instructions, the copies for five steps on and the operands of the next step.
+// Workgroups of one XCD take neighbouring strips of the same chunk, so that they share its records in that XCD's L2.
+template <int NG, int H>
+__global__ __launch_bounds__(256 * H, 1) void k_mm_words_wide(const int* __restrict__ Kw, const char* __restrict__ rec, double* __restrict__ Vp,
+                                                          int np, int nsplit, int steps_per_split, const DevState* __restrict__ st) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if (st->done) return;
+  using G = WideMM<NG, H>;
+  constexpr int NJ = G::kNJ, NW = G::kNW, LD = 32;
+  __shared__ __align__(1024) char lds[G::kRing * G::kSlot];
+  lds_char* L0 = (lds_char*)lds;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int jc = lane & 15, g = lane >> 4, cw = wave & 3, h = wave >> 2;   // the wave's matrix columns and part of the block
+  const int strips = np / 256, nblk = np / 16;               // np is a multiple of 256
+  const int w = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);   // (whole XCDs, see the launch)
+  if (w >= strips * nsplit) return;
+  const int split = w / strips, strip = w % strips;
+  const int ib0 = split * steps_per_split, nk = min(nblk, ib0 + steps_per_split) - ib0;
+  double* const vout = Vp + ((size_t)split * np + strip * 256 + cw * (16 * NJ)) * LD;
+  if (nk <= 0) {                                             // (a last chunk may be empty: its slot is zero)
+    for (int e = h * 64 + lane; e < 16 * NJ * LD; e += 64 * H) vout[e] = 0.0;
+    return;
+  }
+  const int* kb = Kw + ((words_panel_step(strip / 2, np, 1) + ib0) * kWTiles + (strip & 1) * (4 * NJ)) * 256;
+  __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)kb, 0, ((nk - 1) * kWTiles + 4 * NJ) * 1024, 0x00020000);
+  __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc((void*)(rec + (size_t)ib0 * (NG * 1024)), 0,
+                                                                (int)bbmm_plan::dig_buffer_bytes(nk, 0, NG), 0x00020000);
+  // copy e of step k (past the end the last step comes again: the count of copies stays)
+  auto fetch1 = [&](auto EE, int k, int slot) {
+    constexpr int e = decltype(EE)::value, c = e - G::kCopiesK;
+    if constexpr (e < G::kCopiesK)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(L0 + slot + (wave * G::kCopiesK + e) * 1024), 16,
+                                               lane * 16, min(k, nk - 1) * (kWTiles * 1024) + (wave * G::kCopiesK + e) * 1024, 0, 2);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (__attribute__((address_space(3))) void*)(L0 + slot + G::kSlotK + (c * 4 * H + wave) * 1024),
+                                               16, wave * 1024 + lane * 16, min(k, nk - 1) * (NG * 1024) + c * (4 * H * 1024), 0, 0);
+  };
+  const int colp = cw * (NJ * 1024) + (g * 16 + (jc ^ g)) * 16, recp = G::kSlotK + h * (NW * 1024) + lane * 16;
+  i32x4 acc[NJ][NW], op[2][NW], wk[2][NJ];
+#pragma unroll
+  for (int b = 0; b < NJ; ++b)
+#pragma unroll
+    for (int q = 0; q < NW; ++q) acc[b][q] = (i32x4){0, 0, 0, 0};
+  // operand o of a step: the matrix words of the wave's tiles, then the record's digits
+  auto read1 = [&](auto OO, auto buf, int slot) {
+    constexpr int o = decltype(OO)::value;
+    if constexpr (o < NJ) wk[decltype(buf)::value][o] = *(lds_i32x4)(L0 + slot + colp + o * 1024);
+    else op[decltype(buf)::value][o - NJ] = *(lds_i32x4)(L0 + slot + recp + (o - NJ) * 1024);
+  };
+  auto next = [](int slot) { return slot + G::kSlot == G::kRing * G::kSlot ? 0 : slot + G::kSlot; };
+  static_for<0, G::kRing>([&](auto KK) {
+    static_for<0, G::kCopies>([&](auto EE) { fetch1(EE, decltype(KK)::value, decltype(KK)::value * G::kSlot); });
+  });
+  wait_vm<(G::kRing - 1) * G::kCopies>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  static_for<0, NJ + NW>([&](auto OO) { read1(OO, std::integral_constant<int, 0>{}, 0); });
+  int s_cur = 0, s_next = G::kSlot;
+  auto step = [&](int k, auto buf) {
+    constexpr int B = decltype(buf)::value, M = NJ * NW, M1 = M - G::kFirst;
+    static_for<0, M>([&](auto MM) {
+      constexpr int m = decltype(MM)::value, q = m / NJ, b = m % NJ, i = m - G::kFirst;
+      if constexpr (m == G::kFirst) {
+        // This wave's copies of step k + 1 have landed and its reads of step k are done, and so, behind the barrier, are everybody's.
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        wait_vm<(G::kRing - 2) * G::kCopies>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      acc[b][q] = mfma_i8(op[B][q], wk[B][b], acc[b][q]);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (i >= 0) {
+        static_for<i * G::kCopies / M1, (i + 1) * G::kCopies / M1>([&](auto EE) { fetch1(EE, k + G::kRing, s_cur); });
+        static_for<i * (NJ + NW) / M1, (i + 1) * (NJ + NW) / M1>([&](auto OO) { read1(OO, std::integral_constant<int, 1 - B>{}, s_next); });
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    s_cur = s_next;
+    s_next = next(s_next);
+  };
+#pragma unroll 1
+  for (int k = 0; k + 1 < nk; k += 2) {
+    step(k, std::integral_constant<int, 0>{});
+    step(k + 1, std::integral_constant<int, 1>{});
+  }
+  if (nk & 1) step(nk - 1, std::integral_constant<int, 0>{});
+  __builtin_amdgcn_s_waitcnt(0);                             // copies and reads nobody waited for
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  double* T = (double*)lds + wave * (16 * (LD / H + 1));
+#pragma unroll
+  for (int b = 0; b < NJ; ++b)
+    dig_store<NW, LD / H>(acc[b], 1.0 / (double)kX, T, jc, g, st, vout + (size_t)(16 * b + jc) * LD + h * (LD / H), h * (LD / H));
+#endif
 }
 
-void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, int* Kw) {
+}  // namespace
+
+size_t words_bytes(int np, bool whole) { return words_panel_step((np + kWP - 1) / kWP, np, whole) * kWTiles * 1024; }
+
+void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, const DevState* st,
+                        bool whole, double* Xo, double* sqo, int* Kw) {
+  k_prep_words<<<(np + 255) / 256, 256, 0, s>>>(X, n, d, np, KK, hyp, st, Xo, sqo);
   dim3 grid((np + kWP - 1) / kWP, (np / 16 + 3) / 4);
-  k_words_of<<<grid, 256, 0, s>>>(K, pw, tri, 1.0 / outputscale, n, np, Kw);
+  if (kernel == 0) k_build_words<0><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, whole, Kw);
+  else k_build_words<1><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, whole, Kw);
+}
+
+void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, bool whole, int* Kw) {
+  dim3 grid((np + kWP - 1) / kWP, (np / 16 + 3) / 4);
+  k_words_of<<<grid, 256, 0, s>>>(K, pw, tri, 1.0 / outputscale, n, np, whole, Kw);
 }
 
 int launch_mm_words(hipStream_t s, const int* Kw, const void* rec, int ng, double* Vp, int np, int ld, const MmPiece* pieces,
@@ -430,6 +554,19 @@ int launch_mm_words(hipStream_t s, const int* Kw, const void* rec, int ng, doubl
     case 2: k_mm_words<2><<<wgs, 256, 0, s>>>(Kw, (const char*)rec, Vp, np, ld, pieces, first, slot_base, st); break;
     case 4: k_mm_words<4><<<wgs, 256, 0, s>>>(Kw, (const char*)rec, Vp, np, ld, pieces, first, slot_base, st); break;
     case 6: k_mm_words<6><<<wgs, 256, 0, s>>>(Kw, (const char*)rec, Vp, np, ld, pieces, first, slot_base, st); break;
+    default: return 1;
+  }
+  return 0;
+}
+
+int launch_mm_words_wide(hipStream_t s, const int* Kw, const void* rec, int ng, double* Vp, int np, int ld, int nsplit, const DevState* st) {
+  int steps = np / 16, per = (steps + nsplit - 1) / nsplit;
+  if (ld != 32 || per > kDigMaxBlocks) return 1;
+  int grid = (np / 256 * nsplit + 7) / 8 * 8;
+  switch (ng) {
+    case 9: k_mm_words_wide<9, 1><<<grid, 256, 0, s>>>(Kw, (const char*)rec, Vp, np, nsplit, per, st); break;
+    case 12: k_mm_words_wide<12, 1><<<grid, 256, 0, s>>>(Kw, (const char*)rec, Vp, np, nsplit, per, st); break;
+    case 16: k_mm_words_wide<16, 2><<<grid, 512, 0, s>>>(Kw, (const char*)rec, Vp, np, nsplit, per, st); break;
     default: return 1;
   }
   return 0;

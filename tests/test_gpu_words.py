@@ -1,5 +1,5 @@
-"""GPU: the materialised product from digit words (at most 12 columns, panels of 512 columns, tiles of 16) against fp64
-kernel rows, and the iterations that run on it against those on the fp64 matrix pipe."""
+"""GPU: the materialised product from digit words (at most 12 columns: the triangle, panels of 512 columns, tiles of 16; 17 to 32:
+the whole matrix, strips of 256) against fp64 kernel rows, and the iterations that run on it against those on the fp64 matrix pipe."""
 import numpy as np
 import pytest
 
@@ -56,6 +56,10 @@ def _rows(w, rows, M):
 @pytest.mark.parametrize("n,c", [(769, 11), (1024, 1), (1025, 4), (1100, 5), (1280, 8), (1281, 9), (1536, 12), (2300, 11), (5000, 3), (9000, 11)])
 @pytest.mark.parametrize("kernel,d", [(inputs.RBF, 3), (inputs.MATERN52, 20)])
 def test_words_product_against_fp64_rows(ctx, n, c, kernel, d):
+    _check_product(ctx, n, c, kernel, d)
+
+
+def _check_product(ctx, n, c, kernel, d):
     w = _workload(n, d, kernel)
     ctx.bbmm_setup(_problem(w))
     ctx.bbmm_build_khat()
@@ -73,7 +77,16 @@ def test_words_product_against_fp64_rows(ctx, n, c, kernel, d):
     assert np.linalg.norm(V - V64) < 2e-6 * np.linalg.norm(V64)
 
 
-@pytest.mark.parametrize("n,t,sym", [(1100, 10, 1), (2100, 3, 1), (10300, 7, 0)])
+# first size, an odd number of strips, chunks of equal and unequal length, an odd number of steps in a chunk; the narrowest and widest
+# block of every compiled width
+@pytest.mark.parametrize("n,c", [(1025, 17), (3841, 17), (4097, 18), (4400, 19), (5000, 24), (7001, 25), (9000, 32), (12300, 21)])
+@pytest.mark.parametrize("kernel,d", [(inputs.RBF, 3), (inputs.MATERN52, 20)])
+def test_whole_words_product_against_fp64_rows(ctx, n, c, kernel, d):
+    ctx.bbmm_tune("khat_sym", 0)
+    _check_product(ctx, n, c, kernel, d)
+
+
+@pytest.mark.parametrize("n,t,sym", [(1100, 10, 1), (2100, 3, 1), (11300, 7, 0), (8000, 16, 0), (16300, 31, 0)])
 def test_iteration_on_words_matches_the_fp64_one(ctx, n, t, sym):
     """Both runs are converged, so they solve systems whose entries differ by their evaluation: at most 2^-19 of themselves (the fp32
     distances of the stored matrix lose up to four units of 2^-24 of |x|^2 + |x'|^2 <= 16 here), which moves the solution by
@@ -98,7 +111,7 @@ def test_iteration_on_words_matches_the_fp64_one(ctx, n, t, sym):
 
 
 def test_the_fp32_matrix_is_there_after_a_call_that_did_without(ctx):
-    n = 10300
+    n = 11300
     w = _workload(n, 4, inputs.RBF, t=4, k=5, iters=10, noise=0.5)
     ctx.bbmm_solve_logdet_grad(_problem(w))
     K = ctx.bbmm_khat_block(n - 40, 40, 0, 300).cpu().numpy()
@@ -112,6 +125,28 @@ def test_the_fp32_matrix_is_there_after_a_call_that_did_without(ctx):
     Kr[np.arange(3), rows] += w.noise
     ref = Kr @ M.cpu().numpy().astype(np.float64)
     assert np.max(np.abs(V[rows] - ref)) < 1e-4
+
+
+def test_words_of_the_other_form_come_from_the_fp32_matrix(ctx):
+    """A call leaves the triangle's words (5 columns, nothing in fp32) or the whole matrix's (20); variances at 20 and at 5 points then need
+    the other form, whose entries are those of the fp32 matrix: the same bits as on a matrix built by itself."""
+    from paper_1809_11165_amd import binding
+    n = 11300
+    ctx.bbmm_tune("khat_sym", 0)          # (the fixture's default is the triangle)
+    w4, w19 = (_workload(n, 4, inputs.RBF, t=t, k=5, iters=30, noise=0.5) for t in (4, 19))
+    Xs = torch.from_numpy(np.ascontiguousarray(w4.X[:20] + np.float32(0.1))).cuda()
+    with_own = binding.Context(0)
+    for w, ns in ((w4, 20), (w19, 5)):
+        ctx.bbmm_solve_logdet_grad(_problem(w))
+        got = ctx.bbmm_predict_var(inputs.MATERIALISED, Xs[:ns])[0]
+        again = ctx.bbmm_predict_var(inputs.MATERIALISED, Xs[:ns])[0]
+        with_own.bbmm_setup(_problem(w))
+        with_own.bbmm_build_khat()
+        with_own.bbmm_pivoted_cholesky()
+        with_own.bbmm_precond_setup()
+        ref = with_own.bbmm_predict_var(inputs.MATERIALISED, Xs[:ns])[0]
+        assert torch.equal(got, ref) and torch.equal(got, again)
+    with_own.close()
 
 
 def test_points_too_far_out_take_the_fp64_products(ctx):

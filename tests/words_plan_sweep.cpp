@@ -1,6 +1,7 @@
 // CPU check of the work lists of the digit-word product (csrc/bbmm_plan.h, lay_out_triangle with whole panels and bounded pieces):
 // every step of every panel, the blocks on the diagonal included, is dealt out once, no piece is longer than the
-// accumulators allow, every workgroup has work, and slots are in range and used once.
+// accumulators allow, every workgroup has work, and slots are in range and used once.  Row chunks of the product from whole words
+// (wide_split) are no longer than the accumulators allow and few enough for their partial results.
 #include <cstdio>
 #include <cstdlib>
 #include <set>
@@ -45,6 +46,11 @@ int main() {
         require(L.tot[P] == L.cnt[P] + S - 1 - P && L.tot[P] <= L.max_slots, "tot", np, want);
       }
       require(seen.size() == steps, "steps missing", np, want);
+    }
+  for (int np = 256; np <= 300000; np += 256)
+    for (int cus : {8, 104, 256, 304}) {
+      int ns = wide_split(np, cus, kMax), per = (np / 16 + ns - 1) / ns;
+      require(ns >= 1 && ns <= kMaxSplit && per <= kMax, "row chunks", np, cus);
     }
   std::printf("OK %lld checks\n", checks);
   return 0;
