@@ -156,7 +156,7 @@ TRAFFIC_NOTE = ("HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SI
 
 def words_of(n, c, sym):
     """Whether the library's default materialised products of an iteration run on digit words (8-bit matrix pipe)."""
-    return c <= 12 and -(-n // 256) * 256 > (8192 if sym else 10239)
+    return c <= 12 and -(-n // 256) * 256 > (8192 if sym else 11263)
 
 
 def roofline_words(n, c, mm_ms, launches):
@@ -200,7 +200,7 @@ def roofline_sym(n, c, mm_ms, launches, config):
 
 
 def roofline_mat(n, c, mm_ms, launches, config):
-    """Whole K_hat streamed once per product: algorithmic bytes 4 n^2 (K_hat) + 8 n c (block in and out); beyond 10 240 rows and up
+    """Whole K_hat streamed once per product: algorithmic bytes 4 n^2 (K_hat) + 8 n c (block in and out); from 11 264 rows on and up
     to 12 columns an iteration reads half of that (digit words), which the bytes per second of the whole then count too."""
     words = words_of(n, c, False)
     alg_bytes = 4.0 * n * n + 8.0 * n * c
