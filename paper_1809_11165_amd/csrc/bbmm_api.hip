@@ -526,18 +526,20 @@ int stage_build_khat(bbmm_ctx* c, bool tri) {
   return BBMM_OK;
 }
 
-// The fp32 matrix, where a call has done without it so far.
-int need_khat(bbmm_ctx* c) {
-  if (c->khat_mem) return BBMM_OK;
-  int rc = stage_build_khat(c, c->khat_tri);
+// The fp32 matrix; where there is no room for it beside words of this or an earlier problem, in their place.
+int build_khat_first(bbmm_ctx* c, bool tri) {
+  int rc = stage_build_khat(c, tri);
   if (rc != BBMM_ENOMEM || !c->words.p) return rc;
-  HIPCHK(c, hipStreamSynchronize(c->stream));   // no room for both
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   c->words_built = 0;
   HIPCHK(c, hipFree(c->words.p));
   c->words = Buf{};
   ++c->alloc_epoch;
-  return stage_build_khat(c, c->khat_tri);
+  return stage_build_khat(c, tri);
 }
+
+// The same where a call has done without it so far.
+int need_khat(bbmm_ctx* c) { return c->khat_mem ? BBMM_OK : build_khat_first(c, c->khat_tri); }
 
 // K_hat as digit words, for an iteration.  No room for them: c->words_built is 0 and the fp32 matrix serves.
 int stage_build_words(bbmm_ctx* c, int kind) {
@@ -548,9 +550,14 @@ int stage_build_words(bbmm_ctx* c, int kind) {
     c->words_built = 0;
   }
   const bool whole = kind == kWordsWhole;
+  // (beside the fp32 matrix only where that leaves the caller a quarter of the device's memory)
+  size_t free_b = 0, total_b = 0, bytes = words_bytes(c->np, whole);
+  if (c->khat_mem && bytes > c->words.cap &&
+      (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b + c->words.cap < bytes + total_b / 4))
+    return BBMM_OK;
   size_t np = (size_t)c->np;
   struct { Buf* b; size_t bytes; } want[] = {
-      {&c->words, words_bytes(c->np, whole)}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
+      {&c->words, bytes}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
   for (auto& w : want) {
     int rc = ensure(c, *w.b, w.bytes);
     if (rc == BBMM_ENOMEM) {
@@ -1473,7 +1480,7 @@ int bbmm_setup(bbmm_ctx* c, const bbmm_problem* in) {
 int bbmm_build_khat(bbmm_ctx* c) {
   int rc = check_ready(c);
   if (rc) return rc;
-  rc = stage_build_khat(c, c->khat_sym != 0);
+  rc = build_khat_first(c, c->khat_sym != 0);
   if (rc) return rc;
   HIPCHK(c, hipGetLastError());
   return BBMM_OK;
@@ -1880,7 +1887,7 @@ static int solve_call(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out, boo
     // matrix is built only if something asks for it (see need_khat).
     c->khat_tri = c->khat_sym != 0 && mat_split_of(c, ld) == 0;
     if (int kind = wants_words(c, cc)) rc = stage_build_words(c, kind);
-    if (!rc && !c->words_built) rc = stage_build_khat(c, c->khat_tri);
+    if (!rc && !c->words_built) rc = build_khat_first(c, c->khat_tri);
     if (rc) return rc;
     c->khat_built = true;
   } else if (in->mode == BBMM_MODE_SGPR) {
