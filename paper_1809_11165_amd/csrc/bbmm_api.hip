@@ -757,11 +757,10 @@ int mat64_reserve(bbmm_ctx* c, int cc, int ld) {
   return rc ? rc : ensure_vp(c, c->plan_slots[(ld == 32) ? 1 : (cc <= 12 ? 2 : 0)], ld);
 }
 
-// Product with the stored matrix on the fp64 matrix pipe.
+// Product with the stored matrix on the fp64 matrix pipe (need_khat first: a recorded iteration loop must not build it).
 int stage_mat64(bbmm_ctx* c, int cc, int ld, VpShape* shape) {
-  int rc = need_khat(c);
-  if (rc) return rc;
-  rc = mat64_reserve(c, cc, ld);
+  if (!c->khat_mem) return fail(c, BBMM_EINVAL, "internal: the fp32 matrix is not in memory");
+  int rc = mat64_reserve(c, cc, ld);
   if (rc) return rc;
   if (c->khat_tri) {
     if (launch_mm_sym(c->stream, ptr<float>(c->Khat), ptr<double>(c->D4), ptr<double>(c->Vp), c->np, ld, cc,
@@ -850,10 +849,9 @@ int stage_mm(bbmm_ctx* c, int mode, int cc, int ld, int digits, VpShape* shape, 
   return BBMM_OK;
 }
 
-// By k_mm_rows: V <- K_hat D and the partial sums of d^T v, or the caller's fp32 block from M or D4.
+// By k_mm_rows (need_khat first): V <- K_hat D and the partial sums of d^T v, or the caller's fp32 block from M or D4.
 int stage_mm_rows(bbmm_ctx* c, const float* M, int cc, float* out) {
-  int rc = need_khat(c);
-  if (rc) return rc;
+  if (!c->khat_mem) return fail(c, BBMM_EINVAL, "internal: the fp32 matrix is not in memory");
   if (launch_mm_rows(c->stream, ptr<float>(c->Khat), c->np, c->n, c->khat_pw, ptr<double>(c->D4), M, cc, ptr<double>(c->V),
                      ptr<double>(c->gpartial), out, ptr<DevState>(c->st)))
     return fail(c, BBMM_EINVAL, "unsupported layout of the stored matrix");
@@ -931,6 +929,10 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     if (rc) return rc;
   }
   int track = uses_digits(c, mode, cc) ? 1 : 0;
+  if (mode == BBMM_MODE_MATERIALISED && c->khat_built && !track) {   // ahead of the loop: a replayed one builds nothing, and a
+    int rc = need_khat(c);                                           // recorded one would build it with this problem's scalars
+    if (rc) return rc;
+  }
   const bool by_rows = mode == BBMM_MODE_MATERIALISED && !track && mat_rows(c, ld);
   const bool proj = mode == BBMM_MODE_SGPR && sgpr_projected(c);
   SgprLoop pj = {};
@@ -1538,6 +1540,10 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
     if (rc) return rc;
   }
   int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || c->otf_digits == 2) ? 1 : 0;
+  if (mode == BBMM_MODE_MATERIALISED && !digits && c->khat_built) {
+    rc = need_khat(c);
+    if (rc) return rc;
+  }
   if (mode == BBMM_MODE_MATERIALISED && !digits && mat_rows(c, ld)) {
     bool packed = c->np > kMatRowsUnpackedMax;
     if (packed) launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), 0, st);
