@@ -136,7 +136,7 @@ struct bbmm_ctx {
   // earlier one (same sizes, mode, tuning values and buffers; the hyperparameters are read from the
   // device state, so a training loop replays one graph).
   int64_t use_graph = 0;                     // "loop_graph": 0 = always launch kernel by kernel
-  uint64_t alloc_epoch = 0, tune_epoch = 0;  // bumped by every (re)allocation / bbmm_tune call
+  uint64_t alloc_epoch = 0, tune_epoch = 0;  // bumped by every (re)allocation and every work list laid out anew / by every bbmm_tune call
   hipStream_t cap = nullptr;                 // capture stream (the caller's may be the null stream)
   struct LoopGraph {
     LoopKey key;
@@ -307,6 +307,7 @@ int make_plan(bbmm_ctx* c, int rows_p, int cols_p, int ld, int wgs, int slot_cap
   std::vector<int> nseg;
   if (const char* what = bbmm_plan::lay_out_plan(rows_p, cols_p, ld, wgs, slot_cap, plan, nseg))
     return fail(c, BBMM_EINVAL, what);
+  ++c->alloc_epoch;                         // a loop recorded on the list that is here must not run on the new one
   int rc = ensure(c, plan_buf, sizeof(MmPlan) * plan.size());
   if (rc) return rc;
   rc = ensure(c, nseg_buf, sizeof(int) * nseg.size());
@@ -320,6 +321,7 @@ int make_plan(bbmm_ctx* c, int rows_p, int cols_p, int ld, int wgs, int slot_cap
 int ensure_mat_plans(bbmm_ctx* c) {
   if (c->plan_np == c->np && c->plan_tune == c->mat_wgs) return BBMM_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still read the old plans
+  c->plan_np = 0;                           // (until all of them are there)
   // plans: 0 = 16-column block, 1 = 32-column block, 2 = 16-column block with at most 12 columns in use
   for (int v = 0; v < 3; ++v) {
     int ld = (v == 1) ? 32 : 16;
@@ -340,6 +342,8 @@ int build_tri_lists(bbmm_ctx* c, int W, int want, int64_t tune, TriLists& L, int
   HIPCHK(c, hipStreamSynchronize(c->stream));   // earlier launches may still read the old lists
   bbmm_plan::TriHost H;
   if (const char* what = bbmm_plan::lay_out_triangle(c->np, W, want, H, max_steps, whole)) return fail(c, BBMM_EINVAL, what);
+  ++c->alloc_epoch;                         // (as in make_plan)
+  L.np = 0;                                 // (until all of it is there)
   struct Up {
     Buf* b;
     const void* src;
@@ -388,6 +392,7 @@ int ensure_sgpr_plans(bbmm_ctx* c) {
   if (c->sg_np == c->np && c->sg_mp == c->mp && c->sg_tune[0] == c->sgpr_wgs[0] && c->sg_tune[1] == c->sgpr_wgs[1])
     return BBMM_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  c->sg_np = 0;
   for (int v = 0; v < 2; ++v) {
     int ld = v ? 32 : 16;
     int w1 = rect_wgs_of(c, c->np, c->mp, ld, kSgprSlotCap, c->sgpr_wgs[0]);

@@ -1,5 +1,5 @@
 """GPU: recorded iteration loops ("loop_graph") beside what changes between the runs that replay them: the problem whose matrix the
-loop multiplies by.  The reference is the same program with every kernel launched."""
+loop multiplies by, and the work lists of the size before.  The reference is the same program with every kernel launched."""
 import numpy as np
 import pytest
 
@@ -31,6 +31,36 @@ def test_replays_multiply_by_the_matrix_of_the_problem_at_hand(n, t, sym, digits
             torch.cuda.synchronize()
         captures, replays = ctx.bbmm_loop_graph_stats()
         assert (replays > 4) == (graph == 1)
+        got[graph] = [a.cpu().numpy() for a in out]
+        ctx.close()
+    for i, (a, b) in enumerate(zip(got[0], got[1])):
+        assert np.array_equal(a, b), i
+
+
+# every product with a work list laid out for its size: digit words, fp64 triangle, fp64 whole matrix, on the fly by tile pairs, sparse
+# streamed and projected
+@pytest.mark.parametrize("mode,sym,digits,otf_sym,tol,n1,n2", [
+    (inputs.MATERIALISED, 1, 1, 1, 0.0, 8500, 9700), (inputs.MATERIALISED, 1, 0, 1, 0.0, 8500, 9700),
+    (inputs.MATERIALISED, 0, 0, 1, 0.0, 8500, 9700), (inputs.ONTHEFLY, 0, 0, 2, 0.0, 3000, 4200),
+    (inputs.SGPR, 0, 1, 1, 1e-300, 3000, 4200), (inputs.SGPR, 0, 1, 1, 0.0, 3000, 4200)])
+def test_two_sizes_in_turn(mode, sym, digits, otf_sym, tol, n1, n2):
+    from paper_1809_11165_amd import binding
+    w = {}
+    for n in (n1, n2):
+        w[n] = inputs.tiny(n, 4, kernel=inputs.RBF, ard=False, t=4, k=5, iters=16, noise=0.5, seed=3)
+        if mode == inputs.SGPR:
+            w[n] = inputs.with_inducing(w[n], 100, np.random.default_rng(n))
+        w[n].tol = tol
+    got = {}
+    for graph in (0, 1):
+        ctx = binding.Context(0)
+        for key, value in (("khat_sym", sym), ("otf_digits", digits), ("otf_sym", otf_sym), ("loop_graph", graph)):
+            ctx.bbmm_tune(key, value)
+        out = []
+        for n in [n2] * 4 + [n1] + [n2] * 4 + [n1] * 4 + [n2, n1]:
+            out.append(ctx.bbmm_solve_logdet_grad(binding.problem_from_workload(w[n], mode)).U)
+            torch.cuda.synchronize()
+        assert (ctx.bbmm_loop_graph_stats()[1] > 4) == (graph == 1)
         got[graph] = [a.cpu().numpy() for a in out]
         ctx.close()
     for i, (a, b) in enumerate(zip(got[0], got[1])):
