@@ -445,8 +445,8 @@ bool uses_digits(const bbmm_ctx* c, int mode, int cc) {
          dig_split_of(c, cc) <= kMaxSplit;
 }
 
-// A point whose coordinates or their square overflow fp32 is infinitely far from the others (or not a number); the fp64
-// form keeps that to the rows concerned, the digits cannot.  The device knows (DevState::xbad), the host does when it
+// A point whose coordinates or their square overflow fp32 is infinitely far from the others (or not a number), and so may a
+// pair be whose squared distance does; the fp64 form keeps that to the rows concerned, the digits cannot.  The device knows (DevState::xbad), the host does when it
 // has fetched the state: such a run leaves the caller's buffers alone and is repeated with the fp64 form.
 const DevState* unless_far(const bbmm_ctx* c, int mode, int cc) {
   return uses_digits(c, mode, cc) ? (const DevState*)c->st.p : nullptr;
@@ -573,7 +573,7 @@ int stage_build_words(bbmm_ctx* c, int kind) {
   }
   if (c->khat_mem)                          // the matrix that the caller has had built
     launch_words_of(c->stream, ptr<float>(c->Khat), (size_t)(c->khat_pw > 0 ? c->khat_pw : c->np), c->khat_tri ? 1 : 0,
-                    c->prob.outputscale, c->n, c->np, whole, ptr<int>(c->words));
+                    c->prob.outputscale, c->n, c->np, whole, ptr<DevState>(c->st), ptr<int>(c->words));
   else
     launch_build_words(c->stream, c->prob.kernel, c->prob.X, c->n, c->d, c->np, c->KK, c->hyp, ptr<DevState>(c->st), whole,
                        ptr<double>(c->Xo), ptr<double>(c->sqo), ptr<int>(c->words));

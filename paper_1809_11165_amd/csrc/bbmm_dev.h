@@ -45,7 +45,7 @@ struct DevState {
   int status;       // BBMM_* code raised on the device (0 = ok)
   int rank;         // preconditioner rank actually built
   unsigned fin_ticket;   // arrivals of k_ur_fin's blocks (zero between launches)
-  int xbad;         // a coordinate of X or its square is not finite in fp32: no X for the digit products (they return NaN)
+  int xbad;         // a coordinate of X or its square, or an entry of K, is not finite in fp32: no X for the digit products (they return NaN)
   unsigned counter[8][40];   // arrival tickets per kernel family: [0] final, [1 + g] group g
 };
 
@@ -264,11 +264,12 @@ int launch_mm_otf_dig(hipStream_t s, int kernel, int KK, int ng, const void* rec
 #define BBMM_WORDS_PANEL 512
 // whole: all rows of every panel (for launch_mm_words_wide); otherwise the upper triangle (for launch_mm_words)
 size_t words_bytes(int np, bool whole);
-// Xo: np * 4 KK doubles, sqo: np doubles (work space); Kw: words_bytes(np, whole)
-void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, const DevState* st,
+// Xo: np * 4 KK doubles, sqo: np doubles (work space); Kw: words_bytes(np, whole).  Sets st->xbad where an entry is no number.
+void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, DevState* st,
                         bool whole, double* Xo, double* sqo, int* Kw);
 // the same from the stored fp32 matrix (layout as for launch_copy_block; whole: not from a triangle)
-void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, bool whole, int* Kw);
+void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, bool whole, DevState* st,
+                     int* Kw);
 // Partial sums of (K/s) D without the diagonal of K, up to 12 columns (ld = 16); rec: the digits of D alone (launch_digits with
 // KK = 0, ng = dig_groups(columns) <= 6).  Work list: lay_out_triangle with panels of BBMM_WORDS_PANEL columns, whole, at
 // most kDigMaxBlocks steps per piece.

@@ -46,9 +46,11 @@ __device__ inline int entry_word(double k) { return ((int)rint(k * (double)kX) +
 
 // One wave: the tiles of one 16-row step of a panel, in turn.  Distances by fp64 MFMA (rows in the order 4 (m % 4) + m / 4, so
 // that a lane's four results are four consecutive rows), the kernel function in fp32.  Bound by the stores.
+// An entry that is no number (a squared distance beyond fp32: Matern, infinity times zero) has no word: it sets st->xbad, on which the
+// products return NaN and the run is made again with the fp32 entries.
 template <int KIND>
 __global__ __launch_bounds__(256) void k_build_words(const double* __restrict__ Xo, const double* __restrict__ sqo, int n, int np,
-                                                      int KK, int whole, int* __restrict__ Kw) {
+                                                      int KK, int whole, DevState* __restrict__ st, int* __restrict__ Kw) {
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int jc = lane & 15, g = lane >> 4;
   int P = blockIdx.x, step = blockIdx.y * 4 + wave;
@@ -59,6 +61,7 @@ __global__ __launch_bounds__(256) void k_build_words(const double* __restrict__ 
   for (int r = 0; r < 4; ++r) si[r] = sqo[step * 16 + 4 * g + r];
   int ntiles = min(kWTiles, (np - P * kWP) / 16);
   int* out = Kw + ((words_panel_step(P, np, whole) + step) * kWTiles) * 256 + (g * 16 + (jc ^ g)) * 4;
+  bool bad = false;
   for (int t = 0; t < ntiles; ++t) {
     int cb = P * kWTiles + t;
     const double* Br = Xo + (size_t)cb * KK * 64 + lane;
@@ -73,23 +76,27 @@ __global__ __launch_bounds__(256) void k_build_words(const double* __restrict__ 
     for (int r = 0; r < 4; ++r) {
       int i = step * 16 + 4 * g + r;
       float r2 = __builtin_fabsf((float)acc[r]);
-      int v = entry_word((double)fminf(unit_kernel<KIND>(r2), 1.f));
-      w[r] = (i == j || i >= n || j >= n) ? 0 : v;
+      float k = unit_kernel<KIND>(r2);
+      bool entry = i != j && i < n && j < n;
+      bad |= entry && !(k == k);
+      w[r] = entry ? entry_word((double)fminf(k, 1.f)) : 0;
     }
     __builtin_nontemporal_store(w, (i32x4*)(out + (size_t)t * 256));
   }
+  if (bad) st->xbad = 1;
 }
 
 // The same from a stored fp32 matrix (layout as for launch_copy_block), whose entries are s K: an iteration started on a matrix
-// that its caller has had built runs on the entries of that matrix.
+// that its caller has had built runs on the entries of that matrix.  (No word: NaN as above, and infinity, of an outputscale beyond fp32.)
 __global__ __launch_bounds__(256) void k_words_of(const float* __restrict__ K, size_t pw, int tri, double inv_s, int n, int np,
-                                                   int whole, int* __restrict__ Kw) {
+                                                   int whole, DevState* __restrict__ st, int* __restrict__ Kw) {
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int jc = lane & 15, g = lane >> 4;
   int P = blockIdx.x, step = blockIdx.y * 4 + wave;
   if (step * 16 >= (whole ? np : min(np, (P + 1) * kWP))) return;
   int ntiles = min(kWTiles, (np - P * kWP) / 16);
   int* out = Kw + ((words_panel_step(P, np, whole) + step) * kWTiles) * 256 + (g * 16 + (jc ^ g)) * 4;
+  bool bad = false;
   for (int t = 0; t < ntiles; ++t) {
     int j = (P * kWTiles + t) * 16 + jc;
     size_t q = (size_t)j / pw;                               // (the panels of a triangle are 1 024 wide: rows up to this step are there)
@@ -99,10 +106,13 @@ __global__ __launch_bounds__(256) void k_words_of(const float* __restrict__ K, s
     for (int r = 0; r < 4; ++r) {
       int i = step * 16 + 4 * g + r;
       float v = src[(size_t)i * pw];
-      w[r] = (i == j || i >= n || j >= n) ? 0 : entry_word(fmin((double)v * inv_s, 1.0));
+      bool entry = i != j && i < n && j < n;
+      bad |= entry && !(v < __builtin_inff());
+      w[r] = entry ? entry_word(fmin((double)v * inv_s, 1.0)) : 0;
     }
     __builtin_nontemporal_store(w, (i32x4*)(out + (size_t)t * 256));
   }
+  if (bad) st->xbad = 1;
 }
 
 // Geometry of the product for blocks of up to 2 NG columns: a wave owns 128 matrix columns, a workgroup of four waves one panel.
@@ -534,17 +544,17 @@ __global__ __launch_bounds__(256 * H, 1) void k_mm_words_wide(const int* __restr
 
 size_t words_bytes(int np, bool whole) { return words_panel_step((np + kWP - 1) / kWP, np, whole) * kWTiles * 1024; }
 
-void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, const DevState* st,
+void launch_build_words(hipStream_t s, int kernel, const float* X, int n, int d, int np, int KK, HypArgs hyp, DevState* st,
                         bool whole, double* Xo, double* sqo, int* Kw) {
   k_prep_words<<<(np + 255) / 256, 256, 0, s>>>(X, n, d, np, KK, hyp, st, Xo, sqo);
   dim3 grid((np + kWP - 1) / kWP, (np / 16 + 3) / 4);
-  if (kernel == 0) k_build_words<0><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, whole, Kw);
-  else k_build_words<1><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, whole, Kw);
+  if (kernel == 0) k_build_words<0><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, whole, st, Kw);
+  else k_build_words<1><<<grid, 256, 0, s>>>(Xo, sqo, n, np, KK, whole, st, Kw);
 }
 
-void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, bool whole, int* Kw) {
+void launch_words_of(hipStream_t s, const float* K, size_t pw, int tri, double outputscale, int n, int np, bool whole, DevState* st, int* Kw) {
   dim3 grid((np + kWP - 1) / kWP, (np / 16 + 3) / 4);
-  k_words_of<<<grid, 256, 0, s>>>(K, pw, tri, 1.0 / outputscale, n, np, whole, Kw);
+  k_words_of<<<grid, 256, 0, s>>>(K, pw, tri, 1.0 / outputscale, n, np, whole, st, Kw);
 }
 
 int launch_mm_words(hipStream_t s, const int* Kw, const void* rec, int ng, double* Vp, int np, int ld, const MmPiece* pieces,

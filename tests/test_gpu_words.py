@@ -166,3 +166,31 @@ def test_points_too_far_out_take_the_fp64_products(ctx):
         B = torch.randn(n, 4, generator=torch.Generator().manual_seed(1)).cuda()
         out[dig] = ctx.bbmm_mbcg(inputs.MATERIALISED, B)[0].cpu().numpy()
     assert np.array_equal(out[1], out[0], equal_nan=True)
+
+
+@pytest.mark.parametrize("n,sym", [(1500, 1), (11300, 0)])
+def test_entries_that_are_no_numbers_are_not_hidden_by_the_words(ctx, n, sym):
+    """Two opposite points, each with a square below the largest fp32 number and a squared distance above it: the Matern function of that
+    pair is infinity times zero in fp32, and a run on the stored matrix says so.  So must one on words, whether they are evaluated
+    from X or converted."""
+    from paper_1809_11165_amd import binding
+    w = _workload(n, 1, inputs.MATERN52, t=3, k=3, iters=12, noise=0.5)
+    X = w.X.copy()
+    far = 1.6e19 * float(w.lengthscale[0]) / (np.sqrt(5.0) * np.log2(np.e))
+    X[7], X[9] = far, -far
+    w.X = X
+    ctx.bbmm_tune("khat_sym", sym)
+    out = {}
+    for dig in (0, 1):
+        ctx.bbmm_tune("otf_digits", dig)
+        ctx.bbmm_setup(_problem(w))
+        ctx.bbmm_build_khat()
+        ctx.bbmm_pivoted_cholesky()
+        ctx.bbmm_precond_setup()
+        B = torch.randn(n, 4, generator=torch.Generator().manual_seed(1)).cuda()
+        out[dig] = ctx.bbmm_mbcg(inputs.MATERIALISED, B)[0].cpu().numpy()
+        with pytest.raises(binding.BbmmError) as e:
+            ctx.bbmm_solve_logdet_grad(_problem(w))
+        assert e.value.code == binding.ENONFINITE
+    assert np.isnan(out[0]).any()
+    assert np.array_equal(out[1], out[0], equal_nan=True)
