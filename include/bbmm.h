@@ -275,7 +275,7 @@ int bbmm_sgpr_build(bbmm_ctx* ctx);
 int bbmm_sgpr_root_rows(bbmm_ctx* ctx, int64_t row0, int64_t nrows, float* out);
 
 /* V = K_hat M, the product every mBCG iteration is built on (Sec. 3, "Runtime and space").
- * M, V: device n x c float, 1 <= c <= 32.  mode MATERIALISED needs bbmm_build_khat first, mode
+ * M, V: device n x c float, 1 <= c <= 32; V may be M or overlap it.  mode MATERIALISED needs bbmm_build_khat first, mode
  * SGPR bbmm_sgpr_build; an SGPR problem takes mode SGPR only, and no other problem does. */
 int bbmm_kernel_mm(bbmm_ctx* ctx, int32_t mode, const float* M, int64_t c, float* V);
 

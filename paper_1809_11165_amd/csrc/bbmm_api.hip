@@ -1550,7 +1550,9 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
     if (rc) return rc;
   }
   if (mode == BBMM_MODE_MATERIALISED && !digits && mat_rows(c, ld)) {
-    bool packed = c->np > kMatRowsUnpackedMax;
+    // (without a packed copy workgroups would read rows of M that others have overwritten, where V lies over M)
+    uintptr_t m0 = (uintptr_t)M, v0 = (uintptr_t)V, bytes = sizeof(float) * (uintptr_t)c->n * cc;
+    bool packed = c->np > kMatRowsUnpackedMax || (m0 < v0 + bytes && v0 < m0 + bytes);
     if (packed) launch_pack_d4(s, M, c->n, (int)cc, c->np, ld, ptr<double>(c->D4), 0, st);
     rc = stage_mm_rows(c, packed ? nullptr : M, (int)cc, V);
     if (rc) return rc;

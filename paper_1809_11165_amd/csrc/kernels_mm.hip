@@ -365,7 +365,7 @@ __global__ __launch_bounds__(64 * MS_NW, 2) void k_mm_mat_small(const float* __r
 // result is final.
 //   MR_ITER    the block is D4; V (fp64) and the workgroup's share of d^T v, as k_dv leaves them (one launch per iteration less)
 //   MR_PACKED  the block is D4, the result the caller's fp32 one (n x c)
-//   MR_CALL    both are the caller's (nothing is packed)
+//   MR_CALL    both are the caller's (nothing is packed), and do not overlap
 // Bound by latency (n = 1 000: 7.1 us, k_mm_mat_small 8.0 and k_dv 5.4), and from 4 096 rows on by every workgroup's reading the
 // whole block.  Sizes: see mat_rows.
 constexpr int MR_NW = 8;

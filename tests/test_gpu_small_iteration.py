@@ -69,3 +69,26 @@ def test_a_tolerance_stops_a_small_iteration_where_the_oracle_stops():
     P = O.make_preconditioner(L, w.noise)
     ref = O.mbcg(lambda M: K @ M, B.cpu().numpy().astype(np.float64), P.solve, iters)
     assert np.linalg.norm(U.cpu().numpy() - ref.U) < 1e-5 * np.linalg.norm(ref.U)
+
+
+# (workgroups that write their rows while others still read the block: up to 2048 rows it is not packed first)
+@pytest.mark.parametrize("n,c", [(300, 3), (2048, 11), (2048, 16), (3000, 5), (6000, 11)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_a_product_may_overwrite_its_block(n, c, offset):
+    import ctypes as C
+    from paper_1809_11165_amd import binding
+    w = inputs.tiny(n, 3, kernel=inputs.RBF, ard=True, t=2, k=2, iters=2, noise=0.5, seed=5)
+    ctx = binding.Context(0)
+    try:
+        ctx.bbmm_setup(binding.problem_from_workload(w, inputs.MATERIALISED))
+        ctx.bbmm_build_khat()
+        M = torch.randn(n, c, generator=torch.Generator().manual_seed(n)).cuda()
+        ref = ctx.bbmm_kernel_mm(inputs.MATERIALISED, M)
+        for _ in range(5):
+            both = torch.zeros(n * c + offset, device="cuda")
+            both[:n * c] = M.reshape(-1)
+            p = both.data_ptr()
+            assert ctx.lib.bbmm_kernel_mm(ctx.h, inputs.MATERIALISED, C.c_void_p(p), c, C.c_void_p(p + 4 * offset)) == 0
+            assert float((both[offset:].view(n, c) - ref).norm() / ref.norm()) < 1e-6   # (fp32 results, fp64 sums in two orders)
+    finally:
+        ctx.close()
