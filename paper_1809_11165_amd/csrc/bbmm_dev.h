@@ -20,7 +20,7 @@ struct DevState {
   double alpha_cur[BBMM_MAXC];
   double beta_cur[BBMM_MAXC];
   double dvtot[BBMM_MAXC];      // d^T K_hat d of the current iteration, per column
-  double rho_prev[BBMM_MAXC];   // rho, active and m_valid as k_ur_main met them (for k_fin_zd)
+  double rho_prev[BBMM_MAXC];   // rho, active, m_valid and done as k_ur_main met them (for k_fin_zd)
   double Qt[BBMM_MAXK * BBMM_MAXC];   // C^{-1} L^T R, [m][q]
   double G[BBMM_MAXK * BBMM_MAXK];    // lower Cholesky factor of C = sigma^2 I + L^T L, [a][b]
   double Ginv[BBMM_MAXK * BBMM_MAXK]; // G^{-1} (lower triangular, zero padded), [a][b]
@@ -36,7 +36,7 @@ struct DevState {
   double loop_noise, loop_tol, loop_scaleV, loop_addD;
   int active[BBMM_MAXC];
   int m_valid[BBMM_MAXC];
-  int active_prev[BBMM_MAXC], m_valid_prev[BBMM_MAXC];
+  int active_prev[BBMM_MAXC], m_valid_prev[BBMM_MAXC], done_prev;
   int piv[BBMM_MAXK + 1];
   unsigned dmax[BBMM_MAXC];   // per column of D: largest high word of |D| (its exponent scales the digits)
   int dflag[BBMM_MAXC];       // per column of D: 1 = holds +inf, 2 = -inf, 4 = NaN   (zeroed with done)

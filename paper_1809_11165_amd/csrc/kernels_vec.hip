@@ -1060,6 +1060,7 @@ __global__ __launch_bounds__(UT) void k_ur_main(int init, int n, int c,
       alpha[qb] = alpha_from(s_active[qb], s_rho[qb], dvtot[qb * 16 + q], qb * 16 + q, c, &ok);
     }
   }
+  if (!init && blockIdx.x == 0 && threadIdx.x == 0) st->done_prev = done;
   if (done) return;                                   // block-uniform
   if (!init && blockIdx.x == 0 && (int)threadIdx.x < LD) {   // as k_fin_zd reads them (its first block writes the new ones)
     int cq = threadIdx.x;
@@ -1513,7 +1514,7 @@ __global__ __launch_bounds__(VT) void k_fin_zd(int n, int c, const double* __res
   __shared__ double ws[KP > 0 ? KP * LD : 1], xs[KP > 0 ? KP * LD : 1];
   __shared__ double beta_s[LD];
   __shared__ int conv_s[LD];
-  if (st->done) return;
+  if (st->done_prev) return;               // (done itself is written below, while other blocks start: a block's waves could part here)
   double noise = st->loop_noise, tol = st->loop_tol;
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int tq = threadIdx.x & (LD - 1);
@@ -1582,7 +1583,7 @@ __global__ __launch_bounds__(VT) void k_fin_zd(int n, int c, const double* __res
     st->iters_run = iter + 1;
     int conv = 1;
     for (int q = 0; q < LD; ++q) conv &= conv_s[q];
-    if (tol > 0.0 && conv) st->done = 1;                     // (a block that has not started yet leaves its rows of D, which nobody reads then)
+    if (tol > 0.0 && conv) st->done = 1;
   }
   int q = lane & 15, g = lane >> 4;
   double beta = beta_s[q], inv_noise = 1.0 / noise;
