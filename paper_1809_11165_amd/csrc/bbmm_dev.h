@@ -80,6 +80,7 @@ struct SgprLoop {
   double *T4, *S, *H;    // T quad-swizzled, S and H row-major (mp x ld)
   const double* W4;      // A^T L, quad-swizzled, ldw columns
   int ldw;
+  const double* fresh;   // A^T R streamed from R, quad-swizzled (may be null)
   double* pdv;           // partial rows of d^T K_hat d = sigma^2 |d|^2 + |T|^2
   int nb_ur, nb_zd;      // blocks on the n x c blocks; the ones after them work on the mp rows
 };

@@ -1356,7 +1356,8 @@ __global__ __launch_bounds__(UT) void k_ur_fin(int init, int ld, int c, double n
 
 // One entry of S = A^T R and T = A^T D per thread, 256 / ld rows of them per block:
 //   S -= alpha (H + sigma^2 T),  T <- (S - (A^T L) C^{-1} L^T r) / sigma^2 + beta T,
-// the images under A^T of R -= alpha K_hat D and D <- z + beta D (A^T K_hat D = (A^T A + sigma^2 I) T).
+// the images under A^T of R -= alpha K_hat D and D <- z + beta D (A^T K_hat D = (A^T A + sigma^2 I) T).  With proj.fresh, S is read
+// from there, streamed from R itself (see kProjRefresh).
 // FIRST: S from T = A^T z instead.  Either way a partial row of |T|^2, after the nb_zd of sigma^2 |d|^2.
 template <int KP, int NQ, bool FIRST>
 __device__ inline void sgpr_direction(const SgprLoop& pj, const DevState* st, double noise, int block) {
@@ -1370,7 +1371,7 @@ __device__ inline void sgpr_direction(const SgprLoop& pj, const DevState* st, do
   if (FIRST) {
     pj.S[si] = noise * t + w;
   } else {
-    double s = pj.S[si] - st->alpha_cur[col] * (pj.H[si] + noise * t);
+    double s = pj.fresh ? pj.fresh[ti] : pj.S[si] - st->alpha_cur[col] * (pj.H[si] + noise * t);
     pj.S[si] = s;
     t = (s - w) / noise + st->beta_cur[col] * t;
     pj.T4[ti] = t;

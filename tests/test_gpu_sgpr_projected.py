@@ -103,3 +103,21 @@ def test_projected_iteration_from_a_warm_start(ctx):
     prob.u0_init = other.u0_init = u0
     a, b = ctx.bbmm_solve_logdet_grad(prob), ctx.bbmm_solve_logdet_grad(other)
     assert float((a.U - b.U).double().norm() / b.U.double().norm()) < SOLVE_TOL
+
+
+@pytest.mark.parametrize("n,m,c,k", [(20000, 800, 32, 0), (30000, 1024, 16, 10)])
+def test_projected_iteration_nears_the_solution_as_the_streamed_one(ctx, n, m, c, k):
+    """160 iterations at sigma^2 = 0.25 leave solves some 1e-7 from the 64-bit ones.  Both forms lose iterations to rounding (one
+    leaves 0.9 of the distance); the projected one may lose three more: 0.9^-3 = 1.37."""
+    B = torch.from_numpy(np.random.default_rng(n).standard_normal((n, c)).astype(np.float32)).cuda()
+    dist = {}
+    for tol in (1e-300, 0.0):
+        U = _run(ctx, n, m, k, 160, tol, 0.25, B)[0].double()
+        A, b = ctx.bbmm_sgpr_root_rows(0, n).double(), B.double()
+        At = A.T.contiguous()
+        C = At @ A + 0.25 * torch.eye(m, dtype=torch.float64, device="cuda")
+        ref = (b - A @ torch.linalg.solve(C, At @ b)) / 0.25
+        dist[tol] = float(torch.log((U - ref).norm(dim=0) / ref.norm(dim=0)).mean().exp())
+    print(n, m, dist, flush=True)
+    assert 3e-8 < dist[1e-300] < 1e-6           # (rounding the solves to fp32 alone: 2.5e-8)
+    assert dist[0.0] < 1.37 * dist[1e-300]
