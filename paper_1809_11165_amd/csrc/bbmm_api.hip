@@ -116,6 +116,7 @@ struct bbmm_ctx {
   int64_t khat_sym = 0;                      // 1: keep only the upper triangle of K_hat (packed panels)
   bool khat_tri = false;                     // the K_hat currently in memory is such a triangle
   bool khat_mem = false;                     // khat_built is what a caller may use; whether the fp32 matrix is in memory
+  bool khat_read = false;                    // a call that its caller can record in a graph has read it (bbmm_kernel_mm, bbmm_khat_block)
   int words_built = 0;                       // K_hat is in memory as digit words (kWordsTri / kWordsWhole; the iteration's products, see kernels_words.hip)
   // work list of the product from the triangle
   TriLists sym;                              // ... from the stored triangle (panels of 1024 columns)
@@ -506,19 +507,24 @@ int device_status(bbmm_ctx* c) {
 }
 
 // ---- stages on internal buffers -------------------------------------------------------------
+// column panels of 1024 (one 16-row step of a workgroup is then 64 KB of contiguous memory:
+// 1.515 -> 1.498 ms per product at n = 50,000); "khat_panel" = 1 keeps plain row-major
+int khat_panel_of(const bbmm_ctx* c, bool tri) {
+  if (tri) return BBMM_SYM_PANEL;
+  return c->khat_panel == 0 ? 1024 : (c->khat_panel == 1 ? 0 : (int)c->khat_panel);
+}
+
+size_t khat_bytes(const bbmm_ctx* c, bool tri) {
+  size_t pw = (size_t)khat_panel_of(c, tri), np = (size_t)c->np;
+  if (pw == 0) return np * np * sizeof(float);
+  size_t S = (np + pw - 1) / pw;
+  // "khat_sym": the upper triangle in packed panels, all panels but the last being full height
+  return (tri ? pw * pw * (S * (S - 1) / 2) + np * pw : np * S * pw) * sizeof(float);
+}
+
 int stage_build_khat(bbmm_ctx* c, bool tri) {
-  // column panels of 1024 (one 16-row step of a workgroup is then 64 KB of contiguous memory:
-  // 1.515 -> 1.498 ms per product at n = 50,000); "khat_panel" = 1 keeps plain row-major
-  int pw = c->khat_panel == 0 ? 1024 : (c->khat_panel == 1 ? 0 : (int)c->khat_panel);
-  size_t cols_alloc = pw > 0 ? (size_t)((c->np + pw - 1) / pw) * pw : (size_t)c->np;
-  size_t bytes = (size_t)c->np * cols_alloc * sizeof(float);
-  if (tri) {
-    // "khat_sym": the upper triangle in packed panels, all panels but the last being full height
-    pw = BBMM_SYM_PANEL;
-    size_t S = (size_t)((c->np + pw - 1) / pw);
-    bytes = ((size_t)pw * pw * (S * (S - 1) / 2) + (size_t)c->np * pw) * sizeof(float);
-  }
-  int rc = ensure(c, c->Khat, bytes);
+  int pw = khat_panel_of(c, tri);
+  int rc = ensure(c, c->Khat, khat_bytes(c, tri));
   if (rc) return rc;
   c->khat_pw = pw;
   c->khat_tri = tri;
@@ -1541,6 +1547,7 @@ int bbmm_khat_block(bbmm_ctx* c, int64_t row0, int64_t nrows, int64_t col0, int6
   int rc = check_ready(c);
   if (rc) return rc;
   if (!c->khat_built) return fail(c, BBMM_EINVAL, "bbmm_build_khat must run first");
+  c->khat_read = true;
   rc = need_khat(c);
   if (rc) return rc;
   if (!out || row0 < 0 || col0 < 0 || nrows < 0 || ncols < 0 || row0 + nrows > c->n || col0 + ncols > c->n ||
@@ -1567,6 +1574,7 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   }
   int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || c->otf_digits == 2) ? 1 : 0;
   if (mode == BBMM_MODE_MATERIALISED && !digits && c->khat_built) {
+    c->khat_read = true;
     rc = need_khat(c);
     if (rc) return rc;
   }
@@ -1921,8 +1929,15 @@ static int solve_call(bbmm_ctx* c, const bbmm_problem* in, bbmm_result* out, boo
     // matrix is built only if something asks for it (see need_khat).
     c->khat_tri = c->khat_sym != 0 && mat_split_of(c, ld) == 0;
     if (int kind = wants_words(c, cc)) rc = stage_build_words(c, kind);
-    if (!rc && !c->words_built) rc = build_khat_first(c, c->khat_tri);
     if (rc) return rc;
+    // A caller may have recorded a product with it in a graph, whose replays read its memory: it is the matrix of the problem at hand
+    // then, whatever this call runs on.
+    const int words = c->words_built;
+    if (!words || (c->khat_read && khat_bytes(c, c->khat_tri) <= c->Khat.cap)) {
+      rc = build_khat_first(c, c->khat_tri);
+      if (rc) return rc;
+      c->words_built = words;
+    }
     c->khat_built = true;
   } else if (in->mode == BBMM_MODE_SGPR) {
     rc = stage_sgpr_build(c);

@@ -127,6 +127,38 @@ def test_the_fp32_matrix_is_there_after_a_call_that_did_without(ctx):
     assert np.max(np.abs(V[rows] - ref)) < 1e-4
 
 
+@pytest.mark.parametrize("n,t,sym", [(11300, 4, 0), (8500, 4, 1)])
+def test_a_recorded_product_follows_the_calls_that_run_on_words(n, t, sym):
+    """A caller's graph of a product reads the fp32 matrix where it was when the product was recorded: after every later call it has to
+    be that call's, also one that runs on the digit words."""
+    from paper_1809_11165_amd import binding
+    stream = torch.cuda.Stream()
+    w = _workload(n, 4, inputs.RBF, t=t, k=5, iters=10, noise=0.5)
+    M = torch.randn(n, 5, generator=torch.Generator().manual_seed(1)).cuda()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ctx = binding.Context(0)
+        ctx.bbmm_tune("khat_sym", sym)
+        ctx.bbmm_solve_logdet_grad(_problem(w))
+        ctx.bbmm_kernel_mm(inputs.MATERIALISED, M)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            V = ctx.bbmm_kernel_mm(inputs.MATERIALISED, M)
+        for step in range(3):
+            w.noise, w.outputscale = 0.4 + 0.3 * step, 1.5 + 0.5 * step
+            ctx.bbmm_solve_logdet_grad(_problem(w))
+            graph.replay()
+            stream.synchronize()
+            got = V.clone()
+            assert torch.equal(got, ctx.bbmm_kernel_mm(inputs.MATERIALISED, M)), step
+            rows = np.array([0, 777, n - 1])
+            K = O.kernel_block(w.kernel, w.X[rows].astype(np.float64), w.X.astype(np.float64), w.lengthscale, w.outputscale)
+            K[np.arange(3), rows] += w.noise
+            assert np.max(np.abs(got.cpu().numpy()[rows] - K @ M.cpu().numpy().astype(np.float64))) < 2e-4, step
+        ctx.close()
+
+
 def test_words_of_the_other_form_come_from_the_fp32_matrix(ctx):
     """A call leaves the triangle's words (5 columns, nothing in fp32) or the whole matrix's (20); variances at 20 and at 5 points then need
     the other form, whose entries are those of the fp32 matrix: the same bits as on a matrix built by itself."""
