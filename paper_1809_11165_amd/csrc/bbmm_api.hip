@@ -88,6 +88,7 @@ struct LoopKey {
 struct bbmm_ctx {
   int device = 0;
   int num_cus = 256;          // compute units of the device (hipDeviceProp_t::multiProcessorCount)
+  size_t dev_bytes = 0;       // memory of the device
   hipStream_t stream = nullptr;
   hipStream_t side = nullptr;            // second stream (default priority) for the SLQ eigensolves
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -561,11 +562,10 @@ int stage_build_words(bbmm_ctx* c, int kind) {
     c->words_built = 0;
   }
   const bool whole = kind == kWordsWhole;
-  // (beside the fp32 matrix only where that leaves the caller a quarter of the device's memory)
-  size_t free_b = 0, total_b = 0, bytes = words_bytes(c->np, whole);
-  if (c->khat_mem && bytes > c->words.cap &&
-      (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b + c->words.cap < bytes + total_b / 4))
-    return BBMM_OK;
+  // Beside the fp32 matrix only where both fit half of the device.  (By sizes alone: the same program takes the same arithmetic
+  // whatever else is in memory, short of a failed allocation.)
+  const size_t bytes = words_bytes(c->np, whole);
+  if (c->khat_mem && bytes + khat_bytes(c, c->khat_tri) > c->dev_bytes / 2) return BBMM_OK;
   size_t np = (size_t)c->np;
   struct { Buf* b; size_t bytes; } want[] = {
       {&c->words, bytes}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
@@ -1317,6 +1317,7 @@ int bbmm_create(bbmm_ctx** out, int device, void* hip_stream) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
     c->num_cus = cus;
+  if (hipDeviceTotalMem(&c->dev_bytes, device) != hipSuccess) c->dev_bytes = 0;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   if (scratch_of(device, &c->eig_static) != hipSuccess) {
     delete c;

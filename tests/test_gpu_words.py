@@ -181,6 +181,33 @@ def test_words_of_the_other_form_come_from_the_fp32_matrix(ctx):
     with_own.close()
 
 
+def _all_but(left):
+    """Device memory taken so that `left` bytes are free (nothing is written to it)."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.empty(torch.cuda.mem_get_info()[0] - left, dtype=torch.uint8, device="cuda")
+
+
+def test_the_same_arithmetic_beside_other_users_of_the_device():
+    """Words beside a matrix that the caller has had built: by the sizes alone."""
+    from paper_1809_11165_amd import binding
+    w = _workload(11300, 4, inputs.RBF, t=4, k=5, iters=12, noise=0.5)
+    B = torch.randn(w.n, 5, generator=torch.Generator().manual_seed(1)).cuda()
+    out = []
+    for busy in (False, True):
+        own = binding.Context(0)
+        own.bbmm_setup(_problem(w))
+        own.bbmm_build_khat()
+        own.bbmm_pivoted_cholesky()
+        own.bbmm_precond_setup()
+        other = _all_but(16 << 30) if busy else None
+        out.append(own.bbmm_mbcg(inputs.MATERIALISED, B)[0].clone())
+        own.close()
+        del other
+    torch.cuda.empty_cache()
+    assert torch.equal(out[0], out[1])
+
+
 def test_points_too_far_out_take_the_fp64_products(ctx):
     n = 1500
     w = _workload(n, 3, inputs.RBF, t=3, k=3, iters=12, noise=0.5)
