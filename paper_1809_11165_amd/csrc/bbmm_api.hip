@@ -557,8 +557,8 @@ int need_khat(bbmm_ctx* c) { return c->khat_mem ? BBMM_OK : build_khat_first(c, 
 int stage_build_words(bbmm_ctx* c, int kind) {
   if (c->words_built == kind) return BBMM_OK;
   if (c->words_built) {                     // the other form, from a call whose X may be gone: by way of the fp32 matrix
-    int rc = need_khat(c);
-    if (rc) return rc;
+    int rc0 = need_khat(c);
+    if (rc0) return rc0;
     c->words_built = 0;
   }
   const bool whole = kind == kWordsWhole;
@@ -569,14 +569,21 @@ int stage_build_words(bbmm_ctx* c, int kind) {
   size_t np = (size_t)c->np;
   struct { Buf* b; size_t bytes; } want[] = {
       {&c->words, bytes}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
-  for (auto& w : want) {
-    int rc = ensure(c, *w.b, w.bytes);
-    if (rc == BBMM_ENOMEM) {
-      c->err.clear();
-      return BBMM_OK;
-    }
-    if (rc) return rc;
+  auto make_room = [&]() -> int {
+    for (auto& w : want)
+      if (int rc = ensure(c, *w.b, w.bytes)) return rc;
+    return BBMM_OK;
+  };
+  int rc = make_room();
+  if (rc == BBMM_ENOMEM && c->Khat.p && !c->khat_mem && !c->khat_read) {   // an earlier problem's matrix gives way
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    HIPCHK(c, hipFree(c->Khat.p));
+    c->Khat = Buf{};
+    ++c->alloc_epoch;
+    rc = make_room();
   }
+  if (rc == BBMM_OK || rc == BBMM_ENOMEM) c->err.clear();
+  if (rc) return rc == BBMM_ENOMEM ? BBMM_OK : rc;
   if (c->khat_mem)                          // the matrix that the caller has had built
     launch_words_of(c->stream, ptr<float>(c->Khat), (size_t)(c->khat_pw > 0 ? c->khat_pw : c->np), c->khat_tri ? 1 : 0,
                     c->prob.outputscale, c->n, c->np, whole, ptr<DevState>(c->st), ptr<int>(c->words));

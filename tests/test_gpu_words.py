@@ -208,6 +208,26 @@ def test_the_same_arithmetic_beside_other_users_of_the_device():
     assert torch.equal(out[0], out[1])
 
 
+def test_the_matrix_of_an_earlier_problem_gives_way_to_words(ctx):
+    """Its memory is idle, and the words of the next problem fit nowhere else."""
+    from paper_1809_11165_amd import binding
+    ctx.bbmm_tune("khat_sym", 0)
+    big, w = (_workload(n, 4, inputs.RBF, t=4, k=5, iters=12, noise=0.5) for n in (30000, 28000))
+    ref = ctx.bbmm_solve_logdet_grad(_problem(w)).U
+    own = binding.Context(0)
+    own.bbmm_tune("otf_digits", 0)
+    own.bbmm_solve_logdet_grad(_problem(big))
+    own.bbmm_tune("otf_digits", 1)
+    ctx.close()
+    prob = _problem(w)
+    other = _all_but(128 << 20)
+    got = own.bbmm_solve_logdet_grad(prob).U
+    del other
+    own.close()
+    torch.cuda.empty_cache()
+    assert torch.equal(got, ref)
+
+
 def test_points_too_far_out_take_the_fp64_products(ctx):
     n = 1500
     w = _workload(n, 3, inputs.RBF, t=3, k=3, iters=12, noise=0.5)
