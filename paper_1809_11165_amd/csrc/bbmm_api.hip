@@ -70,6 +70,12 @@ constexpr int kMatSmallMaxRows = 8192;
 constexpr int kWordsTriMinRows = 1024, kWordsMinRows = 11264, kWordsMinIters = 8;
 constexpr int kWordsTri = 1, kWordsWhole = 2;
 constexpr int kWordsWholeMinRows = 8192, kWordsWhole32MinRows = 16384;   // up to 24 columns, above
+// Words converted from a matrix in memory cost two to three products that the run has to earn back.  bbmm_build_khat and one run, time over that with
+// fp64 products, 8 / 12 / 20 / 50 iterations: 11 columns, triangle kept, n = 16 500: 1.03 / 0.98 / 0.92 / 0.87; 40 000: 1.08 / 1.03 / 0.96 / 0.91;
+// whole, 11 300: 1.12 / 1.03 / 1.02 / 0.99; 16 500: 1.07 / 1.03 / 1.00 / 0.96; 20 columns, 8 500: 1.13 / 1.08 / 1.03 / 0.98; 16 500: 1.15 / 1.08 /
+// 1.02 / 0.95; 32 columns, 16 500: 1.11 / 1.09 / 1.05 / 1.00; 24 000: 1.11 / 1.02 / 0.97 / 0.92.  So from this many iterations (of the cap: a run that
+// meets its tolerance earlier may lose those products, once per matrix); whole, 25 to 32 columns below 20 480 rows, from twice as many.
+constexpr int kWordsOfTriMinIters = 12, kWordsOfMinIters = 30;
 constexpr int kDkStride = 2 * (BBMM_MAXD + 2);
 
 }  // namespace
@@ -434,10 +440,15 @@ bool may_use_digits(const bbmm_ctx* c) { return !c->sgpr && c->np >= kDigMinRows
 // Digit words that an iteration of the materialised mode takes its products from (0: none).
 int wants_words(const bbmm_ctx* c, int cc) {
   if (c->sgpr || c->otf_digits == 0 || c->far_x || c->maxit < kWordsMinIters) return 0;
-  if (cc <= 12) return c->np >= (c->khat_tri ? kWordsTriMinRows : kWordsMinRows) ? kWordsTri : 0;
-  if (cc <= 16 || c->khat_tri) return 0;
-  int from = c->otf_digits == 2 ? kWordsTriMinRows : cc <= 24 ? kWordsWholeMinRows : kWordsWhole32MinRows;
-  return c->np >= from ? kWordsWhole : 0;
+  if (cc > 12 && (cc <= 16 || c->khat_tri)) return 0;
+  const int kind = cc <= 12 ? kWordsTri : kWordsWhole;
+  int from = kind == kWordsTri ? (c->khat_tri ? kWordsTriMinRows : kWordsMinRows)
+             : c->otf_digits == 2 ? kWordsTriMinRows
+             : cc <= 24 ? kWordsWholeMinRows : kWordsWhole32MinRows;
+  if (c->np < from) return 0;
+  const bool convert = c->words_built != kind && (c->khat_mem || c->words_built != 0);
+  int iters = c->khat_tri ? kWordsOfTriMinIters : cc > 24 && c->np < 20480 ? 2 * kWordsOfMinIters : kWordsOfMinIters;
+  return convert && c->otf_digits != 2 && c->maxit < iters ? 0 : kind;
 }
 
 // Whether a product of this mode and block width runs on the 8-bit matrix pipe.

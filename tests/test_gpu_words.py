@@ -110,6 +110,24 @@ def test_iteration_on_words_matches_the_fp64_one(ctx, n, t, sym):
     assert 0.0 < rel < 2.0 ** -19 * kappa
 
 
+@pytest.mark.parametrize("n,c,sym,first", [(1500, 4, 1, 12), (11300, 5, 0, 30), (8200, 17, 0, 30), (16400, 25, 0, 60), (20300, 25, 0, 30)])
+def test_a_short_run_on_a_built_matrix_takes_its_entries(ctx, n, c, sym, first):
+    """Fewer iterations than a conversion to words is worth: the bits of the run without words."""
+    ctx.bbmm_tune("khat_sym", sym)
+    B = torch.randn(n, c, generator=torch.Generator().manual_seed(1)).cuda()
+    for iters in (first - 1, first):
+        w = _workload(n, 3, inputs.RBF, t=3, k=2, iters=iters, noise=0.5)
+        out = {}
+        for dig in (1, 0):
+            ctx.bbmm_tune("otf_digits", dig)
+            ctx.bbmm_setup(_problem(w))
+            ctx.bbmm_build_khat()
+            ctx.bbmm_pivoted_cholesky()
+            ctx.bbmm_precond_setup()
+            out[dig] = ctx.bbmm_mbcg(inputs.MATERIALISED, B)[0].clone()
+        assert torch.equal(out[1], out[0]) == (iters < first)
+
+
 def test_the_fp32_matrix_is_there_after_a_call_that_did_without(ctx):
     n = 11300
     w = _workload(n, 4, inputs.RBF, t=4, k=5, iters=10, noise=0.5)
@@ -191,7 +209,7 @@ def _all_but(left):
 def test_the_same_arithmetic_beside_other_users_of_the_device():
     """Words beside a matrix that the caller has had built: by the sizes alone."""
     from paper_1809_11165_amd import binding
-    w = _workload(11300, 4, inputs.RBF, t=4, k=5, iters=12, noise=0.5)
+    w = _workload(11300, 4, inputs.RBF, t=4, k=5, iters=30, noise=0.5)
     B = torch.randn(w.n, 5, generator=torch.Generator().manual_seed(1)).cuda()
     out = []
     for busy in (False, True):
@@ -253,7 +271,7 @@ def test_entries_that_are_no_numbers_are_not_hidden_by_the_words(ctx, n, sym):
     pair is infinity times zero in fp32, and a run on the stored matrix says so.  So must one on words, whether they are evaluated
     from X or converted."""
     from paper_1809_11165_amd import binding
-    w = _workload(n, 1, inputs.MATERN52, t=3, k=3, iters=12, noise=0.5)
+    w = _workload(n, 1, inputs.MATERN52, t=3, k=3, iters=30, noise=0.5)
     X = w.X.copy()
     far = 1.6e19 * float(w.lengthscale[0]) / (np.sqrt(5.0) * np.log2(np.e))
     X[7], X[9] = far, -far
