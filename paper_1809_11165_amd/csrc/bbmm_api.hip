@@ -393,7 +393,7 @@ int rect_wgs_of(const bbmm_ctx* c, int rows_p, int cols_p, int ld, int slot_cap,
 }
 
 constexpr int kProjZdBlocks = 1024;          // blocks of its direction update (they leave partial sums)
-constexpr int kProjMinRows = 2304, kProjMaxInducing = 8192;   // (gpartial: kProjZdBlocks + mp ld / 256 rows of ld)
+constexpr int kProjMinRows = 2304;           // (gpartial: kProjZdBlocks + mp ld / 256 rows of ld, mp <= 4096)
 constexpr int kSgprSlotCap = 1024;   // partial results of A^T D: one per workgroup when m <= 1024
 
 int ensure_sgpr_plans(bbmm_ctx* c) {
@@ -689,13 +689,16 @@ int sgpr_first_pass(bbmm_ctx* c, int ld, const double* D4, VpShape* shape, int c
 
 // Whether the iteration carries T = A^T D and S = A^T R along (their recurrences need A^T A, mp x mp, once) instead of
 // streaming A for A^T D in every product.
-// Measured, m = 1024, n = 500 000: see kernels_sgpr.hip.  A^T A costs what mp / 32 such passes do (n mp^2 at
-// 50 TFLOP/s against 4 n mp bytes at 6.3 TB/s), so it is formed where at least twice as many iterations are certain: no
-// tolerance to stop at.
-// (The partial sums of A^T A have K_UX's memory: eight of its upper triangle fit from 4 mp + 512 points on.)
-bool sgpr_projected(const bbmm_ctx* c) {
-  return c->prob.tol <= 0.0 && c->np >= std::max(kProjMinRows, 4 * c->mp + 512) && c->mp <= kProjMaxInducing &&
-         c->maxit >= std::max(16, c->mp / 16);
+// A^T A takes n mp^2 operations at 66 TFLOP/s (m = 1024, n = 500 000: 8.9 ms) and a pass of A that it saves 4 n mp bytes at 6.3 TB/s (0.34 ms with
+// the passes that come back, see kProjRefresh): mp / 40 iterations, and it is formed where more than twice as many are certain, that is, no tolerance
+// to stop at.  (The partial sums of A^T A have K_UX's memory: eight of its upper triangle fit from 4 mp + 512 points on.)
+// Whole calls of 128 iterations, streamed / carried, ms, n = 3 000: m = 500, 11 columns: 9.1 / 8.1; 17 columns: 9.5 / 11.1; n = 4 000: m = 256, 17 columns:
+// 8.2 / 7.9; m = 500: 10.4 / 11.4; n = 5 000: 11.6 / 11.3; n = 10 000: 11.9 / 10.1.  So beyond 16 columns (the blocks for H run twice as long) and 256 rows of
+// T it takes 5 120 points.
+constexpr int kProjWideMinRows = 5120;
+bool sgpr_projected(const bbmm_ctx* c, int ld) {
+  return c->prob.tol <= 0.0 && c->np >= std::max(kProjMinRows, 4 * c->mp + 512) && c->maxit >= std::max(16, c->mp / 16) &&
+         (ld == 16 || c->mp <= 256 || c->np >= kProjWideMinRows);
 }
 
 // Iterations after which S is streamed from R again.  S keeps the rounding errors of all its updates while R shrinks, and T takes them
@@ -981,7 +984,7 @@ int stage_mbcg(bbmm_ctx* c, int mode, int cc, int ld, const float* warm = nullpt
     if (rc) return rc;
   }
   const bool by_rows = mode == BBMM_MODE_MATERIALISED && !track && mat_rows(c, ld);
-  const bool proj = mode == BBMM_MODE_SGPR && sgpr_projected(c);
+  const bool proj = mode == BBMM_MODE_SGPR && sgpr_projected(c, ld);
   SgprLoop pj = {};
   if (proj) {
     nb_zd = std::min(nb_zd, kProjZdBlocks);

@@ -81,6 +81,14 @@ def test_projected_iteration_is_the_streamed_one(ctx, n, m, c, k):
                 assert float((u - v).norm() / v.norm()) < SOLVE_TOL, q
 
 
+# wide blocks on more than 256 inducing points are projected from 5 120 (padded) points on only, where that is the faster form
+@pytest.mark.parametrize("n,m,c,projected", [(4864, 300, 17, False), (4865, 300, 17, True), (4864, 300, 16, True), (3000, 256, 17, True)])
+def test_which_form_runs(ctx, n, m, c, projected):
+    B = torch.from_numpy(np.random.default_rng(n).standard_normal((n, c)).astype(np.float32)).cuda()
+    got, ref = (_run(ctx, n, m, 3, 32, tol, 0.25, B) for tol in (0.0, 1e-300))
+    assert np.array_equal(got[1], ref[1]) != projected
+
+
 def test_projected_iteration_repeats_and_alternates(ctx):
     """First pass, recorded and replayed loops give the same bits, also with streamed calls between them."""
     n, m, t, k, iters = 6007, 200, 6, 5, 32
