@@ -696,8 +696,9 @@ def test_full_path_is_deterministic(ctx):
     assert np.array_equal(a.alpha, b.alpha)
 
 
+# tri 1: the triangle on digit words, 2: on the fp64 matrix pipe (with this "mat_wgs" a call keeps it at any size)
 @pytest.mark.parametrize("mode,tri", [(inputs.ONTHEFLY, 0), (inputs.MATERIALISED, 0), (inputs.MATERIALISED, 1),
-                                      (inputs.SGPR, 0)])
+                                      (inputs.MATERIALISED, 2), (inputs.SGPR, 0)])
 def test_loop_graph_replays_equal_kernel_by_kernel_launches(ctx, mode, tri):
     """The mBCG loop replayed as a HIP graph against the same loop launched kernel by kernel: bit
     for bit, over several replays with other work and synchronisations of the program in between,
@@ -712,7 +713,9 @@ def test_loop_graph_replays_equal_kernel_by_kernel_launches(ctx, mode, tri):
         w.noise, w.outputscale, w.tol = noise, s, tol
         return ctx.bbmm_solve_logdet_grad(_problem(w, mode))
 
-    ctx.bbmm_tune("khat_sym", tri)
+    ctx.bbmm_tune("khat_sym", 1 if tri else 0)
+    ctx.bbmm_tune("mat_wgs", 256 if tri else 0)
+    ctx.bbmm_tune("otf_digits", 0 if tri == 2 else 1)
     try:
         ctx.bbmm_tune("loop_graph", 0)
         ref = [run(*v) for v in variants]
@@ -734,8 +737,8 @@ def test_loop_graph_replays_equal_kernel_by_kernel_launches(ctx, mode, tri):
         # one launch sequence for all four hyperparameter settings: recorded once, replayed 15 times
         assert (cap1 - cap0, rep1 - rep0) == (1, 15)
     finally:
-        ctx.bbmm_tune("loop_graph", 0)
-        ctx.bbmm_tune("khat_sym", 0)
+        for key, value in (("loop_graph", 0), ("khat_sym", 0), ("mat_wgs", 0), ("otf_digits", 1)):
+            ctx.bbmm_tune(key, value)
 
 
 # -------------------------------------------------------------- edge cases -----

@@ -95,12 +95,20 @@ def test_projected_iteration_repeats_and_alternates(ctx):
     _, prob = _setup(ctx, n, m, t, k, iters, 0.0, 100.0)
     _, other = _setup(ctx, n, m, t, k, iters, 1e-300, 100.0)
     first = ctx.bbmm_solve_logdet_grad(prob)
-    for _ in range(4):
-        mid = ctx.bbmm_solve_logdet_grad(other)
-        again = ctx.bbmm_solve_logdet_grad(prob)
-        assert torch.equal(first.U, again.U) and first.logdet == again.logdet
-        assert float((mid.U - first.U).double().norm() / first.U.double().norm()) < SOLVE_TOL
-        torch.cuda.synchronize()
+    ctx.bbmm_tune("loop_graph", 1)
+    try:
+        before = ctx.bbmm_loop_graph_stats()
+        for _ in range(5):
+            mid = ctx.bbmm_solve_logdet_grad(other)
+            again = ctx.bbmm_solve_logdet_grad(prob)
+            assert torch.equal(first.U, again.U) and first.logdet == again.logdet
+            assert np.array_equal(first.alpha, again.alpha)
+            assert float((mid.U - first.U).double().norm() / first.U.double().norm()) < SOLVE_TOL
+            torch.cuda.synchronize()
+        captures, replays = ctx.bbmm_loop_graph_stats()
+        assert (captures - before[0], replays - before[1]) == (2, 8)     # of each form the second run is recorded and replayed
+    finally:
+        ctx.bbmm_tune("loop_graph", 0)
 
 
 def test_projected_iteration_from_a_warm_start(ctx):

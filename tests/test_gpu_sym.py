@@ -116,8 +116,17 @@ def test_product_is_deterministic(ctx):
     assert torch.equal(a, b)
 
 
-def _full_parity(ctx, w, tol_solve=1e-3):
+@pytest.fixture(params=["fp64", "words"])
+def tri(ctx, request):
+    """A context whose calls keep the triangle at any size (a call with this key at its default keeps the whole matrix up to 8192 rows and 16
+    columns), with products on the fp64 matrix pipe or, up to 12 columns, on digit words."""
     ctx.bbmm_tune("khat_sym", 1)
+    ctx.bbmm_tune("mat_wgs", 256)
+    ctx.bbmm_tune("otf_digits", request.param == "words")
+    return ctx
+
+
+def _full_parity(ctx, w, tol_solve=1e-3):
     res = ctx.bbmm_solve_logdet_grad(_problem(w))
     ref = O.bbmm_inference(w.kernel, w.X, w.y, w.lengthscale, w.outputscale, w.noise, w.E1, w.E2,
                            w.k, res.iters_run, forced_pivots=res.pivots)
@@ -134,19 +143,19 @@ def _full_parity(ctx, w, tol_solve=1e-3):
     return res, ref
 
 
-def test_full_path_config1(ctx):
-    res, ref = _full_parity(ctx, inputs.make(1))             # n = 1000: a single panel
+def test_full_path_config1(tri):
+    res, ref = _full_parity(tri, inputs.make(1))             # n = 1000: a single panel
     assert res.iters_run == 20
 
 
-def test_full_path_config2_shape_with_tolerance(ctx):
-    res, ref = _full_parity(ctx, inputs.make(2, n=3000))     # 3 panels, tol 1e-2 or 50 iterations
+def test_full_path_config2_shape_with_tolerance(tri):
+    res, ref = _full_parity(tri, inputs.make(2, n=3000))     # 3 panels, tol 1e-2 or 50 iterations
     assert res.iters_run <= 50
 
 
-def test_full_path_config3_shape(ctx):
+def test_full_path_config3_shape(tri):
     w = inputs.make(3, n=2500)                               # Matern-5/2 ARD d = 16, k = 20, p = 50
-    res, ref = _full_parity(ctx, w)
+    res, ref = _full_parity(tri, w)
     ex = O.exact_inference(w.kernel, w.X, w.y, w.lengthscale, w.outputscale, w.noise, with_traces=False)
     assert res.logdet == pytest.approx(ex.logdet, rel=1e-2)
     assert _colrel(_host(res.u0)[:, None], ex.u0[:, None]) < 1e-3
@@ -154,19 +163,26 @@ def test_full_path_config3_shape(ctx):
 
 def test_full_path_wide_block(ctx):
     # t = 16 probes: 17 columns, i.e. two groups of 16 through the product
+    ctx.bbmm_tune("khat_sym", 1)
     _full_parity(ctx, inputs.make(4, n=3000, iters=40))
 
 
 def test_same_call_in_both_storages_agrees(ctx):
     # the two storages differ only in the order of fp64 sums inside the product
     w = inputs.make(3, n=2300)
+    ctx.bbmm_tune("otf_digits", 0)
     full = ctx.bbmm_solve_logdet_grad(_problem(w))
     ctx.bbmm_tune("khat_sym", 1)
+    ctx.bbmm_tune("mat_wgs", 256)
     tri = ctx.bbmm_solve_logdet_grad(_problem(w))
     assert tri.pivots.tolist() == full.pivots.tolist()
+    assert not np.array_equal(tri.alpha, full.alpha)     # the triangle did run
     assert _colrel(_host(tri.U), _host(full.U)) < 1e-5
     assert tri.logdet == pytest.approx(full.logdet, rel=1e-8)
     assert np.allclose(tri.trace, full.trace, rtol=1e-6)
+    # up to 8192 rows and 16 columns a call keeps the whole matrix by itself
+    ctx.bbmm_tune("mat_wgs", 0)
+    assert np.array_equal(ctx.bbmm_solve_logdet_grad(_problem(w)).alpha, full.alpha)
 
 
 @pytest.mark.parametrize("ns", [1, 13, 17, 32])
@@ -191,16 +207,15 @@ def test_predict_var_on_the_triangle(ctx, ns):
     assert resid == pytest.approx(res_o.resid[-1].max(), rel=5e-2)
 
 
-def test_warm_start_on_the_triangle(ctx):
+def test_warm_start_on_the_triangle(tri):
     # Alg. 1/2 with a current solution as input: r_0 = y - K_hat u_init costs one more product
     w = inputs.tiny(2600, 5, kernel=inputs.RBF, ard=False, t=5, k=8, iters=12, noise=0.3, seed=11)
     from paper_1809_11165_amd import binding
-    ctx.bbmm_tune("khat_sym", 1)
-    cold = ctx.bbmm_solve_logdet_grad(_problem(w))
+    cold = tri.bbmm_solve_logdet_grad(_problem(w))
     prob = _problem(w)
     prob.u0_init = cold.u0.clone()
     prob.pivots_in = cold.pivots
-    warm = ctx.bbmm_solve_logdet_grad(prob)
+    warm = tri.bbmm_solve_logdet_grad(prob)
     ref = O.bbmm_inference(w.kernel, w.X, w.y, w.lengthscale, w.outputscale, w.noise, w.E1, w.E2,
                            w.k, warm.iters_run, forced_pivots=warm.pivots,
                            u0_init=_host(cold.u0))
