@@ -7,10 +7,10 @@ log-det, derivative traces) on the n = 50,000, d = 16, t = 10 Matern-5/2 ARD wor
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--mode sym|mat|otf|sgpr] [--config 3|2|4] [--n N] [--no-cpu]
 
-The default mode keeps the fp32 K_hat materialised as its upper triangle (half the HBM bytes per
-product, every tile used for both of its contributions; the product is then bound by the fp64
-matrix rate).  --mode mat keeps the whole matrix (HBM-bound product), --mode otf rebuilds the tiles
-from X in every product.  --mode sgpr measures the widened path instead (config 5: subset-of-regressors covariance,
+The default mode keeps K_hat materialised as its upper triangle, every tile used for both of its
+contributions (here as 31-bit fixed-point words, multiplied on the 8-bit matrix pipe).  --mode mat
+leaves the choice of the storage to the library (the same words here; the whole fp32 matrix for fewer points),
+--mode otf rebuilds the tiles from X in every product.  --mode sgpr measures the widened path instead (config 5: subset-of-regressors covariance,
 n = 500,000, m = 1024 inducing inputs, d = 8, t = 10, rank-10 preconditioner, 50 iterations);
 the default line is the exact-GP workload above.  --config 2 runs the second roofline point instead
 (RBF, n = 10,000, d = 8, rank-10 preconditioner, stop at a relative residual of 1e-2 or 50 iterations),
@@ -154,23 +154,41 @@ TRAFFIC_NOTE = ("HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SI
                 "workload (profiles/%s), not counted in this run")
 
 
+def padded(n):
+    return -(-n // 256) * 256
+
+
 def words_of(n, c, sym):
-    """Whether the library's default materialised products of an iteration run on digit words (8-bit matrix pipe)."""
-    return c <= 12 and -(-n // 256) * 256 > (8192 if sym else 11263)
+    """Which digit words the library's default materialised products of a call run on (8-bit matrix pipe): "triangle", "whole" or None."""
+    if c <= 12:
+        return "triangle" if padded(n) > (8192 if sym else 11263) else None
+    if c <= 16 or sym:
+        return None
+    return "whole" if padded(n) >= (8192 if c <= 24 else 16384) else None
 
 
-def roofline_words(n, c, mm_ms, launches):
-    """Product from K_hat as digit words (k_mm_words): the upper triangle (with whole 512-column blocks on the diagonal), 4 bytes an
-    entry, is read once, and every 16 x 16 tile takes ceil(c / 2), compiled for 2, 4 or 6, v_mfma_i32_16x16x64_i8 for each of its two
-    uses.  `frac` prices those operations at the dense 8-bit peak; the bytes are given beside it."""
-    np_ = -(-n // 256) * 256
-    tiles = sum(min(np_, 512 * (p + 1)) // 16 * (min(512, np_ - 512 * p) // 16) for p in range(-(-np_ // 512)))
-    groups = next(g for g in (2, 4, 6) if c <= 2 * g)
-    achieved = 2.0 * tiles * groups * MFMA_I8_OPS / (mm_ms * 1e-3) / 1e12
-    return {"bound": "mfma", "achieved": achieved, "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (8-bit)",
-            "frac": achieved / MFMA_I8_PEAK_TOPS, "traffic": None, "kernel": "k_mm_words (with k_digits)",
-            "avg_launch_ms": mm_ms, "launches": launches, "matrix_GBs": tiles * 1024.0 / (mm_ms * 1e-3) / 1e9,
-            "algorithmic_TFLOPs": 2.0 * c * n * n / (mm_ms * 1e-3) / 1e12}
+def roofline_words(n, c, mm_ms, launches, kind):
+    """Product from K_hat as digit words, 4 bytes an entry.  k_mm_words (triangle): the upper triangle (with whole 512-column blocks on the
+    diagonal) is read once, and every 16 x 16 tile takes ceil(c / 2), compiled for 2, 4 or 6, v_mfma_i32_16x16x64_i8 for each of its two
+    uses.  k_mm_words_wide (whole): every tile is read and takes 9, 12 or 16 of them once.  `frac` is the larger of the bytes over the HBM
+    peak and those operations over the dense 8-bit peak."""
+    np_ = padded(n)
+    if kind == "triangle":
+        tiles = sum(min(np_, 512 * (p + 1)) // 16 * (min(512, np_ - 512 * p) // 16) for p in range(-(-np_ // 512)))
+    else:
+        tiles = (np_ // 16) ** 2
+    groups = next(g for g in ((2, 4, 6) if kind == "triangle" else (9, 12, 16)) if c <= 2 * g)
+    tops = (2.0 if kind == "triangle" else 1.0) * tiles * groups * MFMA_I8_OPS / (mm_ms * 1e-3) / 1e12
+    gbs = tiles * 1024.0 / (mm_ms * 1e-3) / 1e9
+    out = {"traffic": None, "kernel": "%s (with k_digits)" % ("k_mm_words" if kind == "triangle" else "k_mm_words_wide"),
+           "avg_launch_ms": mm_ms, "launches": launches, "matrix_GBs": gbs, "matrix_ops_TOPs": tops,
+           "algorithmic_TFLOPs": 2.0 * c * n * n / (mm_ms * 1e-3) / 1e12}
+    if gbs / HBM_PEAK_GBS > tops / MFMA_I8_PEAK_TOPS:
+        out.update({"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS})
+    else:
+        out.update({"bound": "mfma", "achieved": tops, "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (8-bit)",
+                    "frac": tops / MFMA_I8_PEAK_TOPS})
+    return out
 
 
 def roofline_sym(n, c, mm_ms, launches, config):
@@ -183,8 +201,8 @@ def roofline_sym(n, c, mm_ms, launches, config):
 
     Up to 12 columns an iteration's products come from digit words instead, and up to 8192 rows a call keeps the whole matrix."""
     if words_of(n, c, True):
-        return roofline_words(n, c, mm_ms, launches)
-    if -(-n // 256) * 256 <= 8192 and c <= 16:
+        return roofline_words(n, c, mm_ms, launches, words_of(n, c, True))
+    if padded(n) <= 8192 and c <= 16:
         return roofline_mat(n, c, mm_ms, launches, config)
     alg_flops = 2.0 * c * n * n
     achieved = alg_flops / (mm_ms * 1e-3) / 1e12
@@ -200,21 +218,29 @@ def roofline_sym(n, c, mm_ms, launches, config):
 
 
 def roofline_mat(n, c, mm_ms, launches, config):
-    """Whole K_hat streamed once per product: algorithmic bytes 4 n^2 (K_hat) + 8 n c (block in and out); from 11 264 rows on and up
-    to 12 columns an iteration reads half of that (digit words), which the bytes per second of the whole then count too."""
-    words = words_of(n, c, False)
+    """Whole K_hat streamed once per product: algorithmic bytes 4 n^2 (K_hat) + 8 n c (block in and out).  Products on digit words are
+    priced as such."""
+    if words_of(n, c, False):
+        return roofline_words(n, c, mm_ms, launches, words_of(n, c, False))
     alg_bytes = 4.0 * n * n + 8.0 * n * c
     achieved = alg_bytes / (mm_ms * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": None, "traffic_source": None,
-            "kernel": "k_mm_words (8-bit matrix pipe; the triangle is read)" if words else
-                      ("k_mm_mat" if n > 8192 or c > 16 else "k_mm_mat_small"), "avg_launch_ms": mm_ms, "launches": launches}
+            "kernel": "k_mm_mat" if padded(n) > 8192 or c > 16 else "k_mm_mat_small" if padded(n) > 4096 else "k_mm_rows",
+            "avg_launch_ms": mm_ms, "launches": launches}
+
+
+def sgpr_carried(n, m, c, iters, tol):
+    """Whether the library carries A^T D along through a sparse iteration, whose products are then A T alone."""
+    mp = padded(m)
+    return (tol <= 0.0 and padded(n) >= max(2304, 4 * mp + 512) and iters >= max(16, mp // 16)
+            and (c <= 16 or mp <= 256 or padded(n) >= 5120))
 
 
 def otf_uses_digits(n, d):
     """Whether the library's default on-the-fly product runs on the 8-bit matrix pipe."""
-    return d <= 16 and -(-n // 256) * 256 >= 6144
+    return d <= 16 and padded(n) >= 6144
 
 
 def roofline_otf(n, c, d, mm_ms, launches):
@@ -230,7 +256,7 @@ def roofline_otf(n, c, d, mm_ms, launches):
     at half that rate on the same pipe, so the floor of the two together is n^2 (2 d / peak32 + 2 c / peak64):
     `frac_of_mixed_floor` is that floor over the launch time."""
     alg_flops = (2.0 * d + 2.0 * c) * n * n
-    np_ = -(-n // 256) * 256
+    np_ = padded(n)
     out = {"bound": "mfma", "traffic": None, "avg_launch_ms": mm_ms, "launches": launches, "pairs_per_s": n * n / (mm_ms * 1e-3)}
     if otf_uses_digits(n, d):
         tiles, kk = (np_ / 16.0) ** 2, 1 if d <= 4 else (2 if d <= 8 else 4)
@@ -331,27 +357,32 @@ def main():
     if args.config == 4:
         workload = ("config4: exact GP, RBF, 20 Gaussian clusters, n=%d, d=8, t=16, k=20, 100 mBCG iterations" % n)
         metric = "mBCG solve+logdet+grad ms at n=200k,t=16 (config 4)"
-    mode_name = "materialised fp32 K_hat" if mode == inputs.MATERIALISED else "on-the-fly tiles"
+    words = words_of(n, c, args.mode == "sym") if mode == inputs.MATERIALISED else None
+    stored = "K_hat as 31-bit fixed-point words" if words else "fp32 K_hat"
+    mode_name = "materialised " + stored if mode == inputs.MATERIALISED else "on-the-fly tiles"
     if mode == inputs.SGPR:
         # one product = the root A (n x m fp32) streamed once in each layout, the block in and out,
-        # the m x c middle result out and in: 8 n m + 16 n c + 16 m c bytes
+        # the m x c middle result out and in: 8 n m + 16 n c + 16 m c bytes; with A^T D carried along
+        # one layout, the middle result in and the block out
         m = args.m
-        alg_bytes = 8.0 * n * m + 16.0 * n * c + 16.0 * m * c
+        passes = 1 if sgpr_carried(n, m, c, w.iters, w.tol) else 2
+        alg_bytes = passes * (4.0 * n * m + 8.0 * n * c + 8.0 * m * c)
         achieved = alg_bytes / (mm_ms * 1e-3) / 1e9
+        counted = passes == 2 and (n, m) == (500000, 1024)
         roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK_GBS,
-                    "traffic": MEASURED_TRAFFIC_SGPR_N500000_M1024 if (n, m) == (500000, 1024) else None,
-                    "traffic_source": (TRAFFIC_NOTE % "k_mm_mat_cfg5_n500000_sgpr_hbm_counters.txt"
-                                       if (n, m) == (500000, 1024) else None),
-                    "kernel": "k_mm_mat (two launches per product: A^T D, then A T)",
-                    "avg_launch_ms": mm_ms / 2.0, "avg_product_ms": mm_ms, "launches": 2 * mm_launches}
+                    "traffic": MEASURED_TRAFFIC_SGPR_N500000_M1024 if counted else None,
+                    "traffic_source": TRAFFIC_NOTE % "k_mm_mat_cfg5_n500000_sgpr_hbm_counters.txt" if counted else None,
+                    "kernel": "k_mm_mat (%s)" % ("A T alone; A^T D is carried along" if passes == 1 else
+                                                 "two launches per product: A^T D, then A T"),
+                    "avg_launch_ms": mm_ms / passes, "avg_product_ms": mm_ms, "launches": passes * mm_launches}
         workload = ("config5: SGPR (subset of regressors), RBF, n=%d, m=%d, d=8, t=10, k=10, 50 mBCG "
                     "iterations" % (n, m))
         metric = "mBCG solve+logdet+grad ms at n=500k,m=1024,t=10 (SGPR)"
         mode_name = "fp32 root A = K_XU G^-T in both layouts"
     elif args.mode == "sym":
         roofline = roofline_sym(n, c, mm_ms, mm_launches, args.config)
-        mode_name = "materialised fp32 K_hat, upper triangle only (khat_sym)"
+        mode_name = "materialised %s, upper triangle only (khat_sym)" % stored if words or c > 16 or padded(n) > 8192 else mode_name
     elif mode == inputs.MATERIALISED:
         roofline = roofline_mat(n, c, mm_ms, mm_launches, args.config)
     else:
@@ -367,6 +398,8 @@ def main():
                    "arithmetic": ("kernel-matrix entries evaluated in fp32 and multiplied in 31-bit fixed point with 62-bit "
                                   "blocks, exact integer sums; all other sums and the n x c blocks fp64"
                                   if mode == inputs.ONTHEFLY and otf_uses_digits(n, d) else
+                                  "kernel-matrix entries from fp64 distances, stored and multiplied in 31-bit fixed point with "
+                                  "62-bit blocks, exact integer sums; all other sums and the n x c blocks fp64" if words else
                                   "kernel-matrix entries fp32 (stored or generated), products, sums and all "
                                   "n x c blocks fp64"),
                    "iters_run": res.iters_run, "ms_per_iteration": ms_per_step / max(res.iters_run, 1),
@@ -383,7 +416,8 @@ def main():
         try:
             ms_mat, mm_mat, l_mat, r_mat = time_calls(ctx, prob, 1, 3)
             out["roofline_mat"] = dict(roofline_mat(n, c, mm_mat, l_mat, args.config), ms_per_call=ms_mat,
-                                       mode="materialised fp32 K_hat, whole matrix", logdet=r_mat.logdet)
+                                       mode="materialised %s, khat_sym off" % ("K_hat as 31-bit fixed-point words"
+                                                                               if words_of(n, c, False) else "fp32 K_hat"), logdet=r_mat.logdet)
         except binding.BbmmError as e:
             out["roofline_mat"] = {"error": str(e)}
         try:
