@@ -22,9 +22,9 @@
  *     before they return).  A call
  *     that returns host values synchronises the stream once before it returns.
  *   - Precision: K_hat entries are fp32; inside the library every n x c block of
- *     the iteration, the pivoted-Cholesky factor and all sums are fp64 (large products
- *     of an iteration: integers of that accuracy, see "otf_digits").  float
- *     block arguments are converted on entry and rounded once on exit.
+ *     the iteration, the pivoted-Cholesky factor and all sums are fp64.  In large products
+ *     of an iteration entries are 31-bit fixed-point numbers instead and sums integers; sizes and
+ *     error stand at "otf_digits".  float block arguments are converted on entry and rounded once on exit.
  *   - Every function returns an int status (BBMM_OK == 0).  No exceptions,
  *     no exit().  bbmm_last_error() gives a message for the last failure.
  *   - A context is not thread-safe; use one context per stream.
@@ -74,7 +74,10 @@ enum { BBMM_MODE_MATERIALISED = 0, BBMM_MODE_ONTHEFLY = 1, BBMM_MODE_SGPR = 2 };
  *                A = K_XU G^{-T} (K_UU = G G^T) in fp32 in both layouts (8 n m bytes) and
  *                forms products as A (A^T M).  Preconditioner, probes, mBCG, log-det and
  *                traces are those of the SoR matrix; the inducing inputs are fixed, not
- *                hyperparameters.  SGPR supports one shared lengthscale (n_lengthscale 1)
+ *                hyperparameters.  Runs of at least max(16, m / 16) iterations that no tolerance can stop
+ *                carry A^T D and A^T R along in fp64 and stream A^T R anew every eight iterations:
+ *                one pass over A per iteration, solves within rounding of the two-pass form's.
+ *                SGPR supports one shared lengthscale (n_lengthscale 1)
  *                or one per dimension, 1 <= m <= min(n, 4096), d <= 32.
  *   n, d         number of training points and input dimension
  *   t            number of probe vectors z_i (right-hand-side block has t+1 columns)
@@ -188,18 +191,22 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                other block of bbmm_kernel_mm takes the fp64 form.  Points of X whose scaled square
  *                overflows fp32 call for the fp64 form in both (an mBCG run is then made twice).
  *                2: all products (NaN for such X in bbmm_kernel_mm); 0: none.
- *                The same for BBMM_MODE_MATERIALISED: an mBCG run of at least 8 iterations takes its products from the entries as
- *                fixed-point words: on at most 12 columns half of the matrix, from 11264 rows on, and from
- *                1024 on where the triangle is kept ("khat_sym"); on 17 to 24 columns (25 to 32) the whole matrix, from 8192
+ *                The same for BBMM_MODE_MATERIALISED ("otf_sym" does not matter there): an mBCG run of at least 8 iterations takes its
+ *                products from the entries as fixed-point words: on at most 12 columns half of the matrix, from 11264 rows on, and
+ *                from 1024 on where the triangle is kept ("khat_sym"); on 17 to 24 columns (25 to 32) the whole matrix, from 8192
  *                (16384) rows on, unless the triangle is kept.  bbmm_solve_logdet_grad then evaluates the words from X
- *                (fp64 distances) and builds the fp32 matrix only when a later call asks for it; a matrix built by
- *                bbmm_build_khat is converted, and stays.  bbmm_kernel_mm uses the fp32 matrix (2: the words)
+ *                (fp64 distances) and builds the fp32 matrix only when a later call asks for it, or, once bbmm_kernel_mm or
+ *                bbmm_khat_block has read it in this context, where its memory suffices.  A matrix in memory, such as
+ *                bbmm_build_khat leaves, is converted, and stays: for runs of at least 30 iterations (max_iters; 60 on 25 to 32
+ *                columns below 20480 rows; 12 where the triangle is kept), and where matrix and words fit half of the device's
+ *                memory together.  A run for whose words an allocation fails takes fp32 entries.  bbmm_kernel_mm uses the fp32
+ *                matrix (2: the words)
  *   "otf_sym"    the form with fp64 sums.  1 (default): a product of at most 16 columns over at most 32 input
  *                dimensions and at least 12288 (padded) rows evaluates only the tiles on and above
  *                the diagonal and uses each for both of its contributions (K is symmetric);
  *                2: the same for any number of rows; 0: every tile is evaluated for the one
  *                contribution, as it is for wider blocks and inputs.  Same values, fp64 sums in
- *                another order.  0 and 2 also switch "otf_digits" off
+ *                another order.  0 and 2 also switch "otf_digits" off for products on the fly
  *   "ur_blocks"  upper limit of the workgroups of the fused U/R update (default 128, at most 512)
  *   "khat_panel" layout of the materialised K_hat: column panels of that width (a multiple of
  *                256; default 1024), each panel row-major; 1 = plain row-major.  Takes effect at
@@ -215,6 +222,7 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                (the whole-matrix product takes one pass for up to 32), so beyond 16 columns
  *                the whole matrix is the faster storage.  bbmm_solve_logdet_grad
  *                keeps the whole matrix up to 8192 rows and 16 columns, where that is the faster one
+ *                (unless "mat_wgs" is set)
  *   "zd_blocks"  workgroups per compute unit of the direction update (default 16, at most 64)
  *   "sgpr_wgs1", "sgpr_wgs2"  workgroups of the two streaming products of an SGPR product
  *                (A^T M, then A (.)); clamped like "mat_wgs"; takes effect at the next bbmm_sgpr_build

@@ -257,7 +257,8 @@ __global__ __launch_bounds__(256, 1) void k_mm_words(const int* __restrict__ Kw,
       });
     };
     // Four accumulators per piece and lane to doubles in LDS, two pieces (four block columns) in five stages: lanes g, g ^ 1 hold the
-    // two halves of the weights.  (At most 128 terms of four digit products in a step, the entry's top digit being at most 122: 2^31 is not reached.)
+    // two halves of the weights.  (An entry's top digit is at most 123, its others at most 128, as are the block's: 128 terms of 128 (123 + 3 * 128) in a step,
+    // 8.31e6, times 257: 2.135e9 < 2^31.)
     int sh[2], sl[2];
     double sx[2];
     constexpr int kStages = 5 * (NG / 2), kEarly = NG >= 4 ? NG / 2 : 0;     // of these, the first in the last instructions of the step itself
