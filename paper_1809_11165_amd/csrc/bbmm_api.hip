@@ -549,20 +549,39 @@ int stage_build_khat(bbmm_ctx* c, bool tri) {
   return BBMM_OK;
 }
 
+// A buffer's memory back to the device.
+int give_back(bbmm_ctx* c, Buf& b) {
+  if (!b.p) return BBMM_OK;
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  HIPCHK(c, hipFree(b.p));
+  b = Buf{};
+  ++c->alloc_epoch;
+  return BBMM_OK;
+}
+
 // The fp32 matrix; where there is no room for it beside words of this or an earlier problem, in their place.
 int build_khat_first(bbmm_ctx* c, bool tri) {
   int rc = stage_build_khat(c, tri);
   if (rc != BBMM_ENOMEM || !c->words.p) return rc;
-  HIPCHK(c, hipStreamSynchronize(c->stream));
   c->words_built = 0;
-  HIPCHK(c, hipFree(c->words.p));
-  c->words = Buf{};
-  ++c->alloc_epoch;
-  return stage_build_khat(c, tri);
+  rc = give_back(c, c->words);
+  return rc ? rc : stage_build_khat(c, tri);
 }
 
 // The same where a call has done without it so far.
 int need_khat(bbmm_ctx* c) { return c->khat_mem ? BBMM_OK : build_khat_first(c, c->khat_tri); }
+
+// Room for the words and for what the products from them leave and read, for any block that they serve.
+int words_room(bbmm_ctx* c, bool whole, size_t bytes) {
+  size_t np = (size_t)c->np;
+  struct { Buf* b; size_t bytes; } want[] = {
+      {&c->words, bytes}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
+  for (auto& w : want)
+    if (int rc = ensure(c, *w.b, w.bytes)) return rc;
+  int rc = whole ? BBMM_OK : ensure_words_plan(c);
+  if (!rc) rc = whole ? ensure_vp(c, bbmm_plan::wide_split(c->np, c->num_cus, kDigMaxBlocks), 32) : ensure_vp(c, c->wrd.max_slots, 16);
+  return rc ? rc : ensure_records(c, 0, dig_groups(whole ? 32 : 12));
+}
 
 // K_hat as digit words, for an iteration.  No room for them: c->words_built is 0 and the fp32 matrix serves.
 int stage_build_words(bbmm_ctx* c, int kind) {
@@ -577,24 +596,17 @@ int stage_build_words(bbmm_ctx* c, int kind) {
   // whatever else is in memory, short of a failed allocation.)
   const size_t bytes = words_bytes(c->np, whole);
   if (c->khat_mem && bytes + khat_bytes(c, c->khat_tri) > c->dev_bytes / 2) return BBMM_OK;
-  size_t np = (size_t)c->np;
-  struct { Buf* b; size_t bytes; } want[] = {
-      {&c->words, bytes}, {&c->Xo, c->khat_mem ? 0 : np * c->dp * sizeof(double)}, {&c->sqo, c->khat_mem ? 0 : np * sizeof(double)}};
-  auto make_room = [&]() -> int {
-    for (auto& w : want)
-      if (int rc = ensure(c, *w.b, w.bytes)) return rc;
-    return BBMM_OK;
-  };
-  int rc = make_room();
+  int rc = words_room(c, whole, bytes);
   if (rc == BBMM_ENOMEM && c->Khat.p && !c->khat_mem && !c->khat_read) {   // an earlier problem's matrix gives way
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipFree(c->Khat.p));
-    c->Khat = Buf{};
-    ++c->alloc_epoch;
-    rc = make_room();
+    rc = give_back(c, c->Khat);
+    if (!rc) rc = words_room(c, whole, bytes);
   }
-  if (rc == BBMM_OK || rc == BBMM_ENOMEM) c->err.clear();
-  if (rc) return rc == BBMM_ENOMEM ? BBMM_OK : rc;
+  if (rc == BBMM_ENOMEM) {                  // the run on fp32 entries needs the room
+    rc = give_back(c, c->words);
+    c->err.clear();
+    return rc;
+  }
+  if (rc) return rc;
   if (c->khat_mem)                          // the matrix that the caller has had built
     launch_words_of(c->stream, ptr<float>(c->Khat), (size_t)(c->khat_pw > 0 ? c->khat_pw : c->np), c->khat_tri ? 1 : 0,
                     c->prob.outputscale, c->n, c->np, whole, ptr<DevState>(c->st), ptr<int>(c->words));

@@ -200,10 +200,19 @@ def test_words_of_the_other_form_come_from_the_fp32_matrix(ctx):
 
 
 def _all_but(left):
-    """Device memory taken so that `left` bytes are free (nothing is written to it)."""
+    """Device memory taken so that `left` bytes can be allocated, in blocks of 32 MB (nothing is written to it)."""
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
-    return torch.empty(torch.cuda.mem_get_info()[0] - left, dtype=torch.uint8, device="cuda")
+    block = 32 << 20
+    taken = [torch.empty(max(0, torch.cuda.mem_get_info()[0] - left - (8 << 30)), dtype=torch.uint8, device="cuda")]
+    try:
+        while True:
+            taken.append(torch.empty(block, dtype=torch.uint8, device="cuda"))
+    except torch.cuda.OutOfMemoryError:
+        pass
+    del taken[len(taken) - -(-left // block):]
+    torch.cuda.empty_cache()
+    return taken
 
 
 def test_the_same_arithmetic_beside_other_users_of_the_device():
@@ -242,6 +251,26 @@ def test_the_matrix_of_an_earlier_problem_gives_way_to_words(ctx):
     got = own.bbmm_solve_logdet_grad(prob).U
     del other
     own.close()
+    torch.cuda.empty_cache()
+    assert torch.equal(got, ref)
+
+
+def test_a_run_whose_words_leave_no_room_for_its_sums_takes_fp32_entries(ctx):
+    """Room for the words (1.6 GB) and not for the partial results of products from them (0.2 GB)."""
+    ctx.bbmm_tune("khat_sym", 0)
+    w = _workload(28000, 4, inputs.RBF, t=4, k=5, iters=30, noise=0.5)
+    B = torch.randn(w.n, 5, generator=torch.Generator().manual_seed(1)).cuda()
+    ctx.bbmm_setup(_problem(w))
+    ctx.bbmm_build_khat()
+    ctx.bbmm_pivoted_cholesky()
+    ctx.bbmm_precond_setup()
+    ctx.bbmm_tune("otf_digits", 0)
+    ref = ctx.bbmm_mbcg(inputs.MATERIALISED, B)[0].clone()
+    ctx.bbmm_tune("otf_digits", 1)
+    panels = 28160 // 512
+    other = _all_but((panels * (panels + 1) // 2) * 512 * 512 * 4 + (100 << 20))
+    got = ctx.bbmm_mbcg(inputs.MATERIALISED, B)[0].clone()
+    del other
     torch.cuda.empty_cache()
     assert torch.equal(got, ref)
 
