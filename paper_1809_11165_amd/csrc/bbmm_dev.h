@@ -46,7 +46,7 @@ struct DevState {
   int rank;         // preconditioner rank actually built
   unsigned fin_ticket;   // arrivals of k_ur_fin's blocks (zero between launches)
   int xbad;         // a coordinate of X or its square, or an entry of K, is not finite in fp32: no X for the digit products (they return NaN)
-  unsigned counter[8][40];   // arrival tickets per kernel family: [0] final, [1 + g] group g
+  unsigned slq_ticket;   // arrivals of k_slq's blocks (zero between launches)
 };
 
 struct HypArgs {

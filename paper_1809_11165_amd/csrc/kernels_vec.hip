@@ -315,17 +315,6 @@ __device__ inline double kernel_of_rho2(double rho2, const HypArgs& hyp) {
   return hyp.outputscale * (1.0 + s5 * rho + (5.0 / 3.0) * rho2) * exp(-s5 * rho);
 }
 
-__device__ inline double kernel_value_f64(const float* __restrict__ X, int a, int b,
-                                          const HypArgs& hyp) {
-  double rho2 = 0.0;
-  for (int dim = 0; dim < hyp.d; ++dim) {
-    double df = ((double)X[(size_t)a * hyp.d + dim] - (double)X[(size_t)b * hyp.d + dim]) *
-                hyp.inv_ls[dim];
-    rho2 += df * df;
-  }
-  return kernel_of_rho2(rho2, hyp);
-}
-
 // Block-level argmax of (value, lowest index on ties); result valid in every thread.  Shuffles inside a
 // wave, one exchange between the waves (two barriers instead of the sixteen of a tree in LDS).
 __device__ inline void block_argmax(double v, int idx, double* sval, int* sidx, double* outv,
@@ -489,7 +478,7 @@ __global__ __launch_bounds__(VT) void k_pc_step(const float* __restrict__ X, int
       lval = 0.0;                  // already picked
     } else {
       double kv = row;
-      if (!row_in) {               // kernel_value_f64 of the two rows
+      if (!row_in) {               // kernel value in fp64 of the two rows
         double rho2 = 0.0;
 #pragma unroll
         for (int dim = 0; dim < DP; ++dim)
@@ -1871,12 +1860,12 @@ __global__ __launch_bounds__(SLQ_THREADS) void k_slq(const double* __restrict__ 
     st->slq_terms[blockIdx.x] = term;
     if (bad) st->status = bad;
   }
-  if (!last_block_arrives(&st->counter[4][0])) return;
+  if (!last_block_arrives(&st->slq_ticket)) return;
   if (threadIdx.x == 0) {
     double s = 0.0;
     for (int i = 0; i < t; ++i) s += st->slq_terms[i];
     st->slq_mean = s / (double)t;
-    st->counter[4][0] = 0u;
+    st->slq_ticket = 0u;
   }
 }
 
