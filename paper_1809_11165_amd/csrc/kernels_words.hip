@@ -4,7 +4,7 @@
 // blocks: 1.28 ms at n = 50 000, 11 columns, where reading the triangle takes 0.73 ms.  Digits (see kernels_dig.hip) need
 // a quarter of the matrix time; turning stored fp32 entries into digit words inside the product, though, costs three vector
 // instructions and two LDS passes per entry and leaves 1.35 ms (measured).  So the words themselves are stored, which takes
-// 1.13 ms (n = 20 000: 0.19 ms, whole fp32 matrix 0.25): K / s
+// 1.08 ms (n = 20 000: 0.19 ms, whole fp32 matrix 0.25): K / s
 // as 31-bit fixed point, four balanced base-256 digits in four bytes, laid out as the product reads them.
 //
 // Layout: panels of BBMM_WORDS_PANEL columns, panel P keeping rows [0, (P + 1) * BBMM_WORDS_PANEL) (the upper triangle, blocks
