@@ -200,7 +200,7 @@ const char* bbmm_last_error(const bbmm_ctx* ctx);
  *                bbmm_build_khat leaves, is converted, and stays: for runs of at least 30 iterations (max_iters; 60 on 25 to 32
  *                columns below 20480 rows; 12 where the triangle is kept), and where matrix and words fit half of the device's
  *                memory together.  A run for whose words an allocation fails takes fp32 entries.  bbmm_kernel_mm uses the fp32
- *                matrix (2: the words)
+ *                matrix (2: the words, unless its caller is recording it in a graph)
  *   "otf_sym"    the form with fp64 sums.  1 (default): a product of at most 16 columns over at most 32 input
  *                dimensions and at least 12288 (padded) rows evaluates only the tiles on and above
  *                the diagonal and uses each for both of its contributions (K is symmetric);
@@ -283,7 +283,8 @@ int bbmm_sgpr_build(bbmm_ctx* ctx);
 int bbmm_sgpr_root_rows(bbmm_ctx* ctx, int64_t row0, int64_t nrows, float* out);
 
 /* V = K_hat M, the product every mBCG iteration is built on (Sec. 3, "Runtime and space").
- * M, V: device n x c float, 1 <= c <= 32; V may be M or overlap it.  mode MATERIALISED needs bbmm_build_khat first, mode
+ * M, V: device n x c float, 1 <= c <= 32; V may be M or overlap it.  A caller may record it in a graph right behind a call of
+ * bbmm_solve_logdet_grad in mode MATERIALISED: what the product still needs is built at once, outside the graph.  mode MATERIALISED needs bbmm_build_khat first, mode
  * SGPR bbmm_sgpr_build; an SGPR problem takes mode SGPR only, and no other problem does. */
 int bbmm_kernel_mm(bbmm_ctx* ctx, int32_t mode, const float* M, int64_t c, float* V);
 

@@ -320,8 +320,9 @@ int make_plan(bbmm_ctx* c, int rows_p, int cols_p, int ld, int wgs, int slot_cap
   if (rc) return rc;
   rc = ensure(c, nseg_buf, sizeof(int) * nseg.size());
   if (rc) return rc;
-  HIPCHK(c, hipMemcpy(plan_buf.p, plan.data(), sizeof(MmPlan) * plan.size(), hipMemcpyHostToDevice));
-  HIPCHK(c, hipMemcpy(nseg_buf.p, nseg.data(), sizeof(int) * nseg.size(), hipMemcpyHostToDevice));
+  HIPCHK(c, hipMemcpyAsync(plan_buf.p, plan.data(), sizeof(MmPlan) * plan.size(), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(nseg_buf.p, nseg.data(), sizeof(int) * nseg.size(), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   if (max_slots) *max_slots = *std::max_element(nseg.begin(), nseg.end());
   return BBMM_OK;
 }
@@ -364,8 +365,9 @@ int build_tri_lists(bbmm_ctx* c, int W, int want, int64_t tune, TriLists& L, int
   for (const Up& u : ups) {
     int rc = ensure(c, *u.b, std::max<size_t>(u.bytes, 16));
     if (rc) return rc;
-    if (u.bytes) HIPCHK(c, hipMemcpy(u.b->p, u.src, u.bytes, hipMemcpyHostToDevice));
+    if (u.bytes) HIPCHK(c, hipMemcpyAsync(u.b->p, u.src, u.bytes, hipMemcpyHostToDevice, c->stream));
   }
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   L.wgs[0] = H.wgs[0];
   L.wgs[1] = H.wgs[1];
   L.max_slots = H.max_slots;
@@ -817,6 +819,30 @@ int mat64_reserve(bbmm_ctx* c, int cc, int ld) {
   if (int ns = mat_split_of(c, ld)) return ensure_vp(c, ns, ld);
   int rc = ensure_mat_plans(c);
   return rc ? rc : ensure_vp(c, c->plan_slots[(ld == 32) ? 1 : (cc <= 12 ? 2 : 0)], ld);
+}
+
+// Whether the caller records the context's stream in a graph.
+bool recording(const bbmm_ctx* c) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return c->stream && hipStreamIsCapturing(c->stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
+// What a product with the stored matrix needs before its launches.  A caller may be recording the stream: the recording must hold neither
+// the build (with this problem's scalars) nor allocations and uploads, which are done at once then, on the second stream.  (The call
+// that has left the matrix unbuilt has waited for its stream: what the build reads is there.)
+template <class F>
+int ahead_of_recording(bbmm_ctx* c, F prepare) {
+  if (!recording(c)) return prepare();
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  HIPCHK(c, hipThreadExchangeStreamCaptureMode(&mode));
+  hipStream_t user = c->stream;
+  c->stream = c->side;
+  int rc = prepare();
+  hipError_t e = hipStreamSynchronize(c->side);
+  c->stream = user;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!rc && e != hipSuccess) rc = fail(c, BBMM_EHIP, std::string("build ahead of a recording: ") + hipGetErrorString(e));
+  return rc;
 }
 
 // Product with the stored matrix on the fp64 matrix pipe (need_khat first: a recorded iteration loop must not build it).
@@ -1582,7 +1608,7 @@ int bbmm_khat_block(bbmm_ctx* c, int64_t row0, int64_t nrows, int64_t col0, int6
   if (rc) return rc;
   if (!c->khat_built) return fail(c, BBMM_EINVAL, "bbmm_build_khat must run first");
   c->khat_read = true;
-  rc = need_khat(c);
+  rc = ahead_of_recording(c, [&] { return need_khat(c); });
   if (rc) return rc;
   if (!out || row0 < 0 || col0 < 0 || nrows < 0 || ncols < 0 || row0 + nrows > c->n || col0 + ncols > c->n ||
       nrows * ncols > (int64_t)1 << 31)
@@ -1601,15 +1627,20 @@ int bbmm_kernel_mm(bbmm_ctx* c, int32_t mode, const float* M, int64_t cc, float*
   int ld = ld_for((int)cc);
   hipStream_t s = c->stream;
   DevState* st = ptr<DevState>(c->st);
-  // (a product with the stored matrix is that of its fp32 entries, unless otf_digits says otherwise)
-  if (mode == BBMM_MODE_MATERIALISED && c->otf_digits == 2 && c->khat_built && wants_words(c, (int)cc)) {
+  // (a product with the stored matrix is that of its fp32 entries, unless otf_digits says otherwise; also then if it is recorded, since a
+  // later call may leave words of another form)
+  const bool by_words = mode == BBMM_MODE_MATERIALISED && c->otf_digits == 2 && c->khat_built && !recording(c);
+  if (by_words && wants_words(c, (int)cc)) {
     rc = stage_build_words(c, wants_words(c, (int)cc));
     if (rc) return rc;
   }
-  int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || c->otf_digits == 2) ? 1 : 0;
+  int digits = uses_digits(c, mode, (int)cc) && (mode != BBMM_MODE_MATERIALISED || by_words) ? 1 : 0;
   if (mode == BBMM_MODE_MATERIALISED && !digits && c->khat_built) {
     c->khat_read = true;
-    rc = need_khat(c);
+    rc = ahead_of_recording(c, [&] {
+      int rc1 = need_khat(c);
+      return rc1 || mat_rows(c, ld) ? rc1 : mat64_reserve(c, (int)cc, ld);
+    });
     if (rc) return rc;
   }
   if (mode == BBMM_MODE_MATERIALISED && !digits && mat_rows(c, ld)) {

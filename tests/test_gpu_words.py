@@ -177,6 +177,46 @@ def test_a_recorded_product_follows_the_calls_that_run_on_words(n, t, sym):
         ctx.close()
 
 
+@pytest.mark.parametrize("had", [0, 1])
+@pytest.mark.parametrize("n,t,sym,dig", [(11300, 4, 0, 1), (1500, 4, 1, 1), (11300, 19, 0, 1), (11300, 19, 0, 2)])
+def test_a_product_recorded_right_behind_a_call_on_words_holds_no_build(n, t, sym, dig, had):
+    """The call leaves no fp32 matrix (had = 1: memory for one, of an earlier build).  A product that is recorded as the first one has to find it
+    built, and its replays must neither build it nor read another call's (nor, with otf_digits = 2, words of another form)."""
+    from paper_1809_11165_amd import binding
+    stream = torch.cuda.Stream()
+    w = _workload(n, 4, inputs.RBF, t=t, k=5, iters=10, noise=0.5)
+    M = torch.randn(n, 5, generator=torch.Generator().manual_seed(1)).cuda()
+    rows = np.array([0, 777, n - 1])
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ctx = binding.Context(0)
+        ctx.bbmm_tune("khat_sym", sym)
+        if sym:
+            ctx.bbmm_tune("mat_wgs", 256)                  # (keeps the triangle at this size)
+        ctx.bbmm_tune("otf_digits", dig)
+        if had:
+            ctx.bbmm_setup(_problem(w))
+            ctx.bbmm_build_khat()
+        w.noise, w.outputscale = 0.7, 2.5
+        ctx.bbmm_solve_logdet_grad(_problem(w))
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            V = ctx.bbmm_kernel_mm(inputs.MATERIALISED, M)
+        for step in range(4):
+            if step % 2:
+                w.noise, w.outputscale = 0.4 + 0.3 * step, 1.5 + 0.5 * step
+                ctx.bbmm_solve_logdet_grad(_problem(w))
+            V.zero_()
+            graph.replay()
+            stream.synchronize()
+            got = V.clone()
+            assert dig == 2 or torch.equal(got, ctx.bbmm_kernel_mm(inputs.MATERIALISED, M)), step
+            K = O.kernel_block(w.kernel, w.X[rows].astype(np.float64), w.X.astype(np.float64), w.lengthscale, w.outputscale)
+            K[np.arange(3), rows] += w.noise
+            assert np.max(np.abs(got.cpu().numpy()[rows] - K @ M.cpu().numpy().astype(np.float64))) < 2e-4, step
+        ctx.close()
+
+
 def test_words_of_the_other_form_come_from_the_fp32_matrix(ctx):
     """A call leaves the triangle's words (5 columns, nothing in fp32) or the whole matrix's (20); variances at 20 and at 5 points then need
     the other form, whose entries are those of the fp32 matrix: the same bits as on a matrix built by itself."""
