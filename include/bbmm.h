@@ -75,8 +75,9 @@ enum { BBMM_MODE_MATERIALISED = 0, BBMM_MODE_ONTHEFLY = 1, BBMM_MODE_SGPR = 2 };
  *                forms products as A (A^T M).  Preconditioner, probes, mBCG, log-det and
  *                traces are those of the SoR matrix; the inducing inputs are fixed, not
  *                hyperparameters.  Runs of at least max(16, m / 16) iterations that no tolerance can stop
- *                carry A^T D and A^T R along in fp64 and stream A^T R anew every eight iterations:
- *                one pass over A per iteration, solves within rounding of the two-pass form's.
+ *                carry A^T D and A^T R along in fp64 and stream A^T R anew every 48 iterations:
+ *                one pass over A per iteration; unfinished solves lag behind the two-pass form's by about three
+ *                iterations, as those of a plain 64-bit run do by about two.
  *                SGPR supports one shared lengthscale (n_lengthscale 1)
  *                or one per dimension, 1 <= m <= min(n, 4096), d <= 32.
  *   n, d         number of training points and input dimension

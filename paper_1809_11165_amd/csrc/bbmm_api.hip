@@ -703,11 +703,11 @@ int sgpr_first_pass(bbmm_ctx* c, int ld, const double* D4, VpShape* shape, int c
 
 // Whether the iteration carries T = A^T D and S = A^T R along (their recurrences need A^T A, mp x mp, once) instead of
 // streaming A for A^T D in every product.
-// A^T A takes n mp^2 operations at 66 TFLOP/s (m = 1024, n = 500 000: 8.9 ms) and a pass of A that it saves 4 n mp bytes at 6.3 TB/s (0.34 ms with
+// A^T A takes n mp^2 operations at 66 TFLOP/s (m = 1024, n = 500 000: 8.9 ms) and a pass of A that it saves 4 n mp bytes at 6.3 TB/s (0.37 ms with
 // the passes that come back, see kProjRefresh): mp / 40 iterations, and it is formed where more than twice as many are certain, that is, no tolerance
 // to stop at.  (The partial sums of A^T A have K_UX's memory: eight of its upper triangle fit from 4 mp + 512 points on.)
-// Whole calls of 128 iterations, streamed / carried, ms, n = 3 000: m = 500, 11 columns: 9.1 / 8.1; 17 columns: 9.5 / 11.1; n = 4 000: m = 256, 17 columns:
-// 8.2 / 7.9; m = 500: 10.4 / 11.4; n = 5 000: 11.6 / 11.3; n = 10 000: 11.9 / 10.1.  So beyond 16 columns (the blocks for H run twice as long) and 256 rows of
+// Whole calls of 128 iterations, streamed / carried, ms, n = 3 000: m = 500, 11 columns: 9.5 / 8.0; 17 columns: 10.0 / 11.2; n = 4 000: m = 256, 17 columns:
+// 8.4 / 7.9; m = 500: 10.7 / 11.4; n = 5 000: 11.8 / 11.4; n = 10 000: 12.3 / 10.1.  So beyond 16 columns (the blocks for H run twice as long) and 256 rows of
 // T it takes 5 120 points.
 constexpr int kProjWideMinRows = 5120;
 bool sgpr_projected(const bbmm_ctx* c, int ld) {
@@ -716,11 +716,13 @@ bool sgpr_projected(const bbmm_ctx* c, int ld) {
 }
 
 // Iterations after which S is streamed from R again.  S keeps the rounding errors of all its updates while R shrinks, and T takes them
-// divided by sigma^2: the solves of an unfinished run lag behind those of the streamed iteration.  Their distance from the 64-bit
-// solution over that of the streamed iteration's, sigma^2 = 0.25, 32 columns, n = 20 000, m = 800, after 160 iterations (0.9 of the distance is left
-// per iteration): never 1.9, every 16 1.19, 8 1.10, 4 1.08, 2 1.07, 1 1.02.  A whole call, n = 500 000, m = 1024, 128 iterations, ms:
-// 91.7, 94.2, 97.2, 103, 115, 138 (130.9 with every A^T D streamed).  (Streaming T from D instead does not help.)
-constexpr int kProjRefresh = 8;
+// divided by sigma^2: the solves of an unfinished run lag behind those of the streamed iteration (whose sums are better than a plain 64-bit run's), and true
+// residuals stop at the drift of the whole run.  16 calls of 128 iterations at sigma^2 = 0.25, n = 24 000 .. 500 000, m = 700 .. 1024, S anew never / every 64 /
+// 48 / 32 / 16 / 8, geometric means: distance from the solution over that of a 64-bit run of the same length (streamed: 0.78): 1.15 / 1.07 / 1.02 /
+// 0.93 / 0.87 / 0.86; distance from that run over the streamed iteration's: 0.66 / 0.42 / 0.42 / 0.44 / 0.62 / 0.68 (at n = 500 000 alone, where the 64-bit run
+// lags as much itself: 0.34 / 0.20 / 0.29 / 0.57 / 0.73 / 0.74).  A whole call, n = 500 000, m = 1024, ms: 91.9 / 92.2 / 92.6 / 92.9 / 94.5 / 97.4 (131.5 with every
+// A^T D streamed).  So: as near to the solution as the 64-bit run, and nearer to that run than the streamed iteration in all 16.  (Streaming T from D instead does not help.)
+constexpr int kProjRefresh = 48;
 
 // A^T R <- R, to tmpA (quad-swizzled).
 int sgpr_fresh(bbmm_ctx* c, int ld, int cc, SgprLoop* pj) {

