@@ -705,7 +705,7 @@ int sgpr_first_pass(bbmm_ctx* c, int ld, const double* D4, VpShape* shape, int c
 // streaming A for A^T D in every product.
 // A^T A takes n mp^2 operations at 66 TFLOP/s (m = 1024, n = 500 000: 8.9 ms) and a pass of A that it saves 4 n mp bytes at 6.3 TB/s (0.37 ms with
 // the passes that come back, see kProjRefresh): mp / 40 iterations, and it is formed where more than twice as many are certain, that is, no tolerance
-// to stop at.  (The partial sums of A^T A have K_UX's memory: eight of its upper triangle fit from 4 mp + 512 points on.)
+// to stop at (64 of them at m = 1024, n = 500 000: 76.7 ms streamed, 61.9 carried; with fewer, down to some 26, it would be the faster form by less: not tried).  (The partial sums of A^T A have K_UX's memory: eight of its upper triangle fit from 4 mp + 512 points on.)
 // Whole calls of 128 iterations, streamed / carried, ms, n = 3 000: m = 500, 11 columns: 9.5 / 8.0; 17 columns: 10.0 / 11.2; n = 4 000: m = 256, 17 columns:
 // 8.4 / 7.9; m = 500: 10.7 / 11.4; n = 5 000: 11.8 / 11.4; n = 10 000: 12.3 / 10.1.  So beyond 16 columns (the blocks for H run twice as long) and 256 rows of
 // T it takes 5 120 points.
